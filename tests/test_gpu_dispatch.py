@@ -35,14 +35,15 @@ def _random_lists(B, Hl, NB, off, T, seed):
     return idx.cuda(), cnt.cuda()
 
 
-# Query blocks are dealt to the XCDs in runs of 8, 4, 2 or 1 (by how evenly they divide), forwards or in a snake: every row of
-# every head is served exactly once.  A prefix of 9000-odd tokens makes K and V^T of a head outgrow one L2 (runs),
-# without one they fit (single rows); 64 + n rows: runs of 8, 92: of 4, 46: of 2.
+# A KV head is served by a gang of 8, 4, 2 or 1 XCDs (by how many rows it has, and if the heads divide), its query blocks dealt in
+# runs of 8, 4, 2 or 1 (by how evenly they divide), forwards or in a snake: every row of every head is served exactly once.
+# A prefix of 9000-odd tokens makes K and V^T of a head outgrow one L2 (runs), without one they fit (single rows).
 @pytest.mark.parametrize("D,Bs", [(128, 64), (64, 64), (128, 128)])
+@pytest.mark.parametrize("B,Hkv", [(1, 3), (1, 8), (2, 2), (1, 2)])
 @pytest.mark.parametrize("NB,P,shared,n_dense", [(1, 0, 0, 0), (9, 0, 0, 0), (16, 9216, 0, 0), (17, 9216, 1, 0), (46, 9216, 0, 0),
                                                  (92, 18432, 0, 0), (64, 18432, 0, 0), (23, 0, 0, 3), (23, 18432, 1, 11)])
-def test_every_row_is_dealt_once(spa, D, Bs, NB, P, shared, n_dense):
-    B, Hq, Hkv, S = 1, 6, 3, NB * Bs - 5
+def test_every_row_is_dealt_once(spa, D, Bs, B, Hkv, NB, P, shared, n_dense):
+    Hq, S = 2 * Hkv, NB * Bs - 5
     q = _normal((B, Hq, S, D), 11)
     k = _normal((B, Hkv, P + S, D), 12)
     v = torch.ones_like(k)
