@@ -945,8 +945,11 @@ template <int BS, int D>
 hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                   const int32_t* idx, const int32_t* cnt, void* out, Strides os, float* lse,
                   const void* vt, int64_t vt_bph, hipStream_t st) {
-    // lists shared by the heads of a group: two heads per workgroup take every tile from one staged copy
-    if (d.shared && d.G % 2 == 0) return launch_nh<BS, D, 2>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
+    // Lists shared by the heads of a group: two heads per workgroup take every tile from one staged copy.  Not with
+    // head_dim 64 and blocks of 128, where single-head workgroups put three wavefronts on a SIMD and the eight
+    // wavefronts of a pair only two (16384 tokens: 550 -> 535 us).
+    if constexpr (!(D == 64 && BS == 128))
+        if (d.shared && d.G % 2 == 0) return launch_nh<BS, D, 2>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
     return launch_nh<BS, D, 1>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
 }
 
