@@ -57,3 +57,34 @@ def test_every_row_is_dealt_once(spa, D, Bs, B, Hkv, NB, P, shared, n_dense):
     # rounding of fp32 sums and one bf16 rounding (2^-8)
     assert torch.isfinite(out).all()
     assert (out.float() - 1).abs().max().item() <= 2 ** -8
+
+
+# Rows per workgroup of the score kernel go by the number of rows and of key blocks: 4 up to 1024 rows, 8 up to 16384
+# (1025 - 2048 key blocks: 32768), then 16; 4, 8, 16 or 32 key registers per lane.  The lists are the caller-score kernel's
+# on the same scores, bit for bit, at the last row count of one group and the first of the next, with a row tile that
+# is not full, and on both sides of every limit in key blocks.
+@pytest.mark.parametrize("NB,Hq,P_blocks,D,kw", [
+    (128, 8, 0, 128, {}), (129, 8, 0, 64, {}), (7, 8, 249, 128, {}), (7, 8, 250, 64, dict(stride_blocks=5)), (6, 4, 506, 128, {}),
+    (6, 4, 507, 128, dict(n_dense_q_blocks=2)), (5, 8, 1019, 64, {}), (5, 8, 1020, 128, {}), (3, 8, 2045, 128, dict(stride_blocks=7)),
+    (257, 4, 256, 64, {}), (258, 4, 256, 64, {}), (513, 32, 30, 64, {}), (512, 32, 30, 64, {}), (1025, 2, 3, 64, {}), (1030, 32, 0, 64, {})])
+def test_rows_per_workgroup_of_the_score_kernel(spa, NB, Hq, P_blocks, D, kw):
+    Bs, Hkv = 64, Hq // 2
+    q = _normal((1, Hq, NB * Bs - 9, D), 31)
+    k = _normal((1, Hkv, P_blocks * Bs + NB * Bs - 9, D), 32)
+    for shared in (False, True) if Hq * NB <= 2048 else (False,):
+        idx, cnt, sp = spa.select(q, k, Bs, 1, 2, 11, return_scores=True, group_shared=shared, **kw)
+        w_idx, w_cnt = spa.topk_from_scores(sp, 1, 2, 11, **kw)
+        assert torch.equal(idx, w_idx) and torch.equal(cnt, w_cnt)
+        # the scores themselves: fp32 means and products of magnitude below 1 (split bf16 products, 2^-17 each)
+        pick = torch.arange(0, NB, max(1, NB // 5), device="cuda").tolist() + [NB - 1]
+        for h in (0, Hkv - 1):
+            S = q.shape[2]
+            heads = range(2 * h, 2 * h + 2) if shared else [2 * h + 1]
+            kp = torch.stack([x.double().mean(0) for x in k[0, h].split(Bs)])
+            for i in pick:
+                qp = torch.stack([q[0, x, i * Bs:min(S, (i + 1) * Bs)].double().mean(0) for x in heads]).mean(0)
+                want = (kp @ qp) / D ** 0.5
+                n = P_blocks + i + 1
+                got = sp[0, h if shared else 2 * h + 1, i]
+                torch.testing.assert_close(got[:n].double(), want[:n], rtol=1e-4, atol=1e-5)
+                assert torch.isneginf(got[n:]).all()
