@@ -83,6 +83,11 @@ struct SelectScratch {
     float *qp, *kp, *qg, *lvn;
 };
 
+SelectScratch select_scratch(void* ws, const Workspace& w) {
+    return {(float*)((char*)ws + w.qp_off), (float*)((char*)ws + w.kp_off), (float*)((char*)ws + w.qg_off),
+            (float*)((char*)ws + w.lvn_off)};
+}
+
 // Shape, pointer and budget checks of a select call; on success d holds the resolved sizes.
 int check_select(const spa_params* p, const void* q, const void* k, const void* v_or_null, float mass_gamma,
                  const int32_t* block_idx, const int32_t* block_cnt, Dims& d) {
@@ -98,7 +103,7 @@ int check_select(const spa_params* p, const void* q, const void* k, const void* 
 
 int select_launches(Dims d, const spa_params* p, const void* q, const void* k, const void* v_or_null, const int32_t* k_rows,
                     const int32_t* head_pattern, int32_t* block_idx, int32_t* block_cnt, float* pooled_scores_or_null,
-                    const SelectScratch& sc, hipStream_t st);
+                    const SelectScratch& sc, bool rank_by_values, void* vt_or_null, hipStream_t st);
 
 // v_or_null: values for the output-aware ranking score, or nullptr for the plain pooled score
 int select_impl(const spa_params* p, const void* q, const void* k, const void* v_or_null, const int32_t* k_rows,
@@ -111,28 +116,27 @@ int select_impl(const spa_params* p, const void* q, const void* k, const void* v
     if (((uintptr_t)ws) & (kAlign - 1)) return SPA_ERR_BAD_STRIDE;
     Workspace w = carve(d);
     if (ws_bytes < w.total) return SPA_ERR_WORKSPACE_TOO_SMALL;
-    const SelectScratch sc{(float*)((char*)ws + w.qp_off), (float*)((char*)ws + w.kp_off), (float*)((char*)ws + w.qg_off),
-                           (float*)((char*)ws + w.lvn_off)};
+    const SelectScratch sc = select_scratch(ws, w);
     return select_launches(d, p, q, k, v_or_null, k_rows, head_pattern, block_idx, block_cnt, pooled_scores_or_null, sc,
-                           (hipStream_t)hip_stream);
+                           v_or_null != nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
+// rank_by_values: the output-aware score; vt_or_null: where V^T goes, for a fused call (both need v)
 int select_launches(Dims d, const spa_params* p, const void* q, const void* k, const void* v_or_null, const int32_t* k_rows,
                     const int32_t* head_pattern, int32_t* block_idx, int32_t* block_cnt, float* pooled_scores_or_null,
-                    const SelectScratch& sc, hipStream_t st) {
+                    const SelectScratch& sc, bool rank_by_values, void* vt_or_null, hipStream_t st) {
     float* qp = sc.qp;
     float* kp = sc.kp;
     // Group-shared lists rank the mean of the group's pooled queries, which needs them in memory; all other
     // calls pool K only and let the score kernel pool its own query blocks from Q (the Q stream then hides
     // the scoring and selection)
     const bool q_in_kernel = !d.shared;
-    hipError_t e = launch_pool(d, q_in_kernel ? nullptr : q, strides_of(p->q_stride), k, strides_of(p->k_stride), qp, kp, true, st);
-    if (e != hipSuccess) return SPA_ERR_LAUNCH;
-    float* lvn = nullptr;
-    if (v_or_null) {
-        lvn = sc.lvn;
-        if (launch_vnorm(d, v_or_null, strides_of(p->v_stride), lvn, st) != hipSuccess) return SPA_ERR_LAUNCH;
-    }
+    const bool with_v = rank_by_values || vt_or_null != nullptr;       // K and what the call needs of V go in one launch
+    float* const lvn = rank_by_values ? sc.lvn : nullptr;
+    if (with_v && launch_prepare_kv(d, k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride), kp, vt_or_null, lvn, st) != hipSuccess)
+        return SPA_ERR_LAUNCH;
+    if (launch_pool(d, q_in_kernel ? nullptr : q, strides_of(p->q_stride), with_v ? nullptr : k, strides_of(p->k_stride), qp, kp, true, st) != hipSuccess)
+        return SPA_ERR_LAUNCH;
     if (d.shared) {
         // one list per KV head: rank the group by its mean pooled query, then select as if the
         // KV heads were the query heads
@@ -174,9 +178,12 @@ int fused_impl(const spa_params* p, const void* q, const void* k, const void* v,
     if (ws_bytes < w.total) return SPA_ERR_WORKSPACE_TOO_SMALL;
     int32_t* idx = block_idx_or_null ? block_idx_or_null : (int32_t*)((char*)ws + w.idx_off);
     int32_t* cnt = block_cnt_or_null ? block_cnt_or_null : (int32_t*)((char*)ws + w.cnt_off);
-    rc = select_impl(p, q, k, output_aware ? v : nullptr, k_rows, head_pattern, mass_gamma, idx, cnt, nullptr, ws, ws_bytes, hip_stream);
-    if (rc) return rc;
-    return sparse_prefill_attn(p, q, k, v, idx, cnt, out, lse_or_null, ws, ws_bytes, hip_stream);
+    if ((rc = check_select(p, q, k, output_aware ? v : nullptr, mass_gamma, idx, cnt, d))) return rc;
+    hipStream_t st = (hipStream_t)hip_stream;
+    void* const vt = (char*)ws + w.vt_off;
+    if ((rc = select_launches(d, p, q, k, v, k_rows, head_pattern, idx, cnt, nullptr, select_scratch(ws, w), output_aware, vt, st))) return rc;
+    return launch_code(launch_attn_vt(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), vt, d.NBk, idx, cnt, out,
+                                      strides_of(p->o_stride), lse_or_null, st));
 }
 }  // namespace
 
@@ -294,7 +301,7 @@ int sparse_prefill_select_static(const spa_params* p, const void* q, const void*
     char* base = (char*)static_scratch(&e);
     if (base == nullptr) return SPA_ERR_LAUNCH;
     const SelectScratch sc{(float*)(base + c.qp_off), (float*)(base + c.kp_off), (float*)(base + c.qg_off), nullptr};
-    return select_launches(d, p, q, k, nullptr, nullptr, nullptr, block_idx, block_cnt, pooled_scores_or_null, sc,
+    return select_launches(d, p, q, k, nullptr, nullptr, nullptr, block_idx, block_cnt, pooled_scores_or_null, sc, false, nullptr,
                            (hipStream_t)hip_stream);
 }
 

@@ -7,7 +7,7 @@
 // owns the logits of one query: the rescale factor is a per-lane scalar and exp(S^T) is
 // already the B operand of the second product.  Built around what the LDS can deliver:
 //   * V is transposed once per call into a workspace ([.., block, d, token]) by
-//     transpose_v_kernel, so both MFMA A operands (K rows, V^T rows) are plain
+//     transpose_v_kernel (pool.hip), so both MFMA A operands (K rows, V^T rows) are plain
 //     16-byte LDS reads; the LDS transpose read is ~4x slower per byte.
 //   * key blocks are consumed as 64-key sub-tiles, staged by direct
 //     global->LDS loads (global_load_lds_dwordx4, no VGPR round trip) into a
@@ -77,50 +77,6 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds_addr, uint32_t voff, cons
 }
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(lds_void*)p; }
 __device__ __forceinline__ int swap_bits23(int x) { return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1); }
-
-// ---------------------------------------------------------------------------
-// V [B,Hkv,S,D] (strided) -> Vt [B,Hkv,vt_bph,D,BS] contiguous, blocks first .. first + gridDim.x - 1.
-// vt_bph: blocks per head in the V^T allocation (>= the key blocks of the call); first: first block to do
-template <int BS, int D>
-__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, Strides vs, int Hkv,
-                                                          int64_t vt_bph, int S, uint16_t* __restrict__ vt,
-                                                          const int32_t* __restrict__ seq_lens, int Sq, int first) {
-    constexpr int PITCH = D + 2;
-    __shared__ uint16_t tile[BS * PITCH];
-    const int blk = first + blockIdx.x, bh = blockIdx.y;
-    const int b = bh / Hkv, h = bh % Hkv;
-    const uint16_t* src = v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t;
-    const int tid = threadIdx.x;
-    const int Sb = S - Sq + entry_len(seq_lens, b, Sq);    // ragged batch: key tokens of this entry
-    if (blk * BS >= Sb) return;                            // block past its end: never read by the attention kernel
-    const int n_valid = Sb - blk * BS < BS ? Sb - blk * BS : BS;
-#pragma unroll
-    for (int p = 0; p < BS * D / 8 / 256; ++p) {
-        int c = p * 256 + tid;
-        int row = c / (D / 8), col = (c % (D / 8)) * 8;
-        uint4 x = make_uint4(0u, 0u, 0u, 0u);           // tokens past the end of a partial last block: zeros
-        if (row < n_valid) {                            // V itself is not read again: non-temporal load
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (int64_t)row * vs.t + col));
-            x = make_uint4(t[0], t[1], t[2], t[3]);
-        }
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[row * PITCH + col]);   // PITCH even: 4-byte aligned
-        dst[0] = x.x; dst[1] = x.y; dst[2] = x.z; dst[3] = x.w;
-    }
-    __syncthreads();
-    uint16_t* dstb = vt + (((int64_t)bh * vt_bph + blk) * D) * BS;
-    constexpr int CPR = BS / 8;         // 16-byte chunks per output row
-#pragma unroll
-    for (int p = 0; p < BS * D / 8 / 256; ++p) {
-        int c = p * 256 + tid;
-        int d = c / CPR, t0 = (c % CPR) * 8;
-        uint32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            w[e] = (uint32_t)tile[(t0 + 2 * e) * PITCH + d] | ((uint32_t)tile[(t0 + 2 * e + 1) * PITCH + d] << 16);
-        *reinterpret_cast<uint4*>(dstb + (int64_t)d * BS + t0) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Instruction order inside a pipeline step is written out by hand: every group between two
@@ -934,14 +890,6 @@ hipError_t launch_nh(const Dims& d, const void* q, Strides qs, const void* k, St
 }
 
 template <int BS, int D>
-hipError_t launch_tv(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL((transpose_v_kernel<BS, D>), dim3(n, d.B * d.Hkv), dim3(256), 0, st,
-                       (const uint16_t*)v, vs, d.Hkv, vt_bph, d.Skv, (uint16_t*)vt, d.seq_lens, d.S, first);
-    return hipGetLastError();
-}
-
-template <int BS, int D>
 hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                   const int32_t* idx, const int32_t* cnt, void* out, Strides os, float* lse,
                   const void* vt, int64_t vt_bph, hipStream_t st) {
@@ -966,16 +914,6 @@ hipError_t launch_check_lists(const Dims& d, const int32_t* idx, const int32_t* 
     hipLaunchKernelGGL(check_lists_kernel, dim3((unsigned)nwg), dim3(256), 0, st, idx, cnt, Hl, d.NB, d.T, d.off, d.Bs,
                        d.S, d.seq_lens, n_rows, n_bad);
     return hipGetLastError();
-}
-
-hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n,
-                              hipStream_t st) {
-    if (vt == nullptr || vt_bph < d.NBk || first < 0 || n < 0 || first + n > d.NBk) return hipErrorInvalidValue;
-    if (d.D == 128 && d.Bs == 128) return launch_tv<128, 128>(d, v, vs, vt, vt_bph, first, n, st);
-    if (d.D == 128 && d.Bs == 64) return launch_tv<64, 128>(d, v, vs, vt, vt_bph, first, n, st);
-    if (d.D == 64 && d.Bs == 128) return launch_tv<128, 64>(d, v, vs, vt, vt_bph, first, n, st);
-    if (d.D == 64 && d.Bs == 64) return launch_tv<64, 64>(d, v, vs, vt, vt_bph, first, n, st);
-    return hipErrorInvalidValue;
 }
 
 hipError_t launch_attn_vt(const Dims& d, const void* q, Strides qs, const void* k, Strides ks, const void* vt,

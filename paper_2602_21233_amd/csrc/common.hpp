@@ -68,6 +68,9 @@ hipError_t launch_pool(const Dims& d, const void* q, Strides qs, const void* k, 
 hipError_t launch_group_mean(const Dims& d, const float* qp, float* qg, hipStream_t st);
 // lvn [B*Hkv, NB] fp32: ln of the mean value-vector norm of every key block.
 hipError_t launch_vnorm(const Dims& d, const void* v, Strides vs, float* lvn, hipStream_t st);
+// Pooled K (tiled) and, of V in the same launch, V^T for the attention kernel (NBk blocks per head) and / or lvn.
+hipError_t launch_prepare_kv(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt_or_null,
+                             float* lvn_or_null, hipStream_t st);
 // k_rows: optional device array of NB per-query-block budgets (clamped to [0, d.k] in the kernel).
 // lvn: optional; added to the score of key block j (output-aware ranking).
 // kp is in the tiled layout launch_pool writes with k_tiled.

@@ -1,7 +1,10 @@
-// Block mean pooling of Q and K (pattern computation, step 1; Sec. 4.1.1 of the
-// AngelSlim report: the dynamic regime first locates the sparse regions).
+// What reads K and V block by block before scoring and attention: block mean pooling of Q and K (pattern
+// computation, step 1; Sec. 4.1.1 of the AngelSlim report: the dynamic regime first locates the sparse
+// regions), the value magnitudes of the output-aware score, and V transposed per block for the attention
+// kernel.  One kernel for each entry point that asks for one of them, and prepare_kv_kernel, which does what a
+// fused (or output-aware select) call needs of K and V in one launch.
 //
-// Pure HBM stream: every bf16 element of Q and K is read exactly once with
+// Pooling is a pure HBM stream: every bf16 element of Q and K is read exactly once with
 // 16-byte loads, one workgroup per (head, block).  A row of head_dim elements is
 // covered by head_dim/8 adjacent lanes, so each wave instruction reads whole
 // contiguous rows.  Partial sums are fp32; the 16 (or 32) row groups of a
@@ -12,59 +15,30 @@
 namespace spa {
 namespace {
 
+// One block of one head: mean of its tokens.  src: the block's first token; n_valid: its tokens that exist; part:
+// 256 / (D / 8) rows of D floats of LDS.
+// k_tiled: pooled K goes out in the operand layout of the score kernel instead of row
+// major fp32: per KV head, tiles of 32 key blocks (32 * D * 4 bytes); every value is
+// already split into its bf16 head and bf16 tail (x = hi + lo), and inside a tile the 8
+// dims 16s + 8h .. +7 of block r sit at bf16 offset (((2s + h) * 2 + part) * 32 + r) * 8,
+// part 0 = hi, 1 = lo, so a wavefront of that kernel reads whole 1-KB pieces that are its
+// MFMA operands as they are.  dst is then the block's tile, otherwise the block's row.
 template <int D, int BS>
-__global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ q, Strides qs,
-                                                   int n_q_rows /* B*Hq or 0 */, int Hq,
-                                                   const uint16_t* __restrict__ k, Strides ks, int Hkv,
-                                                   float* __restrict__ qp, float* __restrict__ kp, int NBq, int Sq,
-                                                   int NBk, int Skv, int k_tiled,
-                                                   const int32_t* __restrict__ seq_lens) {
+__device__ __forceinline__ void pool_block(const uint16_t* __restrict__ src, int64_t stride_t, int n_valid, float (*part)[D],
+                                           float* __restrict__ dst, bool k_tiled, int blk) {
     constexpr int TPR = D / 8;          // lanes per token row
     constexpr int RPP = 256 / TPR;      // token rows per pass
     constexpr int PASSES = BS / RPP;
-    __shared__ float part[RPP][D];
-
-    const int blk = blockIdx.x;
-    int hy = blockIdx.y;
-    const uint16_t* src;
-    float* dst;
-    int S;                                   // tokens of this tensor (K may carry a prefix)
-    if (hy < n_q_rows) {
-        int b = hy / Hq, h = hy % Hq;
-        Sq = entry_len(seq_lens, b, Sq);     // ragged batch: this entry's own length
-        if (blk * BS >= Sq) return;          // the grid spans the key blocks of the longest entry
-        src = q + b * qs.b + h * qs.h + (int64_t)blk * BS * qs.t;
-        dst = qp + ((int64_t)hy * NBq + blk) * D;
-        S = Sq;
-        k = nullptr;
-    } else {
-        hy -= n_q_rows;
-        int b = hy / Hkv, h = hy % Hkv;
-        Skv = Skv - Sq + entry_len(seq_lens, b, Sq);
-        if (blk * BS >= Skv) return;
-        src = k + b * ks.b + h * ks.h + (int64_t)blk * BS * ks.t;
-        dst = kp + ((int64_t)hy * NBk + blk) * D;
-        S = Skv;
-        qs = ks;
-        // k_tiled: pooled K goes out in the operand layout of the score kernel instead of row
-        // major fp32: per KV head, tiles of 32 key blocks (32 * D * 4 bytes); every value is
-        // already split into its bf16 head and bf16 tail (x = hi + lo), and inside a tile the 8
-        // dims 16s + 8h .. +7 of block r sit at bf16 offset (((2s + h) * 2 + part) * 32 + r) * 8,
-        // part 0 = hi, 1 = lo, so a wavefront of that kernel reads whole 1-KB pieces that are its
-        // MFMA operands as they are.  Heads are ceil(NBk / 32) tiles apart.
-        if (k_tiled) dst = kp + ((int64_t)hy * ((NBk + 31) >> 5) + (blk >> 5)) * (32 * D);
-    }
     const int tid = threadIdx.x;
     const int row0 = tid / TPR, chunk = tid % TPR;
 
     // the last block of a sequence may be partial: tokens past the end are not read
-    const int n_valid = S - blk * BS < BS ? S - blk * BS : BS;
     uint4 raw[PASSES];
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
         raw[p] = make_uint4(0u, 0u, 0u, 0u);
         if (p * RPP + row0 < n_valid)
-            raw[p] = stream_load16(src + (int64_t)(p * RPP + row0) * qs.t + chunk * 8);
+            raw[p] = stream_load16(src + (int64_t)(p * RPP + row0) * stride_t + chunk * 8);
     }
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -82,7 +56,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
 #pragma unroll
         for (int r = 0; r < RPP; ++r) s += part[r][tid];
         const float mean = n_valid == BS ? s * (1.0f / (float)BS) : s / (float)n_valid;
-        if (k != nullptr && k_tiled) {
+        if (k_tiled) {
             const __bf16 hi = (__bf16)mean;                       // round to nearest even, twice
             const __bf16 lo = (__bf16)(mean - (float)hi);
             __bf16* t = reinterpret_cast<__bf16*>(dst);
@@ -93,6 +67,33 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
             dst[tid] = mean;
         }
     }
+}
+// where pooled K block blk of head hy goes
+template <int D>
+__device__ __forceinline__ float* pooled_k(float* kp, int hy, int blk, int NBk, bool k_tiled) {
+    return k_tiled ? kp + ((int64_t)hy * ((NBk + 31) >> 5) + (blk >> 5)) * (32 * D) : kp + ((int64_t)hy * NBk + blk) * D;
+}
+
+template <int D, int BS>
+__global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ q, Strides qs,
+                                                   int n_q_rows /* B*Hq or 0 */, int Hq,
+                                                   const uint16_t* __restrict__ k, Strides ks, int Hkv,
+                                                   float* __restrict__ qp, float* __restrict__ kp, int NBq, int Sq,
+                                                   int NBk, int Skv, int k_tiled,
+                                                   const int32_t* __restrict__ seq_lens) {
+    __shared__ float part[256 / (D / 8)][D];
+    const int blk = blockIdx.x;
+    int hy = blockIdx.y;
+    const bool is_q = hy < n_q_rows;
+    if (!is_q) hy -= n_q_rows;
+    const int H = is_q ? Hq : Hkv, b = hy / H, h = hy % H;
+    const int S_b = entry_len(seq_lens, b, Sq);          // ragged batch: this entry's own length
+    const int S = is_q ? S_b : Skv - Sq + S_b;           // tokens of this tensor (K may carry a prefix)
+    if (blk * BS >= S) return;                           // the grid spans the key blocks of the longest entry
+    const Strides st = is_q ? qs : ks;
+    const uint16_t* src = (is_q ? q : k) + b * st.b + h * st.h + (int64_t)blk * BS * st.t;
+    float* dst = is_q ? qp + ((int64_t)hy * NBq + blk) * D : pooled_k<D>(kp, hy, blk, NBk, k_tiled);
+    pool_block<D, BS>(src, st.t, S - blk * BS < BS ? S - blk * BS : BS, part, dst, !is_q && k_tiled, blk);
 }
 
 template <int D, int BS>
@@ -106,57 +107,127 @@ hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strid
     return hipGetLastError();
 }
 
-// ln of the mean L2 norm of a key block's value vectors (the value-magnitude term of the
-// output-aware ranking score, Sec. 4.1.2 Fig. "Stem" (c)).  Same access pattern as pool_kernel:
-// D/8 adjacent lanes cover one token, combine their partial sums of squares with lane-xor
-// exchanges, and the token norms of the 16 (or 32) row groups are added through LDS in a fixed
-// order.  A block of all-zero values gives -inf.
+// One block of V of one head: transposed to [D][BS] at vt (VT), and / or the ln of the mean L2 norm of its value vectors
+// to *lvn (VN: the value-magnitude term of the output-aware ranking score, Sec. 4.1.2 Fig. "Stem" (c)).  The
+// access pattern of pool_block, V is read once for both.  Norms: D/8 adjacent lanes cover one token, combine their
+// partial sums of squares with lane-xor exchanges, and the token norms of the 16 (or 32) row groups are added
+// through LDS in a fixed order; a block of all-zero values gives -inf.  Tokens past the end: zeros in V^T, a norm of 0.
+// tile: BS * (D + 2) values of LDS (VT), part: 256 / (D / 8) floats (VN).
+template <int D, int BS, bool VT, bool VN>
+__device__ __forceinline__ void value_block(const uint16_t* __restrict__ src, int64_t stride_t, int n_valid, uint16_t* tile,
+                                            float* part, uint16_t* __restrict__ vt, float* __restrict__ lvn) {
+    constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, PITCH = D + 2;
+    const int tid = threadIdx.x;
+    const int row0 = tid / TPR, chunk = tid % TPR;
+    uint4 raw[PASSES];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        raw[p] = make_uint4(0u, 0u, 0u, 0u);
+        if (p * RPP + row0 < n_valid)
+            raw[p] = stream_load16(src + (int64_t)(p * RPP + row0) * stride_t + chunk * 8);
+    }
+    if constexpr (VT) {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[(p * RPP + row0) * PITCH + chunk * 8]);   // PITCH even: 4-byte aligned
+            dst[0] = raw[p].x; dst[1] = raw[p].y; dst[2] = raw[p].z; dst[3] = raw[p].w;
+        }
+    }
+    if constexpr (VN) {
+        float acc = 0.f;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const uint32_t w[4] = {raw[p].x, raw[p].y, raw[p].z, raw[p].w};
+            float sq = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float lo = bf16_lo(w[e]), hi = bf16_hi(w[e]);
+                sq = fmaf(lo, lo, sq);
+                sq = fmaf(hi, hi, sq);
+            }
+#pragma unroll
+            for (int off = 1; off < TPR; off <<= 1) sq += __shfl_xor(sq, off);
+            acc += sqrtf(sq);
+        }
+        if (chunk == 0) part[row0] = acc;
+    }
+    __syncthreads();
+    if constexpr (VN) {
+        if (tid == 0) {
+            float s = 0.f;
+#pragma unroll
+            for (int r = 0; r < RPP; ++r) s += part[r];
+            *lvn = logf(n_valid == BS ? s * (1.0f / (float)BS) : s / (float)n_valid);
+        }
+    }
+    if constexpr (VT) {
+        constexpr int CPR = BS / 8;         // 16-byte chunks per output row
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int c = p * 256 + tid;
+            const int d = c / CPR, t0 = (c % CPR) * 8;
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                w[e] = (uint32_t)tile[(t0 + 2 * e) * PITCH + d] | ((uint32_t)tile[(t0 + 2 * e + 1) * PITCH + d] << 16);
+            *reinterpret_cast<uint4*>(vt + (int64_t)d * BS + t0) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+}
+
 template <int D, int BS>
 __global__ __launch_bounds__(256) void vnorm_kernel(const uint16_t* __restrict__ v, Strides vs, int Hkv, int NB,
                                                     int S, float* __restrict__ lvn,
                                                     const int32_t* __restrict__ seq_lens, int Sq) {
-    constexpr int TPR = D / 8;
-    constexpr int RPP = 256 / TPR;
-    constexpr int PASSES = BS / RPP;
-    __shared__ float part[RPP];
+    __shared__ float part[256 / (D / 8)];
     const int blk = blockIdx.x, hy = blockIdx.y;
     const int b = hy / Hkv, h = hy % Hkv;
-    const uint16_t* src = v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t;
-    const int tid = threadIdx.x;
-    const int row0 = tid / TPR, chunk = tid % TPR;
     S = S - Sq + entry_len(seq_lens, b, Sq);                        // ragged batch: key tokens of this entry
     if (blk * BS >= S) return;
-    const int n_valid = S - blk * BS < BS ? S - blk * BS : BS;      // partial last block
-    uint4 raw[PASSES];
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        raw[p] = make_uint4(0u, 0u, 0u, 0u);                          // a missing token adds a norm of 0
-        if (p * RPP + row0 < n_valid)
-            raw[p] = stream_load16(src + (int64_t)(p * RPP + row0) * vs.t + chunk * 8);
-    }
-    float acc = 0.f;
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        const uint32_t w[4] = {raw[p].x, raw[p].y, raw[p].z, raw[p].w};
-        float sq = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float lo = bf16_lo(w[e]), hi = bf16_hi(w[e]);
-            sq = fmaf(lo, lo, sq);
-            sq = fmaf(hi, hi, sq);
-        }
-#pragma unroll
-        for (int off = 1; off < TPR; off <<= 1) sq += __shfl_xor(sq, off);
-        acc += sqrtf(sq);
-    }
-    if (chunk == 0) part[row0] = acc;
-    __syncthreads();
-    if (tid == 0) {
-        float s = 0.f;
-#pragma unroll
-        for (int r = 0; r < RPP; ++r) s += part[r];
-        lvn[(int64_t)hy * NB + blk] = logf(n_valid == BS ? s * (1.0f / (float)BS) : s / (float)n_valid);
-    }
+    value_block<D, BS, false, true>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t,
+                                    S - blk * BS < BS ? S - blk * BS : BS, nullptr, part, nullptr, lvn + (int64_t)hy * NB + blk);
+}
+
+// V [B,Hkv,S,D] (strided) -> Vt [B,Hkv,vt_bph,D,BS] contiguous, blocks first .. first + gridDim.x - 1.
+// vt_bph: blocks per head in the V^T allocation (>= the key blocks of the call); first: first block to do
+template <int D, int BS>
+__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, Strides vs, int Hkv,
+                                                          int64_t vt_bph, int S, uint16_t* __restrict__ vt,
+                                                          const int32_t* __restrict__ seq_lens, int Sq, int first) {
+    __shared__ uint16_t tile[BS * (D + 2)];
+    const int blk = first + blockIdx.x, bh = blockIdx.y;
+    const int b = bh / Hkv, h = bh % Hkv;
+    const int Sb = S - Sq + entry_len(seq_lens, b, Sq);    // ragged batch: key tokens of this entry
+    if (blk * BS >= Sb) return;                            // block past its end: never read by the attention kernel
+    value_block<D, BS, true, false>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t, Sb - blk * BS < BS ? Sb - blk * BS : BS,
+                                    tile, nullptr, vt + ((int64_t)bh * vt_bph + blk) * D * BS, nullptr);
+}
+
+// Everything a call needs of K and V before it scores: blockIdx.z = 0 pools a block of K (tiled), 1 takes a
+// block of V (VT: transposed for the attention kernel, VN: its magnitude).  HBM-bound streams like the separate kernels,
+// whose launches, ramps and second read of V this saves: fused calls of 512 tokens 27 -> 23 us, 1999 tokens 64 -> 57.6,
+// 16384 tokens (D = 64, shared lists) 557 -> 553 us; 49000 tokens with the output-aware score 3.59 -> 3.51 ms.
+template <int D, int BS, bool VT, bool VN>
+__global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restrict__ k, Strides ks,
+                                                         const uint16_t* __restrict__ v, Strides vs, int Hkv, int NBk, int Skv,
+                                                         float* __restrict__ kp, uint16_t* __restrict__ vt,
+                                                         float* __restrict__ lvn, const int32_t* __restrict__ seq_lens, int Sq) {
+    constexpr int RPP = 256 / (D / 8);
+    constexpr int TILE_B = VT ? BS * (D + 2) * 2 : 0, PART_B = RPP * D * 4;
+    __shared__ __attribute__((aligned(16))) char lds[TILE_B > PART_B ? TILE_B : PART_B];
+    __shared__ float norms[RPP];
+    const int blk = blockIdx.x, hy = blockIdx.y;
+    const int b = hy / Hkv, h = hy % Hkv;
+    const int S = Skv - Sq + entry_len(seq_lens, b, Sq);   // ragged batch: key tokens of this entry
+    if (blk * BS >= S) return;
+    const int n_valid = S - blk * BS < BS ? S - blk * BS : BS;
+    if (blockIdx.z == 0)
+        pool_block<D, BS>(k + b * ks.b + h * ks.h + (int64_t)blk * BS * ks.t, ks.t, n_valid, reinterpret_cast<float(*)[D]>(lds),
+                          pooled_k<D>(kp, hy, blk, NBk, true), true, blk);
+    else
+        value_block<D, BS, VT, VN>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t, n_valid,
+                                   reinterpret_cast<uint16_t*>(lds), norms, VT ? vt + ((int64_t)hy * NBk + blk) * D * BS : nullptr,
+                                   VN ? lvn + (int64_t)hy * NBk + blk : nullptr);
 }
 
 // group-shared selection: the pooled queries of the G heads of a KV group are averaged
@@ -182,7 +253,45 @@ hipError_t launch_vn(const Dims& d, const void* v, Strides vs, float* lvn, hipSt
     return hipGetLastError();
 }
 
+template <int D, int BS>
+hipError_t launch_tv(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL((transpose_v_kernel<D, BS>), dim3(n, d.B * d.Hkv), dim3(256), 0, st,
+                       (const uint16_t*)v, vs, d.Hkv, vt_bph, d.Skv, (uint16_t*)vt, d.seq_lens, d.S, first);
+    return hipGetLastError();
+}
+
+template <int D, int BS>
+hipError_t launch_prep(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt, float* lvn,
+                       hipStream_t st) {
+    const auto kernel = vt == nullptr ? prepare_kv_kernel<D, BS, false, true>
+                                      : (lvn == nullptr ? prepare_kv_kernel<D, BS, true, false> : prepare_kv_kernel<D, BS, true, true>);
+    hipLaunchKernelGGL(kernel, dim3(d.NBk, d.B * d.Hkv, 2), dim3(256), 0, st, (const uint16_t*)k, ks, (const uint16_t*)v, vs,
+                       d.Hkv, d.NBk, d.Skv, kp, (uint16_t*)vt, lvn, d.seq_lens, d.S);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n,
+                              hipStream_t st) {
+    if (vt == nullptr || vt_bph < d.NBk || first < 0 || n < 0 || first + n > d.NBk) return hipErrorInvalidValue;
+    if (d.D == 128 && d.Bs == 128) return launch_tv<128, 128>(d, v, vs, vt, vt_bph, first, n, st);
+    if (d.D == 128 && d.Bs == 64) return launch_tv<128, 64>(d, v, vs, vt, vt_bph, first, n, st);
+    if (d.D == 64 && d.Bs == 128) return launch_tv<64, 128>(d, v, vs, vt, vt_bph, first, n, st);
+    if (d.D == 64 && d.Bs == 64) return launch_tv<64, 64>(d, v, vs, vt, vt_bph, first, n, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_prepare_kv(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt_or_null,
+                             float* lvn_or_null, hipStream_t st) {
+    if (vt_or_null == nullptr && lvn_or_null == nullptr) return hipErrorInvalidValue;
+    if (d.D == 128 && d.Bs == 128) return launch_prep<128, 128>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 128 && d.Bs == 64) return launch_prep<128, 64>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 64 && d.Bs == 128) return launch_prep<64, 128>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 64 && d.Bs == 64) return launch_prep<64, 64>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_group_mean(const Dims& d, const float* qp, float* qg, hipStream_t st) {
     const int64_t n4 = (int64_t)d.NB * d.D / 4, total4 = n4 * d.B * d.Hkv;
