@@ -182,7 +182,7 @@ int fused_impl(const spa_params* p, const void* q, const void* k, const void* v,
     hipStream_t st = (hipStream_t)hip_stream;
     void* const vt = (char*)ws + w.vt_off;
     if ((rc = select_launches(d, p, q, k, v, k_rows, head_pattern, idx, cnt, nullptr, select_scratch(ws, w), output_aware, vt, st))) return rc;
-    return launch_code(launch_attn_vt(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), vt, d.NBk, idx, cnt, out,
+    return launch_code(launch_attn_vt(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), vt, d.NBk, vt_in_halves(d), idx, cnt, out,
                                       strides_of(p->o_stride), lse_or_null, st));
 }
 }  // namespace
@@ -356,7 +356,7 @@ int sparse_prefill_transpose_v(const spa_params* p, const void* v, void* vt, int
     if (vt_blocks_per_head < d.NBk || first_block < 0 || n_blocks < 0 || (int64_t)first_block + n_blocks > d.NBk)
         return SPA_ERR_BAD_SHAPE;
     return launch_code(launch_transpose_v(d, v, strides_of(p->v_stride), vt, vt_blocks_per_head, first_block, n_blocks,
-                                          (hipStream_t)hip_stream));
+                                          false, (hipStream_t)hip_stream));
 }
 
 int sparse_prefill_attn_vt(const spa_params* p, const void* q, const void* k, const void* vt, int64_t vt_blocks_per_head,
@@ -372,7 +372,7 @@ int sparse_prefill_attn_vt(const spa_params* p, const void* q, const void* k, co
     const Dims d = resolved(p);
     if (vt_blocks_per_head < d.NBk) return SPA_ERR_BAD_SHAPE;
     return launch_code(launch_attn_vt(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), vt, vt_blocks_per_head,
-                                      block_idx, block_cnt, out, strides_of(p->o_stride), lse_or_null,
+                                      false, block_idx, block_cnt, out, strides_of(p->o_stride), lse_or_null,
                                       (hipStream_t)hip_stream));
 }
 

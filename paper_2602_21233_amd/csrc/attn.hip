@@ -640,7 +640,10 @@ __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)
 // arithmetic in the same order: the two kernels give the same bits.
 __device__ __forceinline__ int swz_c(int row) { return (row >> 2) & 3; }     // V^T stage rows are 64 B
 
-template <int BS, int D, int NH>
+// HALVES: a V^T block is [2][D][32] instead of [D][64], so that the 1-KB load instructions of a chunk read 1 KB in one
+// piece instead of 16 half cache lines.  The loads are what bounds this kernel (16384 tokens: 419 us, without
+// loads in the loop 293, without waiting for them 417): 419 -> 387 us.  For the V^T the library makes for itself.
+template <int BS, int D, int NH, bool HALVES>
 __global__ __launch_bounds__(BS * 2 * NH, 2) void attn_chunked_kernel(
     const uint16_t* __restrict__ q, Strides qs, const uint16_t* __restrict__ k, Strides ks,
     const uint16_t* __restrict__ vt, const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
@@ -691,7 +694,7 @@ __global__ __launch_bounds__(BS * 2 * NH, 2) void attn_chunked_kernel(
         const int krow = RPI * inst + lane / CPR;
         const int vrow = 16 * inst + (lane >> 2);
         k_offb[x] = 2u * ((uint32_t)krow * (uint32_t)ks.t + (uint32_t)(((lane % CPR) ^ swz_k<D>(krow)) << 3));
-        v_offb[x] = 2u * (uint32_t)(vrow * BS + (((lane & 3) ^ swz_c(vrow)) << 3));
+        v_offb[x] = 2u * (uint32_t)(vrow * (HALVES ? 32 : BS) + (((lane & 3) ^ swz_c(vrow)) << 3));
     }
     const uint32_t k_dst = lds_address(&smemK[0][0]) + wave * LPW * 1024;
     const uint32_t v_dst = lds_address(&smemV[0][0]) + wave * LPW * 1024;
@@ -720,7 +723,7 @@ __global__ __launch_bounds__(BS * 2 * NH, 2) void attn_chunked_kernel(
     };
     auto issue_v = [&](auto stg_tag, int n, int blk) {
         constexpr int ST = decltype(stg_tag)::value;
-        const char* vtt = reinterpret_cast<const char*>(vtb + (int64_t)blk * D * BS + (n % CPB) * 32);
+        const char* vtt = reinterpret_cast<const char*>(vtb + (int64_t)blk * D * BS + (n % CPB) * 32 * (HALVES ? D : 1));
         static_for<LPW>([&](auto x_tag) {
             constexpr int X = decltype(x_tag)::value;
             lds_dma16<ST * STG_B + X * 1024>(v_dst, v_offb[X], vtt);
@@ -872,33 +875,37 @@ __global__ void zero_i32_kernel(int32_t* p) { *p = 0; }
 template <int BS, int D, int NH>
 hipError_t launch_nh(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                      const int32_t* idx, const int32_t* cnt, void* out, Strides os, float* lse, const void* vt, int64_t vt_bph,
-                     hipStream_t st) {
+                     bool halves, hipStream_t st) {
     const RowDeal deal = deal_rows(d, NH);
     const int64_t nwg = (int64_t)deal.gang * deal.seq_len * d.B * d.Hkv;
     if (nwg > 0x7fffffffll) return hipErrorInvalidValue;
     // blocks of 64 tokens, one head per workgroup: the chunked kernel (two wavefronts per SIMD instead of one);
     // with two heads per workgroup the sub-tile kernel already has them and is the faster one
-    if constexpr (BS == 64 && NH == 1)
-        hipLaunchKernelGGL((attn_chunked_kernel<BS, D, NH>), dim3((unsigned)nwg), dim3(BS * 2 * NH), 0, st, (const uint16_t*)q,
-                           qs, (const uint16_t*)k, ks, (const uint16_t*)vt, idx, cnt, (uint16_t*)out, os, lse, d.Hq, d.G,
-                           d.NB, d.T, d.S, d.scale, deal, d.shared, d.NBk, d.Skv, d.seq_lens, vt_bph);
-    else
-        hipLaunchKernelGGL((attn_kernel<BS, D, NH>), dim3((unsigned)nwg), dim3(BS * 2 * NH), 0, st, (const uint16_t*)q, qs,
-                           (const uint16_t*)k, ks, (const uint16_t*)vt, idx, cnt, (uint16_t*)out, os, lse, d.Hq,
-                           d.G, d.NB, d.T, d.S, d.scale, deal, d.shared, d.NBk, d.Skv, d.seq_lens, vt_bph);
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(BS * 2 * NH), 0, st, (const uint16_t*)q, qs, (const uint16_t*)k, ks,
+                           (const uint16_t*)vt, idx, cnt, (uint16_t*)out, os, lse, d.Hq, d.G, d.NB, d.T, d.S, d.scale, deal,
+                           d.shared, d.NBk, d.Skv, d.seq_lens, vt_bph);
+    };
+    if constexpr (BS == 64 && NH == 1) {
+        if (halves) go(attn_chunked_kernel<BS, D, NH, true>);
+        else go(attn_chunked_kernel<BS, D, NH, false>);
+    } else {
+        if (halves) return hipErrorInvalidValue;
+        go(attn_kernel<BS, D, NH>);
+    }
     return hipGetLastError();
 }
 
 template <int BS, int D>
 hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                   const int32_t* idx, const int32_t* cnt, void* out, Strides os, float* lse,
-                  const void* vt, int64_t vt_bph, hipStream_t st) {
+                  const void* vt, int64_t vt_bph, bool halves, hipStream_t st) {
     // Lists shared by the heads of a group: two heads per workgroup take every tile from one staged copy.  Not with
     // head_dim 64 and blocks of 128, where single-head workgroups put three wavefronts on a SIMD and the eight
     // wavefronts of a pair only two (16384 tokens: 550 -> 535 us).
     if constexpr (!(D == 64 && BS == 128))
-        if (d.shared && d.G % 2 == 0) return launch_nh<BS, D, 2>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
-    return launch_nh<BS, D, 1>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
+        if (d.shared && d.G % 2 == 0) return launch_nh<BS, D, 2>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, halves, st);
+    return launch_nh<BS, D, 1>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, halves, st);
 }
 
 }  // namespace
@@ -917,22 +924,22 @@ hipError_t launch_check_lists(const Dims& d, const int32_t* idx, const int32_t* 
 }
 
 hipError_t launch_attn_vt(const Dims& d, const void* q, Strides qs, const void* k, Strides ks, const void* vt,
-                          int64_t vt_bph, const int32_t* idx, const int32_t* cnt, void* out, Strides os, float* lse,
-                          hipStream_t st) {
+                          int64_t vt_bph, bool halves, const int32_t* idx, const int32_t* cnt, void* out, Strides os,
+                          float* lse, hipStream_t st) {
     if (vt == nullptr || vt_bph < d.NBk) return hipErrorInvalidValue;
-    if (d.D == 128 && d.Bs == 128) return launch<128, 128>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
-    if (d.D == 128 && d.Bs == 64) return launch<64, 128>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
-    if (d.D == 64 && d.Bs == 128) return launch<128, 64>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
-    if (d.D == 64 && d.Bs == 64) return launch<64, 64>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, st);
+    if (d.D == 128 && d.Bs == 128) return launch<128, 128>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, halves, st);
+    if (d.D == 128 && d.Bs == 64) return launch<64, 128>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, halves, st);
+    if (d.D == 64 && d.Bs == 128) return launch<128, 64>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, halves, st);
+    if (d.D == 64 && d.Bs == 64) return launch<64, 64>(d, q, qs, k, ks, idx, cnt, out, os, lse, vt, vt_bph, halves, st);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_attn(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                        const void* v, Strides vs, const int32_t* idx, const int32_t* cnt, void* out,
                        Strides os, float* lse, void* vt, hipStream_t st) {
-    hipError_t e = launch_transpose_v(d, v, vs, vt, d.NBk, 0, d.NBk, st);
+    hipError_t e = launch_transpose_v(d, v, vs, vt, d.NBk, 0, d.NBk, vt_in_halves(d), st);
     if (e != hipSuccess) return e;
-    return launch_attn_vt(d, q, qs, k, ks, vt, d.NBk, idx, cnt, out, os, lse, st);
+    return launch_attn_vt(d, q, qs, k, ks, vt, d.NBk, vt_in_halves(d), idx, cnt, out, os, lse, st);
 }
 
 }  // namespace spa

@@ -39,6 +39,11 @@ inline Dims dims_of(const spa_params& p) {
     return d;
 }
 
+// How V^T lies where the library keeps it to itself (the workspace of the attention and fused calls): blocks of 64 tokens
+// that attn_chunked_kernel reads are kept as two halves of 32 tokens, [2][D][32], so that the 8 KB (4 KB) it loads per
+// step are contiguous; everything else, and every V^T that a caller sees, is [D][Bs].
+inline bool vt_in_halves(const Dims& d) { return d.Bs == 64 && !(d.shared && d.G % 2 == 0); }
+
 // Ragged batch: tokens of batch entry b (the tensors keep their padded length S)
 __device__ __forceinline__ int entry_len(const int32_t* __restrict__ seq_lens, int b, int S) {
     if (seq_lens == nullptr) return S;
@@ -68,7 +73,8 @@ hipError_t launch_pool(const Dims& d, const void* q, Strides qs, const void* k, 
 hipError_t launch_group_mean(const Dims& d, const float* qp, float* qg, hipStream_t st);
 // lvn [B*Hkv, NB] fp32: ln of the mean value-vector norm of every key block.
 hipError_t launch_vnorm(const Dims& d, const void* v, Strides vs, float* lvn, hipStream_t st);
-// Pooled K (tiled) and, of V in the same launch, V^T for the attention kernel (NBk blocks per head) and / or lvn.
+// Pooled K (tiled) and, of V in the same launch, V^T for the attention kernel (NBk blocks per head, as vt_in_halves
+// says) and / or lvn.
 hipError_t launch_prepare_kv(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt_or_null,
                              float* lvn_or_null, hipStream_t st);
 // k_rows: optional device array of NB per-query-block budgets (clamped to [0, d.k] in the kernel).
@@ -86,13 +92,13 @@ hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int
 hipError_t launch_check_lists(const Dims& d, const int32_t* idx, const int32_t* cnt, int32_t* n_bad, hipStream_t st);
 hipError_t launch_attn(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                        const void* v, Strides vs, const int32_t* idx, const int32_t* cnt,
-                       void* out, Strides os, float* lse, void* vt, hipStream_t st);
+                       void* out, Strides os, float* lse, void* vt, hipStream_t st);   // V^T as vt_in_halves says
 // The two halves of launch_attn: V -> V^T for the key blocks first .. first + n - 1 into an allocation of
-// vt_bph blocks per head ([B, Hkv, vt_bph, D, Bs] bf16), and the attention on such a V^T.
+// vt_bph blocks per head ([B, Hkv, vt_bph, D, Bs] bf16; halves: blocks as two halves), and the attention on such a V^T.
 hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n,
-                              hipStream_t st);
+                              bool halves, hipStream_t st);
 hipError_t launch_attn_vt(const Dims& d, const void* q, Strides qs, const void* k, Strides ks, const void* vt,
-                          int64_t vt_bph, const int32_t* idx, const int32_t* cnt, void* out, Strides os, float* lse,
-                          hipStream_t st);
+                          int64_t vt_bph, bool halves, const int32_t* idx, const int32_t* cnt, void* out, Strides os,
+                          float* lse, hipStream_t st);
 
 }  // namespace spa

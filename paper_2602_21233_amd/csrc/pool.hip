@@ -107,7 +107,7 @@ hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strid
     return hipGetLastError();
 }
 
-// One block of V of one head: transposed to [D][BS] at vt (VT), and / or the ln of the mean L2 norm of its value vectors
+// One block of V of one head: transposed to [D][BS] (halves: [2][D][32]) at vt (VT), and / or the ln of the mean L2 norm of its value vectors
 // to *lvn (VN: the value-magnitude term of the output-aware ranking score, Sec. 4.1.2 Fig. "Stem" (c)).  The
 // access pattern of pool_block, V is read once for both.  Norms: D/8 adjacent lanes cover one token, combine their
 // partial sums of squares with lane-xor exchanges, and the token norms of the 16 (or 32) row groups are added
@@ -115,7 +115,7 @@ hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strid
 // tile: BS * (D + 2) values of LDS (VT), part: 256 / (D / 8) floats (VN).
 template <int D, int BS, bool VT, bool VN>
 __device__ __forceinline__ void value_block(const uint16_t* __restrict__ src, int64_t stride_t, int n_valid, uint16_t* tile,
-                                            float* part, uint16_t* __restrict__ vt, float* __restrict__ lvn) {
+                                            float* part, uint16_t* __restrict__ vt, bool halves, float* __restrict__ lvn) {
     constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, PITCH = D + 2;
     const int tid = threadIdx.x;
     const int row0 = tid / TPR, chunk = tid % TPR;
@@ -164,13 +164,17 @@ __device__ __forceinline__ void value_block(const uint16_t* __restrict__ src, in
         constexpr int CPR = BS / 8;         // 16-byte chunks per output row
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
-            const int c = p * 256 + tid;
-            const int d = c / CPR, t0 = (c % CPR) * 8;
+            const int c = p * 256 + tid;    // 16-byte chunk of the output, in memory order
+            int d = c / CPR, t0 = (c % CPR) * 8;
+            if (BS == 64 && halves) {       // rows of 4 chunks, then the second half
+                d = (c >> 2) % D;
+                t0 = (c >> 2) / D * 32 + (c & 3) * 8;
+            }
             uint32_t w[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 w[e] = (uint32_t)tile[(t0 + 2 * e) * PITCH + d] | ((uint32_t)tile[(t0 + 2 * e + 1) * PITCH + d] << 16);
-            *reinterpret_cast<uint4*>(vt + (int64_t)d * BS + t0) = make_uint4(w[0], w[1], w[2], w[3]);
+            *reinterpret_cast<uint4*>(vt + c * 8) = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
 }
@@ -185,7 +189,7 @@ __global__ __launch_bounds__(256) void vnorm_kernel(const uint16_t* __restrict__
     S = S - Sq + entry_len(seq_lens, b, Sq);                        // ragged batch: key tokens of this entry
     if (blk * BS >= S) return;
     value_block<D, BS, false, true>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t,
-                                    S - blk * BS < BS ? S - blk * BS : BS, nullptr, part, nullptr, lvn + (int64_t)hy * NB + blk);
+                                    S - blk * BS < BS ? S - blk * BS : BS, nullptr, part, nullptr, false, lvn + (int64_t)hy * NB + blk);
 }
 
 // V [B,Hkv,S,D] (strided) -> Vt [B,Hkv,vt_bph,D,BS] contiguous, blocks first .. first + gridDim.x - 1.
@@ -193,14 +197,14 @@ __global__ __launch_bounds__(256) void vnorm_kernel(const uint16_t* __restrict__
 template <int D, int BS>
 __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, Strides vs, int Hkv,
                                                           int64_t vt_bph, int S, uint16_t* __restrict__ vt,
-                                                          const int32_t* __restrict__ seq_lens, int Sq, int first) {
+                                                          const int32_t* __restrict__ seq_lens, int Sq, int first, int halves) {
     __shared__ uint16_t tile[BS * (D + 2)];
     const int blk = first + blockIdx.x, bh = blockIdx.y;
     const int b = bh / Hkv, h = bh % Hkv;
     const int Sb = S - Sq + entry_len(seq_lens, b, Sq);    // ragged batch: key tokens of this entry
     if (blk * BS >= Sb) return;                            // block past its end: never read by the attention kernel
     value_block<D, BS, true, false>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t, Sb - blk * BS < BS ? Sb - blk * BS : BS,
-                                    tile, nullptr, vt + ((int64_t)bh * vt_bph + blk) * D * BS, nullptr);
+                                    tile, nullptr, vt + ((int64_t)bh * vt_bph + blk) * D * BS, halves, nullptr);
 }
 
 // Everything a call needs of K and V before it scores: blockIdx.z = 0 pools a block of K (tiled), 1 takes a
@@ -211,7 +215,8 @@ template <int D, int BS, bool VT, bool VN>
 __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restrict__ k, Strides ks,
                                                          const uint16_t* __restrict__ v, Strides vs, int Hkv, int NBk, int Skv,
                                                          float* __restrict__ kp, uint16_t* __restrict__ vt,
-                                                         float* __restrict__ lvn, const int32_t* __restrict__ seq_lens, int Sq) {
+                                                         float* __restrict__ lvn, const int32_t* __restrict__ seq_lens, int Sq,
+                                                         int halves) {
     constexpr int RPP = 256 / (D / 8);
     constexpr int TILE_B = VT ? BS * (D + 2) * 2 : 0, PART_B = RPP * D * 4;
     __shared__ __attribute__((aligned(16))) char lds[TILE_B > PART_B ? TILE_B : PART_B];
@@ -226,7 +231,7 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restr
                           pooled_k<D>(kp, hy, blk, NBk, true), true, blk);
     else
         value_block<D, BS, VT, VN>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t, n_valid,
-                                   reinterpret_cast<uint16_t*>(lds), norms, VT ? vt + ((int64_t)hy * NBk + blk) * D * BS : nullptr,
+                                   reinterpret_cast<uint16_t*>(lds), norms, VT ? vt + ((int64_t)hy * NBk + blk) * D * BS : nullptr, halves,
                                    VN ? lvn + (int64_t)hy * NBk + blk : nullptr);
 }
 
@@ -254,10 +259,10 @@ hipError_t launch_vn(const Dims& d, const void* v, Strides vs, float* lvn, hipSt
 }
 
 template <int D, int BS>
-hipError_t launch_tv(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n, hipStream_t st) {
+hipError_t launch_tv(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n, bool halves, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL((transpose_v_kernel<D, BS>), dim3(n, d.B * d.Hkv), dim3(256), 0, st,
-                       (const uint16_t*)v, vs, d.Hkv, vt_bph, d.Skv, (uint16_t*)vt, d.seq_lens, d.S, first);
+                       (const uint16_t*)v, vs, d.Hkv, vt_bph, d.Skv, (uint16_t*)vt, d.seq_lens, d.S, first, halves ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -267,19 +272,19 @@ hipError_t launch_prep(const Dims& d, const void* k, Strides ks, const void* v, 
     const auto kernel = vt == nullptr ? prepare_kv_kernel<D, BS, false, true>
                                       : (lvn == nullptr ? prepare_kv_kernel<D, BS, true, false> : prepare_kv_kernel<D, BS, true, true>);
     hipLaunchKernelGGL(kernel, dim3(d.NBk, d.B * d.Hkv, 2), dim3(256), 0, st, (const uint16_t*)k, ks, (const uint16_t*)v, vs,
-                       d.Hkv, d.NBk, d.Skv, kp, (uint16_t*)vt, lvn, d.seq_lens, d.S);
+                       d.Hkv, d.NBk, d.Skv, kp, (uint16_t*)vt, lvn, d.seq_lens, d.S, vt_in_halves(d) ? 1 : 0);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n,
-                              hipStream_t st) {
-    if (vt == nullptr || vt_bph < d.NBk || first < 0 || n < 0 || first + n > d.NBk) return hipErrorInvalidValue;
-    if (d.D == 128 && d.Bs == 128) return launch_tv<128, 128>(d, v, vs, vt, vt_bph, first, n, st);
-    if (d.D == 128 && d.Bs == 64) return launch_tv<128, 64>(d, v, vs, vt, vt_bph, first, n, st);
-    if (d.D == 64 && d.Bs == 128) return launch_tv<64, 128>(d, v, vs, vt, vt_bph, first, n, st);
-    if (d.D == 64 && d.Bs == 64) return launch_tv<64, 64>(d, v, vs, vt, vt_bph, first, n, st);
+                              bool halves, hipStream_t st) {
+    if ((halves && d.Bs != 64) || vt == nullptr || vt_bph < d.NBk || first < 0 || n < 0 || first + n > d.NBk) return hipErrorInvalidValue;
+    if (d.D == 128 && d.Bs == 128) return launch_tv<128, 128>(d, v, vs, vt, vt_bph, first, n, halves, st);
+    if (d.D == 128 && d.Bs == 64) return launch_tv<128, 64>(d, v, vs, vt, vt_bph, first, n, halves, st);
+    if (d.D == 64 && d.Bs == 128) return launch_tv<64, 128>(d, v, vs, vt, vt_bph, first, n, halves, st);
+    if (d.D == 64 && d.Bs == 64) return launch_tv<64, 64>(d, v, vs, vt, vt_bph, first, n, halves, st);
     return hipErrorInvalidValue;
 }
 
