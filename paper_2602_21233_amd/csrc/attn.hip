@@ -403,7 +403,8 @@ __device__ __forceinline__ void group_weights(const f32x16& s_cur, float c, floa
 // lists shared by the group (one list per KV head): the heads then walk the same key blocks, and
 // two of them take every K and V^T sub-tile from one staged copy, which halves the tile traffic
 // (L2 -> LDS) per FLOP; with blocks of 64 tokens it also puts two wavefronts on every SIMD.
-template <int BS, int D, int NH>
+// HALVES: a V^T block is [2][D][BS / 2], see vt_in_halves.
+template <int BS, int D, int NH, bool HALVES>
 __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)) void attn_kernel(
     const uint16_t* __restrict__ q, Strides qs, const uint16_t* __restrict__ k, Strides ks,
     const uint16_t* __restrict__ vt, const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
@@ -412,6 +413,7 @@ __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)
     constexpr int NWH = BS / 32;        // wavefronts per head
     constexpr int NW = NWH * NH;        // wavefronts
     constexpr int NSUB = BS / KT;       // sub-tiles per key block
+    static_assert(!HALVES || NSUB == 2, "a half block is a sub-tile");
     constexpr int DS = D / 16;          // 16-dim slices of a key row = MFMAs of one logits tile
     constexpr int DT = D / 32;          // 32-row tiles of O^T = MFMAs per 16 keys of the second product
     constexpr int NG = 2 * DS;          // MFMAs (= instruction groups) of a pipeline step
@@ -457,7 +459,7 @@ __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)
         const int krow = RPI * inst + lane / CPR;
         const int vrow = 8 * inst + (lane >> 3);
         k_offb[x] = 2u * ((uint32_t)krow * (uint32_t)ks.t + (uint32_t)(((lane % CPR) ^ swz_k<D>(krow)) << 3));
-        v_offb[x] = 2u * (uint32_t)(vrow * BS + (((lane & 7) ^ swz_v(vrow)) << 3));
+        v_offb[x] = 2u * (uint32_t)(vrow * (HALVES ? KT : BS) + (((lane & 7) ^ swz_v(vrow)) << 3));
     }
     // K and V^T sub-tiles are staged separately: K runs one sub-tile ahead of V^T because the
     // logits are produced two 32-key chunks before the second product consumes them.
@@ -489,7 +491,7 @@ __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)
     };
     auto issue_v = [&](auto buf_tag, int st, int blk) {
         constexpr int BUF = decltype(buf_tag)::value;
-        const char* vtt = reinterpret_cast<const char*>(vtb + (int64_t)blk * D * BS + (st % NSUB) * KT);
+        const char* vtt = reinterpret_cast<const char*>(vtb + (int64_t)blk * D * BS + (st % NSUB) * KT * (HALVES ? D : 1));
         static_for<LPW>([&](auto x_tag) {
             constexpr int X = decltype(x_tag)::value;
             lds_dma16<BUF * TILE_B + X * 1024>(v_dst, v_offb[X], vtt);
@@ -890,8 +892,13 @@ hipError_t launch_nh(const Dims& d, const void* q, Strides qs, const void* k, St
         if (halves) go(attn_chunked_kernel<BS, D, NH, true>);
         else go(attn_chunked_kernel<BS, D, NH, false>);
     } else {
-        if (halves) return hipErrorInvalidValue;
-        go(attn_kernel<BS, D, NH>);
+        if constexpr (BS == 128 && D == 64) {
+            if (halves) go(attn_kernel<BS, D, NH, true>);
+            else go(attn_kernel<BS, D, NH, false>);
+        } else {
+            if (halves) return hipErrorInvalidValue;
+            go(attn_kernel<BS, D, NH, false>);
+        }
     }
     return hipGetLastError();
 }

@@ -39,10 +39,12 @@ inline Dims dims_of(const spa_params& p) {
     return d;
 }
 
-// How V^T lies where the library keeps it to itself (the workspace of the attention and fused calls): blocks of 64 tokens
-// that attn_chunked_kernel reads are kept as two halves of 32 tokens, [2][D][32], so that the 8 KB (4 KB) it loads per
-// step are contiguous; everything else, and every V^T that a caller sees, is [D][Bs].
-inline bool vt_in_halves(const Dims& d) { return d.Bs == 64 && !(d.shared && d.G % 2 == 0); }
+// How V^T lies where the library keeps it to itself (the workspace of the attention and fused calls): [2][D][Bs / 2], the
+// two halves of a block's tokens one after the other, where the attention kernel loads a half block at a time and
+// gains from finding it in one piece: blocks of 64 tokens in attn_chunked_kernel (419 -> 387 us at 16384 tokens)
+// and head_dim 64 with blocks of 128 (560 -> 540 us; head_dim 128: 1.95 ms either way at 32768 tokens).  Everything
+// else, and every V^T that a caller sees, is [D][Bs].
+inline bool vt_in_halves(const Dims& d) { return d.Bs == 64 ? !(d.shared && d.G % 2 == 0) : d.D == 64; }
 
 // Ragged batch: tokens of batch entry b (the tensors keep their padded length S)
 __device__ __forceinline__ int entry_len(const int32_t* __restrict__ seq_lens, int b, int S) {

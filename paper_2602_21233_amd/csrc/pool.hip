@@ -107,7 +107,7 @@ hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strid
     return hipGetLastError();
 }
 
-// One block of V of one head: transposed to [D][BS] (halves: [2][D][32]) at vt (VT), and / or the ln of the mean L2 norm of its value vectors
+// One block of V of one head: transposed to [D][BS] (halves: [2][D][BS / 2]) at vt (VT), and / or the ln of the mean L2 norm of its value vectors
 // to *lvn (VN: the value-magnitude term of the output-aware ranking score, Sec. 4.1.2 Fig. "Stem" (c)).  The
 // access pattern of pool_block, V is read once for both.  Norms: D/8 adjacent lanes cover one token, combine their
 // partial sums of squares with lane-xor exchanges, and the token norms of the 16 (or 32) row groups are added
@@ -166,9 +166,10 @@ __device__ __forceinline__ void value_block(const uint16_t* __restrict__ src, in
         for (int p = 0; p < PASSES; ++p) {
             const int c = p * 256 + tid;    // 16-byte chunk of the output, in memory order
             int d = c / CPR, t0 = (c % CPR) * 8;
-            if (BS == 64 && halves) {       // rows of 4 chunks, then the second half
-                d = (c >> 2) % D;
-                t0 = (c >> 2) / D * 32 + (c & 3) * 8;
+            if (halves) {                   // rows half as long, then the second half of the tokens
+                constexpr int HC = CPR / 2;
+                d = c / HC % D;
+                t0 = c / HC / D * (BS / 2) + c % HC * 8;
             }
             uint32_t w[4];
 #pragma unroll
@@ -280,7 +281,7 @@ hipError_t launch_prep(const Dims& d, const void* k, Strides ks, const void* v, 
 
 hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt, int64_t vt_bph, int first, int n,
                               bool halves, hipStream_t st) {
-    if ((halves && d.Bs != 64) || vt == nullptr || vt_bph < d.NBk || first < 0 || n < 0 || first + n > d.NBk) return hipErrorInvalidValue;
+    if (vt == nullptr || vt_bph < d.NBk || first < 0 || n < 0 || first + n > d.NBk) return hipErrorInvalidValue;
     if (d.D == 128 && d.Bs == 128) return launch_tv<128, 128>(d, v, vs, vt, vt_bph, first, n, halves, st);
     if (d.D == 128 && d.Bs == 64) return launch_tv<128, 64>(d, v, vs, vt, vt_bph, first, n, halves, st);
     if (d.D == 64 && d.Bs == 128) return launch_tv<64, 128>(d, v, vs, vt, vt_bph, first, n, halves, st);
