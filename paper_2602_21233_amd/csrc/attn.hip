@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "row_deal.hpp"
 
 namespace spa {
 namespace {
@@ -86,53 +87,6 @@ __device__ __forceinline__ int swap_bits23(int x) { return (x & ~12) | ((x & 4) 
 // and clusters the VALU work, so the wave stalls on the LDS latency once per MFMA.
 #define SPA_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-// Which XCD serves which rows.  Workgroup ids go round robin over the 8 XCDs and are dispatched in id order,
-// so the XCDs advance through their sequences in step: what has to be equal is the work of the rows that
-// sit at the same position of the 8 sequences.
-// A KV head is served by a gang of `gang` XCDs (8, 4, 2 or 1), 8 / gang heads side by side.  With long sequences it is all
-// eight: the whole chip then works through one head after the other, and what an XCD has in flight
-// are rows of one head anyway.  With few query blocks an eighth of a head's rows does not fill an XCD, which would have
-// rows of several heads in flight and fetch each of their K and V^T tiles for a few rows only; a smaller gang
-// puts more rows of one head behind one L2.
-// Within the gang:
-//   - the n_dense rows of a Tri-shape strip (each visits up to NB blocks) are dealt one by one;
-//   - the other rows are dealt in runs of `run` consecutive rows, last row first; with `snake` every
-//     other round of runs goes backwards (which rounds: alternating with the KV head), so that the XCD
-//     that gets the longest row of one round gets the shortest of the next.
-// Neighbouring rows share their local-window blocks in the XCD's L2, which favours runs of 8 once K and
-// V^T of a head outgrow that L2 (4 MB).  But the XCD with the most rows decides: 16 query blocks in runs of
-// 8 kept two XCDs busy and six idle.  So the runs get shorter until no more than a sixteenth of
-// the dealt places are empty, and rows whose length varies with the position (strided columns, dense
-// strip) are dealt one by one, as are those of heads that fit the L2 whatever the deal.  The snake is
-// for calls in which the ramp of the first T rows, which are shorter than T, is an eighth of the rows or
-// more; elsewhere it only moves neighbouring rows apart.
-// Measured against runs of 8, all forwards, whole calls with 32/8 heads: 1999 tokens 190 -> 74 us; 2048 queries over a
-// prefix of 98304 tokens 1048 -> 368 us; 6 ragged prompts of up to 6000 tokens, blocks of 64, 727 -> 591 us;
-// 32768 tokens 2.10 -> 2.03 ms; group-shared lists, 16384 tokens, D = 64, 628 -> 582 us.  The snake at 131072
-// tokens (a ramp of 69 of 1024 rows): 17.05 -> 17.18 ms, which is why it is left out there.  Gangs, attention kernel
-// alone: 1999 tokens 58 -> 50 us, 2048 queries over the prefix 306 -> 286 us, 1024 queries 174 -> 169 us.
-// seq_len = workgroups per (head, XCD) in the grid; surplus workgroups exit at once.
-struct RowDeal {
-    int gang, n_dense, run, snake, seq_len;
-};
-
-// nh: query heads served by one workgroup (their workgroups per row position number G / nh)
-RowDeal deal_rows(const Dims& d, int nh) {
-    RowDeal r;
-    r.n_dense = d.n_dense < d.NB ? d.n_dense : d.NB;
-    const int n = d.NB - r.n_dense;                       // rows dealt in runs
-    const int slots = 32 * (d.Bs == 64 ? 4 : 2) / nh;     // workgroups an XCD has in flight
-    r.gang = 8;
-    while (r.gang > 1 && (int64_t)d.NB * (d.G / nh) < (int64_t)slots * r.gang && d.B * d.Hkv % (16 / r.gang) == 0) r.gang >>= 1;
-    const bool fits_l2 = (int64_t)d.Skv * d.D * 4 <= 4 << 20;         // K and V^T of a head, bf16
-    r.run = (d.stride > 0 || d.n_dense > 0 || fits_l2) ? 1 : 8;
-    while (r.run > 1 && (n + r.gang * r.run - 1) / (r.gang * r.run) * (r.gang * r.run) > n + n / 16) r.run >>= 1;
-    r.snake = r.run == 1 || 8 * (int64_t)d.T >= d.NBk;
-    const int runs = (n + r.run - 1) / r.run;
-    r.seq_len = ((r.n_dense + r.gang - 1) / r.gang + (runs + r.gang - 1) / r.gang * r.run) * (d.G / nh);
-    return r;
-}
-
 template <int N>
 using IC = std::integral_constant<int, N>;
 // f(IC<0>{}), ..., f(IC<N-1>{})
@@ -163,30 +117,13 @@ struct RowOfWorkgroup {
 template <int BS, int NH>
 __device__ __forceinline__ bool row_of_workgroup(const RowDeal& deal, int Hq, int G, int NB, int S, int Skv_max,
                                                  const int32_t* __restrict__ seq_lens, RowOfWorkgroup& r) {
-    const int gang = deal.gang;
-    const int xcd = blockIdx.x & (gang - 1);              // member of the gang
-    const int slot = blockIdx.x >> 3;
-    const int head_slot = slot / deal.seq_len * (8 / gang) + (blockIdx.x & 7) / gang;     // b * Hkv + kv head
-    const int within = slot % deal.seq_len;
-    const int GH = G / NH;                                // workgroups per row position
-    const int pos = within / GH;                          // position in this XCD's row sequence
-    const int n_single = (deal.n_dense + gang - 1) / gang;
-    if (pos < n_single) {
-        const int hidx = pos * gang + xcd;
-        if (hidx >= deal.n_dense) return false;
-        r.i = NB - 1 - hidx;
-    } else {
-        const int rr = pos - n_single;
-        const int round = rr / deal.run;
-        const int x = (deal.snake & (round ^ head_slot)) ? gang - 1 - xcd : xcd;
-        const int ridx = (round * gang + x) * deal.run + rr % deal.run;
-        if (ridx >= NB - deal.n_dense) return false;
-        r.i = NB - deal.n_dense - 1 - ridx;
-    }
+    DealtRow at;
+    if (!dealt_row(deal, G / NH, NB, (int)blockIdx.x, at)) return false;
     const int Hkv = Hq / G;
-    r.kvh = head_slot % Hkv;
-    r.b = head_slot / Hkv;
-    r.first_head = (within % GH) * NH;
+    r.i = at.i;
+    r.kvh = at.head_slot % Hkv;
+    r.b = at.head_slot / Hkv;
+    r.first_head = at.turn * NH;
     r.Sb = entry_len(seq_lens, r.b, S);
     if (r.i * BS >= r.Sb) return false;
     r.Skv = Skv_max - S + r.Sb;

@@ -1,0 +1,80 @@
+"""The deal of an attention launch (csrc/row_deal.hpp, compiled for the host): which XCD serves which rows."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2602_21233_amd import binding, build
+
+SHIM = r"""
+#include "row_deal.hpp"
+// every workgroup of the launch: (head_slot, query block, turn), or -1 three times for a surplus one
+extern "C" int deal(const spa_params* p, int nh, int* gang, int* out, int cap) {
+    const spa::Dims d = spa::dims_of(*p);
+    const spa::RowDeal r = spa::deal_rows(d, nh);
+    const int nwg = r.gang * r.seq_len * d.B * d.Hkv;
+    *gang = r.gang;
+    for (int x = 0; x < nwg && x < cap; ++x) {
+        spa::DealtRow at;
+        const bool some = spa::dealt_row(r, d.G / nh, d.NB, x, at);
+        out[3 * x] = some ? at.head_slot : -1;
+        out[3 * x + 1] = some ? at.i : -1;
+        out[3 * x + 2] = some ? at.turn : -1;
+    }
+    return nwg;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def deal(tmp_path_factory):
+    d = tmp_path_factory.mktemp("deal")
+    (d / "shim.hip").write_text(SHIM)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", build.CSRC,
+                    str(d / "shim.hip"), "-o", str(d / "shim.so")], check=True, capture_output=True)
+    lib = ctypes.CDLL(str(d / "shim.so"))
+
+    def rows(nh=1, ragged=False, **kw):
+        """gang, [workgroups, 3]"""
+        base = dict(batch=1, n_q_heads=8, n_kv_heads=2, seq_len=2048, head_dim=128, block_size=128, n_sink_blocks=1,
+                    n_local_blocks=4, top_k_blocks=64)
+        base.update(kw)
+        p = binding.make_params(**base)
+        p.seq_lens = 1 if ragged else None              # only asked whether there is one
+        gang = ctypes.c_int()
+        n = lib.deal(ctypes.byref(p), nh, ctypes.byref(gang), None, 0)
+        out = np.empty((n, 3), dtype=np.int32)
+        assert lib.deal(ctypes.byref(p), nh, ctypes.byref(gang), ctypes.c_void_p(out.ctypes.data), n) == n
+        return gang.value, out
+    return rows
+
+
+# Entries of a ragged batch differ in length, so heads of different entries must not sit side by side on the XCDs: the XCDs
+# of the short ones would idle while one of them serves the longest entry alone.
+@pytest.mark.parametrize("block_size", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (8, 1), (8, 2), (16, 2), (28, 4), (32, 8), (12, 3)])
+@pytest.mark.parametrize("S", [100, 900, 1900, 3900, 9000])
+def test_the_xcds_serve_one_entry_of_a_ragged_batch_at_a_time(deal, block_size, Hq, Hkv, S):
+    _, wg = deal(ragged=True, batch=8, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=S, block_size=block_size)
+    entry = np.where(wg[:, 0] >= 0, wg[:, 0] // Hkv, -1).reshape(-1, 8)      # workgroups 8 s .. 8 s + 7: one for each XCD
+    for at_once in entry:
+        assert len(set(at_once[at_once >= 0])) <= 1
+
+
+# One long entry among short ones: the XCD with the most key blocks to visit has at most one row (of all query
+# heads of its group) more than its share, where one XCD serving an entry alone has up to eight times it.
+@pytest.mark.parametrize("block_size", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (8, 1), (8, 2), (16, 2)])
+@pytest.mark.parametrize("S", [1900, 3900])
+def test_a_long_entry_of_a_ragged_batch_is_spread_over_the_xcds(deal, block_size, Hq, Hkv, S):
+    lens = [S] + [S // 12] * 7
+    _, wg = deal(ragged=True, batch=8, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=S, block_size=block_size)
+    work = np.zeros(8)
+    for x, (head_slot, i, _) in enumerate(wg):
+        if head_slot >= 0 and i * block_size < lens[head_slot // Hkv]:
+            work[x % 8] += i + 1                                     # every causal block: T is larger here
+    longest_row = -(-S // block_size) * (Hq // Hkv)
+    assert work.max() <= work.mean() + longest_row
