@@ -1,0 +1,50 @@
+// How many query blocks (rows) a workgroup of the score / selection kernel takes: the rule, for the launcher.
+#pragma once
+#include "common.hpp"
+
+namespace spa {
+
+// 4, 8 or 16; 16 with more than 1024 key blocks is the kernel that scores the columns in two chunks.  Fewer rows as rows get longer: up
+// to 1024 blocks R * (NB padded) fp32 scores stay within 66 KB of LDS, so that two 8-wave workgroups share a CU (measured at
+// 131072 tokens: 125 -> 106 us against 32 rows with one 8-wave workgroup per CU).
+inline int score_rows(const Dims& d) {
+    const int64_t heads = (int64_t)d.B * d.Hq, rows = heads * d.NB;
+    const bool plain = d.gamma_q16 < 0;
+    if (d.NBk > 2048) return 4;
+    // Few rows (a chunk over a long prefix, a short prompt): 4 per workgroup, or most CUs would be idle while a few
+    // pool, score and select 8 or 16 rows one after the other.  Up to 1024 rows, where 8 per workgroup give half of the
+    // CUs one; 1.05 to 1.1 times the time of 8 from 2048 rows on.  Whole select calls, 32 heads: 2048 queries over 29952
+    // tokens 25.9 -> 23.1 us, over 98304 tokens 67 -> 53 (34 of them pool K), over 131072 tokens 85 -> 67.
+    // (A mass budget keeps the larger groups: its second search makes the kernels twice as many, for rare calls.)
+    if (plain && rows <= 1024) return 4;
+    // up to 512 blocks: 8 rows per workgroup give the chip more rounds of workgroups, so that one round's
+    // streaming overlaps another's scoring (0.065 -> 0.062 ms at 32768 tokens, 0.135 -> 0.124 ms at 65536)
+    if (d.NBk <= 512) return 8;
+    const bool two_chunks = d.NBk > 1024;
+    if (!plain) return two_chunks ? 8 : 16;
+    // 513 .. 2048 blocks.  Many rows: 16, as 8 re-read the pooled K twice as often (blocks of 128: 0.20 against 0.19 ms at 768
+    // blocks and 24576 rows, 0.29 against 0.26 ms at 1024 and 32768; 0.84 against 0.78 ms at 262144 tokens and 81920 rows, where
+    // 16 rows are scored in two chunks of 1024 columns to keep two workgroups per CU).
+    if (rows > (two_chunks ? 32768 : 16384)) return 16;
+    // Fewer: more workgroups, unless they only make more rounds.  With blocks of 128 the query stream, twice as long for a row,
+    // hides the rounds, and 8 are the better or equal choice (8192 queries over 98304 tokens, 2048 rows, 71 -> 63 us; 98304 tokens
+    // of 8 heads 85 -> 79; 131072 of 16 heads, 16384 rows, 132 -> 121; 262144 of 16 heads, 32768 rows, 295 -> 291; at worst
+    // 180 -> 185, 25600 queries over 230400 tokens).
+    if (d.Bs == 128) return 8;
+    // With blocks of 64 the rounds of 512 workgroups (two per CU) decide: `depth` is how many rows a place works through one
+    // after the other, and 8 rows are for calls in which that is less of them.  Up to 1.5 rounds of 8-row workgroups
+    // (6144 rows) they win whatever the count, by 2 to 35 %.  With one round of 16-row workgroups they win where rows
+    // differ in length, dealt longest first (52413 tokens of 8 / 1 heads 42 -> 40 us), and lose over a prefix at least as long as
+    // the chunk (12800 queries over 51200 tokens, 32 heads, 74 against 78 us).  With more rounds they win where the
+    // depth says so (95997 tokens of 8 / 8 heads 121 -> 110 us), except in one chunk with head_dim 128 and rows that
+    // differ (40960 tokens of 16 heads 50 against 53 us), and lose otherwise (25600 queries over 38400 tokens, 40 heads, 110
+    // against 118 us; from 16385 rows on 182 against 193 us at 1247 blocks and 28288 rows).
+    const int64_t wg8 = heads * ((d.NB + 7) / 8), wg16 = heads * ((d.NB + 15) / 16);
+    const bool even = d.off >= d.NB;                       // the shortest row has at least half the blocks of the longest
+    if (wg8 <= 768) return 8;
+    if (wg16 <= 512) return even ? 16 : 8;
+    const int64_t depth8 = (wg8 + 511) / 512 * 8, depth16 = (wg16 + 511) / 512 * 16;
+    return depth8 < depth16 && rows <= 16384 && (two_chunks || even || d.D == 64) ? 8 : 16;
+}
+
+}  // namespace spa

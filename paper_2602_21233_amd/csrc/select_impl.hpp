@@ -43,6 +43,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "score_rows.hpp"
 
 namespace spa {
 namespace {
@@ -1209,37 +1210,11 @@ hipError_t launch_plain(const ScoreCall& c) {
 
 template <int D>
 hipError_t launch_mfma_d(const ScoreCall& c) {
-    // rows per workgroup shrink as rows get longer: up to 1024 blocks R * (NB padded) fp32 scores stay
-    // within 66 KB of LDS, so that two 8-wave workgroups share a CU (measured at 131072 tokens:
-    // 125 -> 106 us against 32 rows with one 8-wave workgroup per CU)
-    const int NBk = c.d.NBk;
-    const int64_t rows = (int64_t)c.d.B * c.d.Hq * c.d.NB;
-    const bool plain = c.d.gamma_q16 < 0;
-    // Few rows (a chunk over a long prefix, a short prompt): 4 per workgroup, or most CUs would be idle while a few
-    // pool, score and select 8 or 16 rows one after the other.  Up to 1024 rows, where 8 per workgroup give half of the
-    // CUs one; 1.05 to 1.1 times the time of 8 from 2048 rows on.  Whole select calls, 32 heads: 2048 queries over 29952
-    // tokens 25.9 -> 23.1 us, over 98304 tokens 67 -> 53 (34 of them pool K), over 131072 tokens 85 -> 67.
-    // (A mass budget keeps the larger groups: its second search makes the kernels twice as many, for rare calls.)
-    if (plain && rows <= 1024) {
-        if (NBk <= 256) return launch_plain<D, 4, 4>(c);
-        if (NBk <= 512) return launch_plain<D, 4, 8>(c);
-        if (NBk <= 1024) return launch_plain<D, 4, 16>(c);
-        if (NBk <= 2048) return launch_plain<D, 4, 32>(c);
-    }
-    // up to 512 blocks: 8 rows per workgroup give the chip more rounds of workgroups, so that one round's
-    // streaming overlaps another's scoring (0.065 -> 0.062 ms at 32768 tokens, 0.135 -> 0.124 ms at 65536)
-    if (NBk <= 256) return launch_mfma<D, 8, 4>(c);
-    if (NBk <= 512) return launch_mfma<D, 8, 8>(c);
-    // From 513 blocks 8 rows re-read the pooled K twice as often as 16 (0.20 against 0.19 ms at 768 blocks and
-    // 24576 rows, 0.29 against 0.26 ms at 1024 and 32768), but with fewer rows the rounds decide again: 8192 queries over
-    // 98304 tokens (2048 rows) 71 -> 63 us, 98304 tokens of 8 heads (6144 rows) 85 -> 79 us, 131072 tokens of 16 heads
-    // (16384 rows) 132 -> 121 us; equal at 20480 rows of 640 blocks
-    if (NBk <= 1024) return rows > 16384 || !plain ? launch_mfma<D, 16, 16>(c) : launch_plain<D, 8, 16>(c);
-    // 1025 .. 2048 blocks: 16 rows per workgroup with the columns scored in two chunks of 1024, still two
-    // workgroups per CU (0.84 -> 0.78 ms at 262144 tokens and 81920 rows against 8 rows scored in one pass, which
-    // is what fewer rows take, and a mass budget always: 16384 queries over 131072 tokens (4096 rows) 103 -> 97 us, 65536
-    // (16384 rows) 240 -> 223 us, 262144 tokens of 16 heads (32768 rows) 295 -> 291 us)
-    if (NBk <= 2048) return rows > 32768 && plain ? launch_chunked<D, 2>(c) : launch_mfma<D, 8, 32>(c);
+    const int NBk = c.d.NBk, R = score_rows(c.d);
+    if (NBk <= 256) return R == 4 ? launch_plain<D, 4, 4>(c) : launch_mfma<D, 8, 4>(c);
+    if (NBk <= 512) return R == 4 ? launch_plain<D, 4, 8>(c) : launch_mfma<D, 8, 8>(c);
+    if (NBk <= 1024) return R == 4 ? launch_plain<D, 4, 16>(c) : R == 8 ? launch_plain<D, 8, 16>(c) : launch_mfma<D, 16, 16>(c);
+    if (NBk <= 2048) return R == 4 ? launch_plain<D, 4, 32>(c) : R == 8 ? launch_mfma<D, 8, 32>(c) : launch_chunked<D, 2>(c);
     return launch_mfma<D, 4, 64>(c);
 }
 

@@ -1,12 +1,11 @@
 """The deal of an attention launch (csrc/row_deal.hpp, compiled for the host): which XCD serves which rows."""
 import ctypes
-import os
-import subprocess
 
 import numpy as np
 import pytest
 
-from paper_2602_21233_amd import binding, build
+from host_shim import compile_shim
+from paper_2602_21233_amd import binding
 
 SHIM = r"""
 #include "row_deal.hpp"
@@ -30,12 +29,7 @@ extern "C" int deal(const spa_params* p, int nh, int* gang, int* out, int cap) {
 
 @pytest.fixture(scope="module")
 def deal(tmp_path_factory):
-    d = tmp_path_factory.mktemp("deal")
-    (d / "shim.hip").write_text(SHIM)
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", build.CSRC,
-                    str(d / "shim.hip"), "-o", str(d / "shim.so")], check=True, capture_output=True)
-    lib = ctypes.CDLL(str(d / "shim.so"))
+    lib = compile_shim(tmp_path_factory.mktemp("deal"), SHIM)
 
     def rows(nh=1, ragged=False, **kw):
         """gang, [workgroups, 3]"""

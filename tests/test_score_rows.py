@@ -1,0 +1,57 @@
+"""Rows per workgroup of the score kernel (csrc/score_rows.hpp, compiled for the host)."""
+import ctypes
+
+import pytest
+
+from host_shim import compile_shim
+from paper_2602_21233_amd import binding
+
+SHIM = r"""
+#include "score_rows.hpp"
+extern "C" int score_rows(const spa_params* p, int mass) {
+    spa::Dims d = spa::dims_of(*p);
+    d.gamma_q16 = mass ? 1 : -1;
+    return spa::score_rows(d);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rows_of(tmp_path_factory):
+    lib = compile_shim(tmp_path_factory.mktemp("score_rows"), SHIM)
+
+    def ask(NB, NBk, heads, Bs=64, D=128, mass=False):
+        p = binding.make_params(batch=1, n_q_heads=heads, n_kv_heads=1, seq_len=NB * Bs - 3, head_dim=D, block_size=Bs, n_sink_blocks=1,
+                                n_local_blocks=4, top_k_blocks=64, kv_prefix_len=(NBk - NB) * Bs)
+        return lib.score_rows(ctypes.byref(p), int(mass))
+    return ask
+
+
+# Blocks of 64: calls that 8 rows per workgroup slow down (measured, whole select calls, 16 against 8 rows) keep 16.
+@pytest.mark.parametrize("NB,NBk,heads,D", [
+    (200, 1000, 32, 128),      # 74 against 78 us
+    (200, 2000, 32, 128),      # 123 against 132
+    (400, 640, 40, 128),       # 87 against 93
+    (400, 2000, 40, 128),      # 187 against 199
+    (640, 640, 16, 128),       # 50.4 against 52.6
+    (1000, 1000, 32, 128),
+    (1771, 1771, 16, 64),      # 126 against 134
+    (884, 1247, 32, 128),      # 182 against 193
+    (2000, 2000, 16, 64),      # 148 against 157
+])
+def test_sixteen_rows_where_eight_are_slower(rows_of, NB, NBk, heads, D):
+    assert rows_of(NB, NBk, heads, D=D) == 16
+
+
+# ... and those that gain from them take 8 (or 4).
+@pytest.mark.parametrize("NB,NBk,heads,Bs,D,want", [
+    (100, 1000, 16, 64, 128, 8), (200, 1000, 40, 64, 128, 8), (640, 640, 8, 64, 128, 8), (819, 819, 8, 64, 128, 8),
+    (1500, 1500, 8, 64, 128, 8), (400, 640, 16, 128, 128, 8), (1000, 1000, 16, 128, 128, 8), (2048, 2048, 16, 128, 128, 8),
+    (32, 1000, 32, 64, 128, 4), (32, 2048, 32, 128, 64, 4), (33, 2048, 32, 128, 64, 8), (128, 128, 8, 64, 64, 4), (129, 129, 8, 64, 64, 8),
+    (512, 512, 40, 128, 128, 8), (1024, 1024, 32, 128, 128, 16), (2048, 2048, 40, 128, 128, 16), (2049, 2049, 40, 128, 128, 4)])
+def test_fewer_rows_where_they_are_faster(rows_of, NB, NBk, heads, Bs, D, want):
+    assert rows_of(NB, NBk, heads, Bs, D) == want
+
+
+def test_a_mass_budget_keeps_its_groups(rows_of):
+    assert [rows_of(8, n, 4, mass=True) for n in (64, 256, 512, 513, 1024, 1025, 2048, 2049, 4096)] == [8, 8, 8, 16, 16, 8, 8, 4, 4]
