@@ -149,7 +149,7 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(ref):
-    if _raw_stream is not None:
+    if _raw_stream is not None and ref.is_cuda:      # a CPU tensor gets torch's own error
         return ctypes.c_void_p(_raw_stream(ref.device.index))
     return ctypes.c_void_p(torch.cuda.current_stream(ref.device).cuda_stream)
 

@@ -31,3 +31,12 @@ def test_a_head_dim_axis_that_is_not_contiguous_is_refused():
     q = torch.empty((1, 2, 128, 64), dtype=torch.bfloat16).transpose(2, 3)
     with pytest.raises(AssertionError):
         binding._params_from(q, q, 64, 1, 1, 1, None)
+
+
+def test_the_stream_of_a_cpu_tensor_is_refused_by_torch(monkeypatch):
+    """Lists on the CPU, say: torch.cuda.current_stream names what is wrong, the raw call only says "invalid argument"."""
+    def current_stream(device=None):
+        raise ValueError(f"Expected a cuda device, but got: {device}")
+    monkeypatch.setattr(torch.cuda, "current_stream", current_stream)
+    with pytest.raises(ValueError, match="Expected a cuda device, but got: cpu"):
+        binding._stream(torch.empty(1, dtype=torch.int32))
