@@ -72,3 +72,24 @@ def test_a_long_entry_of_a_ragged_batch_is_spread_over_the_xcds(deal, block_size
             work[x % 8] += i + 1                                     # every causal block: T is larger here
     longest_row = -(-S // block_size) * (Hq // Hkv)
     assert work.max() <= work.mean() + longest_row
+
+
+# Whatever the gang, the runs and the snake: every workgroup of every row of every head is dealt once.
+@pytest.mark.parametrize("D,Bs,nh", [(128, 64, 1), (64, 64, 2), (128, 128, 1), (128, 128, 2), (64, 128, 1)])
+@pytest.mark.parametrize("B,Hkv,ragged", [(1, 3, False), (1, 8, False), (2, 2, False), (2, 2, True), (8, 1, False), (8, 1, True), (3, 4, True)])
+def test_every_row_is_dealt_once(deal, D, Bs, nh, B, Hkv, ragged):
+    seen = set()
+    for NB, P, kw in ((1, 0, {}), (2, 0, {}), (9, 0, {}), (16, 72, {}), (17, 72, {}), (46, 72, {}), (92, 144, {}), (64, 288, {}), (23, 0, dict(n_dense_q_blocks=3)),
+                      (23, 288, dict(n_dense_q_blocks=11)), (11, 0, dict(n_dense_q_blocks=40)), (130, 0, dict(stride_blocks=7)), (520, 0, {}),
+                      (1024, 0, {}), (1100, 500, dict(top_k_blocks=700))):
+        for G in (2, 8):
+            gang, wg = deal(nh=nh, ragged=ragged, batch=B, n_q_heads=G * Hkv, n_kv_heads=Hkv, seq_len=NB * Bs - 5, head_dim=D, block_size=Bs,
+                            kv_prefix_len=P * Bs, **kw)
+            seen.add(gang)
+            served = wg[wg[:, 0] >= 0]
+            assert (wg[wg[:, 0] < 0] == -1).all()
+            code = (served[:, 0].astype(np.int64) * NB + served[:, 1]) * (G // nh) + served[:, 2]
+            assert served[:, 0].max() < B * Hkv and 0 <= served[:, 1].min() and served[:, 1].max() < NB and served[:, 2].max() < G // nh
+            assert np.array_equal(np.sort(code), np.arange(B * Hkv * NB * (G // nh))), (NB, P, kw, G)
+    divides = Hkv if ragged else B * Hkv                   # a head for each XCD of 8, 4 or 2, where so many heads divide
+    assert seen == {8} | {8 // x for x in (2, 4, 8) if divides % x == 0}
