@@ -88,10 +88,10 @@ def test_every_row_is_dealt_once(spa, D, Bs, B, Hkv, ragged, NB, P, shared, n_de
         assert out[b, :, n:].isnan().all()                 # rows past the entry's end are left alone
 
 
-# Rows per workgroup of the score kernel go by the number of rows and of key blocks: 4 up to 1024 rows, 8 up to 16384
-# (1025 - 2048 key blocks: 32768), then 16; 4, 8, 16 or 32 key registers per lane.  The lists are the caller-score kernel's
-# on the same scores, bit for bit, at the last row count of one group and the first of the next, with a row tile that
-# is not full, and on both sides of every limit in key blocks.
+# Rows per workgroup of the score kernel go by the number of rows and of key blocks (test_score_rows.py); 4, 8, 16 or 32 key
+# registers per lane by the key blocks alone.  The lists are the caller-score kernel's on the same scores, bit for bit, at the
+# last row count of one group and the first of the next, with a row tile that is not full, and on both sides of every limit in
+# key blocks.
 @pytest.mark.parametrize("NB,Hq,P_blocks,D,kw", [
     (128, 8, 0, 128, {}), (129, 8, 0, 64, {}), (7, 8, 249, 128, {}), (7, 8, 250, 64, dict(stride_blocks=5)), (6, 4, 506, 128, {}),
     (6, 4, 507, 128, dict(n_dense_q_blocks=2)), (5, 8, 1019, 64, {}), (5, 8, 1020, 128, {}), (3, 8, 2045, 128, dict(stride_blocks=7)),
@@ -117,3 +117,97 @@ def test_rows_per_workgroup_of_the_score_kernel(spa, NB, Hq, P_blocks, D, kw):
                 got = sp[0, h if shared else 2 * h + 1, i]
                 torch.testing.assert_close(got[:n].double(), want[:n], rtol=1e-4, atol=1e-5)
                 assert torch.isneginf(got[n:]).all()
+
+
+# (rows per workgroup, key blocks) of a kernel -> a shape that takes it: query blocks, query heads, prefix blocks
+SCORE_KERNELS = {
+    (4, 256): (13, 16, 200), (4, 512): (13, 16, 470), (4, 1024): (13, 16, 990), (4, 2048): (13, 16, 1018),
+    (8, 256): (37, 32, 200), (8, 512): (37, 32, 470), (8, 1024): (37, 32, 980), (8, 2048): (37, 32, 1000),
+    (16, 1024): (200, 32, 820), (16, 2048): (202, 32, 904)}       # the last: rows on both sides of 1024 blocks, where the chunks meet
+SCORE_OPTIONS = {
+    "plain": {}, "shared": dict(group_shared=True), "strided": dict(stride_blocks=5, stride_reach_blocks=90),
+    "dense": dict(n_dense_q_blocks=3), "strided_shared": dict(stride_blocks=7, group_shared=True), "ragged": dict(ragged=True),
+    "schedule": dict(schedule=True), "head_pattern": dict(head_pattern=True), "output_aware": dict(output_aware=True),
+    "special_values": dict(special=True), "special_output_aware": dict(special=True, output_aware=True),
+    "all": dict(stride_blocks=9, ragged=True, schedule=True, head_pattern=True, output_aware=True)}
+
+
+def score_case(kernel, option):
+    """What the call looks like: batch, query heads, KV heads, query blocks, prefix blocks (as many rows whatever the option)."""
+    NB, heads, P = SCORE_KERNELS[kernel]
+    o = SCORE_OPTIONS[option]
+    B = 2 if o.get("ragged") else 1
+    heads //= B
+    return (B, 2 * heads, heads, NB, P) if o.get("group_shared") else (B, heads, heads // 4, NB, P)
+
+
+# Every kernel of the score stage with every option that changes its control flow: the lists against the rule on the kernel's
+# own scores, from the oracle on some heads and from the caller-score kernel on all, the scores against float64 on some rows.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("option", SCORE_OPTIONS)
+@pytest.mark.parametrize("kernel", SCORE_KERNELS, ids=lambda k: f"{k[0]}rows{k[1]}")
+def test_options_on_every_score_kernel(spa, oracle, kernel, option, D):
+    B, Hq, Hkv, NB, P = score_case(kernel, option)
+    o = dict(SCORE_OPTIONS[option])
+    Bs, ns, nl, topk = 64, 2, 3, 41
+    S, off = NB * Bs - 21, P
+    g = torch.Generator("cuda").manual_seed(51)
+    rand = lambda H, n: torch.randn((B, H, n, D), generator=g, device="cuda").to(torch.bfloat16)
+    q, k = rand(Hq, S), rand(Hkv, P * Bs + S)
+    v = rand(Hkv, P * Bs + S) * (0.25 + torch.rand((B, Hkv, P * Bs + S, 1), generator=g, device="cuda")).to(torch.bfloat16)
+    special = o.pop("special", False)
+    if special:
+        # by key block: zeros (ties at 0), a NaN, an infinity, huge values of either sign; by query block: zeros, large values
+        kind = torch.randint(0, 12, (1, Hkv, off + NB), generator=g, device="cuda").repeat_interleave(Bs, 2)[:, :, :P * Bs + S, None]
+        first = (torch.arange(P * Bs + S, device="cuda") % Bs == 5).view(1, 1, -1, 1)
+        k = k.where(kind > 1, 0.0).where(~((kind == 2) & first), float("nan")).where(~((kind == 3) & first), float("inf"))
+        k = k.where(kind != 4, k.abs() * 1e36).where(kind != 5, -k.abs() * 1e36)
+        v = v.where((kind != 6) & (kind != 0), 0.0)
+        kind = torch.randint(0, 6, (1, Hq, NB), generator=g, device="cuda").repeat_interleave(Bs, 2)[:, :, :S, None]
+        q = q.where(kind > 0, 0.0).where(kind != 1, q.abs() * 1e3)
+    shared = o.get("group_shared", False)
+    Hl, G = (Hkv if shared else Hq), Hq // Hkv
+    lens = [S, S - (NB // 3) * Bs - 7] if o.pop("ragged", False) else [S]
+    sched = torch.linspace(topk, topk // 4, NB).round().to(torch.int32) if o.pop("schedule", False) else None
+    hp = None
+    if o.pop("head_pattern", False):
+        hp = torch.tensor([[h % 4, h % 6, (h * 7) % (topk + 3)] for h in range(Hl)], dtype=torch.int32)
+    aware = o.pop("output_aware", False)
+    dev = lambda t: None if t is None else t.cuda()
+    dl = torch.tensor(lens, dtype=torch.int32).cuda() if B > 1 else None
+    kw = dict(o, seq_lens=dl, top_k_per_block=dev(sched), head_pattern=dev(hp), v=v if aware else None)
+    idx, cnt, sp = spa.select(q, k, Bs, ns, nl, topk, return_scores=True, **kw)
+    idx2, cnt2 = spa.select(q, k, Bs, ns, nl, topk, **kw)
+    assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2)               # the score output does not change the lists
+    if special:
+        tail = sp[..., :off]                               # causal for every row
+        assert tail.isnan().any() and tail.isposinf().any() and tail.isneginf().any() and (aware or (tail == 0).any())
+    rule = dict(stride_blocks=o.get("stride_blocks", 0), n_dense_q_blocks=o.get("n_dense_q_blocks", 0),
+                stride_reach_blocks=o.get("stride_reach_blocks", 0))
+    for b, n in enumerate(lens):
+        nb = -(-n // Bs)
+        assert (cnt[b, :, nb:] == 0).all() and (idx[b, :, nb:] == -1).all()
+        sp_b = sp[b:b + 1, :, :nb, :off + nb].contiguous()
+        sched_b = None if sched is None else sched[:nb].contiguous()
+        t_idx, t_cnt = spa.topk_from_scores(sp_b, ns, nl, topk, top_k_per_block=dev(sched_b), head_pattern=dev(hp), **rule)
+        Tb = t_idx.shape[-1]
+        assert torch.equal(t_cnt[0], cnt[b, :, :nb]) and torch.equal(t_idx[0], idx[b, :, :nb, :Tb]) and (idx[b, :, :nb, Tb:] == -1).all()
+        for h in (0, Hl // 2 + 1):
+            w_idx, w_cnt = oracle.topk(sp_b[:, h:h + 1].cpu(), ns, nl, topk, sched_b, stride=rule["stride_blocks"],
+                                       n_dense=rule["n_dense_q_blocks"], reach=rule["stride_reach_blocks"],
+                                       head_pattern=None if hp is None else hp[h:h + 1].contiguous())
+            assert torch.equal(cnt[b, h, :nb].cpu(), w_cnt[0, 0]) and torch.equal(idx[b, h, :nb, :Tb].cpu(), w_idx[0, 0])
+            if special:
+                continue
+            # fp32 means and products of split bf16 operands, magnitude below 1 (2^-17 each); ln of a mean of fp32 norms
+            kvh = h if shared else h // G
+            keys = k[b, kvh, :P * Bs + n].double()
+            kp = torch.stack([x.mean(0) for x in keys.split(Bs)])
+            lvn = torch.stack([x.double().norm(dim=1).mean().log() for x in v[b, kvh, :P * Bs + n].split(Bs)]) if aware else 0.0
+            for i in sorted({0, 1, nb // 2, nb - 2, nb - 1} | {i for i in (1023 - off, 1024 - off) if 0 <= i < nb}):
+                heads = range(G * h, G * h + G) if shared else [h]
+                qp = torch.stack([q[b, x, i * Bs:min(n, (i + 1) * Bs)].double().mean(0) for x in heads]).mean(0)
+                want = (kp @ qp) / D ** 0.5 + lvn
+                m = off + i + 1
+                torch.testing.assert_close(sp[b, h, i, :m].double(), want[:m], rtol=1e-4, atol=1e-5)
+                assert torch.isneginf(sp[b, h, i, m:off + nb]).all()

@@ -456,18 +456,18 @@ def test_select_special_values_through_the_score_kernel(spa, oracle, NB, D, Bs, 
 
 
 @pytest.mark.parametrize("NB,P_blocks,D,k,kw", [
-    (1025, 0, 128, 96, {}),                                        # one block into the second column chunk
-    (1040, 0, 64, 64, dict(group_shared=True)),                    # a row tile that straddles the chunk border
-    (2048, 0, 128, 200, {}),                                       # both chunks full, a budget of several blocks per lane
-    (1500, 7, 128, 96, dict(schedule=True)),                       # KV prefix: rows shifted against the chunk grid
-    (1300, 0, 128, 40, dict(ragged=[1300, 900])),                  # second entry stays inside the first chunk
+    (1025, 0, 128, 96, {}),                                        # one block past 1024
+    (1040, 0, 64, 64, dict(group_shared=True)),                    # a row tile on both sides of 1024 blocks
+    (2048, 0, 128, 200, {}),                                       # every key register full, a budget of several blocks per lane
+    (1500, 7, 128, 96, dict(schedule=True)),                       # KV prefix
+    (1300, 0, 128, 40, dict(ragged=[1300, 900])),                  # second entry below 1024 blocks
     (1700, 3, 64, 33, dict(stride_blocks=5, n_dense_q_blocks=3)),  # extended static patterns
     (1200, 0, 128, 50, dict(head_pattern=True, output_aware=True)),
 ])
 def test_select_rows_of_1025_to_2048_blocks(spa, oracle, NB, P_blocks, D, k, kw):
-    """Rows of 1025 .. 2048 key blocks take the column-chunked score kernel (16 rows per workgroup, the
-    columns scored in two chunks of 1024, first-chunk scores held in registers meanwhile).  Its
-    scores against the oracle's, its lists against the rule on its own scores (from the oracle and
+    """Rows of 1025 .. 2048 key blocks with 32 keys in the registers of a lane (few rows: 8 rows per workgroup; the
+    column-chunked kernel of long prompts is met in test_gpu_dispatch.py).  Scores against the
+    oracle's, lists against the rule on the kernel's own scores (from the oracle and
     from the caller-score kernel), with every option that changes its control flow."""
     Bs, ns, nl = 64, 2, 3
     kw = dict(kw)
@@ -511,7 +511,7 @@ def test_select_rows_of_1025_to_2048_blocks(spa, oracle, NB, P_blocks, D, k, kw)
         t_idx, t_cnt = spa.topk_from_scores(sp_b, ns, nl, k, top_k_per_block=None if kr is None else kr[:nb].contiguous().cuda(),
                                             **t_kw)
         assert torch.equal(t_idx[0], idx[b, :, :nb, :Tw]) and torch.equal(t_cnt[0], cnt[b, :, :nb]), b
-    # the scores themselves, on rows on both sides of the chunk border and at the ends
+    # the scores themselves, on rows on both sides of 1024 blocks and at the ends
     if lens is None and not output_aware:
         o_qp, o_kp = oracle.pool(q, Bs), oracle.pool(kk, Bs)
         if shared:

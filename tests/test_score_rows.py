@@ -5,6 +5,7 @@ import pytest
 
 from host_shim import compile_shim
 from paper_2602_21233_amd import binding
+from test_gpu_dispatch import SCORE_KERNELS, SCORE_OPTIONS, score_case
 
 SHIM = r"""
 #include "score_rows.hpp"
@@ -55,3 +56,14 @@ def test_fewer_rows_where_they_are_faster(rows_of, NB, NBk, heads, Bs, D, want):
 
 def test_a_mass_budget_keeps_its_groups(rows_of):
     assert [rows_of(8, n, 4, mass=True) for n in (64, 256, 512, 513, 1024, 1025, 2048, 2049, 4096)] == [8, 8, 8, 16, 16, 8, 8, 4, 4]
+
+
+# The GPU test of every option on every score kernel takes the kernels that it names.
+@pytest.mark.parametrize("option", SCORE_OPTIONS)
+@pytest.mark.parametrize("kernel", SCORE_KERNELS)
+@pytest.mark.parametrize("D", [64, 128])
+def test_the_shapes_of_the_gpu_test_take_the_kernels_they_name(rows_of, kernel, option, D):
+    B, Hq, Hkv, NB, P = score_case(kernel, option)
+    rows, blocks = kernel
+    assert blocks // 2 < P + NB <= blocks
+    assert rows_of(NB, P + NB, B * (Hkv if SCORE_OPTIONS[option].get("group_shared") else Hq), D=D) == rows
