@@ -194,9 +194,9 @@ def main():
     vt = torch.empty((w.batch, w.n_kv_heads, w.n_blocks, w.head_dim, Bs), dtype=torch.bfloat16, device="cuda")
 
     def step(events=None):
-        # the same launches sparse_prefill_fused makes (select; then the two halves of
-        # sparse_prefill_attn: V transpose and attention kernel), split so that the attention
-        # kernel alone can be bracketed by events on its own stream
+        # the fused call in its parts (select, V transpose, attention kernel), so that the attention
+        # kernel alone can be bracketed by events on its own stream; sparse_prefill_fused itself does
+        # the pooling of K and the V transpose in one launch
         if flush is not None:
             flush.fill_(1)
         if events:

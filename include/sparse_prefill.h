@@ -217,8 +217,9 @@ int sparse_prefill_attn(const spa_params *p, const void *q, const void *k, const
  * plain 16-byte reads of the staged tile): sparse_prefill_attn makes that copy in `ws` on every
  * call.  A caller that keeps the copy itself, e.g. beside V in its KV cache, so that a chunked
  * prefill (Sec. 4.1: the KV cache generation stage; kv_prefix_len > 0) does not transpose the
- * whole prefix again for every chunk, uses these two calls instead; sparse_prefill_attn is exactly
- * transpose_v of all key blocks into `ws` followed by attn_vt.
+ * whole prefix again for every chunk, uses these two calls instead; sparse_prefill_attn gives
+ * exactly what transpose_v of all key blocks followed by attn_vt gives (how V^T lies in `ws` is the
+ * library's own affair and may differ from the layout below).
  *   vt: [batch, n_kv_heads, vt_blocks_per_head, head_dim, block_size] bf16, contiguous, 16-byte
  *       aligned; vt_blocks_per_head >= NBk (the key blocks of this call; room to grow).  Block j of
  *       (b, kv head) holds V[b, kv head, j*Bs + t, d] at [d, t]; tokens past the end of a partial

@@ -3,11 +3,12 @@
 //
 // Transposed formulation: S^T = K Q^T, O^T += V^T P^T with v_mfma_f32_32x32x16_bf16, one
 // workgroup per (batch, head, query block) (two heads of a KV group per workgroup when the group
-// shares its block list), one wavefront per 32 query rows.  A lane then
+// shares its block list, except with head_dim 64 and blocks of 128), one wavefront per 32 query rows.  A lane then
 // owns the logits of one query: the rescale factor is a per-lane scalar and exp(S^T) is
 // already the B operand of the second product.  Built around what the LDS can deliver:
-//   * V is transposed once per call into a workspace ([.., block, d, token]) by
-//     transpose_v_kernel (pool.hip), so both MFMA A operands (K rows, V^T rows) are plain
+//   * V is transposed block by block before the kernel runs (pool.hip: transpose_v_kernel, in a fused call
+//     prepare_kv_kernel), to [.., block, d, token] or, where the library keeps it to itself and the kernel loads half a block at
+//     a time, [.., block, half, d, token] (vt_in_halves).  Both MFMA A operands (K rows, V^T rows) are then plain
 //     16-byte LDS reads; the LDS transpose read is ~4x slower per byte.
 //   * key blocks are consumed as 64-key sub-tiles, staged by direct
 //     global->LDS loads (global_load_lds_dwordx4, no VGPR round trip) into a
@@ -519,8 +520,10 @@ __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)
     }
     int blk1 = blk_of(1), blk2 = blk_of(2);        // key blocks of sub-tiles t+1 and t+2
     // The chunks of the diagonal block that start behind the wavefront's last query are masked altogether: their
-    // steps are left out, 3/8 of a block per row (kernel alone: 1999 tokens 50.4 -> 48.8 us, 32768 tokens 2.00 -> 1.98 ms, 16384
-    // tokens with blocks of 64 431 -> 424 us).  last_chunk: the last one with a key in sight.
+    // steps are left out, 3/8 of a block per row of 128, 1/4 of 64 (kernel alone, blocks of 128: 1999 tokens 46.5 -> 45.0 us, 32768
+    // tokens 1.99 -> 1.97 ms, 16384 tokens with head_dim 64 546 -> 538 us).  A value behind a wavefront's last query then takes no
+    // part in its rows, while inside the last chunk with a key in sight the weight of a masked key is 0 and 0 * inf still is
+    // NaN.  last_chunk: the last one with a key in sight.
     const int last_chunk = 2 * (n_st - NSUB) + wq;
 
     // One 64-key sub-tile t = steps 2t and 2t+1.  Reads K(t+1) (look-ahead logits) and V^T(t).
@@ -584,8 +587,9 @@ __global__ __launch_bounds__(BS * 2 * NH, NH == 1 ? BS / 64 : (BS == 64 ? 2 : 1)
 __device__ __forceinline__ int swz_c(int row) { return (row >> 2) & 3; }     // V^T stage rows are 64 B
 
 // HALVES: a V^T block is [2][D][32] instead of [D][64], so that the 1-KB load instructions of a chunk read 1 KB in one
-// piece instead of 16 half cache lines.  The loads are what bounds this kernel (16384 tokens: 419 us, without
-// loads in the loop 293, without waiting for them 417): 419 -> 387 us.  For the V^T the library makes for itself.
+// piece instead of 16 half cache lines.  The loads are what bounds this kernel: without the halves, 16384 tokens take 419 us on
+// one card, without loads in the loop 293, without waiting for them 417.  Both sides on another card: 429 -> 397 us, ragged prompts
+// of up to 6000 tokens 510 -> 483, head_dim 64 227 -> 219.  For the V^T the library makes for itself.
 template <int BS, int D, int NH, bool HALVES>
 __global__ __launch_bounds__(BS * 2 * NH, 2) void attn_chunked_kernel(
     const uint16_t* __restrict__ q, Strides qs, const uint16_t* __restrict__ k, Strides ks,
@@ -698,7 +702,9 @@ __global__ __launch_bounds__(BS * 2 * NH, 2) void attn_chunked_kernel(
     auto mask_diag = [&](f32x16& s, int cib) { mask_diagonal_chunk(s, 32 * cib, wq, half, q_in_blk); };
 
     int blk_v = blk_of(1), blk_k = blk_of(3);             // key blocks of the next V^T and K chunk to request
-    const int last_chunk = n_ch - CPB + wq;               // last chunk with a key in sight of this wavefront's queries
+    // last chunk with a key in sight of this wavefront's queries; the steps behind it (1/4 of a block per row of 64) only load
+    // (16384 tokens 402 -> 397 us, ragged prompts of up to 6000 tokens 488 -> 483)
+    const int last_chunk = n_ch - CPB + wq;
 
     // Step n, P = n % 2: logits of chunk n + 2 (K stage P), weights of chunk n + 1, O^T += V^T(chunk n,
     // stage P) pc^T; the instruction groups of the kernel above.  K chunk n + 2 and V^T chunk n were

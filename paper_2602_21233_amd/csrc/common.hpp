@@ -41,8 +41,9 @@ inline Dims dims_of(const spa_params& p) {
 
 // How V^T lies where the library keeps it to itself (the workspace of the attention and fused calls): [2][D][Bs / 2], the
 // two halves of a block's tokens one after the other, where the attention kernel loads a half block at a time and
-// gains from finding it in one piece: blocks of 64 tokens in attn_chunked_kernel (419 -> 387 us at 16384 tokens)
-// and head_dim 64 with blocks of 128 (560 -> 540 us; head_dim 128: 1.95 ms either way at 32768 tokens).  Everything
+// gains from finding it in one piece: blocks of 64 tokens in attn_chunked_kernel (429 -> 397 us at 16384 tokens)
+// and, a little, head_dim 64 with blocks of 128 (fused calls of 300 tokens 16.6 -> 16.3 us, of 2048 queries over 98304 tokens of 8 / 1
+// heads 120.7 -> 119.7; 538 us either way at 16384 tokens.  head_dim 128: 1.95 ms either way at 32768 tokens).  Everything
 // else, and every V^T that a caller sees, is [D][Bs].
 inline bool vt_in_halves(const Dims& d) { return d.Bs == 64 ? !(d.shared && d.G % 2 == 0) : d.D == 64; }
 
@@ -89,9 +90,9 @@ hipError_t launch_score_topk(const Dims& d, const float* qp, const float* kp, co
                              float* scores_or_null, const void* q, Strides qs, hipStream_t st);
 hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int32_t* k_rows,
                                    const int32_t* head_pattern, int32_t* idx, int32_t* cnt, hipStream_t st);
-// vt is scratch for V transposed per block, B*Hkv*NBk*Bs*D bf16.
 // counts, into *n_bad (device), the list rows that break the attention kernel's layout rules
 hipError_t launch_check_lists(const Dims& d, const int32_t* idx, const int32_t* cnt, int32_t* n_bad, hipStream_t st);
+// vt is scratch for V transposed per block, B*Hkv*NBk*Bs*D bf16.
 hipError_t launch_attn(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                        const void* v, Strides vs, const int32_t* idx, const int32_t* cnt,
                        void* out, Strides os, float* lse, void* vt, hipStream_t st);   // V^T as vt_in_halves says

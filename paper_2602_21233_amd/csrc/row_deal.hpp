@@ -26,8 +26,10 @@ namespace spa {
 // 8 kept two XCDs busy and six idle.  So the runs get shorter until no more than a sixteenth of
 // the dealt places are empty, and rows whose length varies with the position (strided columns, dense
 // strip) are dealt one by one, as are those of heads that fit the L2 whatever the deal.  The snake is
-// for calls in which the ramp of the first T rows, which are shorter than T, is an eighth of the rows or
-// more; elsewhere it only moves neighbouring rows apart.
+// for rows dealt one by one, and for calls with at most 8 T key blocks: without a prefix the ramp of the first T rows, which
+// are shorter than T, is then an eighth of the rows or more.  Elsewhere it only moves neighbouring rows apart.  Over a prefix
+// of T blocks or more no row is shorter and the snake does nothing for the balance, nor against it: 1024 to 8192 queries over 8192 to
+// 65536 tokens, blocks of 64 and 128, take the same time with it, without it, and by the ramp that is left (within 0.5 %).
 // Measured against runs of 8, all forwards, whole calls with 32/8 heads: 1999 tokens 190 -> 74 us; 2048 queries over a
 // prefix of 98304 tokens 1048 -> 368 us; 6 ragged prompts of up to 6000 tokens, blocks of 64, 727 -> 591 us;
 // 32768 tokens 2.10 -> 2.03 ms; group-shared lists, 16384 tokens, D = 64, 628 -> 582 us.  The snake at 131072
@@ -43,7 +45,11 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     RowDeal r;
     r.n_dense = d.n_dense < d.NB ? d.n_dense : d.NB;
     const int n = d.NB - r.n_dense;                       // rows dealt in runs
-    const int slots = 32 * (d.Bs == 64 ? 4 : 2) / nh;     // workgroups an XCD has in flight
+    // Workgroups an XCD has in flight, by the LDS that head_dim 128 needs.  With head_dim 64 a CU holds half as many again; gangs
+    // are then larger than they have to be, which is the better choice at some sizes and not at others (32 / 8 heads: 4096
+    // tokens 91 us, 83 with the gang of the true count; 8192 tokens 298 and 302; 16 / 2 heads: 8192 tokens 164 and 145, with
+    // blocks of 64 131 and 137).
+    const int slots = 32 * (d.Bs == 64 ? 4 : 2) / nh;
     const int heads = d.seq_lens != nullptr ? d.Hkv : d.B * d.Hkv;    // heads with the same rows: may sit side by side
     r.gang = 8;
     while (r.gang > 1 && (int64_t)d.NB * (d.G / nh) < (int64_t)slots * r.gang && heads % (16 / r.gang) == 0) r.gang >>= 1;

@@ -211,3 +211,22 @@ def test_options_on_every_score_kernel(spa, oracle, kernel, option, D):
                 m = off + i + 1
                 torch.testing.assert_close(sp[b, h, i, :m].double(), want[:m], rtol=1e-4, atol=1e-5)
                 assert torch.isneginf(sp[b, h, i, m:off + nb]).all()
+
+
+# Chunks of the diagonal block that start behind a wavefront's last query (32 queries each) are left out: values there may be
+# anything, the wavefront's rows keep their bits.
+@pytest.mark.parametrize("D,Bs", [(128, 64), (64, 64), (128, 128), (64, 128)])
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("NB", [1, 2, 7])
+def test_values_behind_a_wavefronts_queries_take_no_part(spa, D, Bs, shared, NB):
+    q, k, v = _normal((1, 4, NB * Bs, D), 61), _normal((1, 2, NB * Bs, D), 62), _normal((1, 2, NB * Bs, D), 63)
+    idx, cnt = spa.select(q, k, Bs, 1, 2, 3, group_shared=shared)
+    pattern = (1, 2, 3, 0, 0)
+    want = spa.attn(q, k, v, idx, cnt, Bs, pattern=pattern, group_shared=shared)
+    for end in range((NB - 1) * Bs + 32, NB * Bs, 32):     # the first keys behind the wavefronts of the last block
+        bad = v.clone()
+        bad[:, :, end:] = float("nan")
+        got = spa.attn(q, k, bad, idx, cnt, Bs, pattern=pattern, group_shared=shared)
+        assert torch.equal(got[:, :, :end], want[:, :, :end])
+        vt = spa.transpose_v(bad, Bs)
+        assert torch.equal(spa.attn_vt(q, k, vt, idx, cnt, Bs, pattern=pattern, group_shared=shared)[:, :, :end], want[:, :, :end])
