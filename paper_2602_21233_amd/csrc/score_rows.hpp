@@ -31,20 +31,23 @@ inline int score_rows(const Dims& d) {
     // of 8 heads 85 -> 79; 131072 of 16 heads, 16384 rows, 132 -> 121; 262144 of 16 heads, 32768 rows, 295 -> 291; at worst
     // 180 -> 185, 25600 queries over 230400 tokens).
     if (d.Bs == 128) return 8;
-    // With blocks of 64 the rounds of 512 workgroups (two per CU) decide: `depth` is how many rows a place works through one
-    // after the other, and 8 rows are for calls in which that is less of them.  Up to 1.5 rounds of 8-row workgroups
-    // (6144 rows) they win whatever the count, by 2 to 35 %.  With one round of 16-row workgroups they win where rows
-    // differ in length, dealt longest first (52413 tokens of 8 / 1 heads 42 -> 40 us), and lose over a prefix at least as long as
-    // the chunk (12800 queries over 51200 tokens, 32 heads, 74 against 78 us).  With more rounds they win where the
-    // depth says so (95997 tokens of 8 / 8 heads 121 -> 110 us), except in one chunk with head_dim 128 and rows that
-    // differ (40960 tokens of 16 heads 50 against 53 us), and lose otherwise (25600 queries over 38400 tokens, 40 heads, 110
-    // against 118 us; from 16385 rows on 182 against 193 us at 1247 blocks and 28288 rows).
+    // With blocks of 64 the rounds of 512 workgroups (two per CU) show.  Up to 1.5 rounds of 8-row workgroups (6144 rows) 8 rows
+    // win whatever the count, by 2 to 35 %.  From there on:
+    //   - over a prefix at least as long as the chunk all rows are about as long, and what counts is `depth`, how many of them a
+    //     place works through one after the other: 8 rows where that is less (12797 queries over 83200 tokens, 40 heads, 118 -> 109
+    //     us), 16 where it is the same (12797 queries over 51200 tokens, 32 heads, 74 against 78 us with 8; 25597 over 38400
+    //     tokens, 40 heads, 110 against 118 us);
+    //   - rows that differ in length are dealt longest first and even the rounds out.  8 rows win up to one round of 16-row
+    //     workgroups (52413 tokens of 8 / 1 heads 42 -> 40 us) and, with head_dim 64 or two chunks, up to 14336 rows (95997 tokens
+    //     of 8 / 8 heads 121 -> 110 us; 47485 tokens of 16 heads, head_dim 64, 45 -> 43 us).  16 elsewhere: 40960 tokens of 16 heads 50
+    //     against 53 us, 113341 tokens of 16 heads, head_dim 64, 126 against 134, 28288 rows of 1247 blocks 182 against 193.
     const int64_t wg8 = heads * ((d.NB + 7) / 8), wg16 = heads * ((d.NB + 15) / 16);
-    const bool even = d.off >= d.NB;                       // the shortest row has at least half the blocks of the longest
     if (wg8 <= 768) return 8;
-    if (wg16 <= 512) return even ? 16 : 8;
-    const int64_t depth8 = (wg8 + 511) / 512 * 8, depth16 = (wg16 + 511) / 512 * 16;
-    return depth8 < depth16 && rows <= 16384 && (two_chunks || even || d.D == 64) ? 8 : 16;
+    if (d.off >= d.NB) {
+        const int64_t depth8 = (wg8 + 511) / 512 * 8, depth16 = (wg16 + 511) / 512 * 16;
+        return depth8 < depth16 && rows <= 16384 ? 8 : 16;
+    }
+    return wg16 <= 512 || (rows <= 14336 && (two_chunks || d.D == 64)) ? 8 : 16;
 }
 
 }  // namespace spa
