@@ -9,14 +9,23 @@ namespace spa {
 // so the XCDs advance through their sequences in step: what has to be equal is the work of the rows that
 // sit at the same position of the 8 sequences.
 // A KV head is served by a gang of `gang` XCDs (8, 4, 2 or 1), 8 / gang heads side by side.  With long sequences it is all
-// eight: the whole chip then works through one head after the other, and what an XCD has in flight
-// are rows of one head anyway.  With few query blocks an eighth of a head's rows does not fill an XCD, which would have
-// rows of several heads in flight and fetch each of their K and V^T tiles for a few rows only; a smaller gang
-// puts more rows of one head behind one L2.  In a ragged batch only heads of one entry sit side by side: entries differ in
+// eight; with few query blocks an eighth of a head's rows does not fill an XCD, which would have rows of several heads in flight
+// and fetch each of their K and V^T tiles for a few rows only; a smaller gang puts more rows of one head behind one L2.
+// At any time `width` of the gang's XCDs are at the same head, so that 8 / width heads are in flight, each behind few L2s: fewer
+// of its tiles are fetched more than once.  The XCDs go from head to head after every piece of row positions (at least what an XCD has
+// in flight), so that in the end all of the gang have served all of the heads alike: heads may differ in the
+// length of their lists.  The limit is half of the memory-side cache (128 of 256 MB, for queries and outputs pass through it
+// too), which has to hold the K and V^T of all heads in flight.  Attention kernel, 32/8 heads, one XCD (the rule: as few as the limit allows) against
+// eight at a head: 8192 tokens 496 -> 481 us, 16384 932 -> 898, with blocks of 64 424 -> 401, with head_dim 64 528 -> 512, 32768 tokens
+// 1.95 -> 1.90 ms, with blocks of 64 1473 -> 1394 us.  With 8, 4, 2, 1 at a head: 40960 tokens (21 MB a head) 2.63, 2.54, 2.53, 2.53 ms; 49000
+// tokens (25 MB) of 40/8 heads 4.75, 4.65, 4.53, 4.53, of 32/8 heads with a decaying budget 3.40, 3.40, 3.43, 3.46; 131072 tokens (67 MB) 15.96,
+// 15.79, 15.96, 16.49; 262144 tokens of 40/8 heads (134 MB) 66.3, 64.2, 66.3, 68.5 (two runs of one side differ by 2 %).  Pieces half
+// as long cost 2 to 3 % with blocks of 64, twice as long or no change of heads at all gives nothing more.
+// In a ragged batch only heads of one entry sit side by side: entries differ in
 // length, which the host does not see, and an XCD that serves one entry's head alone idles after a short one.  Attention
 // kernel, 8 entries of 4 / 1 heads with blocks of 128, one of 3900 tokens and the others of 325: 106 us with an entry
 // for each XCD, 57 this way; lengths down from 3900 in steps 109 -> 79; all of 3900 tokens 131 -> 150, the price of not knowing.
-// Within the gang:
+// Among the XCDs at a head:
 //   - the n_dense rows of a Tri-shape strip (each visits up to NB blocks) are dealt one by one;
 //   - the other rows are dealt in runs of `run` consecutive rows, last row first; with `snake` every
 //     other round of runs goes backwards (which rounds: alternating with the KV head), so that the XCD
@@ -35,9 +44,11 @@ namespace spa {
 // 32768 tokens 2.10 -> 2.03 ms; group-shared lists, 16384 tokens, D = 64, 628 -> 582 us.  The snake at 131072
 // tokens (a ramp of 69 of 1024 rows): 17.05 -> 17.18 ms, which is why it is left out there.  Gangs, attention kernel
 // alone: 1999 tokens 58 -> 50 us, 2048 queries over the prefix 306 -> 286 us, 1024 queries 174 -> 169 us.
-// seq_len = workgroups per (head, XCD) in the grid; surplus workgroups exit at once.
+// seq_len = workgroups per (head, XCD) in the grid; surplus workgroups exit at once.  places = workgroups of an XCD for the heads that are
+// side by side; what divides workgroup ids is kept as a shift where it can be, every workgroup starts with these.
 struct RowDeal {
     int gang, n_dense, run, snake, seq_len;
+    int places, width_log2, run_log2, piece_log2, n_single;
 };
 
 // nh: query heads served by one workgroup (their workgroups per row position number G / nh)
@@ -45,6 +56,7 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     RowDeal r;
     r.n_dense = d.n_dense < d.NB ? d.n_dense : d.NB;
     const int n = d.NB - r.n_dense;                       // rows dealt in runs
+    const int GH = d.G / nh;
     // Workgroups an XCD has in flight, by the LDS that head_dim 128 needs.  With head_dim 64 a CU holds half as many again; gangs
     // are then larger than they have to be, which is the better choice at some sizes and not at others (32 / 8 heads: 4096
     // tokens 91 us, 83 with the gang of the true count; 8192 tokens 298 and 302; 16 / 2 heads: 8192 tokens 164 and 145, with
@@ -52,13 +64,22 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     const int slots = 32 * (d.Bs == 64 ? 4 : 2) / nh;
     const int heads = d.seq_lens != nullptr ? d.Hkv : d.B * d.Hkv;    // heads with the same rows: may sit side by side
     r.gang = 8;
-    while (r.gang > 1 && (int64_t)d.NB * (d.G / nh) < (int64_t)slots * r.gang && heads % (16 / r.gang) == 0) r.gang >>= 1;
-    const bool fits_l2 = (int64_t)d.Skv * d.D * 4 <= 4 << 20;         // K and V^T of a head, bf16
-    r.run = (d.stride > 0 || d.n_dense > 0 || fits_l2) ? 1 : 8;
-    while (r.run > 1 && (n + r.gang * r.run - 1) / (r.gang * r.run) * (r.gang * r.run) > n + n / 16) r.run >>= 1;
+    while (r.gang > 1 && (int64_t)d.NB * GH < (int64_t)slots * r.gang && heads % (16 / r.gang) == 0) r.gang >>= 1;
+    const int64_t kv_bytes = (int64_t)d.Skv * d.D * 4;                // K and V^T of a head, bf16
+    int width = r.gang;
+    while (width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
+    r.width_log2 = __builtin_ctz(width);
+    r.piece_log2 = 0;
+    while ((GH << r.piece_log2) < slots) ++r.piece_log2;
+    r.run = (d.stride > 0 || d.n_dense > 0 || kv_bytes <= 4 << 20) ? 1 : 8;
+    while (r.run > 1 && (n + width * r.run - 1) / (width * r.run) * (width * r.run) > n + n / 16) r.run >>= 1;
     r.snake = r.run == 1 || 8 * (int64_t)d.T >= d.NBk;
+    r.run_log2 = __builtin_ctz(r.run);
+    r.n_single = (r.n_dense + width - 1) / width;
     const int runs = (n + r.run - 1) / r.run;
-    r.seq_len = ((r.n_dense + r.gang - 1) / r.gang + (runs + r.gang - 1) / r.gang * r.run) * (d.G / nh);
+    const int turns = r.gang / width;                     // heads that the gang has side by side
+    r.seq_len = ((r.n_single + (runs + width - 1) / width * r.run) * GH + turns - 1) / turns;
+    r.places = r.seq_len * turns;
     return r;
 }
 
@@ -69,23 +90,23 @@ struct DealtRow {
 
 // Row of workgroup `block`, GH workgroups per row; false: a surplus workgroup.
 __host__ __device__ __forceinline__ bool dealt_row(const RowDeal& deal, int GH, int NB, int block, DealtRow& r) {
-    const int gang = deal.gang;
-    const int xcd = block & (gang - 1);                   // member of the gang
+    const int wl = deal.width_log2, width = 1 << wl;
+    const int xcd = block & (width - 1);                  // which of the XCDs that are at this head now
     const int slot = block >> 3;
-    r.head_slot = slot / deal.seq_len * (8 / gang) + (block & 7) / gang;
-    const int within = slot % deal.seq_len;
+    const int group = slot / deal.places, within = slot - group * deal.places;
     const int pos = within / GH;                          // position in this XCD's row sequence
-    const int n_single = (deal.n_dense + gang - 1) / gang;
-    r.turn = within % GH;
-    if (pos < n_single) {
-        const int hidx = pos * gang + xcd;
+    r.turn = within - pos * GH;
+    const int side = 8 >> wl;                             // heads side by side
+    r.head_slot = group * side + ((((block & 7) >> wl) + (pos >> deal.piece_log2)) & (side - 1));
+    if (pos < deal.n_single) {
+        const int hidx = pos * width + xcd;
         r.i = NB - 1 - hidx;
         return hidx < deal.n_dense;
     }
-    const int rr = pos - n_single;
-    const int round = rr / deal.run;
-    const int x = (deal.snake & (round ^ r.head_slot)) ? gang - 1 - xcd : xcd;
-    const int ridx = (round * gang + x) * deal.run + rr % deal.run;
+    const int rr = pos - deal.n_single;
+    const int round = rr >> deal.run_log2;
+    const int x = (deal.snake & (round ^ r.head_slot)) ? width - 1 - xcd : xcd;
+    const int ridx = ((round * width + x) << deal.run_log2) + (rr & (deal.run - 1));
     r.i = NB - deal.n_dense - 1 - ridx;
     return ridx < NB - deal.n_dense;
 }

@@ -93,3 +93,29 @@ def test_every_row_is_dealt_once(deal, D, Bs, nh, B, Hkv, ragged):
             assert np.array_equal(np.sort(code), np.arange(B * Hkv * NB * (G // nh))), (NB, P, kw, G)
     divides = Hkv if ragged else B * Hkv                   # a head for each XCD of 8, 4 or 2, where so many heads divide
     assert seen == {8} | {8 // x for x in (2, 4, 8) if divides % x == 0}
+
+
+# Long calls: as many heads in flight as the memory-side cache holds K and V^T of, and, since heads may differ in the length of
+# their lists, each XCD serves the rows of all heads alike, to within a few pieces (what an XCD has in flight).
+@pytest.mark.parametrize("D,Bs", [(128, 128), (128, 64), (64, 128)])
+@pytest.mark.parametrize("B,Hkv", [(1, 8), (2, 4), (1, 4), (1, 2), (1, 3)])
+@pytest.mark.parametrize("S", [16384, 50001, 131072, 262143])
+def test_heads_side_by_side_fit_the_cache_and_every_xcd_serves_them_alike(deal, D, Bs, B, Hkv, S):
+    G, NB = 4, -(-S // Bs)
+    if NB > 4096:
+        pytest.skip("more than 4096 key blocks")
+    gang, wg = deal(batch=B, n_q_heads=G * Hkv, n_kv_heads=Hkv, seq_len=S, head_dim=D, block_size=Bs)
+    if gang < 8:
+        pytest.skip("a short call")
+    in_flight = 8 * 32 * (4 if Bs == 64 else 2)
+    first = wg[:in_flight, 0]
+    side = len(set(first[first >= 0]))
+    assert side == 1 or side * S * D * 4 <= 128 << 20
+    if (B * Hkv) % (2 * side) == 0 and side < 8:
+        assert 2 * side * S * D * 4 > 128 << 20
+    rows = np.zeros((8, B * Hkv), dtype=np.int64)
+    for x in range(8):
+        served = wg[x::8, 0]
+        rows[x] = np.bincount(served[served >= 0], minlength=B * Hkv)
+    piece = in_flight // 8
+    assert abs(rows - NB * G / 8).max() <= 2 * piece
