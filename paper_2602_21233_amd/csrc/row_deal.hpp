@@ -44,11 +44,18 @@ namespace spa {
 // 32768 tokens 2.10 -> 2.03 ms; group-shared lists, 16384 tokens, D = 64, 628 -> 582 us.  The snake at 131072
 // tokens (a ramp of 69 of 1024 rows): 17.05 -> 17.18 ms, which is why it is left out there.  Gangs, attention kernel
 // alone: 1999 tokens 58 -> 50 us, 2048 queries over the prefix 306 -> 286 us, 1024 queries 174 -> 169 us.
+// Launches of 33 to 64 workgroups per XCD, two to a CU, all in flight at once: the first 32 go to CUs of their own, longest row first, and
+// the others join them in that order, so the CU that has the longest row would get the longest of the rest.  `fold` (that
+// count) deals the others shortest first.  Only where every row visits all of its causal blocks (T >= NBk): rows cut to T are
+// about as long as each other, and under a decaying budget the last rows are the short ones (2000 tokens, 8 falling to 2 blocks,
+// 33 -> 35 us).  Attention kernel, 32/8 heads: 1999 tokens 43.3 -> 40.5 us, two of 1024 32.1 -> 27.0, four of 512 21.3 -> 19.4, 1024 with blocks
+// of 64 23.3 -> 21.3; 8000 tokens of 8/8 heads 143 -> 133.  With more than two to a CU (blocks of 64, 2000 tokens) it gives nothing, with more
+// than one round (4096 tokens) it costs 3 %.
 // seq_len = workgroups per (head, XCD) in the grid; surplus workgroups exit at once.  places = workgroups of an XCD for the heads that are
 // side by side; what divides workgroup ids is kept as a shift where it can be, every workgroup starts with these.
 struct RowDeal {
     int gang, n_dense, run, snake, seq_len;
-    int places, width_log2, run_log2, piece_log2, n_single;
+    int places, width_log2, run_log2, piece_log2, n_single, fold;
 };
 
 // nh: query heads served by one workgroup (their workgroups per row position number G / nh)
@@ -80,6 +87,8 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     const int turns = r.gang / width;                     // heads that the gang has side by side
     r.seq_len = ((r.n_single + (runs + width - 1) / width * r.run) * GH + turns - 1) / turns;
     r.places = r.seq_len * turns;
+    const int64_t per_xcd = (int64_t)r.gang * r.seq_len * d.B * d.Hkv / 8;
+    r.fold = slots >= 64 && d.T >= d.NBk && per_xcd > 32 && per_xcd <= 64 ? (int)per_xcd : 0;
     return r;
 }
 
@@ -92,7 +101,8 @@ struct DealtRow {
 __host__ __device__ __forceinline__ bool dealt_row(const RowDeal& deal, int GH, int NB, int block, DealtRow& r) {
     const int wl = deal.width_log2, width = 1 << wl;
     const int xcd = block & (width - 1);                  // which of the XCDs that are at this head now
-    const int slot = block >> 3;
+    int slot = block >> 3;
+    if (slot >= 32 && deal.fold != 0) slot = deal.fold + 31 - slot;
     const int group = slot / deal.places, within = slot - group * deal.places;
     const int pos = within / GH;                          // position in this XCD's row sequence
     r.turn = within - pos * GH;

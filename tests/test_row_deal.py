@@ -119,3 +119,16 @@ def test_heads_side_by_side_fit_the_cache_and_every_xcd_serves_them_alike(deal, 
         rows[x] = np.bincount(served[served >= 0], minlength=B * Hkv)
     piece = in_flight // 8
     assert abs(rows - NB * G / 8).max() <= 2 * piece
+
+
+# All rows in flight at once, two workgroups to a CU (workgroups k and k + 32 of an XCD): the longest
+# row shares its CU with the shortest, and no CU has more than these two (a block more where GH does not divide 32).
+@pytest.mark.parametrize("B,Hq,Hkv,S,Bs", [(1, 32, 8, 1999, 128), (1, 32, 8, 1500, 128), (2, 32, 8, 1024, 128), (1, 40, 8, 1024, 128),
+                                           (1, 8, 8, 8000, 128), (1, 32, 8, 1024, 64), (1, 16, 2, 4000, 128)])
+def test_the_cu_with_the_longest_row_gets_the_shortest_beside_it(deal, B, Hq, Hkv, S, Bs):
+    _, wg = deal(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=S, block_size=Bs)
+    blocks = np.where(wg[:, 0] >= 0, wg[:, 1] + 1, 0).reshape(-1, 8)         # causal blocks; [workgroup of the XCD, XCD]
+    assert 32 < len(blocks) <= 64
+    load = blocks[:32].copy()
+    load[: len(blocks) - 32] += blocks[32:]
+    assert load.max() <= blocks.max() + blocks[32:][blocks[32:] > 0].min() + (32 % (Hq // Hkv) != 0)
