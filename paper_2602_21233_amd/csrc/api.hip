@@ -5,6 +5,7 @@
 #include <mutex>
 
 #include "common.hpp"
+#include "score_rows.hpp"
 
 using namespace spa;
 
@@ -77,15 +78,14 @@ int set_mass_budget(Dims& d, float mass_gamma) {
 }  // namespace
 
 namespace {
-// The scratch regions of the select stage: pooled Q and the group means (group-shared lists only),
-// pooled K in the score kernel's operand layout, ln of the value magnitudes (output-aware score only).
+// The scratch regions of the select stage: pooled Q (group-shared lists only), pooled K in the score kernel's operand layout, ln of the value magnitudes
+// (output-aware score only).
 struct SelectScratch {
-    float *qp, *kp, *qg, *lvn;
+    float *qp, *kp, *lvn;
 };
 
 SelectScratch select_scratch(void* ws, const Workspace& w) {
-    return {(float*)((char*)ws + w.qp_off), (float*)((char*)ws + w.kp_off), (float*)((char*)ws + w.qg_off),
-            (float*)((char*)ws + w.lvn_off)};
+    return {(float*)((char*)ws + w.qp_off), (float*)((char*)ws + w.kp_off), (float*)((char*)ws + w.lvn_off)};
 }
 
 // Shape, pointer and budget checks of a select call; on success d holds the resolved sizes.
@@ -125,29 +125,24 @@ int select_impl(const spa_params* p, const void* q, const void* k, const void* v
 int select_launches(Dims d, const spa_params* p, const void* q, const void* k, const void* v_or_null, const int32_t* k_rows,
                     const int32_t* head_pattern, int32_t* block_idx, int32_t* block_cnt, float* pooled_scores_or_null,
                     const SelectScratch& sc, bool rank_by_values, void* vt_or_null, hipStream_t st) {
-    float* qp = sc.qp;
     float* kp = sc.kp;
-    // Group-shared lists rank the mean of the group's pooled queries, which needs them in memory; all other
-    // calls pool K only and let the score kernel pool its own query blocks from Q (the Q stream then hides
-    // the scoring and selection)
-    const bool q_in_kernel = !d.shared;
+    // The score kernel pools its own query blocks from Q (the Q stream then hides the scoring and selection); only for
+    // group-shared lists of few rows they are pooled beforehand with K
     const bool with_v = rank_by_values || vt_or_null != nullptr;       // K and what the call needs of V go in one launch
     float* const lvn = rank_by_values ? sc.lvn : nullptr;
-    if (with_v && launch_prepare_kv(d, k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride), kp, vt_or_null, lvn, st) != hipSuccess)
-        return SPA_ERR_LAUNCH;
-    if (launch_pool(d, q_in_kernel ? nullptr : q, strides_of(p->q_stride), with_v ? nullptr : k, strides_of(p->k_stride), qp, kp, true, st) != hipSuccess)
-        return SPA_ERR_LAUNCH;
+    Dims lists = d;                                       // one list per KV head: selected as if the KV heads were the query heads
     if (d.shared) {
-        // one list per KV head: rank the group by its mean pooled query, then select as if the
-        // KV heads were the query heads
-        float* qg = sc.qg;
-        if (launch_group_mean(d, qp, qg, st) != hipSuccess) return SPA_ERR_LAUNCH;
-        d.Hq = d.Hkv;
-        d.G = 1;
-        qp = qg;
+        lists.Hq = d.Hkv;
+        lists.G = 1;
     }
-    return launch_code(launch_score_topk(d, qp, kp, k_rows, head_pattern, lvn, block_idx, block_cnt, pooled_scores_or_null,
-                                         q_in_kernel ? q : nullptr, strides_of(p->q_stride), st));
+    const int group = d.shared ? d.G : 1;
+    float* const qp = group > 1 && !group_pooled_in_kernel(lists) ? sc.qp : nullptr;
+    if (with_v && launch_prepare_kv(d, q, strides_of(p->q_stride), qp, k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride), kp, vt_or_null, lvn, st) != hipSuccess)
+        return SPA_ERR_LAUNCH;
+    if (!with_v && launch_pool(d, qp != nullptr ? q : nullptr, strides_of(p->q_stride), k, strides_of(p->k_stride), qp, kp, true, st) != hipSuccess)
+        return SPA_ERR_LAUNCH;
+    return launch_code(launch_score_topk(lists, kp, k_rows, head_pattern, lvn, block_idx, block_cnt, pooled_scores_or_null, q,
+                                         strides_of(p->q_stride), group, qp, st));
 }
 
 int topk_impl(const spa_params* p, const float* pooled_scores, const int32_t* k_rows,
@@ -300,7 +295,7 @@ int sparse_prefill_select_static(const spa_params* p, const void* q, const void*
     hipError_t e;
     char* base = (char*)static_scratch(&e);
     if (base == nullptr) return SPA_ERR_LAUNCH;
-    const SelectScratch sc{(float*)(base + c.qp_off), (float*)(base + c.kp_off), (float*)(base + c.qg_off), nullptr};
+    const SelectScratch sc{(float*)(base + c.qp_off), (float*)(base + c.kp_off), nullptr};
     return select_launches(d, p, q, k, nullptr, nullptr, nullptr, block_idx, block_cnt, pooled_scores_or_null, sc, false, nullptr,
                            (hipStream_t)hip_stream);
 }

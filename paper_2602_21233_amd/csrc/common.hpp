@@ -72,22 +72,21 @@ inline Strides strides_of(const int64_t s[3]) { return Strides{s[0], s[1], s[2]}
 // heads ceil(NBk / 32) tiles apart) instead of row major [.., NBk, D].
 hipError_t launch_pool(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
                        float* qp, float* kp, bool k_tiled, hipStream_t st);
-// qg[b, kv head, :] = mean over the G query heads of the group of qp[b, head, :]  (n = NB * D values per head)
-hipError_t launch_group_mean(const Dims& d, const float* qp, float* qg, hipStream_t st);
 // lvn [B*Hkv, NB] fp32: ln of the mean value-vector norm of every key block.
 hipError_t launch_vnorm(const Dims& d, const void* v, Strides vs, float* lvn, hipStream_t st);
 // Pooled K (tiled) and, of V in the same launch, V^T for the attention kernel (NBk blocks per head, as vt_in_halves
-// says) and / or lvn.
-hipError_t launch_prepare_kv(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt_or_null,
-                             float* lvn_or_null, hipStream_t st);
+// says) and / or lvn; with qp, the pooled queries too.
+hipError_t launch_prepare_kv(const Dims& d, const void* q, Strides qs, float* qp_or_null, const void* k, Strides ks, const void* v,
+                             Strides vs, float* kp, void* vt_or_null, float* lvn_or_null, hipStream_t st);
 // k_rows: optional device array of NB per-query-block budgets (clamped to [0, d.k] in the kernel).
 // lvn: optional; added to the score of key block j (output-aware ranking).
 // kp is in the tiled layout launch_pool writes with k_tiled.
 // head_pattern: optional device array [Hq][3] = (n_sink, n_local, top_k) per query head.
-// q: if not nullptr, the kernel pools the query blocks from Q itself (layout qs) and qp is not read.
-hipError_t launch_score_topk(const Dims& d, const float* qp, const float* kp, const int32_t* k_rows,
+// q: the queries, layout qs; the kernel pools them.  group: query heads per list (their pooled queries are averaged);
+// with more than one, qp: the pooled queries [B, Hq * group, NB, D] (Hq lists), or nullptr: pooled in the kernel, too.
+hipError_t launch_score_topk(const Dims& d, const float* kp, const int32_t* k_rows,
                              const int32_t* head_pattern, const float* lvn, int32_t* idx, int32_t* cnt,
-                             float* scores_or_null, const void* q, Strides qs, hipStream_t st);
+                             float* scores_or_null, const void* q, Strides qs, int group, const float* qp, hipStream_t st);
 hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int32_t* k_rows,
                                    const int32_t* head_pattern, int32_t* idx, int32_t* cnt, hipStream_t st);
 // counts, into *n_bad (device), the list rows that break the attention kernel's layout rules

@@ -216,7 +216,8 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
 }
 
 // Everything a call needs of K and V before it scores: blockIdx.z = 0 pools a block of K (tiled), 1 takes a
-// block of V (VT: transposed for the attention kernel, VN: its magnitude).  HBM-bound streams like the separate kernels,
+// block of V (VT: transposed for the attention kernel, VN: its magnitude), 2 + g pools a block of query head g of the KV
+// group, where the score kernel does not do that itself.  HBM-bound streams like the separate kernels,
 // whose launches, ramps and second read of V this saves: fused calls of 512 tokens 27 -> 23 us, 1999 tokens 64 -> 57.6,
 // 16384 tokens (D = 64, shared lists) 557 -> 553 us; 49000 tokens with the output-aware score 3.59 -> 3.51 ms.
 template <int D, int BS, bool VT, bool VN>
@@ -224,13 +225,21 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restr
                                                          const uint16_t* __restrict__ v, Strides vs, int Hkv, int NBk, int Skv,
                                                          float* __restrict__ kp, uint16_t* __restrict__ vt,
                                                          float* __restrict__ lvn, const int32_t* __restrict__ seq_lens, int Sq,
-                                                         int halves) {
+                                                         int halves, const uint16_t* __restrict__ q, Strides qs,
+                                                         float* __restrict__ qp, int NBq) {
     constexpr int RPP = 256 / (D / 8);
     constexpr int TILE_B = VT ? BS * (D + 2) * 2 : 0, PART_B = RPP * D * 4;
     __shared__ __attribute__((aligned(16))) char lds[TILE_B > PART_B ? TILE_B : PART_B];
     __shared__ float norms[RPP];
     const int blk = blockIdx.x, hy = blockIdx.y;
     const int b = hy / Hkv, h = hy % Hkv;
+    if (blockIdx.z >= 2) {                                 // a query head of the group
+        const int Sb = entry_len(seq_lens, b, Sq), G = (int)gridDim.z - 2, g = (int)blockIdx.z - 2;
+        if (blk * BS >= Sb) return;
+        pool_block<D, BS>(q + b * qs.b + (h * G + g) * qs.h + (int64_t)blk * BS * qs.t, qs.t, Sb - blk * BS < BS ? Sb - blk * BS : BS,
+                          reinterpret_cast<float(*)[D]>(lds), qp + (((int64_t)hy * G + g) * NBq + blk) * D, false, blk);
+        return;
+    }
     const int S = Skv - Sq + entry_len(seq_lens, b, Sq);   // ragged batch: key tokens of this entry
     if (blk * BS >= S) return;
     const int n_valid = S - blk * BS < BS ? S - blk * BS : BS;
@@ -241,22 +250,6 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restr
         value_block<D, BS, VT, VN>(v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t, n_valid,
                                    reinterpret_cast<uint16_t*>(lds), norms, VT ? vt + ((int64_t)hy * NBk + blk) * D * BS : nullptr, halves,
                                    VN ? lvn + (int64_t)hy * NBk + blk : nullptr);
-}
-
-// group-shared selection: the pooled queries of the G heads of a KV group are averaged
-__global__ __launch_bounds__(256) void group_mean_kernel(const float4* __restrict__ qp, float4* __restrict__ qg, int G,
-                                                         int64_t n4 /* float4 per head */, int64_t total4) {
-    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (x >= total4) return;
-    const int64_t head = x / n4, within = x % n4;      // head = b * Hkv + kv head
-    const float4* src = qp + head * G * n4 + within;
-    float4 acc = src[0];
-    for (int g = 1; g < G; ++g) {
-        const float4 t = src[g * n4];
-        acc.x += t.x; acc.y += t.y; acc.z += t.z; acc.w += t.w;
-    }
-    const float inv = 1.0f / (float)G;
-    qg[x] = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
 }
 
 template <int D, int BS>
@@ -275,12 +268,13 @@ hipError_t launch_tv(const Dims& d, const void* v, Strides vs, void* vt, int64_t
 }
 
 template <int D, int BS>
-hipError_t launch_prep(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt, float* lvn,
-                       hipStream_t st) {
+hipError_t launch_prep(const Dims& d, const void* q, Strides qs, float* qp, const void* k, Strides ks, const void* v, Strides vs,
+                       float* kp, void* vt, float* lvn, hipStream_t st) {
     const auto kernel = vt == nullptr ? prepare_kv_kernel<D, BS, false, true>
                                       : (lvn == nullptr ? prepare_kv_kernel<D, BS, true, false> : prepare_kv_kernel<D, BS, true, true>);
-    hipLaunchKernelGGL(kernel, dim3(d.NBk, d.B * d.Hkv, 2), dim3(256), 0, st, (const uint16_t*)k, ks, (const uint16_t*)v, vs,
-                       d.Hkv, d.NBk, d.Skv, kp, (uint16_t*)vt, lvn, d.seq_lens, d.S, vt_in_halves(d) ? 1 : 0);
+    hipLaunchKernelGGL(kernel, dim3(d.NBk, d.B * d.Hkv, qp == nullptr ? 2 : 2 + d.G), dim3(256), 0, st, (const uint16_t*)k, ks,
+                       (const uint16_t*)v, vs, d.Hkv, d.NBk, d.Skv, kp, (uint16_t*)vt, lvn, d.seq_lens, d.S, vt_in_halves(d) ? 1 : 0,
+                       (const uint16_t*)q, qs, qp, d.NB);
     return hipGetLastError();
 }
 
@@ -296,21 +290,14 @@ hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_prepare_kv(const Dims& d, const void* k, Strides ks, const void* v, Strides vs, float* kp, void* vt_or_null,
-                             float* lvn_or_null, hipStream_t st) {
+hipError_t launch_prepare_kv(const Dims& d, const void* q, Strides qs, float* qp_or_null, const void* k, Strides ks, const void* v,
+                             Strides vs, float* kp, void* vt_or_null, float* lvn_or_null, hipStream_t st) {
     if (vt_or_null == nullptr && lvn_or_null == nullptr) return hipErrorInvalidValue;
-    if (d.D == 128 && d.Bs == 128) return launch_prep<128, 128>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
-    if (d.D == 128 && d.Bs == 64) return launch_prep<128, 64>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
-    if (d.D == 64 && d.Bs == 128) return launch_prep<64, 128>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
-    if (d.D == 64 && d.Bs == 64) return launch_prep<64, 64>(d, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 128 && d.Bs == 128) return launch_prep<128, 128>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 128 && d.Bs == 64) return launch_prep<128, 64>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 64 && d.Bs == 128) return launch_prep<64, 128>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 64 && d.Bs == 64) return launch_prep<64, 64>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_group_mean(const Dims& d, const float* qp, float* qg, hipStream_t st) {
-    const int64_t n4 = (int64_t)d.NB * d.D / 4, total4 = n4 * d.B * d.Hkv;
-    hipLaunchKernelGGL(group_mean_kernel, dim3((unsigned)((total4 + 255) / 256)), dim3(256), 0, st,
-                       (const float4*)qp, (float4*)qg, d.G, n4, total4);
-    return hipGetLastError();
 }
 
 hipError_t launch_vnorm(const Dims& d, const void* v, Strides vs, float* lvn, hipStream_t st) {

@@ -15,8 +15,10 @@ inline int score_rows(const Dims& d) {
     // pool, score and select 8 or 16 rows one after the other.  Up to 1024 rows, where 8 per workgroup give half of the
     // CUs one; 1.05 to 1.1 times the time of 8 from 2048 rows on.  Whole select calls, 32 heads: 2048 queries over 29952
     // tokens 25.9 -> 23.1 us, over 98304 tokens 67 -> 53 (34 of them pool K), over 131072 tokens 85 -> 67.
+    // Lists shared by a KV group, whose workgroups stream the queries of all heads of the group: up to 2048 rows (32768 tokens
+    // of 8 KV heads 67 -> 56 us).
     // (A mass budget keeps the larger groups: its second search makes the kernels twice as many, for rare calls.)
-    if (plain && rows <= 1024) return 4;
+    if (plain && rows <= (d.shared ? 2048 : 1024)) return 4;
     // up to 512 blocks: 8 rows per workgroup give the chip more rounds of workgroups, so that one round's
     // streaming overlaps another's scoring (0.065 -> 0.062 ms at 32768 tokens, 0.135 -> 0.124 ms at 65536)
     if (d.NBk <= 512) return 8;
@@ -48,6 +50,16 @@ inline int score_rows(const Dims& d) {
         return depth8 < depth16 && rows <= 16384 ? 8 : 16;
     }
     return wg16 <= 512 || (rows <= 14336 && (two_chunks || d.D == 64)) ? 8 : 16;
+}
+
+// Lists shared by a KV group (d: with the KV heads as heads): do the workgroups of the score kernel pool the queries of all heads of
+// the group themselves?  Each streams as many blocks as it has rows times the heads of a group, 50 to 60 GB/s for a workgroup, so it
+// takes enough of them.  With 79 to 256 workgroups the pooling launch of K does it faster: select calls of 20000 tokens, 16/2
+// heads, 33 us in the kernel, 22 that way; 4096 tokens 18.8 and 15.5; 16384 tokens, head_dim 64, 18.8 and 18.1; 1000 tokens
+// (fused) 45 and 39.  With 392 and more the kernel: 50000 tokens with a mass budget 91.8 against 99.1, 32768 tokens 56 against 63.
+inline bool group_pooled_in_kernel(const Dims& d) {
+    const int R = score_rows(d);
+    return (int64_t)d.B * d.Hq * ((d.NB + R - 1) / R) >= 320;
 }
 
 }  // namespace spa

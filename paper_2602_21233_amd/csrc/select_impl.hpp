@@ -11,8 +11,8 @@
 //   Phase 0 - query pooling (step 1 for Q, in the kernel).  The workgroup streams its R
 //   query blocks from Q and pools them itself, so that the Q stream of the select stage
 //   (four fifths of its bytes) runs while other workgroups score and select; the split
-//   pooled queries go straight to LDS.  (Group-shared lists read pooled queries from
-//   memory instead.)
+//   pooled queries go straight to LDS.  (Group-shared lists: the mean of the group's pooled
+//   queries.)
 //   Phase 1 - scores on the matrix cores.  The fp32 pooled vectors are split
 //   into a bf16 head and a bf16 tail (x = hi + lo, |x - hi - lo| <= 2^-18 |x|)
 //   and each 32x32 tile of Qp Kp^T is accumulated in fp32 from three
@@ -227,14 +227,6 @@ __global__ __launch_bounds__(kWaves * 64) void topk_from_scores_kernel(
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) float f32x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-// x = hi + lo with both parts bf16 (round to nearest even twice)
-__device__ __forceinline__ void split_bf16(const float4 a, const float4 b, bf16x8& hi, bf16x8& lo) {
-    f32x8 x = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    hi = __builtin_convertvector(x, bf16x8);
-    f32x8 back = __builtin_convertvector(hi, f32x8);
-    lo = __builtin_convertvector(x - back, bf16x8);
-}
 
 // sum of v over the 64 lanes (DPP row reductions + row broadcasts), returned wave-uniform
 __device__ __forceinline__ int wave_sum(int v) {
@@ -539,7 +531,6 @@ __device__ __forceinline__ int mass_budget_regs(const uint32_t (&key)[MAXC], uin
 
 // Everything the score + top-k step of one workgroup needs besides its rows.
 struct ScoreArgs {
-    const float* qp;              // pooled Q [B*Hq, NB, D] fp32
     const float* kp;              // pooled K, tiled in operand layout by the pooling kernel
     int Hq, G, NB /* query blocks */, NBk, off /* block position of query block 0 */;
     Pattern pt;
@@ -555,30 +546,50 @@ struct ScoreArgs {
     uint32_t gamma_q16;           // cumulative-mass budget in 16-bit fixed point (MASS kernels only)
     const int32_t* seq_lens;      // ragged batch: tokens per batch entry, or nullptr
     int S, Bs;                    // padded query tokens, block size (to turn seq_lens into block counts)
-    const uint16_t* q;            // QPOOL kernels: the queries themselves (pooled in the kernel), layout qs
+    const uint16_t* q;            // the queries themselves (pooled in the kernel), layout qs
     Strides qs;
+    int group;                    // GROUP kernels: query heads h * group .. + group - 1 share list h
+    const float* qp;              // GROUP kernels: pooled queries [B * Hq * group, NB, D] fp32, or nullptr: pooled in the kernel
 };
 
 // Phase 0 of the score kernels: the split pooled queries (MFMA A operands) of the query blocks
 // i0 .. i0 + R - 1 of head bh go to LDS behind the SW words of score space at S, in the space of the
 // phase-2 counters, instead of being held in 8 * D / 16 registers per lane: the kernels stay within
 // 128 registers.  Needs R * D * 4 bytes <= the counters' NWV KB.
-// QPOOL: the workgroup pools its R query blocks from Q itself (the block mean pooling of step 1,
-// same arithmetic in the same order as pool_kernel) instead of reading pooled queries.  Streaming
+// The workgroup pools its R query blocks from Q itself (the block mean pooling of step 1,
+// same arithmetic in the same order as pool_kernel).  Streaming
 // 16 blocks (512 KB) per workgroup with two blocks per 256 threads in flight keeps the HBM busy
 // while the other workgroup of the CU scores and selects: the Q stream, four fifths of the bytes
 // of the select stage, hides the rest of the stage.  Ends with a barrier.
-template <int D, int R, int SW, int NWV, bool QPOOL>
+// GROUP: a row's query is the mean of the pooled queries of a.group heads (lists shared by a KV group).  Their blocks are streamed one
+// after the other and added in head order, so that here, too, the Q stream hides the rest: select calls of 32/8 heads against
+// pooled and averaged queries from two launches before 32768 tokens 65 -> 56 us, 65536 126 -> 109, 131072 256 -> 211, 262144 of
+// 40/8 heads 634 -> 503.  A workgroup then reads 512 KB and more; where there are too few of them to fill the chip (the
+// rule is group_pooled_in_kernel), the pooling launch of K has pooled the heads' queries, too, and they are averaged here.
+template <int D, int R, int SW, int NWV, bool GROUP>
 __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, const int i0, float* S) {
-    constexpr int DS = D / 16;
     const int NB = a.NB;
     const int b = bh / a.Hq, h = bh % a.Hq;
-    const float* qbase = a.qp + (int64_t)bh * NB * D;
     // LDS copy of the split queries: the 8 dims 16s + 8 * half .. +7 of row r, part p (0 = hi, 1 = lo)
     // at bf16 offset ((((s * 2 + p) * R + r) * 2 + half) * 8
     __bf16* const qlds = reinterpret_cast<__bf16*>(S + SW);
     static_assert(R * D * 4 <= NWV * 256 * 4, "staged queries must fit the counters' space");
-    if constexpr (QPOOL) {
+    if (GROUP && a.qp != nullptr) {
+        for (int x = threadIdx.x; x < R * D; x += NWV * 64) {
+            const int r = x / D, d = x % D;
+            const int row = i0 + r < NB ? i0 + r : NB - 1;    // rows past the end are computed but never used
+            const float* src = a.qp + ((int64_t)bh * a.group * NB + row) * D + d;
+            float sum = src[0];
+            for (int g = 1; g < a.group; ++g) sum += src[(int64_t)g * NB * D];
+            float mean = sum * (1.0f / (float)a.group);
+            asm("" : "+v"(mean));                            // rounded before it is split
+            const __bf16 hi = (__bf16)mean;
+            const int at = ((((d >> 4) * 2 + 0) * R + r) * 2 + ((d >> 3) & 1)) * 8 + (d & 7);
+            qlds[at] = hi;
+            qlds[at + R * 2 * 8] = (__bf16)(mean - (float)hi);
+        }
+        __syncthreads();
+    } else {
         constexpr int TPR = D / 8, RPP = 256 / TPR;      // lanes per token row, token rows per pass
         constexpr int NGRP = NWV / 4;                    // groups of 256 threads, one block at a time each
         constexpr int ROWS = (R + NGRP - 1) / NGRP;      // query blocks per group
@@ -591,7 +602,7 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
         const int Sq_b = entry_len(a.seq_lens, b, a.S);
         typedef float (*Part)[D];
         Part const part = reinterpret_cast<Part>(PART_IN_S ? S : S + SW + NWV * 256) + grp * 2 * RPP;   // two buffers of RPP rows per group
-        const uint16_t* const qhead = a.q + b * a.qs.b + h * a.qs.h;
+        const uint16_t* const qhead = a.q + b * a.qs.b + (GROUP ? h * a.group : h) * a.qs.h;
         const int64_t tstride = a.qs.t;
         // tokens of this group's rr-th block that exist (0: block past the call, the entry or the tile)
         auto valid_tokens = [&](int rr) {
@@ -616,9 +627,9 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
 #pragma unroll
             for (int p2 = 0; p2 < PASSES; ++p2) voff[p2] = 2u * ((uint32_t)(p2 * RPP + prow) * (uint32_t)tstride + (uint32_t)chunk * 8u);
             const int grp_u = __builtin_amdgcn_readfirstlane(grp);
-            auto load = [&](auto slot_tag, int rr) {
+            auto load = [&](auto slot_tag, int rr, int g) {      // block rr of this group of threads, head g of the KV group
                 constexpr int SLOT = decltype(slot_tag)::value;
-                const char* const base = reinterpret_cast<const char*>(qhead + (int64_t)(i0 + grp_u + rr * NGRP) * Bs * tstride);
+                const char* const base = reinterpret_cast<const char*>(qhead + (GROUP ? g * a.qs.h : 0) + (int64_t)(i0 + grp_u + rr * NGRP) * Bs * tstride);
                 const int nv = FULL ? Bs : valid_tokens(rr);
 #pragma unroll
                 for (int p2 = 0; p2 < PASSES; ++p2) {
@@ -630,10 +641,10 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
                     }
                 }
             };
-            static_for_sel<(DEPTH < ROWS ? DEPTH : ROWS)>([&](auto rr_tag) { load(rr_tag, decltype(rr_tag)::value); });
-            static_for_sel<ROWS>([&](auto rr_tag) {
-                constexpr int RR = decltype(rr_tag)::value;
-                constexpr int SLOT = RR % DEPTH;
+            // the block in a slot: partial sums of its token rows to LDS, the slot's next load, then the means of the D columns
+            float mean = 0.f;                             // threads 0 .. D - 1 of the group
+            auto reduce = [&](auto slot_tag, int rr, auto&& next) {
+                constexpr int SLOT = decltype(slot_tag)::value;
                 float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int p2 = 0; p2 < PASSES; ++p2) {
@@ -642,25 +653,73 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
                     acc[4] += bf16_lo(raw[SLOT][p2].z); acc[5] += bf16_hi(raw[SLOT][p2].z);
                     acc[6] += bf16_lo(raw[SLOT][p2].w); acc[7] += bf16_hi(raw[SLOT][p2].w);
                 }
-                Part const buf = part + (RR & 1) * RPP;
+                Part const buf = part + SLOT * RPP;       // slots alternate: one barrier a block
 #pragma unroll
                 for (int e = 0; e < 8; ++e) buf[prow][chunk * 8 + e] = acc[e];
-                if constexpr (RR + DEPTH < ROWS) load(IC_sel<SLOT>{}, RR + DEPTH);
+                next();
                 __syncthreads();
-                const int r = grp + RR * NGRP;
-                if (t256 < D && r < R) {
+                if (t256 < D) {
                     float sum = 0.f;
 #pragma unroll
                     for (int rr2 = 0; rr2 < RPP; ++rr2) sum += buf[rr2][t256];
-                    const int nv = FULL ? Bs : valid_tokens(RR);
-                    const float mean = nv == Bs ? sum * (1.0f / (float)Bs) : (nv > 0 ? sum / (float)nv : 0.f);
-                    const __bf16 hi = (__bf16)mean;                   // round to nearest even, twice
-                    const __bf16 lo = (__bf16)(mean - (float)hi);
+                    const int nv = FULL ? Bs : valid_tokens(rr);
+                    mean = nv == Bs ? sum * (1.0f / (float)Bs) : (nv > 0 ? sum / (float)nv : 0.f);
+                }
+            };
+            auto put = [&](int rr, float x) {             // the pooled query of block rr, split
+                const int r = grp + rr * NGRP;
+                if (t256 < D && r < R) {
+                    const __bf16 hi = (__bf16)x;                      // round to nearest even, twice
+                    const __bf16 lo = (__bf16)(x - (float)hi);
                     const int at = ((((t256 >> 4) * 2 + 0) * R + r) * 2 + ((t256 >> 3) & 1)) * 8 + (t256 & 7);
                     qlds[at] = hi;
                     qlds[at + R * 2 * 8] = lo;
                 }
-            });
+            };
+            static_assert(DEPTH == 2, "the slots alternate");
+            if constexpr (!GROUP) {
+                static_for_sel<(DEPTH < ROWS ? DEPTH : ROWS)>([&](auto rr_tag) { load(rr_tag, decltype(rr_tag)::value, 0); });
+                static_for_sel<ROWS>([&](auto rr_tag) {
+                    constexpr int RR = decltype(rr_tag)::value;
+                    reduce(IC_sel<RR % DEPTH>{}, RR, [&]() { if constexpr (RR + DEPTH < ROWS) load(IC_sel<RR % DEPTH>{}, RR + DEPTH, 0); });
+                    put(RR, mean);
+                });
+            } else {
+                // the ROWS * group blocks in a row, two in flight; the loop's loads are all unconditional, its last two
+                // blocks are peeled
+                static_assert(ROWS % 2 == 0, "an even number of blocks");
+                const int ng = a.group;
+                const float inv = 1.0f / (float)ng;
+                int rr = 0, g = 0, rr_l = 0, g_l = 0;     // next block to reduce, to load
+                float sum_g = 0.f;
+                auto load_next = [&](auto slot_tag) {
+                    load(slot_tag, rr_l, g_l);
+                    if (++g_l == ng) { g_l = 0; ++rr_l; }
+                };
+                auto add = [&]() {
+                    sum_g = g == 0 ? mean : sum_g + mean;
+                    if (++g == ng) {
+                        float x = sum_g * inv;
+                        asm("" : "+v"(x));               // rounded before it is split, not contracted with the difference
+                        put(rr, x);
+                        g = 0;
+                        ++rr;
+                    }
+                };
+                load_next(IC_sel<0>{});
+                load_next(IC_sel<1>{});
+#pragma nounroll
+                for (int x = 2; x < ROWS * ng; x += 2) {
+                    reduce(IC_sel<0>{}, rr, [&]() { load_next(IC_sel<0>{}); });
+                    add();
+                    reduce(IC_sel<1>{}, rr, [&]() { load_next(IC_sel<1>{}); });
+                    add();
+                }
+                reduce(IC_sel<0>{}, rr, []() {});
+                add();
+                reduce(IC_sel<1>{}, rr, []() {});
+                add();
+            }
         };
         // whole tile inside the call, the entry and (rows per group) the tile: every block is full
         const bool full = R % NGRP == 0 && (int64_t)(i0 + R) * Bs <= (int64_t)Sq_b;
@@ -671,27 +730,14 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
             if (full) pool_rows(IC_sel<P64>{}, IC_sel<1>{}); else pool_rows(IC_sel<P64>{}, IC_sel<0>{});
         }
         __syncthreads();
-    } else {
-        const int t = threadIdx.x;
-        if (t < R * DS * 2) {
-            const int r = t % R, s2 = (t / R) >> 1, hf = (t / R) & 1;
-            int row = i0 + r;
-            if (row > NB - 1) row = NB - 1;               // rows past the end are computed but never used
-            const float* src = qbase + (int64_t)row * D + 16 * s2 + 8 * hf;
-            bf16x8 hi, lo;
-            split_bf16(*reinterpret_cast<const float4*>(src), *reinterpret_cast<const float4*>(src + 4), hi, lo);
-            *reinterpret_cast<bf16x8*>(qlds + (((s2 * 2 + 0) * R + r) * 2 + hf) * 8) = hi;
-            *reinterpret_cast<bf16x8*>(qlds + (((s2 * 2 + 1) * R + r) * 2 + hf) * 8) = lo;
-        }
-        __syncthreads();
     }
 }
 
 // Scores, top-k and merged lists of the query blocks i0 .. i0 + R - 1 of head bh = b * Hq + h, by a
 // 512-thread workgroup.  S: R * (MAXC * 64 + 8) floats of LDS for the scores, then 256 counters per
 // wavefront.  Ends without a barrier; the caller must not reuse S before one.
-// The split pooled queries are staged in LDS by stage_queries (QPOOL: pooled from Q in the kernel).
-template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool QPOOL>
+// The split pooled queries are staged in LDS by stage_queries.
+template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP>
 __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S) {
     constexpr int LD = MAXC * 64 + 8;          // +8 words: the two lane halves of a store hit different banks
     constexpr int DS = D / 16;
@@ -719,7 +765,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
     // ---- phase 0 / phase 1 ------------------------------------------------------------
     // LDS copy of the split queries: the 8 dims 16s + 8 * half .. +7 of row r, part p (0 = hi, 1 = lo)
     // at bf16 offset ((((s * 2 + p) * R + r) * 2 + half) * 8
-    stage_queries<D, R, R * LD, NWV, QPOOL>(a, bh, i0, S);
+    stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
     const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
     // The pooled K arrives tiled in operand layout and already split into bf16 head and tail:
     // tile jt of 32 key blocks is 32 * D * 4 bytes, and the 8 dims 16s + 8 * half .. +7 of block
@@ -881,7 +927,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
 // first chunk wait in registers (16 per lane and row) while the second chunk is scored, then each
 // row is selected exactly as in the plain kernel, from 32 scores per lane.  (No cumulative-mass
 // variant: that budget keeps the 8-row kernel.)
-template <int D, int R, int MAXCH, bool EXT, int NWV, bool QPOOL>
+template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
 __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, const int bh, const int i0, float* S) {
     constexpr int CC = 16;                     // 64-block register chunks per column chunk
     constexpr int CW = CC * 64;                // key blocks per column chunk
@@ -909,7 +955,7 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     const int n_jt = ((i_last + off) >> 5) + 1;           // 32-wide key-block tiles with some causal j
     const int n_ch = (i_last + off) / CW + 1;             // column chunks with some causal j (workgroup-uniform)
 
-    stage_queries<D, R, R * LD, NWV, QPOOL>(a, bh, i0, S);
+    stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
     const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
 
     head_config(a.head_pattern, h, pt, k);
@@ -1086,19 +1132,19 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     });
 }
 
-template <int D, int R, int MAXCH, bool EXT, int NWV, bool QPOOL>
+template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
 __global__ __launch_bounds__(NWV * 64, 4) void score_topk_chunked_kernel(ScoreArgs a, int n_tiles) {
     extern __shared__ __attribute__((aligned(128))) float S[];   // [R][1024 + 8] scores of one column chunk, then the staged queries
     const int nwg = gridDim.x;
     int wg = blockIdx.x;
     if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);   // each XCD a contiguous slice, as in the plain kernel
     const int tile = n_tiles - 1 - wg % n_tiles;          // long rows first
-    score_topk_rows_chunked<D, R, MAXCH, EXT, NWV, QPOOL>(a, wg / n_tiles, tile * R, S);
+    score_topk_rows_chunked<D, R, MAXCH, EXT, NWV, GROUP>(a, wg / n_tiles, tile * R, S);
 }
 
 // Two workgroups per CU (4 wavefronts per SIMD): at most 128 registers, which is why the query
 // operands are staged in LDS.
-template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool QPOOL>
+template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP>
 __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs a, int n_tiles) {
     extern __shared__ __attribute__((aligned(128))) float S[];   // [R][LD] scores of this workgroup's rows, then 256 counters per wave
     // Workgroup ids go round robin over the 8 XCDs; give each XCD a contiguous slice of the
@@ -1107,7 +1153,7 @@ __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs 
     int wg = blockIdx.x;
     if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
     const int tile = n_tiles - 1 - wg % n_tiles;          // long rows first
-    score_topk_rows<D, R, MAXC, EXT, MASS, NWV, QPOOL>(a, wg / n_tiles, tile * R, S);
+    score_topk_rows<D, R, MAXC, EXT, MASS, NWV, GROUP>(a, wg / n_tiles, tile * R, S);
 }
 
 // Dynamic LDS above the default cap has to be requested per kernel and device.  That is done on the
@@ -1134,18 +1180,19 @@ hipError_t allow_lds(const void* kernel, size_t bytes) {
     return e;
 }
 
-ScoreArgs score_args(const Dims& d, const float* qp, const float* kp, const int32_t* k_rows, const int32_t* head_pattern,
-                     const float* lvn, int32_t* idx, int32_t* cnt, float* scores_or_null, const void* q, Strides qs) {
-    return ScoreArgs{qp, kp, d.Hq, d.G, d.NB, d.NBk, d.off, pattern_of(d), d.k, k_rows, head_pattern, lvn, d.T, d.scale,
-                     idx, cnt, scores_or_null, d.gamma_q16 >= 0 ? (uint32_t)d.gamma_q16 : 0u, d.seq_lens, d.S, d.Bs, (const uint16_t*)q, qs};
+ScoreArgs score_args(const Dims& d, const float* kp, const int32_t* k_rows, const int32_t* head_pattern,
+                     const float* lvn, int32_t* idx, int32_t* cnt, float* scores_or_null, const void* q, Strides qs,
+                     int group, const float* qp) {
+    return ScoreArgs{kp, d.Hq, d.G, d.NB, d.NBk, d.off, pattern_of(d), d.k, k_rows, head_pattern, lvn, d.T, d.scale,
+                     idx, cnt, scores_or_null, d.gamma_q16 >= 0 ? (uint32_t)d.gamma_q16 : 0u, d.seq_lens, d.S, d.Bs, (const uint16_t*)q, qs, group, qp};
 }
 
 size_t keys_lds_bytes(int NB) { return (size_t)kWaves * (((NB + 63) >> 6) << 6) * sizeof(uint32_t); }
 
 }  // namespace
 
-#define SPA_SCORE_TOPK_ARGS const Dims& d, const float* qp, const float* kp, const int32_t* k_rows, const int32_t* head_pattern, \
-    const float* lvn, int32_t* idx, int32_t* cnt, float* scores_or_null, const void* q, Strides qs, hipStream_t st
+#define SPA_SCORE_TOPK_ARGS const Dims& d, const float* kp, const int32_t* k_rows, const int32_t* head_pattern, \
+    const float* lvn, int32_t* idx, int32_t* cnt, float* scores_or_null, const void* q, Strides qs, int group, const float* qp, hipStream_t st
 
 #ifdef SPA_SELECT_D
 namespace {
@@ -1156,43 +1203,43 @@ struct ScoreCall {
     hipStream_t st;
 };
 
-template <int D, int R, int MAXC, bool EXT, bool MASS, bool QPOOL, int NWV = (R * (MAXC * 64 + 8) * 4 > 80 * 1024 ? 16 : 8)>
+template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, int NWV = (R * (MAXC * 64 + 8) * 4 > 80 * 1024 ? 16 : 8)>
 hipError_t launch_mfma_e(const ScoreCall& c) {
     constexpr size_t part_words = 2 * (NWV / 4) * (256 / (D / 8)) * D;    // partial sums of the in-kernel pooling
     constexpr size_t lds = ((size_t)R * (MAXC * 64 + 8) + NWV * 256 +
-                            (QPOOL && part_words > (size_t)R * (MAXC * 64 + 8) ? part_words : 0)) * sizeof(float);
-    hipError_t e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, QPOOL>, lds);
+                            (part_words > (size_t)R * (MAXC * 64 + 8) ? part_words : 0)) * sizeof(float);
+    hipError_t e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
     dim3 grid((unsigned)(n_tiles * c.d.B * c.d.Hq));
-    hipLaunchKernelGGL((score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, QPOOL>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
+    hipLaunchKernelGGL((score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
     return hipGetLastError();
 }
 
 template <int D, int R, int MAXC, bool EXT, bool MASS>
 hipError_t launch_mfma_q(const ScoreCall& c) {
-    if (c.a.q != nullptr) return launch_mfma_e<D, R, MAXC, EXT, MASS, true>(c);
+    if (c.a.group > 1) return launch_mfma_e<D, R, MAXC, EXT, MASS, true>(c);
     return launch_mfma_e<D, R, MAXC, EXT, MASS, false>(c);
 }
 
-template <int D, int MAXCH, bool EXT, bool QPOOL>
+template <int D, int MAXCH, bool EXT, bool GROUP>
 hipError_t launch_chunked_e(const ScoreCall& c) {
     constexpr int R = 16, NWV = 8;
     constexpr size_t lds = ((size_t)R * (1024 + 8) + NWV * 256) * sizeof(float);
     static_assert(2 * (NWV / 4) * (256 / (D / 8)) * D <= R * (1024 + 8), "the pooling partial sums fit the score space");
-    hipError_t e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, QPOOL>, lds);
+    hipError_t e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
     dim3 grid((unsigned)(n_tiles * c.d.B * c.d.Hq));
-    hipLaunchKernelGGL((score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, QPOOL>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
+    hipLaunchKernelGGL((score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
     return hipGetLastError();
 }
 
 template <int D, int MAXCH>
 hipError_t launch_chunked(const ScoreCall& c) {
-    const bool qpool = c.a.q != nullptr;
-    if (extended(c.d)) return qpool ? launch_chunked_e<D, MAXCH, true, true>(c) : launch_chunked_e<D, MAXCH, true, false>(c);
-    return qpool ? launch_chunked_e<D, MAXCH, false, true>(c) : launch_chunked_e<D, MAXCH, false, false>(c);
+    const bool group = c.a.group > 1;
+    if (extended(c.d)) return group ? launch_chunked_e<D, MAXCH, true, true>(c) : launch_chunked_e<D, MAXCH, true, false>(c);
+    return group ? launch_chunked_e<D, MAXCH, false, true>(c) : launch_chunked_e<D, MAXCH, false, false>(c);
 }
 
 template <int D, int R, int MAXC>
@@ -1223,7 +1270,7 @@ hipError_t launch_mfma_d(const ScoreCall& c) {
 #define SPA_CAT2(a, b) a##b
 #define SPA_CAT(a, b) SPA_CAT2(a, b)
 hipError_t SPA_CAT(launch_score_topk_d, SPA_SELECT_D)(SPA_SCORE_TOPK_ARGS) {
-    const ScoreCall c{d, score_args(d, qp, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs), st};
+    const ScoreCall c{d, score_args(d, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, group, qp), st};
     return launch_mfma_d<SPA_SELECT_D>(c);
 }
 
@@ -1249,8 +1296,8 @@ hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int
 }
 
 hipError_t launch_score_topk(SPA_SCORE_TOPK_ARGS) {
-    if (d.D == 128) return launch_score_topk_d128(d, qp, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, st);
-    if (d.D == 64) return launch_score_topk_d64(d, qp, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, st);
+    if (d.D == 128) return launch_score_topk_d128(d, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, group, qp, st);
+    if (d.D == 64) return launch_score_topk_d64(d, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, group, qp, st);
     return hipErrorInvalidValue;
 }
 #endif

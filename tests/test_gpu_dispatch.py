@@ -230,3 +230,38 @@ def test_values_behind_a_wavefronts_queries_take_no_part(spa, D, Bs, shared, NB)
         assert torch.equal(got[:, :, :end], want[:, :, :end])
         vt = spa.transpose_v(bad, Bs)
         assert torch.equal(spa.attn_vt(q, k, vt, idx, cnt, Bs, pattern=pattern, group_shared=shared)[:, :, :end], want[:, :, :end])
+
+
+# Lists shared by a KV group: the queries of the group's heads are pooled and averaged by the score kernel itself (320 workgroups
+# and more) or pooled with K and averaged by the score kernel, from a call with V (fused) or without (select).  Either way a row ranks the
+# mean of its heads' block means: scores against fp64 (rtol 1e-4, atol 1e-5: fp32 sums of 128 products of magnitude <= 1), lists
+# and counts as the rule gives on those scores.
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,Bs,P,ragged", [
+    (1, 4, 2, 70, 64, 64, 0, False),             # one row and a bit
+    (2, 6, 2, 64 * 9 + 1, 128, 64, 64 * 40, True),   # a last block of one token, empty blocks
+    (1, 10, 2, 128 * 33 + 77, 128, 128, 0, False),   # groups of five
+    (4, 16, 8, 128 * 39 + 5, 64, 128, 0, False),     # 4 x 8 x 10 workgroups of 4 rows: 320
+    (4, 24, 8, 64 * 42 - 1, 128, 64, 64 * 300, True),    # groups of three, 352 workgroups, longer rows
+    (8, 16, 8, 64 * 39, 64, 64, 0, False),           # 8 rows a workgroup, 320 of them
+])
+def test_group_means_of_pooled_queries(spa, B, Hq, Hkv, S, D, Bs, P, ragged):
+    G = Hq // Hkv
+    q, k, v = _normal((B, Hq, S, D), 1), _normal((B, Hkv, P + S, D), 2), _normal((B, Hkv, P + S, D), 3)
+    lens = [max(1, S - 37 * b * Bs // 20) for b in range(B)] if ragged else [S] * B
+    kw = dict(seq_lens=torch.tensor(lens, dtype=torch.int32, device="cuda")) if ragged else {}
+    idx, cnt, sp = spa.select(q, k, Bs, 1, 2, 6, return_scores=True, group_shared=True, **kw)
+    _, idx2, cnt2 = spa.fused(q, k, v, Bs, 1, 2, 6, return_lists=True, group_shared=True, **kw)
+    mean = lambda x: torch.stack([x[:, i: i + Bs].double().mean(1) for i in range(0, x.shape[1], Bs)], 1)
+    for b, n in enumerate(lens):
+        nb, off = -(-n // Bs), P // Bs
+        qp = mean(q[b, :, :n]).view(Hkv, G, nb, D).mean(1)
+        kp = mean(k[b, :, : P + n])
+        want = qp @ kp.transpose(1, 2).contiguous() / D ** 0.5
+        seen = torch.arange(off + nb, device="cuda") <= torch.arange(off, off + nb, device="cuda").unsqueeze(1)
+        got = sp[b, :, :nb, : off + nb].double()
+        assert torch.allclose(got[:, seen], want[:, seen], rtol=1e-4, atol=1e-5), (b, (got[:, seen] - want[:, seen]).abs().max())
+        assert torch.equal(idx[b, :, :nb], idx2[b, :, :nb]) and torch.equal(cnt[b], cnt2[b])
+        assert (cnt[b, :, nb:] == 0).all()
+    blocks = dict(seq_lens=torch.tensor([-(-n // Bs) * 64 for n in lens], dtype=torch.int32, device="cuda")) if ragged else {}
+    again, n_again = spa.topk_from_scores(sp, 1, 2, 6, **blocks)         # takes its lengths in blocks of 64
+    assert torch.equal(again, idx) and torch.equal(n_again, cnt)
