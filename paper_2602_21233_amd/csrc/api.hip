@@ -130,6 +130,9 @@ int select_launches(Dims d, const spa_params* p, const void* q, const void* k, c
     // group-shared lists of few rows they are pooled beforehand with K
     const bool with_v = rank_by_values || vt_or_null != nullptr;       // K and what the call needs of V go in one launch
     float* const lvn = rank_by_values ? sc.lvn : nullptr;
+    if (small_call(d, rank_by_values))
+        return launch_code(launch_score_small(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride),
+                                              vt_or_null, k_rows, head_pattern, block_idx, block_cnt, pooled_scores_or_null, st));
     Dims lists = d;                                       // one list per KV head: selected as if the KV heads were the query heads
     if (d.shared) {
         lists.Hq = d.Hkv;

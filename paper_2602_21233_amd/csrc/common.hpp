@@ -87,6 +87,11 @@ hipError_t launch_prepare_kv(const Dims& d, const void* q, Strides qs, float* qp
 hipError_t launch_score_topk(const Dims& d, const float* kp, const int32_t* k_rows,
                              const int32_t* head_pattern, const float* lvn, int32_t* idx, int32_t* cnt,
                              float* scores_or_null, const void* q, Strides qs, int group, const float* qp, hipStream_t st);
+// A small call (small_call in score_rows.hpp) in one launch: no pooled K, no launch_prepare_kv before; vt_or_null: V^T, as vt_in_halves
+// says.
+hipError_t launch_score_small(const Dims& d, const void* q, Strides qs, const void* k, Strides ks, const void* v, Strides vs,
+                              void* vt_or_null, const int32_t* k_rows, const int32_t* head_pattern, int32_t* idx, int32_t* cnt,
+                              float* scores_or_null, hipStream_t st);
 hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int32_t* k_rows,
                                    const int32_t* head_pattern, int32_t* idx, int32_t* cnt, hipStream_t st);
 // counts, into *n_bad (device), the list rows that break the attention kernel's layout rules

@@ -52,6 +52,15 @@ inline int score_rows(const Dims& d) {
     return wg16 <= 512 || (rows <= 14336 && (two_chunks || d.D == 64)) ? 8 : 16;
 }
 
+// Does a call go through score_topk_small_kernel, one launch instead of two?  Where the launches are what it takes: the score workgroups
+// then pool all of the K they see, one after the other, which pays up to 96 KB of K a head.  Fused calls, 32/8 heads: 300
+// tokens with head_dim 64 (38 KB) 19.4 -> 16.5 us, 300 with head_dim 128 (77 KB) 20.9 -> 20.3, 512 with head_dim 64 19.1 -> 18.3; but 777
+// with head_dim 64 (99 KB) 21.8 -> 22.9, 512 with head_dim 128, blocks of 64 (131 KB), 20.8 -> 22.1, 1024 (262 KB) 30.9 -> 34.4.
+// (At most 12 key blocks then: they are one tile.)  Not with a mass budget, shared lists or the output-aware score, whose kernels it would double.
+inline bool small_call(const Dims& d, bool rank_by_values) {
+    return d.gamma_q16 < 0 && !d.shared && !rank_by_values && (int64_t)d.Skv * d.D * 2 <= 96 << 10 && score_rows(d) == 4;
+}
+
 // Lists shared by a KV group (d: with the KV heads as heads): do the workgroups of the score kernel pool the queries of all heads of
 // the group themselves?  Each streams as many blocks as it has rows times the heads of a group, 50 to 60 GB/s for a workgroup, so it
 // takes enough of them.  With 79 to 256 workgroups the pooling launch of K does it faster: select calls of 20000 tokens, 16/2

@@ -44,6 +44,7 @@
 
 #include "common.hpp"
 #include "score_rows.hpp"
+#include "value_block.hpp"
 
 namespace spa {
 namespace {
@@ -733,12 +734,90 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
     }
 }
 
+// Small calls: what a workgroup needs to pool K itself, and the call's V^T.
+struct KeyArgs {
+    const uint16_t* k;
+    Strides ks;
+    const uint16_t* v;            // with vt: V -> V^T, blocks of Bs tokens, halves as vt_in_halves says
+    Strides vs;
+    uint16_t* vt;
+    int Skv, Hkv, halves;
+    int n_heads;                  // batch entries times KV heads
+};
+
+// where the pooled K tile of such a workgroup lies in its LDS (words): behind scores, counters and partial sums
+template <int D, int R, int LD, int NWV>
+__host__ __device__ constexpr int key_tile_at() {
+    return R * LD + NWV * 256 + 2 * (NWV / 4) * (256 / (D / 8)) * D;
+}
+
+// Means of the key blocks 0 .. n_blk - 1 (n_blk <= 32; kh: the head's first token, Skv tokens) to an operand tile in LDS, in
+// the layout and with the arithmetic of the pooling kernel (pool.hip).  Two groups of 256 threads take the blocks in turn, two in flight
+// each; all loads are unconditional, tokens past the end re-read the last one and count 0.  Ends with a barrier.
+template <int D, int BS, int NWV>
+__device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t, int n_blk, int Skv, float* part_base, __bf16* tile) {
+    constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, NGRP = NWV / 4;
+    const int t = threadIdx.x, grp = t >> 8, t256 = t & 255, prow = t256 / TPR, chunk = t256 % TPR;
+    typedef float (*Part)[D];
+    Part const part = reinterpret_cast<Part>(part_base) + grp * 2 * RPP;
+    uint4 raw[2][PASSES];
+    auto block_of = [&](int x) { const int j = x * NGRP + grp; return j < n_blk ? j : n_blk - 1; };
+    auto load = [&](auto slot_tag, int x) {
+        constexpr int SLOT = decltype(slot_tag)::value;
+        const int j = block_of(x), last = Skv - 1 - j * BS;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int row = p * RPP + prow < last ? p * RPP + prow : last;
+            raw[SLOT][p] = *reinterpret_cast<const uint4*>(kh + (int64_t)(j * BS + row) * stride_t + chunk * 8);
+        }
+    };
+    auto reduce = [&](auto slot_tag, int x) {
+        constexpr int SLOT = decltype(slot_tag)::value;
+        const int j = block_of(x), n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const uint32_t keep = p * RPP + prow < n_valid ? 0xffffffffu : 0u;
+            const uint4 w = make_uint4(raw[SLOT][p].x & keep, raw[SLOT][p].y & keep, raw[SLOT][p].z & keep, raw[SLOT][p].w & keep);
+            acc[0] += bf16_lo(w.x); acc[1] += bf16_hi(w.x);
+            acc[2] += bf16_lo(w.y); acc[3] += bf16_hi(w.y);
+            acc[4] += bf16_lo(w.z); acc[5] += bf16_hi(w.z);
+            acc[6] += bf16_lo(w.w); acc[7] += bf16_hi(w.w);
+        }
+        Part const buf = part + SLOT * RPP;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) buf[prow][chunk * 8 + e] = acc[e];
+        load(slot_tag, x + 2);
+        __syncthreads();
+        if (t256 < D && x * NGRP + grp < n_blk) {
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < RPP; ++r) sum += buf[r][t256];
+            float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
+            asm("" : "+v"(mean));                         // rounded before it is split, as in the pooling kernel
+            const __bf16 hi = (__bf16)mean;
+            const int at = (((t256 >> 3) * 2) * 32 + j) * 8 + (t256 & 7);
+            tile[at] = hi;
+            tile[at + 32 * 8] = (__bf16)(mean - (float)hi);
+        }
+    };
+    load(IC_sel<0>{}, 0);
+    load(IC_sel<1>{}, 1);
+    const int n = (n_blk + NGRP - 1) / NGRP;
+#pragma nounroll
+    for (int x = 0; x < n; x += 2) {                      // the same number of rounds for both groups
+        reduce(IC_sel<0>{}, x);
+        reduce(IC_sel<1>{}, x + 1);
+    }
+    __syncthreads();
+}
+
 // Scores, top-k and merged lists of the query blocks i0 .. i0 + R - 1 of head bh = b * Hq + h, by a
 // 512-thread workgroup.  S: R * (MAXC * 64 + 8) floats of LDS for the scores, then 256 counters per
 // wavefront.  Ends without a barrier; the caller must not reuse S before one.
 // The split pooled queries are staged in LDS by stage_queries.
-template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP>
-__device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S) {
+template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, bool KIN = false>
+__device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S, const KeyArgs* keys = nullptr) {
     constexpr int LD = MAXC * 64 + 8;          // +8 words: the two lane halves of a store hit different banks
     constexpr int DS = D / 16;
     const float* __restrict__ kp = a.kp;
@@ -755,7 +834,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
 
     const int b = bh / Hq, h = bh % Hq;
     const int Hkv = Hq / G;
-    const float* kbase = kp + (int64_t)(b * Hkv + h / G) * ((NBk + 31) >> 5) * (32 * D);   // tiled, see fetch_tile
+    const float* kbase = KIN ? nullptr : kp + (int64_t)(b * Hkv + h / G) * ((NBk + 31) >> 5) * (32 * D);   // tiled, see tile_ptr
     const float* lvbase = lvn != nullptr ? lvn + (int64_t)(b * Hkv + h / G) * NBk : nullptr;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
@@ -767,6 +846,18 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
     // at bf16 offset ((((s * 2 + p) * R + r) * 2 + half) * 8
     stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
     const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
+    if constexpr (KIN) {                                  // one tile, pooled by the workgroup itself
+        constexpr int part_at = 2 * (NWV / 4) * (256 / (D / 8)) * D <= R * LD ? 0 : R * LD + NWV * 256;
+        float* const tile = S + key_tile_at<D, R, LD, NWV>();
+        const int Skv_b = keys->Skv - a.S + entry_len(a.seq_lens, b, a.S);
+        const uint16_t* const kh = keys->k + b * keys->ks.b + (h / G) * keys->ks.h;
+        int n_blk = (Skv_b + a.Bs - 1) / a.Bs;            // the entry's blocks; causally visible ones
+        n_blk = n_blk < i_last + off + 1 ? n_blk : i_last + off + 1;
+        if (n_blk <= 0) {                                 // an empty entry: its rows get empty lists
+        } else if (a.Bs == 128) stage_keys<D, 128, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
+        else stage_keys<D, 64, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
+        kbase = tile;
+    }
     // The pooled K arrives tiled in operand layout and already split into bf16 head and tail:
     // tile jt of 32 key blocks is 32 * D * 4 bytes, and the 8 dims 16s + 8 * half .. +7 of block
     // l32 sit at bf16 offset (((2s + half) * 2 + part) * 32 + l32) * 8 (part 0 = hi, 1 = lo), so
@@ -1156,6 +1247,33 @@ __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs 
     score_topk_rows<D, R, MAXC, EXT, MASS, NWV, GROUP>(a, wg / n_tiles, tile * R, S);
 }
 
+// Small calls (small_call): one launch instead of prepare_kv_kernel (or pool_kernel) and the score kernel.  Every workgroup pools the K blocks
+// its rows can see itself, from L2, and the workgroups behind the first n_score transpose two blocks of V each.
+// Bound by launches and latency: 512 tokens of one head, head_dim 64, blocks of 64, 19.1 -> 16.3 us for the whole call (prepare_kv_kernel 2.9 us
+// and its launch away, 1.5 us more here).
+template <int D, bool EXT>
+__global__ __launch_bounds__(512, 4) void score_topk_small_kernel(ScoreArgs a, KeyArgs keys, int n_tiles, int n_score) {
+    extern __shared__ __attribute__((aligned(128))) float S[];
+    constexpr int R = 4, NWV = 8;
+    const int wg = blockIdx.x;
+    if (wg < n_score) {
+        score_topk_rows<D, R, 4, EXT, false, NWV, false, true>(a, wg / n_tiles, (n_tiles - 1 - wg % n_tiles) * R, S, &keys);
+        return;
+    }
+    const int half = threadIdx.x >> 8, x = 2 * (wg - n_score) + half;        // block of V
+    const int hy = x / a.NBk, blk = x % a.NBk;
+    const int b = hy / keys.Hkv, h = hy % keys.Hkv;
+    const int Sb = hy < keys.n_heads ? keys.Skv - a.S + entry_len(a.seq_lens, b, a.S) : 0;
+    int n_valid = Sb - blk * a.Bs;
+    n_valid = n_valid < 0 ? 0 : (n_valid > a.Bs ? a.Bs : n_valid);
+    const uint16_t* src = keys.v + (n_valid > 0 ? b * keys.vs.b + h * keys.vs.h + (int64_t)blk * a.Bs * keys.vs.t : 0);
+    uint16_t* dst = keys.vt + (int64_t)x * D * a.Bs;
+    uint16_t* tile = reinterpret_cast<uint16_t*>(S) + half * (a.Bs * (D + 2));
+    const int tid = threadIdx.x & 255;
+    if (a.Bs == 128) value_block<D, 128, true, false>(tid, src, keys.vs.t, n_valid, tile, nullptr, dst, keys.halves, nullptr);
+    else value_block<D, 64, true, false>(tid, src, keys.vs.t, n_valid, tile, nullptr, dst, keys.halves, nullptr);
+}
+
 // Dynamic LDS above the default cap has to be requested per kernel and device.  That is done on the
 // first launch of a (kernel, device) pair and remembered: later launches, also those recorded into a
 // stream capture, make no runtime call besides the launch itself.
@@ -1193,6 +1311,9 @@ size_t keys_lds_bytes(int NB) { return (size_t)kWaves * (((NB + 63) >> 6) << 6) 
 
 #define SPA_SCORE_TOPK_ARGS const Dims& d, const float* kp, const int32_t* k_rows, const int32_t* head_pattern, \
     const float* lvn, int32_t* idx, int32_t* cnt, float* scores_or_null, const void* q, Strides qs, int group, const float* qp, hipStream_t st
+
+#define SPA_SCORE_SMALL_ARGS const Dims& d, const void* q, Strides qs, const void* k, Strides ks, const void* v, Strides vs, void* vt_or_null, \
+    const int32_t* k_rows, const int32_t* head_pattern, int32_t* idx, int32_t* cnt, float* scores_or_null, hipStream_t st
 
 #ifdef SPA_SELECT_D
 namespace {
@@ -1255,6 +1376,19 @@ hipError_t launch_plain(const ScoreCall& c) {
     return extended(c.d) ? launch_mfma_q<D, R, MAXC, true, false>(c) : launch_mfma_q<D, R, MAXC, false, false>(c);
 }
 
+template <int D, bool EXT>
+hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
+    constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + 8, 8>() + 32 * D) * sizeof(float);
+    const size_t v_lds = keys.vt != nullptr ? 2 * c.d.Bs * (D + 2) * sizeof(uint16_t) : 0;
+    const size_t lds = v_lds > score_lds ? v_lds : score_lds;
+    hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, EXT>, lds);
+    if (e != hipSuccess) return e;
+    const int n_tiles = (c.d.NB + 3) / 4, n_score = n_tiles * c.d.B * c.d.Hq;
+    const int n_v = keys.vt != nullptr ? (c.d.B * c.d.Hkv * c.d.NBk + 1) / 2 : 0;
+    hipLaunchKernelGGL((score_topk_small_kernel<D, EXT>), dim3((unsigned)(n_score + n_v)), dim3(512), lds, c.st, c.a, keys, n_tiles, n_score);
+    return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_mfma_d(const ScoreCall& c) {
     const int NBk = c.d.NBk, R = score_rows(c.d);
@@ -1273,9 +1407,16 @@ hipError_t SPA_CAT(launch_score_topk_d, SPA_SELECT_D)(SPA_SCORE_TOPK_ARGS) {
     const ScoreCall c{d, score_args(d, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, group, qp), st};
     return launch_mfma_d<SPA_SELECT_D>(c);
 }
+hipError_t SPA_CAT(launch_score_small_d, SPA_SELECT_D)(SPA_SCORE_SMALL_ARGS) {
+    const ScoreCall c{d, score_args(d, nullptr, k_rows, head_pattern, nullptr, idx, cnt, scores_or_null, q, qs, 1, nullptr), st};
+    const KeyArgs keys{(const uint16_t*)k, ks, (const uint16_t*)v, vs, (uint16_t*)vt_or_null, d.Skv, d.Hkv, vt_in_halves(d) ? 1 : 0, d.B * d.Hkv};
+    return extended(d) ? launch_small_e<SPA_SELECT_D, true>(c, keys) : launch_small_e<SPA_SELECT_D, false>(c, keys);
+}
 
 #else
 hipError_t launch_score_topk_d128(SPA_SCORE_TOPK_ARGS);
+hipError_t launch_score_small_d128(SPA_SCORE_SMALL_ARGS);
+hipError_t launch_score_small_d64(SPA_SCORE_SMALL_ARGS);
 hipError_t launch_score_topk_d64(SPA_SCORE_TOPK_ARGS);
 
 hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int32_t* k_rows,
@@ -1298,6 +1439,12 @@ hipError_t launch_topk_from_scores(const Dims& d, const float* scores, const int
 hipError_t launch_score_topk(SPA_SCORE_TOPK_ARGS) {
     if (d.D == 128) return launch_score_topk_d128(d, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, group, qp, st);
     if (d.D == 64) return launch_score_topk_d64(d, kp, k_rows, head_pattern, lvn, idx, cnt, scores_or_null, q, qs, group, qp, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_score_small(SPA_SCORE_SMALL_ARGS) {
+    if (d.D == 128) return launch_score_small_d128(d, q, qs, k, ks, v, vs, vt_or_null, k_rows, head_pattern, idx, cnt, scores_or_null, st);
+    if (d.D == 64) return launch_score_small_d64(d, q, qs, k, ks, v, vs, vt_or_null, k_rows, head_pattern, idx, cnt, scores_or_null, st);
     return hipErrorInvalidValue;
 }
 #endif

@@ -245,23 +245,49 @@ def test_values_behind_a_wavefronts_queries_take_no_part(spa, D, Bs, shared, NB)
     (8, 16, 8, 64 * 39, 64, 64, 0, False),           # 8 rows a workgroup, 320 of them
 ])
 def test_group_means_of_pooled_queries(spa, B, Hq, Hkv, S, D, Bs, P, ragged):
-    G = Hq // Hkv
+    _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, True)
+
+
+def _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, shared, kw=None):
     q, k, v = _normal((B, Hq, S, D), 1), _normal((B, Hkv, P + S, D), 2), _normal((B, Hkv, P + S, D), 3)
     lens = [max(1, S - 37 * b * Bs // 20) for b in range(B)] if ragged else [S] * B
-    kw = dict(seq_lens=torch.tensor(lens, dtype=torch.int32, device="cuda")) if ragged else {}
-    idx, cnt, sp = spa.select(q, k, Bs, 1, 2, 6, return_scores=True, group_shared=True, **kw)
-    _, idx2, cnt2 = spa.fused(q, k, v, Bs, 1, 2, 6, return_lists=True, group_shared=True, **kw)
+    if ragged and not shared:
+        lens[-1] = 0
+    kw = dict(kw or {}, **(dict(seq_lens=torch.tensor(lens, dtype=torch.int32, device="cuda")) if ragged else {}))
+    idx, cnt, sp = spa.select(q, k, Bs, 1, 2, 6, return_scores=True, group_shared=shared, **kw)
+    out, idx2, cnt2 = spa.fused(q, k, v, Bs, 1, 2, 6, return_lists=True, group_shared=shared, **kw)
+    if not kw:                                                           # the fused call's V^T is the attention call's
+        assert torch.equal(out, spa.attn(q, k, v, idx, cnt, Bs, group_shared=shared))
     mean = lambda x: torch.stack([x[:, i: i + Bs].double().mean(1) for i in range(0, x.shape[1], Bs)], 1)
     for b, n in enumerate(lens):
         nb, off = -(-n // Bs), P // Bs
-        qp = mean(q[b, :, :n]).view(Hkv, G, nb, D).mean(1)
+        assert (cnt[b, :, nb:] == 0).all()
+        if n == 0:
+            continue
+        qp = mean(q[b, :, :n])
+        qp = qp.view(Hkv, Hq // Hkv, nb, D)
         kp = mean(k[b, :, : P + n])
-        want = qp @ kp.transpose(1, 2).contiguous() / D ** 0.5
+        want = ((qp.mean(1) if shared else qp.flatten(1, 2)) @ kp.transpose(1, 2).contiguous() / D ** 0.5).view(-1, nb, off + nb)
         seen = torch.arange(off + nb, device="cuda") <= torch.arange(off, off + nb, device="cuda").unsqueeze(1)
         got = sp[b, :, :nb, : off + nb].double()
         assert torch.allclose(got[:, seen], want[:, seen], rtol=1e-4, atol=1e-5), (b, (got[:, seen] - want[:, seen]).abs().max())
         assert torch.equal(idx[b, :, :nb], idx2[b, :, :nb]) and torch.equal(cnt[b], cnt2[b])
-        assert (cnt[b, :, nb:] == 0).all()
-    blocks = dict(seq_lens=torch.tensor([-(-n // Bs) * 64 for n in lens], dtype=torch.int32, device="cuda")) if ragged else {}
-    again, n_again = spa.topk_from_scores(sp, 1, 2, 6, **blocks)         # takes its lengths in blocks of 64
+    if ragged:
+        kw["seq_lens"] = torch.tensor([-(-n // Bs) * 64 for n in lens], dtype=torch.int32, device="cuda")   # in blocks of 64 there
+    again, n_again = spa.topk_from_scores(sp, 1, 2, 6, **kw)
     assert torch.equal(again, idx) and torch.equal(n_again, cnt)
+
+
+# Calls of up to 96 KB of K a head: K pooled by the score workgroups, V transposed beside them, in one launch.
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,Bs,P,ragged,kw", [
+    (1, 1, 1, 1, 64, 64, 0, False, {}),
+    (1, 1, 1, 512, 64, 64, 0, False, {}),
+    (1, 4, 2, 768, 64, 64, 0, False, dict(stride_blocks=3)),     # the largest: 12 blocks
+    (2, 6, 2, 767, 64, 128, 0, False, {}),                       # groups of three, an odd number of blocks of V
+    (3, 4, 1, 300, 128, 64, 0, True, {}),                        # lengths down to none
+    (1, 8, 8, 129, 128, 128, 128, False, {}),                    # a prefix, a block of one token
+    (1, 4, 2, 65, 64, 64, 64 * 10, False, dict(n_dense_q_blocks=1)),
+    (2, 2, 2, 385, 128, 128, 0, True, {}),                       # just above: the two launches
+])
+def test_small_calls(spa, B, Hq, Hkv, S, D, Bs, P, ragged, kw):
+    _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, False, kw)
