@@ -67,6 +67,15 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 struct Strides { int64_t b, h, t; };
 inline Strides strides_of(const int64_t s[3]) { return Strides{s[0], s[1], s[2]}; }
 
+// Pooled K as the score kernel reads it: per KV head, tiles of 32 key blocks (32 * D * 4 bytes), every value split into its bf16 head
+// and tail (x = hi + lo), laid out as the B operand of v_mfma_f32_16x16x32_bf16 (32x32x16 products find theirs in quarters of a piece): 1-KB pieces (32 dims, 16 blocks, head or tail)
+// in which lane l finds the 8 dims 8 * (l >> 4) of block l & 15.  bf16 offset in the tile of the head of dim d of block blk;
+// its tail is kKeyTail further.
+constexpr int kKeyTail = 512;
+__device__ __forceinline__ int key_tile_offset(int d, int blk) {
+    return ((((d >> 5) * 2 + ((blk >> 4) & 1)) * 2 * 4 + ((d >> 3) & 3)) * 16 + (blk & 15)) * 8 + (d & 7);
+}
+
 // Launchers (one per kernel file).  Each returns a hipError_t from the launch.
 // k_tiled: write the pooled K in the score kernel's operand layout (tiles of 32 key blocks,
 // heads ceil(NBk / 32) tiles apart) instead of row major [.., NBk, D].

@@ -18,11 +18,8 @@ namespace {
 
 // One block of one head: mean of its tokens.  src: the block's first token; n_valid: its tokens that exist; part:
 // 256 / (D / 8) rows of D floats of LDS.
-// k_tiled: pooled K goes out in the operand layout of the score kernel instead of row
-// major fp32: per KV head, tiles of 32 key blocks (32 * D * 4 bytes); every value is
-// already split into its bf16 head and bf16 tail (x = hi + lo), and inside a tile the 8
-// dims 16s + 8h .. +7 of block r sit at bf16 offset (((2s + h) * 2 + part) * 32 + r) * 8,
-// part 0 = hi, 1 = lo, so a wavefront of that kernel reads whole 1-KB pieces that are its
+// k_tiled: pooled K goes out in the operand layout of the score kernel (key_tile_offset) instead of row
+// major fp32, so a wavefront of that kernel reads whole 1-KB pieces that are its
 // MFMA operands as they are.  dst is then the block's tile, otherwise the block's row.
 template <int D, int BS>
 __device__ __forceinline__ void pool_block(const uint16_t* __restrict__ src, int64_t stride_t, int n_valid, float (*part)[D],
@@ -61,9 +58,9 @@ __device__ __forceinline__ void pool_block(const uint16_t* __restrict__ src, int
             const __bf16 hi = (__bf16)mean;                       // round to nearest even, twice
             const __bf16 lo = (__bf16)(mean - (float)hi);
             __bf16* t = reinterpret_cast<__bf16*>(dst);
-            const int at = (((tid >> 3) * 2) * 32 + (blk & 31)) * 8 + (tid & 7);
+            const int at = key_tile_offset(tid, blk);
             t[at] = hi;
-            t[at + 32 * 8] = lo;
+            t[at + kKeyTail] = lo;
         } else {
             dst[tid] = mean;
         }

@@ -15,8 +15,8 @@
 //   queries.)
 //   Phase 1 - scores on the matrix cores.  The fp32 pooled vectors are split
 //   into a bf16 head and a bf16 tail (x = hi + lo, |x - hi - lo| <= 2^-18 |x|)
-//   and each 32x32 tile of Qp Kp^T is accumulated in fp32 from three
-//   v_mfma_f32_32x32x16_bf16 products (hi.hi + hi.lo + lo.hi); the dropped
+//   and each tile of Qp Kp^T is accumulated in fp32 from three bf16
+//   products (hi.hi + hi.lo + lo.hi; 16 rows: v_mfma_f32_16x16x32_bf16, fewer: 32x32x16); the dropped
 //   lo.lo term is below 2^-17 of a product.  The wavefronts take the key-block
 //   tiles round robin, reading Kp straight from L2 in operand layout.  The scores
 //   of the R rows stay in LDS; the NB x NB matrix never exists in memory unless
@@ -227,7 +227,11 @@ __global__ __launch_bounds__(kWaves * 64) void topk_from_scores_kernel(
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) float f32x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// words between the score rows in LDS beyond a multiple of 64: the four lane groups of a store, rows 4 apart, hit different banks
+constexpr int kRowPad = 4;
 
 // sum of v over the 64 lanes (DPP row reductions + row broadcasts), returned wave-uniform
 __device__ __forceinline__ int wave_sum(int v) {
@@ -553,6 +557,13 @@ struct ScoreArgs {
     const float* qp;              // GROUP kernels: pooled queries [B * Hq * group, NB, D] fp32, or nullptr: pooled in the kernel
 };
 
+// LDS copy of the split queries, A operands in groups of 8 dims by R rows: bf16 offset of the head of dim d of row r; its
+// tail is 4 * R * 8 further
+template <int R>
+__device__ __forceinline__ int query_offset(int d, int r) {
+    return ((((d >> 5) * 2) * 4 + ((d >> 3) & 3)) * R + r) * 8 + (d & 7);
+}
+
 // Phase 0 of the score kernels: the split pooled queries (MFMA A operands) of the query blocks
 // i0 .. i0 + R - 1 of head bh go to LDS behind the SW words of score space at S, in the space of the
 // phase-2 counters, instead of being held in 8 * D / 16 registers per lane: the kernels stay within
@@ -571,8 +582,6 @@ template <int D, int R, int SW, int NWV, bool GROUP>
 __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, const int i0, float* S) {
     const int NB = a.NB;
     const int b = bh / a.Hq, h = bh % a.Hq;
-    // LDS copy of the split queries: the 8 dims 16s + 8 * half .. +7 of row r, part p (0 = hi, 1 = lo)
-    // at bf16 offset ((((s * 2 + p) * R + r) * 2 + half) * 8
     __bf16* const qlds = reinterpret_cast<__bf16*>(S + SW);
     static_assert(R * D * 4 <= NWV * 256 * 4, "staged queries must fit the counters' space");
     if (GROUP && a.qp != nullptr) {
@@ -585,9 +594,9 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
             float mean = sum * (1.0f / (float)a.group);
             asm("" : "+v"(mean));                            // rounded before it is split
             const __bf16 hi = (__bf16)mean;
-            const int at = ((((d >> 4) * 2 + 0) * R + r) * 2 + ((d >> 3) & 1)) * 8 + (d & 7);
+            const int at = query_offset<R>(d, r);
             qlds[at] = hi;
-            qlds[at + R * 2 * 8] = (__bf16)(mean - (float)hi);
+            qlds[at + 4 * R * 8] = (__bf16)(mean - (float)hi);
         }
         __syncthreads();
     } else {
@@ -672,9 +681,9 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
                 if (t256 < D && r < R) {
                     const __bf16 hi = (__bf16)x;                      // round to nearest even, twice
                     const __bf16 lo = (__bf16)(x - (float)hi);
-                    const int at = ((((t256 >> 4) * 2 + 0) * R + r) * 2 + ((t256 >> 3) & 1)) * 8 + (t256 & 7);
+                    const int at = query_offset<R>(t256, r);
                     qlds[at] = hi;
-                    qlds[at + R * 2 * 8] = lo;
+                    qlds[at + 4 * R * 8] = lo;
                 }
             };
             static_assert(DEPTH == 2, "the slots alternate");
@@ -731,6 +740,78 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
             if (full) pool_rows(IC_sel<P64>{}, IC_sel<1>{}); else pool_rows(IC_sel<P64>{}, IC_sel<0>{});
         }
         __syncthreads();
+    }
+}
+
+// Scores of a tile from its two accumulators (key blocks j and j + 16; a lane holds the rows 4 * (lane >> 4) .. + 3) to the LDS rows, whose
+// first column is key block col0, and to memory if asked for.  Output-aware ranking: the key block's ln(value magnitude) joins.
+template <int R, int LD>
+__device__ __forceinline__ void store_scores(const ScoreArgs& a, const f32x4 (&acc)[2], float* S, int col0, int j, int bh, int i0,
+                                             const float* lvbase) {
+    const int row0 = 4 * ((threadIdx.x & 63) >> 4);
+    if (row0 >= R) return;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int ju = j + 16 * u;
+        const float lv = lvbase != nullptr ? lvbase[ju < a.NBk ? ju : a.NBk - 1] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int mrow = row0 + r;
+            const float sc = lvbase != nullptr ? a.scale * acc[u][r] + lv : a.scale * acc[u][r];
+            S[mrow * LD + ju - col0] = sc;
+            const int i = i0 + mrow;
+            if (a.scores_out != nullptr && i < a.NB && ju < a.NBk)
+                a.scores_out[((int64_t)bh * a.NB + i) * a.NBk + ju] = ju <= i + a.off ? sc : -INFINITY;
+        }
+    }
+}
+
+// Scores of the key tiles jt_first, jt_first + NWV, .. below jt_end for 16 rows, from v_mfma_f32_16x16x32_bf16: with 32x32x16 products, half of
+// whose rows were copies, the matrix cores and the LDS were busy twice as long, and the 16 accumulators made the
+// two-chunk kernel spill 28 to 44 registers (select calls, 262144 tokens of 40/8 heads 736 -> 701 us, of 32/8 heads 600 -> 567, 131072 tokens
+// 244 -> 241).  NBUF = D / 16: a register buffer of a whole tile, each piece refilled with the same piece of
+// the wave's next tile as soon as its three products are issued.  NBUF = D / 32: a rolling buffer of half a tile; slot x % NBUF
+// holds piece x (32 dims of 16 blocks) and is refilled with piece x + NBUF, of this tile or the next, so a load still has half a tile of
+// MFMA work to arrive.
+template <int D, int R, int LD, int NBUF, int NWV>
+__device__ __forceinline__ void score_tiles(const ScoreArgs& a, const float* kbase, const __bf16* qlds, float* S, int col0, int jt_first,
+                                            int jt_end, int bh, int i0, const float* lvbase) {
+    constexpr int DS = D / 16;
+    const int lane = threadIdx.x & 63;
+    const __bf16* const qlane = qlds + ((lane >> 4) * R + (lane & 15) % R) * 8;
+    auto tile_ptr = [&](int jt) { return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + lane * 8; };
+    bf16x8 kraw[2 * NBUF];                                // [2b] = hi, [2b + 1] = lo of the piece in slot b
+    if (jt_first < jt_end) {
+        const __bf16* src = tile_ptr(jt_first);
+#pragma unroll
+        for (int x = 0; x < NBUF; ++x) {
+            kraw[2 * x] = *reinterpret_cast<const bf16x8*>(src + x * 1024);
+            kraw[2 * x + 1] = *reinterpret_cast<const bf16x8*>(src + x * 1024 + kKeyTail);
+        }
+    }
+    for (int jt = jt_first; jt < jt_end; jt += NWV) {
+        const int j = 32 * jt + (lane & 15);              // and j + 16
+        const __bf16* cur = tile_ptr(jt);
+        const __bf16* next = tile_ptr(jt + NWV < jt_end ? jt + NWV : jt);      // the last tile refills from itself: in bounds, never used
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int s = 0; s < DS / 2; ++s) {
+            const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlane + (s * 2 + 0) * 4 * R * 8);
+            const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlane + (s * 2 + 1) * 4 * R * 8);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int x = 2 * s + u, slot = x % NBUF;
+                const bf16x8 k_hi = kraw[2 * slot], k_lo = kraw[2 * slot + 1];
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ql, k_hi, acc[u], 0, 0, 0);
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh, k_lo, acc[u], 0, 0, 0);
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh, k_hi, acc[u], 0, 0, 0);
+                const int x_fill = (x + NBUF) % DS;                            // the piece this slot holds next
+                const __bf16* from = x + NBUF < DS ? cur : next;
+                kraw[2 * slot] = *reinterpret_cast<const bf16x8*>(from + x_fill * 1024);
+                kraw[2 * slot + 1] = *reinterpret_cast<const bf16x8*>(from + x_fill * 1024 + kKeyTail);
+            }
+        }
+        store_scores<R, LD>(a, acc, S, col0, j, bh, i0, lvbase);
     }
 }
 
@@ -796,9 +877,9 @@ __device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t,
             float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
             asm("" : "+v"(mean));                         // rounded before it is split, as in the pooling kernel
             const __bf16 hi = (__bf16)mean;
-            const int at = (((t256 >> 3) * 2) * 32 + j) * 8 + (t256 & 7);
+            const int at = key_tile_offset(t256, j);
             tile[at] = hi;
-            tile[at + 32 * 8] = (__bf16)(mean - (float)hi);
+            tile[at + kKeyTail] = (__bf16)(mean - (float)hi);
         }
     };
     load(IC_sel<0>{}, 0);
@@ -813,13 +894,13 @@ __device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t,
 }
 
 // Scores, top-k and merged lists of the query blocks i0 .. i0 + R - 1 of head bh = b * Hq + h, by a
-// 512-thread workgroup.  S: R * (MAXC * 64 + 8) floats of LDS for the scores, then 256 counters per
+// 512-thread workgroup.  S: R * (MAXC * 64 + kRowPad) floats of LDS for the scores, then 256 counters per
 // wavefront.  Ends without a barrier; the caller must not reuse S before one.
 // The split pooled queries are staged in LDS by stage_queries.
 template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, bool KIN = false>
 __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S, const KeyArgs* keys = nullptr) {
-    constexpr int LD = MAXC * 64 + 8;          // +8 words: the two lane halves of a store hit different banks
-    constexpr int DS = D / 16;
+    constexpr int LD = MAXC * 64 + kRowPad;
+    constexpr int DS = D / 16;                 // 1-KB piece pairs of a tile: 32 dims by 16 blocks
     const float* __restrict__ kp = a.kp;
     const int Hq = a.Hq, G = a.G, NB = a.NB, NBk = a.NBk, off = a.off, T = a.T;
     Pattern pt = a.pt;
@@ -837,13 +918,10 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
     const float* kbase = KIN ? nullptr : kp + (int64_t)(b * Hkv + h / G) * ((NBk + 31) >> 5) * (32 * D);   // tiled, see tile_ptr
     const float* lvbase = lvn != nullptr ? lvn + (int64_t)(b * Hkv + h / G) * NBk : nullptr;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5, l32 = lane & 31;
     const int i_last = (i0 + R - 1 < NB - 1) ? i0 + R - 1 : NB - 1;
     const int n_jt = ((i_last + off) >> 5) + 1;           // 32-wide key-block tiles with some causal j
 
     // ---- phase 0 / phase 1 ------------------------------------------------------------
-    // LDS copy of the split queries: the 8 dims 16s + 8 * half .. +7 of row r, part p (0 = hi, 1 = lo)
-    // at bf16 offset ((((s * 2 + p) * R + r) * 2 + half) * 8
     stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
     const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
     if constexpr (KIN) {                                  // one tile, pooled by the workgroup itself
@@ -858,56 +936,62 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
         else stage_keys<D, 64, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
         kbase = tile;
     }
-    // The pooled K arrives tiled in operand layout and already split into bf16 head and tail:
-    // tile jt of 32 key blocks is 32 * D * 4 bytes, and the 8 dims 16s + 8 * half .. +7 of block
-    // l32 sit at bf16 offset (((2s + half) * 2 + part) * 32 + l32) * 8 (part 0 = hi, 1 = lo), so
-    // every load instruction of a wavefront covers 1-KB pieces (row-major rows would cost 32 cache
+    // The pooled K arrives tiled in operand layout and already split into bf16 head and tail (key_tile_offset), so
+    // every load instruction of a wavefront covers whole pieces (row-major rows would cost 32 cache
     // lines per instruction) and what it loads is the MFMA operand.  One register buffer serves
-    // as a whole-tile pipeline: as soon as the three products of a 16-dim slice have been issued,
+    // as a whole-tile pipeline: as soon as the three products of a slice have been issued,
     // the same registers are refilled with that slice of the wave's next tile, so every load has a
     // full tile of MFMA work to arrive.  Blocks past NBk in the last tile hold whatever the
     // workspace held: their columns are never ranked or written out.
-    bf16x8 kraw[2 * DS];                                  // [2s] = hi, [2s + 1] = lo of slice s
-    auto tile_ptr = [&](int jt) {
-        return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + (half * 64 + l32) * 8;
-    };
-    if (wave < n_jt) {
-        const __bf16* src = tile_ptr(wave);
+    if constexpr (R == 16) {
+        score_tiles<D, R, LD, DS, NWV>(a, kbase, qlds, S, 0, wave, n_jt, bh, i0, lvbase);
+    } else {
+        // 4 or 8 rows: 32x32x16 products on the same tiles.  The rows are copied to fill them, but few tiles fall to a wavefront and the two
+        // stores a row and tile count for more (select calls: 65536 tokens 120 us with 16-row products, 117.5 this way, with a mass
+        // budget 137 and 132, 49000 tokens with the output-aware score 108 and 104).
+        bf16x8 kraw[2 * DS];                                  // [2s] = hi, [2s + 1] = lo of 16-dim slice s
+        const int half = lane >> 5, l32 = lane & 31;
+        auto tile_ptr = [&](int jt) {
+            return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + (l32 >> 4) * 1024 + half * 128 + (l32 & 15) * 8;
+        };
+        auto piece = [](int s) { return (s >> 1) * 2048 + (s & 1) * 256; };
+        if (wave < n_jt) {
+            const __bf16* src = tile_ptr(wave);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) {
-            kraw[2 * s] = *reinterpret_cast<const bf16x8*>(src + s * 1024);
-            kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(src + s * 1024 + 256);
+            for (int s = 0; s < DS; ++s) {
+                kraw[2 * s] = *reinterpret_cast<const bf16x8*>(src + piece(s));
+                kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(src + piece(s) + kKeyTail);
+            }
         }
-    }
-    for (int jt = wave; jt < n_jt; jt += NWV) {
-        const int j = 32 * jt + l32;
-        // output-aware ranking: the key block's ln(value magnitude) joins its score
-        const float lv = lvbase != nullptr ? lvbase[j < NBk ? j : NBk - 1] : 0.f;
-        // the last tile refills from itself: in bounds, never used
-        const __bf16* next = tile_ptr(jt + NWV < n_jt ? jt + NWV : jt);
-        f32x16 acc;
+        const __bf16* const qlane = qlds + (half * R + l32 % R) * 8;
+        for (int jt = wave; jt < n_jt; jt += NWV) {
+            const int j = 32 * jt + l32;
+            const float lv = lvbase != nullptr ? lvbase[j < NBk ? j : NBk - 1] : 0.f;
+            const __bf16* next = tile_ptr(jt + NWV < n_jt ? jt + NWV : jt);
+            f32x16 acc;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-        for (int s = 0; s < DS; ++s) {
-            const bf16x8 k_hi = kraw[2 * s], k_lo = kraw[2 * s + 1];
-            const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlds + (((s * 2 + 0) * R + l32 % R) * 2 + half) * 8);
-            const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlds + (((s * 2 + 1) * R + l32 % R) * 2 + half) * 8);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql, k_hi, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_lo, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_hi, acc, 0, 0, 0);
-            kraw[2 * s] = *reinterpret_cast<const bf16x8*>(next + s * 1024);
-            kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(next + s * 1024 + 256);
-        }
+            for (int s = 0; s < DS; ++s) {
+                const bf16x8 k_hi = kraw[2 * s], k_lo = kraw[2 * s + 1];
+                const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlane + (((s >> 1) * 2 + 0) * 4 + (s & 1) * 2) * R * 8);
+                const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlane + (((s >> 1) * 2 + 1) * 4 + (s & 1) * 2) * R * 8);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql, k_hi, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_lo, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_hi, acc, 0, 0, 0);
+                kraw[2 * s] = *reinterpret_cast<const bf16x8*>(next + piece(s));
+                kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(next + piece(s) + kKeyTail);
+            }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int mrow = 8 * (r >> 2) + 4 * half + (r & 3);     // row of the 32x32 result held in acc[r]
-            if (mrow < R) {
-                const float sc = lvbase != nullptr ? scale * acc[r] + lv : scale * acc[r];
-                S[mrow * LD + j] = sc;
-                const int i = i0 + mrow;
-                if (scores_out != nullptr && i < NB && j < NBk)
-                    scores_out[((int64_t)bh * NB + i) * NBk + j] = j <= i + off ? sc : -INFINITY;
+            for (int r = 0; r < 16; ++r) {
+                const int mrow = 8 * (r >> 2) + 4 * half + (r & 3);     // row of the 32x32 result held in acc[r]
+                if (mrow < R) {
+                    const float sc = lvbase != nullptr ? scale * acc[r] + lv : scale * acc[r];
+                    S[mrow * LD + j] = sc;
+                    const int i = i0 + mrow;
+                    if (scores_out != nullptr && i < NB && j < NBk)
+                        scores_out[((int64_t)bh * NB + i) * NBk + j] = j <= i + off ? sc : -INFINITY;
+                }
             }
         }
     }
@@ -1022,7 +1106,7 @@ template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
 __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, const int bh, const int i0, float* S) {
     constexpr int CC = 16;                     // 64-block register chunks per column chunk
     constexpr int CW = CC * 64;                // key blocks per column chunk
-    constexpr int LD = CW + 8;
+    constexpr int LD = CW + kRowPad;
     constexpr int DS = D / 16;
     constexpr int RPW = R / NWV;               // rows per wavefront
     constexpr int MAXC = MAXCH * CC;
@@ -1031,7 +1115,6 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     const int Hq = a.Hq, G = a.G, NB = a.NB, NBk = a.NBk, off = a.off, T = a.T;
     Pattern pt = a.pt;
     int k = a.k;
-    const float scale = a.scale;
     int32_t* __restrict__ idx = a.idx;
     int32_t* __restrict__ cnt = a.cnt;
     float* __restrict__ scores_out = a.scores_out;
@@ -1041,7 +1124,6 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     const float* kbase = kp + (int64_t)(b * Hkv + h / G) * ((NBk + 31) >> 5) * (32 * D);
     const float* lvbase = a.lvn != nullptr ? a.lvn + (int64_t)(b * Hkv + h / G) * NBk : nullptr;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5, l32 = lane & 31;
     const int i_last = (i0 + R - 1 < NB - 1) ? i0 + R - 1 : NB - 1;
     const int n_jt = ((i_last + off) >> 5) + 1;           // 32-wide key-block tiles with some causal j
     const int n_ch = (i_last + off) / CW + 1;             // column chunks with some causal j (workgroup-uniform)
@@ -1053,62 +1135,11 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     const int NB_b = (entry_len(a.seq_lens, b, a.S) + a.Bs - 1) / a.Bs;      // ragged batch
     pt.NB = off + NB_b;
 
-    auto tile_ptr = [&](int jt) {
-        return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + (half * 64 + l32) * 8;
-    };
-    // Scores of column chunk c into S (phase 1 of the plain kernel, restricted to the chunk's tiles).
-    // NBUF = DS: the whole-tile register pipeline of the plain kernel (a slice's registers are refilled
-    // with the same slice of the wave's next tile as soon as its three products are issued).
-    // NBUF = DS / 2, for the second chunk, when 32 registers per lane hold the first chunk's scores: a
-    // rolling buffer of half a tile; slot s % NBUF holds slice s and is refilled with slice s + NBUF,
-    // of this tile or the next, so a load still has half a tile of MFMA work to arrive.
+    // Scores of column chunk c into S; of the second one with half a tile in registers, when 32 registers per lane hold the first
+    // one's scores
     auto score_chunk = [&](int c, auto nbuf_tag) {
-        constexpr int NBUF = decltype(nbuf_tag)::value;
-        bf16x8 kraw[2 * NBUF];                            // [2b] = hi, [2b + 1] = lo of the slice in slot b
         const int jt_end = n_jt < (c + 1) * (CW / 32) ? n_jt : (c + 1) * (CW / 32);
-        const int jt_first = c * (CW / 32) + wave;
-        if (jt_first < jt_end) {
-            const __bf16* src = tile_ptr(jt_first);
-#pragma unroll
-            for (int s = 0; s < NBUF; ++s) {
-                kraw[2 * s] = *reinterpret_cast<const bf16x8*>(src + s * 1024);
-                kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(src + s * 1024 + 256);
-            }
-        }
-        for (int jt = jt_first; jt < jt_end; jt += NWV) {
-            const int j = 32 * jt + l32;
-            const float lv = lvbase != nullptr ? lvbase[j < NBk ? j : NBk - 1] : 0.f;
-            const __bf16* cur = tile_ptr(jt);
-            const __bf16* next = tile_ptr(jt + NWV < jt_end ? jt + NWV : jt);      // the last tile refills from itself: in bounds, never used
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-            for (int s = 0; s < DS; ++s) {
-                const int slot = s % NBUF;
-                const bf16x8 k_hi = kraw[2 * slot], k_lo = kraw[2 * slot + 1];
-                const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlds + (((s * 2 + 0) * R + l32 % R) * 2 + half) * 8);
-                const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlds + (((s * 2 + 1) * R + l32 % R) * 2 + half) * 8);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql, k_hi, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_lo, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_hi, acc, 0, 0, 0);
-                const int s_fill = (s + NBUF) % DS;                               // the slice this slot holds next
-                const __bf16* from = s + NBUF < DS ? cur : next;
-                kraw[2 * slot] = *reinterpret_cast<const bf16x8*>(from + s_fill * 1024);
-                kraw[2 * slot + 1] = *reinterpret_cast<const bf16x8*>(from + s_fill * 1024 + 256);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int mrow = 8 * (r >> 2) + 4 * half + (r & 3);
-                if (mrow < R) {
-                    const float sc = lvbase != nullptr ? scale * acc[r] + lv : scale * acc[r];
-                    S[mrow * LD + j - c * CW] = sc;
-                    const int i = i0 + mrow;
-                    if (scores_out != nullptr && i < NB && j < NBk)
-                        scores_out[((int64_t)bh * NB + i) * NBk + j] = j <= i + off ? sc : -INFINITY;
-                }
-            }
-        }
+        score_tiles<D, R, LD, decltype(nbuf_tag)::value, NWV>(a, kbase, qlds, S, c * CW, c * (CW / 32) + wave, jt_end, bh, i0, lvbase);
     };
     // scores of the blocks c * CW + 64 m + lane of row r from the chunk's scores in S (columns past the
     // computed tiles hold junk; they lie beyond the causal limit and are never candidates)
@@ -1324,11 +1355,11 @@ struct ScoreCall {
     hipStream_t st;
 };
 
-template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, int NWV = (R * (MAXC * 64 + 8) * 4 > 80 * 1024 ? 16 : 8)>
+template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, int NWV = (R * (MAXC * 64 + kRowPad) * 4 > 80 * 1024 ? 16 : 8)>
 hipError_t launch_mfma_e(const ScoreCall& c) {
     constexpr size_t part_words = 2 * (NWV / 4) * (256 / (D / 8)) * D;    // partial sums of the in-kernel pooling
-    constexpr size_t lds = ((size_t)R * (MAXC * 64 + 8) + NWV * 256 +
-                            (part_words > (size_t)R * (MAXC * 64 + 8) ? part_words : 0)) * sizeof(float);
+    constexpr size_t lds = ((size_t)R * (MAXC * 64 + kRowPad) + NWV * 256 +
+                            (part_words > (size_t)R * (MAXC * 64 + kRowPad) ? part_words : 0)) * sizeof(float);
     hipError_t e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
@@ -1346,8 +1377,8 @@ hipError_t launch_mfma_q(const ScoreCall& c) {
 template <int D, int MAXCH, bool EXT, bool GROUP>
 hipError_t launch_chunked_e(const ScoreCall& c) {
     constexpr int R = 16, NWV = 8;
-    constexpr size_t lds = ((size_t)R * (1024 + 8) + NWV * 256) * sizeof(float);
-    static_assert(2 * (NWV / 4) * (256 / (D / 8)) * D <= R * (1024 + 8), "the pooling partial sums fit the score space");
+    constexpr size_t lds = ((size_t)R * (1024 + kRowPad) + NWV * 256) * sizeof(float);
+    static_assert(2 * (NWV / 4) * (256 / (D / 8)) * D <= R * (1024 + kRowPad), "the pooling partial sums fit the score space");
     hipError_t e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
@@ -1378,7 +1409,7 @@ hipError_t launch_plain(const ScoreCall& c) {
 
 template <int D, bool EXT>
 hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
-    constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + 8, 8>() + 32 * D) * sizeof(float);
+    constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + kRowPad, 8>() + 32 * D) * sizeof(float);
     const size_t v_lds = keys.vt != nullptr ? 2 * c.d.Bs * (D + 2) * sizeof(uint16_t) : 0;
     const size_t lds = v_lds > score_lds ? v_lds : score_lds;
     hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, EXT>, lds);
