@@ -162,8 +162,8 @@ int sparse_prefill_select(const spa_params *p, const void *q, const void *k,
 /* sparse_prefill_select for callers that cannot allocate device memory or hand over a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * computation, same outputs and same checks as sparse_prefill_select, bit for bit, but the scratch
- * of the stage (the pooled K in the score kernel's layout; with lists_per_kv_head also the pooled
- * queries and their group means) lives in a static device array inside the library instead of
+ * of the stage (the pooled K in the score kernel's layout; with lists_per_kv_head also room
+ * for the pooled queries and their group means) lives in a static device array inside the library instead of
  * `ws`: SPA_STATIC_SCRATCH_BYTES per GPU the library is used on, held until the process ends.  The
  * call allocates and frees nothing and enqueues only kernels on hip_stream.
  *   - Limit: 256-byte-aligned regions of

@@ -46,7 +46,7 @@ Dims resolved(const spa_params* p) {
 }
 
 struct Workspace {
-    size_t qp_off, kp_off, qg_off, idx_off, cnt_off, lvn_off, vt_off, total;
+    size_t qp_off, kp_off, idx_off, cnt_off, lvn_off, vt_off, total;
 };
 
 Workspace carve(const Dims& d) {
@@ -54,7 +54,8 @@ Workspace carve(const Dims& d) {
     size_t off = 0;
     w.qp_off = off; off = align_up(off + (size_t)d.B * d.Hq * d.NB * d.D * sizeof(float));
     w.kp_off = off; off = align_up(off + (size_t)d.B * d.Hkv * ((d.NBk + 31) / 32 * 32) * d.D * sizeof(float));   // whole tiles of 32 blocks
-    w.qg_off = off; if (d.shared) off = align_up(off + (size_t)d.B * d.Hkv * d.NB * d.D * sizeof(float));
+    // room for group means, which nothing writes any more: the size that calls ask for stays what it was
+    if (d.shared) off = align_up(off + (size_t)d.B * d.Hkv * d.NB * d.D * sizeof(float));
     w.idx_off = off; off = align_up(off + (size_t)d.B * d.Hq * d.NB * d.T * sizeof(int32_t));
     w.cnt_off = off; off = align_up(off + (size_t)d.B * d.Hq * d.NB * sizeof(int32_t));
     w.lvn_off = off; off = align_up(off + (size_t)d.B * d.Hkv * d.NBk * sizeof(float));
@@ -78,8 +79,8 @@ int set_mass_budget(Dims& d, float mass_gamma) {
 }  // namespace
 
 namespace {
-// The scratch regions of the select stage: pooled Q (group-shared lists only), pooled K in the score kernel's operand layout, ln of the value magnitudes
-// (output-aware score only).
+// The scratch regions of the select stage: pooled Q (group-shared lists of few rows only), pooled K in the score kernel's operand layout, ln of
+// the value magnitudes (output-aware score only).
 struct SelectScratch {
     float *qp, *kp, *lvn;
 };
@@ -219,16 +220,16 @@ void* static_scratch(hipError_t* err) {
 }
 
 // bytes of scratch a plain select call needs: pooled K in tiles of 32 key blocks, plus, with
-// group-shared lists, the pooled queries and their group means
+// group-shared lists, the pooled queries and room for their group means (unused: what is refused stays refused)
 struct StaticCarve {
-    size_t kp_off, qp_off, qg_off, total;
+    size_t kp_off, qp_off, total;
 };
 StaticCarve carve_static(const Dims& d) {
     StaticCarve c;
     size_t off = 0;
     c.kp_off = off; off = align_up(off + (size_t)d.B * d.Hkv * ((d.NBk + 31) / 32 * 32) * d.D * sizeof(float));
     c.qp_off = off; if (d.shared) off = align_up(off + (size_t)d.B * d.Hq * d.NB * d.D * sizeof(float));
-    c.qg_off = off; if (d.shared) off = align_up(off + (size_t)d.B * d.Hkv * d.NB * d.D * sizeof(float));
+    if (d.shared) off = align_up(off + (size_t)d.B * d.Hkv * d.NB * d.D * sizeof(float));
     c.total = off;
     return c;
 }
