@@ -1412,7 +1412,9 @@ hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
     constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + kRowPad, 8>() + 32 * D) * sizeof(float);
     const size_t v_lds = keys.vt != nullptr ? 2 * c.d.Bs * (D + 2) * sizeof(uint16_t) : 0;
     const size_t lds = v_lds > score_lds ? v_lds : score_lds;
-    hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, EXT>, lds);
+    // asked for once, for the largest call: a fused call in a capture may follow selections that need less
+    constexpr size_t v_most = 2 * 128 * (D + 2) * sizeof(uint16_t);
+    hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, EXT>, v_most > score_lds ? v_most : score_lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + 3) / 4, n_score = n_tiles * c.d.B * c.d.Hq;
     const int n_v = keys.vt != nullptr ? (c.d.B * c.d.Hkv * c.d.NBk + 1) / 2 : 0;
