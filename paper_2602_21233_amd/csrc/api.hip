@@ -141,9 +141,9 @@ int select_launches(Dims d, const spa_params* p, const void* q, const void* k, c
     }
     const int group = d.shared ? d.G : 1;
     float* const qp = group > 1 && !group_pooled_in_kernel(lists) ? sc.qp : nullptr;
-    if (with_v && launch_prepare_kv(d, q, strides_of(p->q_stride), qp, k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride), kp, vt_or_null, lvn, st) != hipSuccess)
+    if (with_v && launch_prepare_kv(d, q, strides_of(p->q_stride), qp, k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride), kp, key_layout(lists), vt_or_null, lvn, st) != hipSuccess)
         return SPA_ERR_LAUNCH;
-    if (!with_v && launch_pool(d, qp != nullptr ? q : nullptr, strides_of(p->q_stride), k, strides_of(p->k_stride), qp, kp, true, st) != hipSuccess)
+    if (!with_v && launch_pool(d, qp != nullptr ? q : nullptr, strides_of(p->q_stride), k, strides_of(p->k_stride), qp, kp, key_layout(lists), st) != hipSuccess)
         return SPA_ERR_LAUNCH;
     return launch_code(launch_score_topk(lists, kp, k_rows, head_pattern, lvn, block_idx, block_cnt, pooled_scores_or_null, q,
                                          strides_of(p->q_stride), group, qp, st));
@@ -278,7 +278,7 @@ int sparse_prefill_pool(const spa_params* p, const void* q, const void* k, float
     if (k && (rc = check_tensor(k, p->k_stride, p->head_dim))) return rc;
     Dims d = resolved(p);
     return launch_code(launch_pool(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), q_pooled,
-                                   k_pooled, false, (hipStream_t)hip_stream));
+                                   k_pooled, kKeyRows, (hipStream_t)hip_stream));
 }
 
 

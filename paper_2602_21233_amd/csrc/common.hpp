@@ -67,29 +67,31 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 struct Strides { int64_t b, h, t; };
 inline Strides strides_of(const int64_t s[3]) { return Strides{s[0], s[1], s[2]}; }
 
-// Pooled K as the score kernel reads it: per KV head, tiles of 32 key blocks (32 * D * 4 bytes), every value split into its bf16 head
-// and tail (x = hi + lo), laid out as the B operand of v_mfma_f32_16x16x32_bf16 (32x32x16 products find theirs in quarters of a piece): 1-KB pieces (32 dims, 16 blocks, head or tail)
-// in which lane l finds the 8 dims 8 * (l >> 4) of block l & 15.  bf16 offset in the tile of the head of dim d of block blk;
-// its tail is kKeyTail further.
-constexpr int kKeyTail = 512;
-__device__ __forceinline__ int key_tile_offset(int d, int blk) {
-    return ((((d >> 5) * 2 + ((blk >> 4) & 1)) * 2 * 4 + ((d >> 3) & 3)) * 16 + (blk & 15)) * 8 + (d & 7);
+// How pooled K lies.  Rows: [.., NBk, D] fp32.  The other two are what the score kernels read: per KV head, tiles of 32 key blocks
+// (32 * D * 4 bytes), every value split into its bf16 head and tail (x = hi + lo), laid out as the B operand of the kernel's matrix
+// products: for 32x32x16 ones pieces of 512 bytes (8 dims of 32 blocks, head or tail), for 16x16x32 ones pieces of 1 KB (32 dims of 16
+// blocks, head or tail) in which lane l finds the 8 dims 8 * (l >> 4) of block l & 15.  Which one a call takes: key_layout.
+enum KeyLayout { kKeyRows, kKeyTiles32, kKeyTiles16 };
+// bf16 offset in the tile of the head of dim d of block blk, and how much further its tail is
+__host__ __device__ __forceinline__ int key_tile_offset(KeyLayout layout, int d, int blk) {
+    return layout == kKeyTiles16 ? ((((d >> 5) * 2 + ((blk >> 4) & 1)) * 2 * 4 + ((d >> 3) & 3)) * 16 + (blk & 15)) * 8 + (d & 7)
+                                 : ((d >> 3) * 2 * 32 + (blk & 31)) * 8 + (d & 7);
 }
+__host__ __device__ constexpr int key_tail(KeyLayout layout) { return layout == kKeyTiles16 ? 512 : 256; }
 
 // Launchers (one per kernel file).  Each returns a hipError_t from the launch.
-// k_tiled: write the pooled K in the score kernel's operand layout (tiles of 32 key blocks,
-// heads ceil(NBk / 32) tiles apart) instead of row major [.., NBk, D].
+// Tiles of pooled K: heads are ceil(NBk / 32) tiles apart.
 hipError_t launch_pool(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
-                       float* qp, float* kp, bool k_tiled, hipStream_t st);
+                       float* qp, float* kp, KeyLayout k_layout, hipStream_t st);
 // lvn [B*Hkv, NB] fp32: ln of the mean value-vector norm of every key block.
 hipError_t launch_vnorm(const Dims& d, const void* v, Strides vs, float* lvn, hipStream_t st);
 // Pooled K (tiled) and, of V in the same launch, V^T for the attention kernel (NBk blocks per head, as vt_in_halves
 // says) and / or lvn; with qp, the pooled queries too.
 hipError_t launch_prepare_kv(const Dims& d, const void* q, Strides qs, float* qp_or_null, const void* k, Strides ks, const void* v,
-                             Strides vs, float* kp, void* vt_or_null, float* lvn_or_null, hipStream_t st);
+                             Strides vs, float* kp, KeyLayout k_layout, void* vt_or_null, float* lvn_or_null, hipStream_t st);
 // k_rows: optional device array of NB per-query-block budgets (clamped to [0, d.k] in the kernel).
 // lvn: optional; added to the score of key block j (output-aware ranking).
-// kp is in the tiled layout launch_pool writes with k_tiled.
+// kp is in the layout that key_layout names.
 // head_pattern: optional device array [Hq][3] = (n_sink, n_local, top_k) per query head.
 // q: the queries, layout qs; the kernel pools them.  group: query heads per list (their pooled queries are averaged);
 // with more than one, qp: the pooled queries [B, Hq * group, NB, D] (Hq lists), or nullptr: pooled in the kernel, too.

@@ -18,12 +18,12 @@ namespace {
 
 // One block of one head: mean of its tokens.  src: the block's first token; n_valid: its tokens that exist; part:
 // 256 / (D / 8) rows of D floats of LDS.
-// k_tiled: pooled K goes out in the operand layout of the score kernel (key_tile_offset) instead of row
-// major fp32, so a wavefront of that kernel reads whole 1-KB pieces that are its
+// layout: pooled K goes out in the operand layout of the score kernel (key_tile_offset) or row
+// major fp32; in the former a wavefront of that kernel reads whole 1-KB pieces that are its
 // MFMA operands as they are.  dst is then the block's tile, otherwise the block's row.
 template <int D, int BS>
 __device__ __forceinline__ void pool_block(const uint16_t* __restrict__ src, int64_t stride_t, int n_valid, float (*part)[D],
-                                           float* __restrict__ dst, bool k_tiled, int blk) {
+                                           float* __restrict__ dst, KeyLayout layout, int blk) {
     constexpr int TPR = D / 8;          // lanes per token row
     constexpr int RPP = 256 / TPR;      // token rows per pass
     constexpr int PASSES = BS / RPP;
@@ -54,13 +54,13 @@ __device__ __forceinline__ void pool_block(const uint16_t* __restrict__ src, int
 #pragma unroll
         for (int r = 0; r < RPP; ++r) s += part[r][tid];
         const float mean = n_valid == BS ? s * (1.0f / (float)BS) : s / (float)n_valid;
-        if (k_tiled) {
+        if (layout != kKeyRows) {
             const __bf16 hi = (__bf16)mean;                       // round to nearest even, twice
             const __bf16 lo = (__bf16)(mean - (float)hi);
             __bf16* t = reinterpret_cast<__bf16*>(dst);
-            const int at = key_tile_offset(tid, blk);
+            const int at = key_tile_offset(layout, tid, blk);
             t[at] = hi;
-            t[at + kKeyTail] = lo;
+            t[at + key_tail(layout)] = lo;
         } else {
             dst[tid] = mean;
         }
@@ -68,8 +68,8 @@ __device__ __forceinline__ void pool_block(const uint16_t* __restrict__ src, int
 }
 // where pooled K block blk of head hy goes
 template <int D>
-__device__ __forceinline__ float* pooled_k(float* kp, int hy, int blk, int NBk, bool k_tiled) {
-    return k_tiled ? kp + ((int64_t)hy * ((NBk + 31) >> 5) + (blk >> 5)) * (32 * D) : kp + ((int64_t)hy * NBk + blk) * D;
+__device__ __forceinline__ float* pooled_k(float* kp, int hy, int blk, int NBk, KeyLayout layout) {
+    return layout != kKeyRows ? kp + ((int64_t)hy * ((NBk + 31) >> 5) + (blk >> 5)) * (32 * D) : kp + ((int64_t)hy * NBk + blk) * D;
 }
 
 template <int D, int BS>
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
                                                    int n_q_rows /* B*Hq or 0 */, int Hq,
                                                    const uint16_t* __restrict__ k, Strides ks, int Hkv,
                                                    float* __restrict__ qp, float* __restrict__ kp, int NBq, int Sq,
-                                                   int NBk, int Skv, int k_tiled,
+                                                   int NBk, int Skv, KeyLayout k_layout,
                                                    const int32_t* __restrict__ seq_lens) {
     __shared__ float part[256 / (D / 8)][D];
     const int blk = blockIdx.x;
@@ -90,25 +90,25 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
         const int S = entry_len(seq_lens, b, Sq);            // ragged batch: this entry's own length
         if (blk * BS >= S) return;                           // the grid spans the key blocks of the longest entry
         pool_block<D, BS>(q + b * qs.b + h * qs.h + (int64_t)blk * BS * qs.t, qs.t, S - blk * BS < BS ? S - blk * BS : BS, part,
-                          qp + ((int64_t)hy * NBq + blk) * D, false, blk);
+                          qp + ((int64_t)hy * NBq + blk) * D, kKeyRows, blk);
     } else {
         hy -= n_q_rows;
         const int b = hy / Hkv, h = hy % Hkv;
         const int S = Skv - Sq + entry_len(seq_lens, b, Sq); // K may carry a prefix
         if (blk * BS >= S) return;
         pool_block<D, BS>(k + b * ks.b + h * ks.h + (int64_t)blk * BS * ks.t, ks.t, S - blk * BS < BS ? S - blk * BS : BS, part,
-                          pooled_k<D>(kp, hy, blk, NBk, k_tiled), k_tiled, blk);
+                          pooled_k<D>(kp, hy, blk, NBk, k_layout), k_layout, blk);
     }
 }
 
 template <int D, int BS>
 hipError_t launch(const Dims& d, const void* q, Strides qs, const void* k, Strides ks, float* qp,
-                  float* kp, bool k_tiled, hipStream_t st) {
+                  float* kp, KeyLayout k_layout, hipStream_t st) {
     int nq = q ? d.B * d.Hq : 0, nk = k ? d.B * d.Hkv : 0;
     if (nq + nk == 0) return hipSuccess;
     dim3 grid(nk ? d.NBk : d.NB, nq + nk);
     hipLaunchKernelGGL((pool_kernel<D, BS>), grid, dim3(256), 0, st, (const uint16_t*)q, qs, nq, d.Hq,
-                       (const uint16_t*)k, ks, d.Hkv, qp, kp, d.NB, d.S, d.NBk, d.Skv, k_tiled ? 1 : 0, d.seq_lens);
+                       (const uint16_t*)k, ks, d.Hkv, qp, kp, d.NB, d.S, d.NBk, d.Skv, k_layout, d.seq_lens);
     return hipGetLastError();
 }
 
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
                                     tile, nullptr, vt + ((int64_t)bh * vt_bph + blk) * D * BS, halves, nullptr);
 }
 
-// Everything a call needs of K and V before it scores: blockIdx.z = 0 pools a block of K (tiled), 1 takes a
+// Everything a call needs of K and V before it scores: blockIdx.z = 0 pools a block of K, 1 takes a
 // block of V (VT: transposed for the attention kernel, VN: its magnitude), 2 + g pools a block of query head g of the KV
 // group, where the score kernel does not do that itself.  HBM-bound streams like the separate kernels,
 // whose launches, ramps and second read of V this saves: fused calls of 512 tokens 27 -> 23 us, 1999 tokens 64 -> 57.6,
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restr
                                                          const uint16_t* __restrict__ v, Strides vs, int Hkv, int NBk, int Skv,
                                                          float* __restrict__ kp, uint16_t* __restrict__ vt,
                                                          float* __restrict__ lvn, const int32_t* __restrict__ seq_lens, int Sq,
-                                                         int halves, const uint16_t* __restrict__ q, Strides qs,
+                                                         int halves, KeyLayout k_layout, const uint16_t* __restrict__ q, Strides qs,
                                                          float* __restrict__ qp, int NBq) {
     constexpr int RPP = 256 / (D / 8);
     constexpr int TILE_B = VT ? BS * (D + 2) * 2 : 0, PART_B = RPP * D * 4;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restr
         const int Sb = entry_len(seq_lens, b, Sq), G = (int)gridDim.z - 2, g = (int)blockIdx.z - 2;
         if (blk * BS >= Sb) return;
         pool_block<D, BS>(q + b * qs.b + (h * G + g) * qs.h + (int64_t)blk * BS * qs.t, qs.t, Sb - blk * BS < BS ? Sb - blk * BS : BS,
-                          reinterpret_cast<float(*)[D]>(lds), qp + (((int64_t)hy * G + g) * NBq + blk) * D, false, blk);
+                          reinterpret_cast<float(*)[D]>(lds), qp + (((int64_t)hy * G + g) * NBq + blk) * D, kKeyRows, blk);
         return;
     }
     const int S = Skv - Sq + entry_len(seq_lens, b, Sq);   // ragged batch: key tokens of this entry
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(const uint16_t* __restr
     const int n_valid = S - blk * BS < BS ? S - blk * BS : BS;
     if (blockIdx.z == 0)
         pool_block<D, BS>(k + b * ks.b + h * ks.h + (int64_t)blk * BS * ks.t, ks.t, n_valid, reinterpret_cast<float(*)[D]>(lds),
-                          pooled_k<D>(kp, hy, blk, NBk, true), true, blk);
+                          pooled_k<D>(kp, hy, blk, NBk, k_layout), k_layout, blk);
     else
         value_block<D, BS, VT, VN>(threadIdx.x, v + b * vs.b + h * vs.h + (int64_t)blk * BS * vs.t, vs.t, n_valid,
                                    reinterpret_cast<uint16_t*>(lds), norms, VT ? vt + ((int64_t)hy * NBk + blk) * D * BS : nullptr, halves,
@@ -194,12 +194,12 @@ hipError_t launch_tv(const Dims& d, const void* v, Strides vs, void* vt, int64_t
 
 template <int D, int BS>
 hipError_t launch_prep(const Dims& d, const void* q, Strides qs, float* qp, const void* k, Strides ks, const void* v, Strides vs,
-                       float* kp, void* vt, float* lvn, hipStream_t st) {
+                       float* kp, KeyLayout k_layout, void* vt, float* lvn, hipStream_t st) {
     const auto kernel = vt == nullptr ? prepare_kv_kernel<D, BS, false, true>
                                       : (lvn == nullptr ? prepare_kv_kernel<D, BS, true, false> : prepare_kv_kernel<D, BS, true, true>);
     hipLaunchKernelGGL(kernel, dim3(d.NBk, d.B * d.Hkv, qp == nullptr ? 2 : 2 + d.G), dim3(256), 0, st, (const uint16_t*)k, ks,
                        (const uint16_t*)v, vs, d.Hkv, d.NBk, d.Skv, kp, (uint16_t*)vt, lvn, d.seq_lens, d.S, vt_in_halves(d) ? 1 : 0,
-                       (const uint16_t*)q, qs, qp, d.NB);
+                       k_layout, (const uint16_t*)q, qs, qp, d.NB);
     return hipGetLastError();
 }
 
@@ -216,12 +216,12 @@ hipError_t launch_transpose_v(const Dims& d, const void* v, Strides vs, void* vt
 }
 
 hipError_t launch_prepare_kv(const Dims& d, const void* q, Strides qs, float* qp_or_null, const void* k, Strides ks, const void* v,
-                             Strides vs, float* kp, void* vt_or_null, float* lvn_or_null, hipStream_t st) {
+                             Strides vs, float* kp, KeyLayout k_layout, void* vt_or_null, float* lvn_or_null, hipStream_t st) {
     if (vt_or_null == nullptr && lvn_or_null == nullptr) return hipErrorInvalidValue;
-    if (d.D == 128 && d.Bs == 128) return launch_prep<128, 128>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
-    if (d.D == 128 && d.Bs == 64) return launch_prep<128, 64>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
-    if (d.D == 64 && d.Bs == 128) return launch_prep<64, 128>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
-    if (d.D == 64 && d.Bs == 64) return launch_prep<64, 64>(d, q, qs, qp_or_null, k, ks, v, vs, kp, vt_or_null, lvn_or_null, st);
+    if (d.D == 128 && d.Bs == 128) return launch_prep<128, 128>(d, q, qs, qp_or_null, k, ks, v, vs, kp, k_layout, vt_or_null, lvn_or_null, st);
+    if (d.D == 128 && d.Bs == 64) return launch_prep<128, 64>(d, q, qs, qp_or_null, k, ks, v, vs, kp, k_layout, vt_or_null, lvn_or_null, st);
+    if (d.D == 64 && d.Bs == 128) return launch_prep<64, 128>(d, q, qs, qp_or_null, k, ks, v, vs, kp, k_layout, vt_or_null, lvn_or_null, st);
+    if (d.D == 64 && d.Bs == 64) return launch_prep<64, 64>(d, q, qs, qp_or_null, k, ks, v, vs, kp, k_layout, vt_or_null, lvn_or_null, st);
     return hipErrorInvalidValue;
 }
 
@@ -234,11 +234,11 @@ hipError_t launch_vnorm(const Dims& d, const void* v, Strides vs, float* lvn, hi
 }
 
 hipError_t launch_pool(const Dims& d, const void* q, Strides qs, const void* k, Strides ks,
-                       float* qp, float* kp, bool k_tiled, hipStream_t st) {
-    if (d.D == 128 && d.Bs == 128) return launch<128, 128>(d, q, qs, k, ks, qp, kp, k_tiled, st);
-    if (d.D == 128 && d.Bs == 64) return launch<128, 64>(d, q, qs, k, ks, qp, kp, k_tiled, st);
-    if (d.D == 64 && d.Bs == 128) return launch<64, 128>(d, q, qs, k, ks, qp, kp, k_tiled, st);
-    if (d.D == 64 && d.Bs == 64) return launch<64, 64>(d, q, qs, k, ks, qp, kp, k_tiled, st);
+                       float* qp, float* kp, KeyLayout k_layout, hipStream_t st) {
+    if (d.D == 128 && d.Bs == 128) return launch<128, 128>(d, q, qs, k, ks, qp, kp, k_layout, st);
+    if (d.D == 128 && d.Bs == 64) return launch<128, 64>(d, q, qs, k, ks, qp, kp, k_layout, st);
+    if (d.D == 64 && d.Bs == 128) return launch<64, 128>(d, q, qs, k, ks, qp, kp, k_layout, st);
+    if (d.D == 64 && d.Bs == 64) return launch<64, 64>(d, q, qs, k, ks, qp, kp, k_layout, st);
     return hipErrorInvalidValue;
 }
 

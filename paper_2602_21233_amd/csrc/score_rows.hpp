@@ -52,6 +52,16 @@ inline int score_rows(const Dims& d) {
     return wg16 <= 512 || (rows <= 14336 && (two_chunks || d.D == 64)) ? 8 : 16;
 }
 
+// Which matrix products score R rows: 16x16x32 ones for 16 rows of head_dim 128, 32x32x16 ones, whose surplus rows are copies, for
+// the others.  With 16 rows of head_dim 128 the former halve the matrix work and the LDS reads, and their 8 accumulators instead
+// of 16 end the spills of the two-chunk kernel (select calls, 262144 tokens of 40/8 heads 759 -> 695 us, blocks of 64 2048 of 32 heads
+// 431 -> 406, 1247 of 32 heads 185 -> 174).  With head_dim 64 nothing spilled, and they cost as much as they give (1771 blocks of 16 heads
+// 133.9 -> 137.9 us, 131072 tokens of 32 heads 155.1 -> 157.7, 1000 blocks 112.0 -> 111.0).  With 4 or 8 rows few tiles fall to a wavefront
+// (65536 tokens 117.5 -> 120 us, with a mass budget 132 -> 137), and 32x32x16 products on the other's tiles, a quarter of a KB at a time,
+// take 14 registers more and 1 to 2.5 % longer (12800 queries over 51200 tokens, 40 heads, 89.4 -> 91.2).
+constexpr bool sixteen_row_products(int D, int R) { return D == 128 && R == 16; }
+inline KeyLayout key_layout(const Dims& d) { return sixteen_row_products(d.D, score_rows(d)) ? kKeyTiles16 : kKeyTiles32; }
+
 // Does a call go through score_topk_small_kernel, one launch instead of two?  Where the launches are what it takes: the score workgroups
 // then pool all of the K they see, one after the other, which pays up to 96 KB of K a head.  Fused calls, 32/8 heads: 300
 // tokens with head_dim 64 (38 KB) 19.4 -> 16.5 us, 300 with head_dim 128 (77 KB) 20.9 -> 20.3, 512 with head_dim 64 19.1 -> 18.3; but 777

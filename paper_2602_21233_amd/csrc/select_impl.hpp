@@ -16,7 +16,7 @@
 //   Phase 1 - scores on the matrix cores.  The fp32 pooled vectors are split
 //   into a bf16 head and a bf16 tail (x = hi + lo, |x - hi - lo| <= 2^-18 |x|)
 //   and each tile of Qp Kp^T is accumulated in fp32 from three bf16
-//   products (hi.hi + hi.lo + lo.hi; 16 rows: v_mfma_f32_16x16x32_bf16, fewer: 32x32x16); the dropped
+//   products (hi.hi + hi.lo + lo.hi; v_mfma_f32_16x16x32_bf16 for 16 rows of head_dim 128, otherwise 32x32x16); the dropped
 //   lo.lo term is below 2^-17 of a product.  The wavefronts take the key-block
 //   tiles round robin, reading Kp straight from L2 in operand layout.  The scores
 //   of the R rows stay in LDS; the NB x NB matrix never exists in memory unless
@@ -230,8 +230,9 @@ typedef __attribute__((ext_vector_type(8))) float f32x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// words between the score rows in LDS beyond a multiple of 64: the four lane groups of a store, rows 4 apart, hit different banks
-constexpr int kRowPad = 4;
+// words between the score rows in LDS beyond a multiple of 64: with 16-row products the four lane groups of a store, rows 4 apart, hit
+// different banks, with 32-row ones the two lane halves (4 words there take no measurably longer: 118.5 against 118.2 us at 65536 tokens)
+constexpr int row_pad(int D, int R) { return sixteen_row_products(D, R) ? 4 : 8; }
 
 // sum of v over the 64 lanes (DPP row reductions + row broadcasts), returned wave-uniform
 __device__ __forceinline__ int wave_sum(int v) {
@@ -557,12 +558,15 @@ struct ScoreArgs {
     const float* qp;              // GROUP kernels: pooled queries [B * Hq * group, NB, D] fp32, or nullptr: pooled in the kernel
 };
 
-// LDS copy of the split queries, A operands in groups of 8 dims by R rows: bf16 offset of the head of dim d of row r; its
-// tail is 4 * R * 8 further
-template <int R>
+// LDS copy of the split queries, the A operands of the kernel's matrix products: bf16 offset of the head of dim d of row r; its
+// tail is query_tail further
+template <int D, int R>
 __device__ __forceinline__ int query_offset(int d, int r) {
-    return ((((d >> 5) * 2) * 4 + ((d >> 3) & 3)) * R + r) * 8 + (d & 7);
+    if constexpr (sixteen_row_products(D, R)) return ((((d >> 5) * 2) * 4 + ((d >> 3) & 3)) * R + r) * 8 + (d & 7);
+    return ((((d >> 4) * 2) * R + r) * 2 + ((d >> 3) & 1)) * 8 + (d & 7);
 }
+template <int D, int R>
+constexpr int query_tail() { return (sixteen_row_products(D, R) ? 4 : 2) * R * 8; }
 
 // Phase 0 of the score kernels: the split pooled queries (MFMA A operands) of the query blocks
 // i0 .. i0 + R - 1 of head bh go to LDS behind the SW words of score space at S, in the space of the
@@ -594,9 +598,9 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
             float mean = sum * (1.0f / (float)a.group);
             asm("" : "+v"(mean));                            // rounded before it is split
             const __bf16 hi = (__bf16)mean;
-            const int at = query_offset<R>(d, r);
+            const int at = query_offset<D, R>(d, r);
             qlds[at] = hi;
-            qlds[at + 4 * R * 8] = (__bf16)(mean - (float)hi);
+            qlds[at + query_tail<D, R>()] = (__bf16)(mean - (float)hi);
         }
         __syncthreads();
     } else {
@@ -681,9 +685,9 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
                 if (t256 < D && r < R) {
                     const __bf16 hi = (__bf16)x;                      // round to nearest even, twice
                     const __bf16 lo = (__bf16)(x - (float)hi);
-                    const int at = query_offset<R>(t256, r);
+                    const int at = query_offset<D, R>(t256, r);
                     qlds[at] = hi;
-                    qlds[at + 4 * R * 8] = lo;
+                    qlds[at + query_tail<D, R>()] = lo;
                 }
             };
             static_assert(DEPTH == 2, "the slots alternate");
@@ -743,75 +747,97 @@ __device__ __forceinline__ void stage_queries(const ScoreArgs& a, const int bh, 
     }
 }
 
-// Scores of a tile from its two accumulators (key blocks j and j + 16; a lane holds the rows 4 * (lane >> 4) .. + 3) to the LDS rows, whose
-// first column is key block col0, and to memory if asked for.  Output-aware ranking: the key block's ln(value magnitude) joins.
-template <int R, int LD>
-__device__ __forceinline__ void store_scores(const ScoreArgs& a, const f32x4 (&acc)[2], float* S, int col0, int j, int bh, int i0,
-                                             const float* lvbase) {
-    const int row0 = 4 * ((threadIdx.x & 63) >> 4);
-    if (row0 >= R) return;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int ju = j + 16 * u;
-        const float lv = lvbase != nullptr ? lvbase[ju < a.NBk ? ju : a.NBk - 1] : 0.f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int mrow = row0 + r;
-            const float sc = lvbase != nullptr ? a.scale * acc[u][r] + lv : a.scale * acc[u][r];
-            S[mrow * LD + ju - col0] = sc;
-            const int i = i0 + mrow;
-            if (a.scores_out != nullptr && i < a.NB && ju < a.NBk)
-                a.scores_out[((int64_t)bh * a.NB + i) * a.NBk + ju] = ju <= i + a.off ? sc : -INFINITY;
-        }
-    }
+// One score of row mrow and key block j to the LDS rows, whose first column is key block col0, and to memory if asked for.  Output-aware
+// ranking: the key block's ln(value magnitude) lv joins.
+template <int LD>
+__device__ __forceinline__ void store_score(const ScoreArgs& a, float dot, float* S, int col0, int mrow, int j, int bh, int i0,
+                                            bool with_lv, float lv) {
+    const float sc = with_lv ? a.scale * dot + lv : a.scale * dot;
+    S[mrow * LD + j - col0] = sc;
+    const int i = i0 + mrow;
+    if (a.scores_out != nullptr && i < a.NB && j < a.NBk)
+        a.scores_out[((int64_t)bh * a.NB + i) * a.NBk + j] = j <= i + a.off ? sc : -INFINITY;
 }
 
-// Scores of the key tiles jt_first, jt_first + NWV, .. below jt_end for 16 rows, from v_mfma_f32_16x16x32_bf16: with 32x32x16 products, half of
-// whose rows were copies, the matrix cores and the LDS were busy twice as long, and the 16 accumulators made the
-// two-chunk kernel spill 28 to 44 registers (select calls, 262144 tokens of 40/8 heads 736 -> 701 us, of 32/8 heads 600 -> 567, 131072 tokens
-// 244 -> 241).  NBUF = D / 16: a register buffer of a whole tile, each piece refilled with the same piece of
-// the wave's next tile as soon as its three products are issued.  NBUF = D / 32: a rolling buffer of half a tile; slot x % NBUF
-// holds piece x (32 dims of 16 blocks) and is refilled with piece x + NBUF, of this tile or the next, so a load still has half a tile of
-// MFMA work to arrive.
+// Scores of the key tiles jt_first, jt_first + NWV, .. below jt_end for R rows.  The pooled K arrives tiled in operand layout and already
+// split into bf16 head and tail (key_tile_offset), so a load instruction of a wavefront covers whole pieces (row-major rows would
+// cost 32 cache lines per instruction) and what it loads is the MFMA operand.  NBUF = D / 16: a register buffer of a whole tile, each piece
+// refilled with the same piece of the wave's next tile as soon as its three products are issued, so every load has a full tile of
+// MFMA work to arrive.  NBUF = D / 32: a rolling buffer of half a tile; slot x % NBUF holds piece x and is refilled with piece x + NBUF, of
+// this tile or the next, so a load still has half a tile of MFMA work.  Blocks past NBk in the last tile hold whatever the workspace held:
+// their columns are never ranked or written out.  Which products: sixteen_row_products.
 template <int D, int R, int LD, int NBUF, int NWV>
 __device__ __forceinline__ void score_tiles(const ScoreArgs& a, const float* kbase, const __bf16* qlds, float* S, int col0, int jt_first,
                                             int jt_end, int bh, int i0, const float* lvbase) {
-    constexpr int DS = D / 16;
-    const int lane = threadIdx.x & 63;
-    const __bf16* const qlane = qlds + ((lane >> 4) * R + (lane & 15) % R) * 8;
-    auto tile_ptr = [&](int jt) { return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + lane * 8; };
+    constexpr int DS = D / 16;                            // pieces of a tile: 16 dims of 32 blocks, or 32 dims of 16 blocks
+    constexpr bool ROWS16 = sixteen_row_products(D, R);
+    constexpr int TAIL = key_tail(ROWS16 ? kKeyTiles16 : kKeyTiles32);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int at = ROWS16 ? lane * 8 : (half * 64 + l32) * 8;
+    auto tile_ptr = [&](int jt) { return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + at; };
     bf16x8 kraw[2 * NBUF];                                // [2b] = hi, [2b + 1] = lo of the piece in slot b
     if (jt_first < jt_end) {
         const __bf16* src = tile_ptr(jt_first);
 #pragma unroll
         for (int x = 0; x < NBUF; ++x) {
             kraw[2 * x] = *reinterpret_cast<const bf16x8*>(src + x * 1024);
-            kraw[2 * x + 1] = *reinterpret_cast<const bf16x8*>(src + x * 1024 + kKeyTail);
+            kraw[2 * x + 1] = *reinterpret_cast<const bf16x8*>(src + x * 1024 + TAIL);
         }
     }
     for (int jt = jt_first; jt < jt_end; jt += NWV) {
-        const int j = 32 * jt + (lane & 15);              // and j + 16
         const __bf16* cur = tile_ptr(jt);
         const __bf16* next = tile_ptr(jt + NWV < jt_end ? jt + NWV : jt);      // the last tile refills from itself: in bounds, never used
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        auto refill = [&](int x) {                        // piece x has been used
+            const int slot = x % NBUF, x_fill = (x + NBUF) % DS;
+            const __bf16* from = x + NBUF < DS ? cur : next;
+            kraw[2 * slot] = *reinterpret_cast<const bf16x8*>(from + x_fill * 1024);
+            kraw[2 * slot + 1] = *reinterpret_cast<const bf16x8*>(from + x_fill * 1024 + TAIL);
+        };
+        if constexpr (ROWS16) {
+            const __bf16* const qlane = qlds + ((lane >> 4) * R + (lane & 15)) * 8;
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};       // blocks lane & 15 and 16 more, rows 4 * (lane >> 4) .. + 3
 #pragma unroll
-        for (int s = 0; s < DS / 2; ++s) {
-            const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlane + (s * 2 + 0) * 4 * R * 8);
-            const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlane + (s * 2 + 1) * 4 * R * 8);
+            for (int s = 0; s < DS / 2; ++s) {
+                const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlane + (s * 2 + 0) * 4 * R * 8);
+                const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlane + (s * 2 + 1) * 4 * R * 8);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const bf16x8 k_hi = kraw[2 * ((2 * s + u) % NBUF)], k_lo = kraw[2 * ((2 * s + u) % NBUF) + 1];
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ql, k_hi, acc[u], 0, 0, 0);
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh, k_lo, acc[u], 0, 0, 0);
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh, k_hi, acc[u], 0, 0, 0);
+                    refill(2 * s + u);
+                }
+            }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const int x = 2 * s + u, slot = x % NBUF;
-                const bf16x8 k_hi = kraw[2 * slot], k_lo = kraw[2 * slot + 1];
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ql, k_hi, acc[u], 0, 0, 0);
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh, k_lo, acc[u], 0, 0, 0);
-                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh, k_hi, acc[u], 0, 0, 0);
-                const int x_fill = (x + NBUF) % DS;                            // the piece this slot holds next
-                const __bf16* from = x + NBUF < DS ? cur : next;
-                kraw[2 * slot] = *reinterpret_cast<const bf16x8*>(from + x_fill * 1024);
-                kraw[2 * slot + 1] = *reinterpret_cast<const bf16x8*>(from + x_fill * 1024 + kKeyTail);
+                const int j = 32 * jt + 16 * u + (lane & 15);
+                const float lv = lvbase != nullptr ? lvbase[j < a.NBk ? j : a.NBk - 1] : 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) store_score<LD>(a, acc[u][r], S, col0, 4 * (lane >> 4) + r, j, bh, i0, lvbase != nullptr, lv);
+            }
+        } else {
+            const int j = 32 * jt + l32;
+            const float lv = lvbase != nullptr ? lvbase[j < a.NBk ? j : a.NBk - 1] : 0.f;
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+            for (int s = 0; s < DS; ++s) {
+                const bf16x8 k_hi = kraw[2 * (s % NBUF)], k_lo = kraw[2 * (s % NBUF) + 1];
+                const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlds + (((s * 2 + 0) * R + l32 % R) * 2 + half) * 8);
+                const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlds + (((s * 2 + 1) * R + l32 % R) * 2 + half) * 8);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql, k_hi, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_lo, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_hi, acc, 0, 0, 0);
+                refill(s);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int mrow = 8 * (r >> 2) + 4 * half + (r & 3);            // row of the 32x32 result held in acc[r]
+                if (mrow < R) store_score<LD>(a, acc[r], S, col0, mrow, j, bh, i0, lvbase != nullptr, lv);
             }
         }
-        store_scores<R, LD>(a, acc, S, col0, j, bh, i0, lvbase);
     }
 }
 
@@ -877,9 +903,9 @@ __device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t,
             float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
             asm("" : "+v"(mean));                         // rounded before it is split, as in the pooling kernel
             const __bf16 hi = (__bf16)mean;
-            const int at = key_tile_offset(t256, j);
+            const int at = key_tile_offset(kKeyTiles32, t256, j);
             tile[at] = hi;
-            tile[at + kKeyTail] = (__bf16)(mean - (float)hi);
+            tile[at + key_tail(kKeyTiles32)] = (__bf16)(mean - (float)hi);
         }
     };
     load(IC_sel<0>{}, 0);
@@ -894,13 +920,12 @@ __device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t,
 }
 
 // Scores, top-k and merged lists of the query blocks i0 .. i0 + R - 1 of head bh = b * Hq + h, by a
-// 512-thread workgroup.  S: R * (MAXC * 64 + kRowPad) floats of LDS for the scores, then 256 counters per
+// 512-thread workgroup.  S: R * (MAXC * 64 + row_pad) floats of LDS for the scores, then 256 counters per
 // wavefront.  Ends without a barrier; the caller must not reuse S before one.
 // The split pooled queries are staged in LDS by stage_queries.
 template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, bool KIN = false>
 __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S, const KeyArgs* keys = nullptr) {
-    constexpr int LD = MAXC * 64 + kRowPad;
-    constexpr int DS = D / 16;                 // 1-KB piece pairs of a tile: 32 dims by 16 blocks
+    constexpr int LD = MAXC * 64 + row_pad(D, R);
     const float* __restrict__ kp = a.kp;
     const int Hq = a.Hq, G = a.G, NB = a.NB, NBk = a.NBk, off = a.off, T = a.T;
     Pattern pt = a.pt;
@@ -915,7 +940,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
 
     const int b = bh / Hq, h = bh % Hq;
     const int Hkv = Hq / G;
-    const float* kbase = KIN ? nullptr : kp + (int64_t)(b * Hkv + h / G) * ((NBk + 31) >> 5) * (32 * D);   // tiled, see tile_ptr
+    const float* kbase = KIN ? nullptr : kp + (int64_t)(b * Hkv + h / G) * ((NBk + 31) >> 5) * (32 * D);   // tiles, see key_layout
     const float* lvbase = lvn != nullptr ? lvn + (int64_t)(b * Hkv + h / G) * NBk : nullptr;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i_last = (i0 + R - 1 < NB - 1) ? i0 + R - 1 : NB - 1;
@@ -936,65 +961,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
         else stage_keys<D, 64, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
         kbase = tile;
     }
-    // The pooled K arrives tiled in operand layout and already split into bf16 head and tail (key_tile_offset), so
-    // every load instruction of a wavefront covers whole pieces (row-major rows would cost 32 cache
-    // lines per instruction) and what it loads is the MFMA operand.  One register buffer serves
-    // as a whole-tile pipeline: as soon as the three products of a slice have been issued,
-    // the same registers are refilled with that slice of the wave's next tile, so every load has a
-    // full tile of MFMA work to arrive.  Blocks past NBk in the last tile hold whatever the
-    // workspace held: their columns are never ranked or written out.
-    if constexpr (R == 16) {
-        score_tiles<D, R, LD, DS, NWV>(a, kbase, qlds, S, 0, wave, n_jt, bh, i0, lvbase);
-    } else {
-        // 4 or 8 rows: 32x32x16 products on the same tiles.  The rows are copied to fill them, but few tiles fall to a wavefront and the two
-        // stores a row and tile count for more (select calls: 65536 tokens 120 us with 16-row products, 117.5 this way, with a mass
-        // budget 137 and 132, 49000 tokens with the output-aware score 108 and 104).
-        bf16x8 kraw[2 * DS];                                  // [2s] = hi, [2s + 1] = lo of 16-dim slice s
-        const int half = lane >> 5, l32 = lane & 31;
-        auto tile_ptr = [&](int jt) {
-            return reinterpret_cast<const __bf16*>(kbase + (int64_t)jt * (32 * D)) + (l32 >> 4) * 1024 + half * 128 + (l32 & 15) * 8;
-        };
-        auto piece = [](int s) { return (s >> 1) * 2048 + (s & 1) * 256; };
-        if (wave < n_jt) {
-            const __bf16* src = tile_ptr(wave);
-#pragma unroll
-            for (int s = 0; s < DS; ++s) {
-                kraw[2 * s] = *reinterpret_cast<const bf16x8*>(src + piece(s));
-                kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(src + piece(s) + kKeyTail);
-            }
-        }
-        const __bf16* const qlane = qlds + (half * R + l32 % R) * 8;
-        for (int jt = wave; jt < n_jt; jt += NWV) {
-            const int j = 32 * jt + l32;
-            const float lv = lvbase != nullptr ? lvbase[j < NBk ? j : NBk - 1] : 0.f;
-            const __bf16* next = tile_ptr(jt + NWV < n_jt ? jt + NWV : jt);
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-            for (int s = 0; s < DS; ++s) {
-                const bf16x8 k_hi = kraw[2 * s], k_lo = kraw[2 * s + 1];
-                const bf16x8 qh = *reinterpret_cast<const bf16x8*>(qlane + (((s >> 1) * 2 + 0) * 4 + (s & 1) * 2) * R * 8);
-                const bf16x8 ql = *reinterpret_cast<const bf16x8*>(qlane + (((s >> 1) * 2 + 1) * 4 + (s & 1) * 2) * R * 8);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql, k_hi, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_lo, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh, k_hi, acc, 0, 0, 0);
-                kraw[2 * s] = *reinterpret_cast<const bf16x8*>(next + piece(s));
-                kraw[2 * s + 1] = *reinterpret_cast<const bf16x8*>(next + piece(s) + kKeyTail);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int mrow = 8 * (r >> 2) + 4 * half + (r & 3);     // row of the 32x32 result held in acc[r]
-                if (mrow < R) {
-                    const float sc = lvbase != nullptr ? scale * acc[r] + lv : scale * acc[r];
-                    S[mrow * LD + j] = sc;
-                    const int i = i0 + mrow;
-                    if (scores_out != nullptr && i < NB && j < NBk)
-                        scores_out[((int64_t)bh * NB + i) * NBk + j] = j <= i + off ? sc : -INFINITY;
-                }
-            }
-        }
-    }
+    score_tiles<D, R, LD, D / 16, NWV>(a, kbase, qlds, S, 0, wave, n_jt, bh, i0, lvbase);
     if (scores_out != nullptr) {                          // key blocks past the last computed tile
         const int j_first = 32 * n_jt;
         for (int r = 0; r < R && i0 + r < NB; ++r)
@@ -1106,8 +1073,7 @@ template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
 __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, const int bh, const int i0, float* S) {
     constexpr int CC = 16;                     // 64-block register chunks per column chunk
     constexpr int CW = CC * 64;                // key blocks per column chunk
-    constexpr int LD = CW + kRowPad;
-    constexpr int DS = D / 16;
+    constexpr int LD = CW + row_pad(D, R);
     constexpr int RPW = R / NWV;               // rows per wavefront
     constexpr int MAXC = MAXCH * CC;
     static_assert(R % NWV == 0 && MAXCH == 2, "two column chunks");
@@ -1154,7 +1120,7 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     for (int rr = 0; rr < RPW; ++rr)
 #pragma unroll
         for (int m = 0; m < CC; ++m) x0[rr][m] = -INFINITY;
-    score_chunk(0, IC_sel<DS>{});
+    score_chunk(0, IC_sel<D / 16>{});
     __syncthreads();
     if (n_ch > 1) {                                       // workgroup-uniform
 #pragma unroll
@@ -1163,7 +1129,7 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
             if (iq < NB && iq < NB_b) load_scores(wave + rr * NWV, x0[rr]);
         }
         __syncthreads();                                  // every row's first-chunk scores are in registers
-        score_chunk(1, IC_sel<DS / 2>{});
+        score_chunk(1, IC_sel<D / 32>{});
         __syncthreads();
     }
     if (scores_out != nullptr) {                          // key blocks past the last computed tile
@@ -1256,7 +1222,7 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
 
 template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
 __global__ __launch_bounds__(NWV * 64, 4) void score_topk_chunked_kernel(ScoreArgs a, int n_tiles) {
-    extern __shared__ __attribute__((aligned(128))) float S[];   // [R][1024 + 8] scores of one column chunk, then the staged queries
+    extern __shared__ __attribute__((aligned(128))) float S[];   // [R][1024 + row_pad] scores of one column chunk, then the staged queries
     const int nwg = gridDim.x;
     int wg = blockIdx.x;
     if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);   // each XCD a contiguous slice, as in the plain kernel
@@ -1355,11 +1321,11 @@ struct ScoreCall {
     hipStream_t st;
 };
 
-template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, int NWV = (R * (MAXC * 64 + kRowPad) * 4 > 80 * 1024 ? 16 : 8)>
+template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, int NWV = (R * (MAXC * 64 + row_pad(D, R)) * 4 > 80 * 1024 ? 16 : 8)>
 hipError_t launch_mfma_e(const ScoreCall& c) {
     constexpr size_t part_words = 2 * (NWV / 4) * (256 / (D / 8)) * D;    // partial sums of the in-kernel pooling
-    constexpr size_t lds = ((size_t)R * (MAXC * 64 + kRowPad) + NWV * 256 +
-                            (part_words > (size_t)R * (MAXC * 64 + kRowPad) ? part_words : 0)) * sizeof(float);
+    constexpr size_t lds = ((size_t)R * (MAXC * 64 + row_pad(D, R)) + NWV * 256 +
+                            (part_words > (size_t)R * (MAXC * 64 + row_pad(D, R)) ? part_words : 0)) * sizeof(float);
     hipError_t e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
@@ -1377,8 +1343,8 @@ hipError_t launch_mfma_q(const ScoreCall& c) {
 template <int D, int MAXCH, bool EXT, bool GROUP>
 hipError_t launch_chunked_e(const ScoreCall& c) {
     constexpr int R = 16, NWV = 8;
-    constexpr size_t lds = ((size_t)R * (1024 + kRowPad) + NWV * 256) * sizeof(float);
-    static_assert(2 * (NWV / 4) * (256 / (D / 8)) * D <= R * (1024 + kRowPad), "the pooling partial sums fit the score space");
+    constexpr size_t lds = ((size_t)R * (1024 + row_pad(D, R)) + NWV * 256) * sizeof(float);
+    static_assert(2 * (NWV / 4) * (256 / (D / 8)) * D <= R * (1024 + row_pad(D, R)), "the pooling partial sums fit the score space");
     hipError_t e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
@@ -1409,7 +1375,7 @@ hipError_t launch_plain(const ScoreCall& c) {
 
 template <int D, bool EXT>
 hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
-    constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + kRowPad, 8>() + 32 * D) * sizeof(float);
+    constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + row_pad(D, 4), 8>() + 32 * D) * sizeof(float);
     const size_t v_lds = keys.vt != nullptr ? 2 * c.d.Bs * (D + 2) * sizeof(uint16_t) : 0;
     const size_t lds = v_lds > score_lds ? v_lds : score_lds;
     // asked for once, for the largest call: a fused call in a capture may follow selections that need less
