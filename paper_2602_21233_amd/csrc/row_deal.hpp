@@ -28,8 +28,9 @@ namespace spa {
 // Among the XCDs at a head:
 //   - the n_dense rows of a Tri-shape strip (each visits up to NB blocks) are dealt one by one;
 //   - the other rows are dealt in runs of `run` consecutive rows, last row first; with `snake` every
-//     other round of runs goes backwards (which rounds: alternating with the KV head), so that the XCD
-//     that gets the longest row of one round gets the shortest of the next.
+//     other round of runs goes backwards (which rounds: alternating with the heads one after the other, not with those side by side,
+//     or an XCD that goes from head to head with every round has the same place in all of them: 16 / 2 heads of 12288 tokens, one XCD with
+//     18 % more than its share, 503 -> 590 us), so that the XCD that gets the longest row of one round gets the shortest of the next.
 // Neighbouring rows share their local-window blocks in the XCD's L2, which favours runs of 8 once K and
 // V^T of a head outgrow that L2 (4 MB).  But the XCD with the most rows decides: 16 query blocks in runs of
 // 8 kept two XCDs busy and six idle.  So the runs get shorter until no more than a sixteenth of
@@ -115,7 +116,7 @@ __host__ __device__ __forceinline__ bool dealt_row(const RowDeal& deal, int GH, 
     }
     const int rr = pos - deal.n_single;
     const int round = rr >> deal.run_log2;
-    const int x = (deal.snake & (round ^ r.head_slot)) ? width - 1 - xcd : xcd;
+    const int x = (deal.snake & (round ^ group)) ? width - 1 - xcd : xcd;
     const int ridx = ((round * width + x) << deal.run_log2) + (rr & (deal.run - 1));
     r.i = NB - deal.n_dense - 1 - ridx;
     return ridx < NB - deal.n_dense;
