@@ -13,8 +13,9 @@ namespace spa {
 // and fetch each of their K and V^T tiles for a few rows only; a smaller gang puts more rows of one head behind one L2.
 // At any time `width` of the gang's XCDs are at the same head, so that 8 / width heads are in flight, each behind few L2s: fewer
 // of its tiles are fetched more than once.  The XCDs go from head to head after every piece of row positions (at least what an XCD has
-// in flight), so that in the end all of the gang have served all of the heads alike: heads may differ in the
-// length of their lists.  The limit is half of the memory-side cache (128 of 256 MB, for queries and outputs pass through it
+// in flight), so that in the end all of the gang have served all of the heads alike.  Where width is the whole gang they stay: a change
+// only has more L2s fetch a head (5312 queries over 30464 tokens, blocks of 64, 398 -> 391 us;
+// 2763 tokens, blocks of 64, 43.3 -> 43.0).  The limit is half of the memory-side cache (128 of 256 MB, for queries and outputs pass through it
 // too), which has to hold the K and V^T of all heads in flight.  Attention kernel, 32/8 heads, one XCD (the rule: as few as the limit allows) against
 // eight at a head: 8192 tokens 496 -> 481 us, 16384 932 -> 898, with blocks of 64 424 -> 401, with head_dim 64 528 -> 512, 32768 tokens
 // 1.95 -> 1.90 ms, with blocks of 64 1473 -> 1394 us.  With 8, 4, 2, 1 at a head: 40960 tokens (21 MB a head) 2.63, 2.54, 2.53, 2.53 ms; 49000
@@ -28,8 +29,8 @@ namespace spa {
 // Among the XCDs at a head:
 //   - the n_dense rows of a Tri-shape strip (each visits up to NB blocks) are dealt one by one;
 //   - the other rows are dealt in runs of `run` consecutive rows, last row first; with `snake` every
-//     other round of runs goes backwards (which rounds: alternating with the heads one after the other, not with those side by side,
-//     or an XCD that goes from head to head with every round has the same place in all of them: 16 / 2 heads of 12288 tokens, one XCD with
+//     other round of runs goes backwards (which rounds: alternating with the KV head, where the XCDs change heads with those one after
+//     the other, or an XCD that goes on to the next head with every round has the same place in all of them: 16 / 2 heads of 12288 tokens, one XCD with
 //     18 % more than its share, 503 -> 590 us), so that the XCD that gets the longest row of one round gets the shortest of the next.
 // Neighbouring rows share their local-window blocks in the XCD's L2, which favours runs of 8 once K and
 // V^T of a head outgrow that L2 (4 MB).  But the XCD with the most rows decides: 16 query blocks in runs of
@@ -54,6 +55,8 @@ namespace spa {
 // than one round (4096 tokens) it costs 3 %.
 // seq_len = workgroups per (head, XCD) in the grid; surplus workgroups exit at once.  places = workgroups of an XCD for the heads that are
 // side by side; what divides workgroup ids is kept as a shift where it can be, every workgroup starts with these.
+constexpr int kNoChange = 30;   // piece_log2 of XCDs that stay at their heads
+
 struct RowDeal {
     int gang, n_dense, run, snake, seq_len;
     int places, width_log2, run_log2, piece_log2, n_single, fold;
@@ -79,6 +82,7 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     r.width_log2 = __builtin_ctz(width);
     r.piece_log2 = 0;
     while ((GH << r.piece_log2) < slots) ++r.piece_log2;
+    if (width == r.gang) r.piece_log2 = kNoChange;
     r.run = (d.stride > 0 || d.n_dense > 0 || kv_bytes <= 4 << 20) ? 1 : 8;
     while (r.run > 1 && (n + width * r.run - 1) / (width * r.run) * (width * r.run) > n + n / 16) r.run >>= 1;
     r.snake = r.run == 1 || 8 * (int64_t)d.T >= d.NBk;
@@ -116,7 +120,8 @@ __host__ __device__ __forceinline__ bool dealt_row(const RowDeal& deal, int GH, 
     }
     const int rr = pos - deal.n_single;
     const int round = rr >> deal.run_log2;
-    const int x = (deal.snake & (round ^ group)) ? width - 1 - xcd : xcd;
+    const int turned = deal.piece_log2 == kNoChange ? r.head_slot : group;
+    const int x = (deal.snake & (round ^ turned)) ? width - 1 - xcd : xcd;
     const int ridx = ((round * width + x) << deal.run_log2) + (rr & (deal.run - 1));
     r.i = NB - deal.n_dense - 1 - ridx;
     return ridx < NB - deal.n_dense;
