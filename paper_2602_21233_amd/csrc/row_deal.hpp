@@ -22,6 +22,12 @@ namespace spa {
 // tokens (25 MB) of 40/8 heads 4.75, 4.65, 4.53, 4.53, of 32/8 heads with a decaying budget 3.40, 3.40, 3.43, 3.46; 131072 tokens (67 MB) 15.96,
 // 15.79, 15.96, 16.49; 262144 tokens of 40/8 heads (134 MB) 66.3, 64.2, 66.3, 68.5 (two runs of one side differ by 2 %).  Pieces half
 // as long cost 2 to 3 % with blocks of 64, twice as long or no change of heads at all gives nothing more.
+// All that is for heads with lists as long as each other: the XCDs advance in step, so those at heads with short lists wait for those
+// at long ones, and changing heads evens that out only in part.  A fused call with budgets per head or a mass budget keeps width = gang:
+// 16384 tokens, one KV head of 8 with eight times the budget of the others, 789 us against 949 with one XCD at a head (8192 tokens
+// 335 and 389, 32768 1809 and 1996, blocks of 64, 16384 tokens, 579 and 645); every second KV head 1290 and 1293, every fourth query head 1361 and
+// 1335; budgets drawn at random 0.95 to 1.11 times the time; a mass budget of 0.9, 32768 tokens, 3442 and 3476.  An attention call
+// does not say how its lists came about and is taken at its pattern's word: the same budget for all.
 // In a ragged batch only heads of one entry sit side by side: entries differ in
 // length, which the host does not see, and an XCD that serves one entry's head alone idles after a short one.  Attention
 // kernel, 8 entries of 4 / 1 heads with blocks of 128, one of 3900 tokens and the others of 325: 106 us with an entry
@@ -78,7 +84,8 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     while (r.gang > 1 && (int64_t)d.NB * GH < (int64_t)slots * r.gang && heads % (16 / r.gang) == 0) r.gang >>= 1;
     const int64_t kv_bytes = (int64_t)d.Skv * d.D * 4;                // K and V^T of a head, bf16
     int width = r.gang;
-    while (width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
+    const bool alike = !d.head_budgets && d.gamma_q16 < 0;            // lists of all heads as long as each other
+    while (alike && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
     r.width_log2 = __builtin_ctz(width);
     r.piece_log2 = 0;
     while ((GH << r.piece_log2) < slots) ++r.piece_log2;

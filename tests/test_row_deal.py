@@ -9,9 +9,18 @@ from paper_2602_21233_amd import binding
 
 SHIM = r"""
 #include "row_deal.hpp"
+// what only a fused call knows of its lists
+static int head_budgets, mass;
+extern "C" void lists_by(int by_head, int by_mass) { head_budgets = by_head; mass = by_mass; }
+static spa::Dims dims(const spa_params* p) {
+    spa::Dims d = spa::dims_of(*p);
+    if (head_budgets) d.head_budgets = 1;
+    if (mass) d.gamma_q16 = 58982;
+    return d;
+}
 // every workgroup of the launch: (head_slot, query block, turn), or -1 three times for a surplus one
 extern "C" int deal(const spa_params* p, int nh, int* gang, int* out, int cap) {
-    const spa::Dims d = spa::dims_of(*p);
+    const spa::Dims d = dims(p);
     const spa::RowDeal r = spa::deal_rows(d, nh);
     const int nwg = r.gang * r.seq_len * d.B * d.Hkv;
     *gang = r.gang;
@@ -31,13 +40,14 @@ extern "C" int deal(const spa_params* p, int nh, int* gang, int* out, int cap) {
 def deal(tmp_path_factory):
     lib = compile_shim(tmp_path_factory.mktemp("deal"), SHIM)
 
-    def rows(nh=1, ragged=False, **kw):
+    def rows(nh=1, ragged=False, head_budgets=False, mass=False, **kw):
         """gang, [workgroups, 3]"""
         base = dict(batch=1, n_q_heads=8, n_kv_heads=2, seq_len=2048, head_dim=128, block_size=128, n_sink_blocks=1,
                     n_local_blocks=4, top_k_blocks=64)
         base.update(kw)
         p = binding.make_params(**base)
         p.seq_lens = 1 if ragged else None              # only asked whether there is one
+        lib.lists_by(head_budgets, mass)
         gang = ctypes.c_int()
         n = lib.deal(ctypes.byref(p), nh, ctypes.byref(gang), None, 0)
         out = np.empty((n, 3), dtype=np.int32)
@@ -157,3 +167,16 @@ def test_an_xcd_of_a_short_call_serves_a_head_to_its_end(deal, Hq, Hkv, S, Bs, P
         heads = wg[x::8, 0]
         heads = heads[heads >= 0]
         assert (heads[1:] != heads[:-1]).sum() == len(set(heads)) - 1 == Hkv * gang // 8 - 1
+
+
+# Heads whose lists differ in length (budgets per head, a mass budget) sit side by side only as the gangs do: with all XCDs at one head
+# where the rows fill them (16384 tokens, one KV head of 8 with a large budget, 949 -> 789 us).
+@pytest.mark.parametrize("why", ["head_budgets", "mass"])
+@pytest.mark.parametrize("D,Bs", [(128, 128), (128, 64), (64, 128)])
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 32, 8), (2, 16, 4), (1, 16, 4), (1, 40, 8), (1, 12, 2)])
+@pytest.mark.parametrize("S", [1999, 6000, 16384, 50001])
+def test_heads_of_their_own_budgets_are_not_put_side_by_side(deal, why, D, Bs, B, Hq, Hkv, S):
+    gang, wg = deal(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=S, head_dim=D, block_size=Bs, **{why: True})
+    head = wg[:, 0].reshape(-1, 8)                         # workgroups 8 s .. 8 s + 7: one for each XCD
+    for at_once in head:
+        assert len(set(at_once[at_once >= 0])) <= 8 // gang
