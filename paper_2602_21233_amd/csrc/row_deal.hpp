@@ -15,12 +15,14 @@ namespace spa {
 // of its tiles are fetched more than once.  The XCDs go from head to head after every piece of row positions (at least what an XCD has
 // in flight), so that in the end all of the gang have served all of the heads alike.  Where width is the whole gang they stay: a change
 // only has more L2s fetch a head (5312 queries over 30464 tokens, blocks of 64, 398 -> 391 us;
-// 2763 tokens, blocks of 64, 43.3 -> 43.0).  The limit is half of the memory-side cache (128 of 256 MB, for queries and outputs pass through it
-// too), which has to hold the K and V^T of all heads in flight.  Attention kernel, 32/8 heads, one XCD (the rule: as few as the limit allows) against
-// eight at a head: 8192 tokens 496 -> 481 us, 16384 932 -> 898, with blocks of 64 424 -> 401, with head_dim 64 528 -> 512, 32768 tokens
-// 1.95 -> 1.90 ms, with blocks of 64 1473 -> 1394 us.  With 8, 4, 2, 1 at a head: 40960 tokens (21 MB a head) 2.63, 2.54, 2.53, 2.53 ms; 49000
-// tokens (25 MB) of 40/8 heads 4.75, 4.65, 4.53, 4.53, of 32/8 heads with a decaying budget 3.40, 3.40, 3.43, 3.46; 131072 tokens (67 MB) 15.96,
-// 15.79, 15.96, 16.49; 262144 tokens of 40/8 heads (134 MB) 66.3, 64.2, 66.3, 68.5 (two runs of one side differ by 2 %).  Pieces half
+// 2763 tokens, blocks of 64, 43.3 -> 43.0).  The rule: as few XCDs at a head as half of the memory-side cache (128 of 256 MB,
+// for queries and outputs pass through it too) holds K and V^T of the heads in flight, up to 32 MB a head (65536 tokens of head_dim 128).
+// Attention kernel, 32/8 heads, one XCD at a head against eight: 8192 tokens 501 -> 480 us, 12000 with lists of 35 blocks 695 -> 615, 24000
+// 1429 -> 1361, with blocks of 64 1006 -> 918, 24000 with lists of 19 blocks 873 -> 815.  With 8, 4, 2, 1 at a head: 49152
+// tokens (25 MB a head) of 40/8 heads 6.96, 6.83, 6.77, 6.71 ms, 65536 9.46, 9.39, 9.29, 9.27, of 32/8 heads 7.32, 7.34, 7.32, 7.33.  Beyond that it depends on
+// the lists, and mostly costs: 81920 tokens 9.65, 9.49, 9.42, 9.55, but with keys that drift along the sequence 98304 tokens 12.16, 12.28, 12.31, 12.57,
+// 131072 16.67, 16.83, 16.95, 17.35, 196608 25.66, 25.93, 26.31, 27.18, 262144 of 40/8 heads 67.1, 67.2, 68.2, 70.5; 8192 queries over 131072 tokens
+// 1111, 1125, 1121, 1137 us (two runs of one side differ by 0.5 %). Pieces half
 // as long cost 2 to 3 % with blocks of 64, twice as long or no change of heads at all gives nothing more.
 // All that is for heads with lists as long as each other: the XCDs advance in step, so those at heads with short lists wait for those
 // at long ones, and changing heads evens that out only in part.  A fused call with budgets per head or a mass budget keeps width = gang:
@@ -85,7 +87,7 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     const int64_t kv_bytes = (int64_t)d.Skv * d.D * 4;                // K and V^T of a head, bf16
     int width = r.gang;
     const bool alike = !d.head_budgets && d.gamma_q16 < 0;            // lists of all heads as long as each other
-    while (alike && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
+    while (alike && kv_bytes <= 32 << 20 && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
     r.width_log2 = __builtin_ctz(width);
     r.piece_log2 = 0;
     while ((GH << r.piece_log2) < slots) ++r.piece_log2;

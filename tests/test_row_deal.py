@@ -105,8 +105,8 @@ def test_every_row_is_dealt_once(deal, D, Bs, nh, B, Hkv, ragged):
     assert seen == {8} | {8 // x for x in (2, 4, 8) if divides % x == 0}
 
 
-# Long calls: as many heads in flight as the memory-side cache holds K and V^T of, and, since heads may differ in the length of
-# their lists, each XCD serves the rows of all heads alike, to within a few pieces (what an XCD has in flight).
+# Long calls: as many heads in flight as half of the memory-side cache holds K and V^T of, one beyond 32 MB a head, and
+# each XCD serves the rows of all heads alike, to within a few pieces (what an XCD has in flight).
 @pytest.mark.parametrize("D,Bs", [(128, 128), (128, 64), (64, 128)])
 @pytest.mark.parametrize("B,Hkv", [(1, 8), (2, 4), (1, 4), (1, 2), (1, 3)])
 @pytest.mark.parametrize("S", [16384, 50001, 131072, 262143])
@@ -121,7 +121,9 @@ def test_heads_side_by_side_fit_the_cache_and_every_xcd_serves_them_alike(deal, 
     first = wg[:in_flight, 0]
     side = len(set(first[first >= 0]))
     assert side == 1 or side * S * D * 4 <= 128 << 20
-    if (B * Hkv) % (2 * side) == 0 and side < 8:
+    if S * D * 4 > 32 << 20:
+        assert side == 1                                   # 98304 tokens 12.16 ms, with two heads side by side 12.28
+    elif (B * Hkv) % (2 * side) == 0 and side < 8:
         assert 2 * side * S * D * 4 > 128 << 20
     rows = np.zeros((8, B * Hkv), dtype=np.int64)
     for x in range(8):
