@@ -179,6 +179,7 @@ int fused_impl(const spa_params* p, const void* q, const void* k, const void* v,
     int32_t* cnt = block_cnt_or_null ? block_cnt_or_null : (int32_t*)((char*)ws + w.cnt_off);
     if ((rc = check_select(p, q, k, output_aware ? v : nullptr, mass_gamma, idx, cnt, d))) return rc;
     d.head_budgets = head_pattern != nullptr;
+    d.row_budgets = k_rows != nullptr;
     hipStream_t st = (hipStream_t)hip_stream;
     void* const vt = (char*)ws + w.vt_off;
     if ((rc = select_launches(d, p, q, k, v, k_rows, head_pattern, idx, cnt, nullptr, select_scratch(ws, w), output_aware, vt, st))) return rc;

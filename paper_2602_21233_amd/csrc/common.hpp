@@ -20,6 +20,7 @@ struct Dims {
     int gamma_q16;                // cumulative-mass budget in 16-bit fixed point, -1 = none
     const int32_t* seq_lens;      // device array [B] of per-entry token counts (ragged batch), or nullptr
     int head_budgets;             // 1: the lists are made with budgets of each head's own (known of a fused call only)
+    int row_budgets;              // 1: with budgets of each query block's own, at most k (known of a fused call only)
 };
 
 inline Dims dims_of(const spa_params& p) {
@@ -37,7 +38,7 @@ inline Dims dims_of(const spa_params& p) {
     d.scale = p.softmax_scale;
     d.gamma_q16 = -1;
     d.seq_lens = p.seq_lens;
-    d.head_budgets = 0;
+    d.head_budgets = d.row_budgets = 0;
     return d;
 }
 

@@ -56,10 +56,15 @@ namespace spa {
 // alone: 1999 tokens 58 -> 50 us, 2048 queries over the prefix 306 -> 286 us, 1024 queries 174 -> 169 us.
 // Launches of 33 to 64 workgroups per XCD, two to a CU, all in flight at once: the first 32 go to CUs of their own, longest row first, and
 // the others join them in that order, so the CU that has the longest row would get the longest of the rest.  `fold` (that
-// count) deals the others shortest first.  Only where every row visits all of its causal blocks (T >= NBk): rows cut to T are
-// about as long as each other, and under a decaying budget the last rows are the short ones (2000 tokens, 8 falling to 2 blocks,
-// 33 -> 35 us).  Attention kernel, 32/8 heads: 1999 tokens 43.3 -> 40.5 us, two of 1024 32.1 -> 27.0, four of 512 21.3 -> 19.4, 1024 with blocks
-// of 64 23.3 -> 21.3; 8000 tokens of 8/8 heads 143 -> 133.  With more than two to a CU (blocks of 64, 2000 tokens) it gives nothing, with more
+// count) deals the others shortest first.  Only where the longest rows, those that visit all of their causal blocks, are the last ones,
+// so that there is a shortest of the rest: with room for all blocks (T >= NBk; a Tri-shape strip, too, whatever the other rows do) and no budget per
+// row that may cut the last ones short.  Of a fused call's budgets only the largest is known here; a quarter of it has to do, the
+// least of the decaying budgets that the package makes.  Rows cut to one length are about as long as each other, and of a budget that
+// falls too far the last rows are the short ones.  Not in a ragged batch: the first 32 are then often rows past an entry's end, and it depends on which
+// entry is the long one.  Attention kernel, 32/8 heads: 1999 tokens 44.5 -> 42.2 us, two of 1000 32.6 -> 27.8, four of 500 22.0 -> 20.1, 2000 with two
+// dense rows and 4 blocks of budget 43.8 -> 41.1, 2000 with a budget that falls from 64 to 16 44.5 -> 42.0, but from 12 to 3 35.5 -> 36.6, from 8 to 2 34.0
+// -> 35.9, 8000 tokens of 8/8 heads from 64 to 16 101.8 -> 109.6; entries of 166 and 1000 tokens 21.1 -> 24.1, of 1000 and 667 25.5 -> 24.1, with
+// blocks of 64 and 16/4 heads 19.7 -> 20.5.  With more than two to a CU (blocks of 64, 2000 tokens) it gives nothing, with more
 // than one round (4096 tokens) it costs 3 %.
 // seq_len = workgroups per (head, XCD) in the grid; surplus workgroups exit at once.  places = workgroups of an XCD for the heads that are
 // side by side; what divides workgroup ids is kept as a shift where it can be, every workgroup starts with these.
@@ -102,7 +107,8 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     r.seq_len = ((r.n_single + (runs + width - 1) / width * r.run) * GH + turns - 1) / turns;
     r.places = r.seq_len * turns;
     const int64_t per_xcd = (int64_t)r.gang * r.seq_len * d.B * d.Hkv / 8;
-    r.fold = slots >= 64 && d.T >= d.NBk && per_xcd > 32 && per_xcd <= 64 ? (int)per_xcd : 0;
+    const bool rows_in_full = d.T >= d.NBk && (!d.row_budgets || (int64_t)d.ns + d.nl + d.k / 4 >= d.NBk);
+    r.fold = slots >= 64 && rows_in_full && d.seq_lens == nullptr && per_xcd > 32 && per_xcd <= 64 ? (int)per_xcd : 0;
     return r;
 }
 
