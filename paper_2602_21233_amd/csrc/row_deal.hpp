@@ -24,6 +24,10 @@ namespace spa {
 // 131072 16.67, 16.83, 16.95, 17.35, 196608 25.66, 25.93, 26.31, 27.18, 262144 of 40/8 heads 67.1, 67.2, 68.2, 70.5; 8192 queries over 131072 tokens
 // 1111, 1125, 1121, 1137 us (two runs of one side differ by 0.5 %). Pieces half
 // as long cost 2 to 3 % with blocks of 64, twice as long or no change of heads at all gives nothing more.
+// Gangs of two whose rows visit less than a quarter of the blocks keep their two heads, with blocks of 128: what a row reads is then little beside
+// what the second L2 fetches for a head (7680 tokens, lists of 11 blocks, 154 us, 156 with one XCD at a head, shared by a group 166
+// and 170; 6272 queries over 24064 tokens, shared lists of 10, 119.0 and 123.1; lists of 19 blocks 236 and 235; 5000 tokens, shared lists of 19, 156 and
+// 146; blocks of 64, 5000 tokens, lists of 7 and 11, 55.0 and 54.6, 73.9 and 73.4).
 // All that is for heads with lists as long as each other: the XCDs advance in step, so those at heads with short lists wait for those
 // at long ones, and changing heads evens that out only in part.  A fused call with budgets per head or a mass budget keeps width = gang:
 // 16384 tokens, one KV head of 8 with eight times the budget of the others, 789 us against 949 with one XCD at a head (8192 tokens
@@ -92,7 +96,8 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     const int64_t kv_bytes = (int64_t)d.Skv * d.D * 4;                // K and V^T of a head, bf16
     int width = r.gang;
     const bool alike = !d.head_budgets && d.gamma_q16 < 0;            // lists of all heads as long as each other
-    while (alike && kv_bytes <= 32 << 20 && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
+    const bool few = r.gang == 2 && d.Bs == 128 && 4 * (int64_t)d.T < d.NBk;
+    while (alike && !few && kv_bytes <= 32 << 20 && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
     r.width_log2 = __builtin_ctz(width);
     r.piece_log2 = 0;
     while ((GH << r.piece_log2) < slots) ++r.piece_log2;

@@ -200,3 +200,15 @@ def test_shortest_rows_join_the_longest_only_where_those_are_the_last(deal, want
     i = wg[::8, 1]                                         # query blocks of an XCD's workgroups, in their order
     second = i[32:][i[32:] >= 0]
     assert (second[0] < second[-1]) == want
+
+
+# A gang of two whose rows visit less than a quarter of the blocks keeps the XCDs at its own heads, with blocks of 128 (7680 tokens, lists
+# of 11 blocks, 156 -> 154 us).
+@pytest.mark.parametrize("kw,side", [
+    (dict(seq_len=7680, top_k_blocks=8), 4), (dict(seq_len=7680, top_k_blocks=16), 8), (dict(seq_len=7680, top_k_blocks=9), 4), (dict(seq_len=7680, top_k_blocks=10), 8),
+    (dict(seq_len=5000, top_k_blocks=8, block_size=64), 8), (dict(seq_len=5000, top_k_blocks=4), 4), (dict(seq_len=12000, top_k_blocks=8), 8)])
+def test_gangs_of_two_with_short_lists_stay_at_their_heads(deal, kw, side):
+    gang, wg = deal(n_q_heads=32, n_kv_heads=8, **kw)
+    assert gang == (4 if kw["seq_len"] == 12000 else 2)
+    head = wg[:, 0].reshape(-1, 8)
+    assert max(len(set(at_once[at_once >= 0])) for at_once in head) == side
