@@ -22,7 +22,9 @@ namespace spa {
 // tokens (25 MB a head) of 40/8 heads 6.96, 6.83, 6.77, 6.71 ms, 65536 9.46, 9.39, 9.29, 9.27, of 32/8 heads 7.32, 7.34, 7.32, 7.33.  Beyond that it depends on
 // the lists, and mostly costs: 81920 tokens 9.65, 9.49, 9.42, 9.55, but with keys that drift along the sequence 98304 tokens 12.16, 12.28, 12.31, 12.57,
 // 131072 16.67, 16.83, 16.95, 17.35, 196608 25.66, 25.93, 26.31, 27.18, 262144 of 40/8 heads 67.1, 67.2, 68.2, 70.5; 8192 queries over 131072 tokens
-// 1111, 1125, 1121, 1137 us (two runs of one side differ by 0.5 %). Pieces half
+// 1111, 1125, 1121, 1137 us (two runs of one side differ by 0.5 %).  Calls with a Tri-shape strip have no such limit: their XCDs, at one head, all wait for
+// its dense rows, one head after the other (8 dense rows and lists of 21 blocks, with 8 and 4: 73728 tokens 4.61 and 4.26 ms, 131072 8.73 and 8.08, lists
+// of 69 18.7 and 18.2; 2 dense rows, 131072 12.0 and 10.6). Pieces half
 // as long cost 2 to 3 % with blocks of 64, twice as long or no change of heads at all gives nothing more.
 // Gangs of two whose rows visit less than a quarter of the blocks keep their two heads, with blocks of 128: what a row reads is then little beside
 // what the second L2 fetches for a head (7680 tokens, lists of 11 blocks, 154 us, 156 with one XCD at a head, shared by a group 166
@@ -97,7 +99,8 @@ inline RowDeal deal_rows(const Dims& d, int nh) {
     int width = r.gang;
     const bool alike = !d.head_budgets && d.gamma_q16 < 0;            // lists of all heads as long as each other
     const bool few = r.gang == 2 && d.Bs == 128 && 4 * (int64_t)d.T < d.NBk;
-    while (alike && !few && kv_bytes <= 32 << 20 && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
+    const bool spread = kv_bytes <= 32 << 20 || d.n_dense > 0;
+    while (alike && !few && spread && width > 1 && heads % (16 / width) == 0 && (16 / width) * kv_bytes <= 128 << 20) width >>= 1;
     r.width_log2 = __builtin_ctz(width);
     r.piece_log2 = 0;
     while ((GH << r.piece_log2) < slots) ++r.piece_log2;

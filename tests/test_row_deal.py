@@ -126,6 +126,9 @@ def test_heads_side_by_side_fit_the_cache_and_every_xcd_serves_them_alike(deal, 
         assert side == 1                                   # 98304 tokens 12.16 ms, with two heads side by side 12.28
     elif (B * Hkv) % (2 * side) == 0 and side < 8:
         assert 2 * side * S * D * 4 > 128 << 20
+    if (B * Hkv) % 2 == 0 and 32 << 20 < S * D * 4 <= 64 << 20:    # a Tri-shape strip: two heads, 131072 tokens 8.73 -> 8.08 ms
+        _, wg = deal(batch=B, n_q_heads=G * Hkv, n_kv_heads=Hkv, seq_len=S, head_dim=D, block_size=Bs, n_dense_q_blocks=8)
+        assert len(set(wg[:in_flight, 0])) - (wg[:in_flight, 0].min() < 0) == 2
     rows = np.zeros((8, B * Hkv), dtype=np.int64)
     for x in range(8):
         served = wg[x::8, 0]
