@@ -134,11 +134,7 @@ int select_launches(Dims d, const spa_params* p, const void* q, const void* k, c
     if (small_call(d, rank_by_values))
         return launch_code(launch_score_small(d, q, strides_of(p->q_stride), k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride),
                                               vt_or_null, k_rows, head_pattern, block_idx, block_cnt, pooled_scores_or_null, st));
-    Dims lists = d;                                       // one list per KV head: selected as if the KV heads were the query heads
-    if (d.shared) {
-        lists.Hq = d.Hkv;
-        lists.G = 1;
-    }
+    const Dims lists = list_dims(d);
     const int group = d.shared ? d.G : 1;
     float* const qp = group > 1 && !group_pooled_in_kernel(lists) ? sc.qp : nullptr;
     if (with_v && launch_prepare_kv(d, q, strides_of(p->q_stride), qp, k, strides_of(p->k_stride), v_or_null, strides_of(p->v_stride), kp, key_layout(lists), vt_or_null, lvn, st) != hipSuccess)

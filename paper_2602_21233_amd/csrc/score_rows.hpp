@@ -4,7 +4,16 @@
 
 namespace spa {
 
-// 4, 8 or 16; 16 with more than 1024 key blocks is the kernel that scores the columns in two chunks.  Fewer rows as rows get longer: up
+// What the score kernel selects for a call: with one list per KV head as if the KV heads were the query heads; shared: several heads share one
+inline Dims list_dims(Dims d) {
+    if (!d.shared) return d;
+    d.shared = d.G > 1;
+    d.Hq = d.Hkv;
+    d.G = 1;
+    return d;
+}
+
+// Rows per workgroup for the lists d (list_dims): 4, 8 or 16; 16 with more than 1024 key blocks is the kernel that scores the columns in two chunks.  Fewer rows as rows get longer: up
 // to 1024 blocks R * (NB padded) fp32 scores stay within 66 KB of LDS, so that two 8-wave workgroups share a CU (measured at
 // 131072 tokens: 125 -> 106 us against 32 rows with one 8-wave workgroup per CU).
 inline int score_rows(const Dims& d) {
@@ -15,8 +24,8 @@ inline int score_rows(const Dims& d) {
     // pool, score and select 8 or 16 rows one after the other.  Up to 1024 rows, where 8 per workgroup give half of the
     // CUs one; 1.05 to 1.1 times the time of 8 from 2048 rows on.  Whole select calls, 32 heads: 2048 queries over 29952
     // tokens 25.9 -> 23.1 us, over 98304 tokens 67 -> 53 (34 of them pool K), over 131072 tokens 85 -> 67.
-    // Lists shared by a KV group, whose workgroups stream the queries of all heads of the group: up to 2048 rows (32768 tokens
-    // of 8 KV heads 67 -> 56 us).
+    // Lists shared by several heads, whose workgroups stream the queries of all of them: up to 2048 rows (2040 rows, 8 against 4 per
+    // workgroup: 32/8 heads 63.3 and 56.7 us, 16/8 40.6 and 38.4, 40/8 74.9 and 66.0; 1400 rows 45.1 and 44.9, 29.0 and 30.2, 52.8 and 52.2).
     // (A mass budget keeps the larger groups: its second search makes the kernels twice as many, for rare calls.)
     if (plain && rows <= (d.shared ? 2048 : 1024)) return 4;
     // up to 512 blocks: 8 rows per workgroup give the chip more rounds of workgroups, so that one round's

@@ -9,16 +9,13 @@ from test_gpu_dispatch import SCORE_KERNELS, SCORE_OPTIONS, score_case
 
 SHIM = r"""
 #include "score_rows.hpp"
-extern "C" int score_rows(const spa_params* p, int mass) {
+static spa::Dims lists_of(const spa_params* p, int mass) {
     spa::Dims d = spa::dims_of(*p);
     d.gamma_q16 = mass ? 1 : -1;
-    return spa::score_rows(d);
+    return spa::list_dims(d);
 }
-extern "C" int sixteen_row_tiles(const spa_params* p, int mass) {
-    spa::Dims d = spa::dims_of(*p);
-    d.gamma_q16 = mass ? 1 : -1;
-    return spa::key_layout(d) == spa::kKeyTiles16;
-}
+extern "C" int score_rows(const spa_params* p, int mass) { return spa::score_rows(lists_of(p, mass)); }
+extern "C" int sixteen_row_tiles(const spa_params* p, int mass) { return spa::key_layout(lists_of(p, mass)) == spa::kKeyTiles16; }
 """
 
 
@@ -26,9 +23,11 @@ extern "C" int sixteen_row_tiles(const spa_params* p, int mass) {
 def rows_of(tmp_path_factory):
     lib = compile_shim(tmp_path_factory.mktemp("score_rows"), SHIM)
 
-    def ask(NB, NBk, heads, Bs=64, D=128, mass=False, what="score_rows"):
-        p = binding.make_params(batch=1, n_q_heads=heads, n_kv_heads=1, seq_len=NB * Bs - 3, head_dim=D, block_size=Bs, n_sink_blocks=1,
-                                n_local_blocks=4, top_k_blocks=64, kv_prefix_len=(NBk - NB) * Bs)
+    def ask(NB, NBk, heads, Bs=64, D=128, mass=False, what="score_rows", group=None):
+        """heads: lists; group: query heads that share one (None: a list for each)"""
+        p = binding.make_params(batch=1, n_q_heads=heads * (group or 1), n_kv_heads=heads if group else 1, seq_len=NB * Bs - 3, head_dim=D,
+                                block_size=Bs, n_sink_blocks=1, n_local_blocks=4, top_k_blocks=64, kv_prefix_len=(NBk - NB) * Bs,
+                                lists_per_kv_head=group is not None)
         return getattr(lib, what)(ctypes.byref(p), int(mass))
     return ask
 
@@ -61,6 +60,14 @@ def test_fewer_rows_where_they_are_faster(rows_of, NB, NBk, heads, Bs, D, want):
 
 def test_a_mass_budget_keeps_its_groups(rows_of):
     assert [rows_of(8, n, 4, mass=True) for n in (64, 256, 512, 513, 1024, 1025, 2048, 2049, 4096)] == [8, 8, 8, 16, 16, 8, 8, 4, 4]
+
+
+# Lists shared by several heads keep 4 rows up to 2048 rows; a list of one head is a list like any other (32 heads, 1400 rows over 32768 tokens
+# and their own, 71.5 us with 8, 73.4 with 4).
+@pytest.mark.parametrize("rows,group,want", [(1024, 1, 4), (1032, 1, 8), (2040, 1, 8), (1032, 2, 4), (2048, 2, 4), (2048, 4, 4), (2056, 4, 8)])
+def test_four_rows_for_more_lists_only_where_heads_share_them(rows_of, rows, group, want):
+    assert rows_of(rows // 8, rows // 8, 8, Bs=128, group=group) == want
+    assert rows_of(rows // 8, rows // 8, 8, Bs=128) == (4 if rows <= 1024 else 8)
 
 
 # 16-row products, and the pooled K laid out for them, are for 16 rows of head_dim 128: 4 or 8 rows lose 1 to 2.5 % to them or to their
