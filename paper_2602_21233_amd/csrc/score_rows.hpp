@@ -80,14 +80,14 @@ inline bool small_call(const Dims& d, bool rank_by_values) {
     return d.gamma_q16 < 0 && !d.shared && !rank_by_values && (int64_t)d.Skv * d.D * 2 <= 96 << 10 && score_rows(d) == 4;
 }
 
-// Lists shared by a KV group (d: with the KV heads as heads): do the workgroups of the score kernel pool the queries of all heads of
-// the group themselves?  Each streams as many blocks as it has rows times the heads of a group, 50 to 60 GB/s for a workgroup, so it
-// takes enough of them.  With 79 to 256 workgroups the pooling launch of K does it faster: select calls of 20000 tokens, 16/2
-// heads, 33 us in the kernel, 22 that way; 4096 tokens 18.8 and 15.5; 16384 tokens, head_dim 64, 18.8 and 18.1; 1000 tokens
-// (fused) 45 and 39.  With 392 and more the kernel: 50000 tokens with a mass budget 91.8 against 99.1, 32768 tokens 56 against 63.
+// Lists shared by several heads: do the workgroups of the score kernel pool the queries of all of them themselves?  Each streams as
+// many blocks as it has rows times the heads of a group, 50 to 60 GB/s for a workgroup, so it takes enough of them: 352, with
+// head_dim 64, whose blocks are half as long, 384.  Select calls, pooled beforehand with K against in the kernel, 32/8 heads: 38000 tokens (304 workgroups) 74.0 and
+// 78.3 us, 40000 (320) 77.7 and 80.6, 42000 (336) 81.3 and 82.5, 44000 (344) 85.1 and 84.3, 46000 (360) 88.7 and 86.5, 50000 (392) 95.8 and 89.4, with 4 rows
+// 22000 (344) 43.4 and 44.5, 26000 (408) 51.3 and 48.5; head_dim 64, 40000 40.4 and 42.8, 48000 (376) 46.4 and 47.2, 50000 (392) 48.8 and 48.0.
 inline bool group_pooled_in_kernel(const Dims& d) {
     const int R = score_rows(d);
-    return (int64_t)d.B * d.Hq * ((d.NB + R - 1) / R) >= 320;
+    return (int64_t)d.B * d.Hq * ((d.NB + R - 1) / R) >= (d.D == 64 ? 384 : 352);
 }
 
 }  // namespace spa

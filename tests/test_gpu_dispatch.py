@@ -232,8 +232,8 @@ def test_values_behind_a_wavefronts_queries_take_no_part(spa, D, Bs, shared, NB)
         assert torch.equal(spa.attn_vt(q, k, vt, idx, cnt, Bs, pattern=pattern, group_shared=shared)[:, :, :end], want[:, :, :end])
 
 
-# Lists shared by a KV group: the queries of the group's heads are pooled and averaged by the score kernel itself (320 workgroups
-# and more) or pooled with K and averaged by the score kernel, from a call with V (fused) or without (select).  Either way a row ranks the
+# Lists shared by a KV group: the queries of the group's heads are pooled and averaged by the score kernel itself (352 workgroups
+# and more, 384 with head_dim 64) or pooled with K and averaged by the score kernel, from a call with V (fused) or without (select).  Either way a row ranks the
 # mean of its heads' block means: scores against fp64 (rtol 1e-4, atol 1e-5: fp32 sums of 128 products of magnitude <= 1), lists
 # and counts as the rule gives on those scores.
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,Bs,P,ragged", [
@@ -241,8 +241,10 @@ def test_values_behind_a_wavefronts_queries_take_no_part(spa, D, Bs, shared, NB)
     (2, 6, 2, 64 * 9 + 1, 128, 64, 64 * 40, True),   # a last block of one token, empty blocks
     (1, 10, 2, 128 * 33 + 77, 128, 128, 0, False),   # groups of five
     (4, 16, 8, 128 * 39 + 5, 64, 128, 0, False),     # 4 x 8 x 10 workgroups of 4 rows: 320
+    (4, 16, 8, 128 * 47 + 5, 64, 128, 0, False),     # 4 x 8 x 12: 384
     (4, 24, 8, 64 * 42 - 1, 128, 64, 64 * 300, True),    # groups of three, 352 workgroups, longer rows
     (8, 16, 8, 64 * 39, 64, 64, 0, False),           # 8 rows a workgroup, 320 of them
+    (8, 16, 8, 64 * 47, 64, 64, 0, False),           # 384
 ])
 def test_group_means_of_pooled_queries(spa, B, Hq, Hkv, S, D, Bs, P, ragged):
     _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, True)

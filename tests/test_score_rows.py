@@ -15,6 +15,7 @@ static spa::Dims lists_of(const spa_params* p, int mass) {
     return spa::list_dims(d);
 }
 extern "C" int score_rows(const spa_params* p, int mass) { return spa::score_rows(lists_of(p, mass)); }
+extern "C" int pooled_in_kernel(const spa_params* p, int mass) { return spa::group_pooled_in_kernel(lists_of(p, mass)); }
 extern "C" int sixteen_row_tiles(const spa_params* p, int mass) { return spa::key_layout(lists_of(p, mass)) == spa::kKeyTiles16; }
 """
 
@@ -68,6 +69,14 @@ def test_a_mass_budget_keeps_its_groups(rows_of):
 def test_four_rows_for_more_lists_only_where_heads_share_them(rows_of, rows, group, want):
     assert rows_of(rows // 8, rows // 8, 8, Bs=128, group=group) == want
     assert rows_of(rows // 8, rows // 8, 8, Bs=128) == (4 if rows <= 1024 else 8)
+
+
+# Queries of a group are pooled by the score kernel from 352 workgroups on (384 with head_dim 64), with K below (40000 tokens of 8 KV
+# heads, 320 workgroups, 77.7 us, 80.6 in the kernel; 46000, 360 workgroups, 88.7 and 86.5).
+@pytest.mark.parametrize("NB,heads,D,want", [(313, 8, 128, False), (344, 8, 128, False), (345, 8, 128, True), (172, 8, 128, False), (173, 8, 128, True),
+                                             (345, 8, 64, False), (376, 8, 64, False), (377, 8, 64, True), (192, 8, 64, True), (16, 1, 128, False), (1250, 2, 128, False)])
+def test_group_means_in_the_score_kernel_where_its_workgroups_fill_the_chip(rows_of, NB, heads, D, want):
+    assert bool(rows_of(NB, NB, heads, Bs=128, D=D, what="pooled_in_kernel", group=4)) == want
 
 
 # 16-row products, and the pooled K laid out for them, are for 16 rows of head_dim 128: 4 or 8 rows lose 1 to 2.5 % to them or to their
