@@ -72,12 +72,16 @@ constexpr bool sixteen_row_products(int D, int R) { return D == 128 && R == 16; 
 inline KeyLayout key_layout(const Dims& d) { return sixteen_row_products(d.D, score_rows(d)) ? kKeyTiles16 : kKeyTiles32; }
 
 // Does a call go through score_topk_small_kernel, one launch instead of two?  Where the launches are what it takes: the score workgroups
-// then pool all of the K they see, one after the other, which pays up to 96 KB of K a head.  Fused calls, 32/8 heads: 300
-// tokens with head_dim 64 (38 KB) 19.4 -> 16.5 us, 300 with head_dim 128 (77 KB) 20.9 -> 20.3, 512 with head_dim 64 19.1 -> 18.3; but 777
-// with head_dim 64 (99 KB) 21.8 -> 22.9, 512 with head_dim 128, blocks of 64 (131 KB), 20.8 -> 22.1, 1024 (262 KB) 30.9 -> 34.4.
-// (At most 12 key blocks then: they are one tile.)  Not with a mass budget, shared lists or the output-aware score, whose kernels it would double.
+// then pool all of the K they see, two blocks at a time, one round after the other, which pays up to 64 KB of K a head, and to 96 KB in two
+// rounds (4 blocks).  Two launches against one, calls in a row, fused: 300 tokens of 32/8 heads with head_dim 64 (3 blocks) 19.9 and 17.5 us, 384 with
+// head_dim 128 (3 blocks, 96 KB) 22.2 and 21.9, 512 with head_dim 64, blocks of 64 (8 blocks, 64 KB), 19.8 and 18.9, of one head 19.9 and 17.5; but 384 with
+// head_dim 128, blocks of 64 (6 blocks, 96 KB), 19.7 and 20.1, 640 with head_dim 64 (10 and 5 blocks, 80 KB) 20.0 and 21.2, 20.3 and 20.9.  Replayed from a graph, where a launch
+// costs less, the first four are 17.1 and 16.6, 21.8 and 21.4, 17.5 and 18.1, 16.8 and 17.1.  Selections alone 15.7 and 12.9 in a row; from a
+// graph 6.9 and 6.5 with 4 blocks of 64, 7.4 and 7.7 with 8, 8.1 and 8.7 with 2 of 128, head_dim 128.
+// (At most 8 key blocks then: they are one tile.)  Not with a mass budget, shared lists or the output-aware score, whose kernels it would double.
 inline bool small_call(const Dims& d, bool rank_by_values) {
-    return d.gamma_q16 < 0 && !d.shared && !rank_by_values && (int64_t)d.Skv * d.D * 2 <= 96 << 10 && score_rows(d) == 4;
+    const int64_t k_bytes = (int64_t)d.Skv * d.D * 2;
+    return d.gamma_q16 < 0 && !d.shared && !rank_by_values && (k_bytes <= 64 << 10 || (k_bytes <= 96 << 10 && d.NBk <= 4)) && score_rows(d) == 4;
 }
 
 // Lists shared by several heads: do the workgroups of the score kernel pool the queries of all of them themselves?  Each streams as

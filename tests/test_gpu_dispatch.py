@@ -280,11 +280,15 @@ def _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, shared, kw=None):
     assert torch.equal(again, idx) and torch.equal(n_again, cnt)
 
 
-# Calls of up to 96 KB of K a head: K pooled by the score workgroups, V transposed beside them, in one launch.
+# Calls of up to 64 KB of K a head (96 in 4 blocks): K pooled by the score workgroups, V transposed beside them, in one launch.
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,Bs,P,ragged,kw", [
     (1, 1, 1, 1, 64, 64, 0, False, {}),
     (1, 1, 1, 512, 64, 64, 0, False, {}),
-    (1, 4, 2, 768, 64, 64, 0, False, dict(stride_blocks=3)),     # the largest: 12 blocks
+    (1, 4, 2, 768, 64, 64, 0, False, dict(stride_blocks=3)),     # 12 blocks: two launches
+    (3, 4, 2, 511, 64, 64, 0, False, dict(stride_blocks=3)),     # the largest: 8 blocks
+    (1, 6, 2, 383, 128, 128, 0, False, {}),                      # 96 KB in 3 blocks
+    (2, 4, 2, 64, 64, 64, 64 * 7, True, {}),                     # a prefix, 8 blocks
+    (1, 4, 2, 257, 128, 64, 0, False, {}),                       # just above 64 KB in 5 blocks
     (2, 6, 2, 767, 64, 128, 0, False, {}),                       # groups of three, an odd number of blocks of V
     (3, 4, 1, 300, 128, 64, 0, True, {}),                        # lengths down to none
     (1, 8, 8, 129, 128, 128, 128, False, {}),                    # a prefix, a block of one token
