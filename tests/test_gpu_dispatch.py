@@ -20,6 +20,34 @@ def _normal(shape, seed):
     return torch.randn(shape, generator=g).to(torch.bfloat16).cuda()
 
 
+# A fused call may be captured after nothing but selections and attention calls: what a small call's kernel needs for V^T has been asked for by the
+# first selection.  (First of the tests that launch that kernel, so that none of them has asked for it.)
+@pytest.mark.parametrize("D,Bs,kw", [(128, 128, {}), (64, 64, dict(stride_blocks=3))])
+def test_a_small_fused_call_is_captured_after_selections(spa, D, Bs, kw):
+    from paper_2602_21233_amd import binding
+    S, ns, nl, k = 3 * Bs - 5, 1, 1, 1
+    q, kk, v = _normal((1, 4, S, D), 71), _normal((1, 2, S, D), 72), _normal((1, 2, S, D), 73)
+    idx, cnt = spa.select(q, kk, Bs, ns, nl, k, **kw)
+    want = spa.attn(q, kk, v, idx, cnt, Bs, pattern=(ns, nl, k, kw.get("stride_blocks", 0), 0))
+    p = binding.make_params(batch=1, n_q_heads=4, n_kv_heads=2, seq_len=S, head_dim=D, block_size=Bs, n_sink_blocks=ns, n_local_blocks=nl,
+                            top_k_blocks=k, q=q, k=kk, v=v, out=q, **kw)
+    ws = torch.empty(spa.workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(q)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        spa.fused(q, kk, v, Bs, ns, nl, k, workspace=ws, out=out, **kw)
+    for rep in range(3):
+        out.zero_()
+        ws.random_(0, 255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), rep
+        spa.fused(q.flip(2).contiguous(), kk, v, Bs, ns, nl, k, **kw)      # eager work between replays
+        torch.cuda.synchronize()
+
+
 def _random_lists(B, Hl, NB, off, T, most, seed):
     """Well-formed lists of T places: up to `most` blocks, some earlier ones, ascending, then the diagonal block."""
     g = torch.Generator().manual_seed(seed)
@@ -119,7 +147,8 @@ def test_rows_per_workgroup_of_the_score_kernel(spa, NB, Hq, P_blocks, D, kw):
                 assert torch.isneginf(got[n:]).all()
 
 
-# (rows per workgroup, key blocks) of a kernel -> a shape that takes it: query blocks, query heads, prefix blocks
+# (rows per workgroup, key blocks) of a kernel -> a shape that takes it: query blocks, lists (query heads, or KV heads where a group shares
+# one), prefix blocks
 SCORE_KERNELS = {
     (4, 256): (13, 16, 200), (4, 512): (13, 16, 470), (4, 1024): (13, 16, 990), (4, 2048): (13, 16, 1018),
     (8, 256): (37, 32, 200), (8, 512): (37, 32, 470), (8, 1024): (37, 32, 980), (8, 2048): (37, 32, 1000),
@@ -133,11 +162,14 @@ SCORE_OPTIONS = {
 
 
 def score_case(kernel, option):
-    """What the call looks like: batch, query heads, KV heads, query blocks, prefix blocks (as many rows whatever the option)."""
+    """What the call looks like: batch, query heads, KV heads, query blocks, prefix blocks (as many rows whatever the option, except that
+    lists shared by a group take 4 rows per workgroup up to 2048 rows)."""
     NB, heads, P = SCORE_KERNELS[kernel]
     o = SCORE_OPTIONS[option]
     B = 2 if o.get("ragged") else 1
     heads //= B
+    if o.get("group_shared") and kernel[0] == 8:
+        NB, P = 65, P - 28
     return (B, 2 * heads, heads, NB, P) if o.get("group_shared") else (B, heads, heads // 4, NB, P)
 
 
@@ -245,6 +277,10 @@ def test_values_behind_a_wavefronts_queries_take_no_part(spa, D, Bs, shared, NB)
     (4, 24, 8, 64 * 42 - 1, 128, 64, 64 * 300, True),    # groups of three, 352 workgroups, longer rows
     (8, 16, 8, 64 * 39, 64, 64, 0, False),           # 8 rows a workgroup, 320 of them
     (8, 16, 8, 64 * 47, 64, 64, 0, False),           # 384
+    (1, 64, 32, 64 * 89 - 3, 64, 64, 64 * 200, False),   # ... over 289 key blocks
+    (1, 96, 32, 64 * 90 - 7, 128, 64, 64 * 500, False),  # groups of three, 590
+    (1, 64, 32, 64 * 90, 128, 64, 64 * 1000, False),     # 1090
+    (1, 32, 16, 64 * 520 - 9, 128, 64, 0, False),        # 16 rows a workgroup, 528 of them
 ])
 def test_group_means_of_pooled_queries(spa, B, Hq, Hkv, S, D, Bs, P, ragged):
     _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, True)
@@ -288,7 +324,7 @@ def _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, shared, kw=None):
     (3, 4, 2, 511, 64, 64, 0, False, dict(stride_blocks=3)),     # the largest: 8 blocks
     (1, 6, 2, 383, 128, 128, 0, False, {}),                      # 96 KB in 3 blocks
     (2, 4, 2, 64, 64, 64, 64 * 7, True, {}),                     # a prefix, 8 blocks
-    (1, 4, 2, 257, 128, 64, 0, False, {}),                       # just above 64 KB in 5 blocks
+    (1, 4, 2, 513, 64, 64, 0, False, {}),                        # just above 64 KB, in 9 blocks
     (2, 6, 2, 767, 64, 128, 0, False, {}),                       # groups of three, an odd number of blocks of V
     (3, 4, 1, 300, 128, 64, 0, True, {}),                        # lengths down to none
     (1, 8, 8, 129, 128, 128, 128, False, {}),                    # a prefix, a block of one token
@@ -297,3 +333,17 @@ def _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, shared, kw=None):
 ])
 def test_small_calls(spa, B, Hq, Hkv, S, D, Bs, P, ragged, kw):
     _check_selection(spa, B, Hq, Hkv, S, D, Bs, P, ragged, False, kw)
+
+
+# ... with Q, K and V as views into one projection, each with strides of its own, tokens of other heads in between.
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,Bs", [(2, 4, 2, 200, 64, 64), (1, 4, 2, 511, 64, 64), (3, 2, 1, 383, 128, 128), (2, 6, 2, 191, 128, 64)])
+def test_small_calls_on_strided_views(spa, B, Hq, Hkv, S, D, Bs):
+    qkv = _normal((B, S, Hq + 3 * Hkv + 1, D), 81)
+    q, k, v = (qkv[:, :, i: i + n].permute(0, 2, 1, 3) for i, n in ((0, Hq), (Hq, Hkv), (Hq + 2 * Hkv + 1, Hkv)))
+    got = spa.fused(q, k, v, Bs, 1, 2, 1, return_lists=True)
+    want = spa.fused(q.contiguous(), k.contiguous(), v.contiguous(), Bs, 1, 2, 1, return_lists=True)
+    assert not v.is_contiguous() and v.stride() != k.contiguous().stride()
+    assert all(torch.equal(x, y) for x, y in zip(got, want))
+    idx, cnt = spa.select(q, k, Bs, 1, 2, 1)
+    assert torch.equal(idx, got[1]) and torch.equal(cnt, got[2])
+    assert torch.equal(got[0], spa.attn(q.contiguous(), k.contiguous(), v.contiguous(), idx, cnt, Bs, pattern=(1, 2, 1, 0, 0)))

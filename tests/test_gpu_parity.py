@@ -473,7 +473,7 @@ def test_select_rows_of_1025_to_2048_blocks(spa, oracle, NB, P_blocks, D, k, kw)
     kw = dict(kw)
     lens = kw.pop("ragged", None)
     B = 1 if lens is None else len(lens)
-    Hq, Hkv = 2, 1
+    Hq, Hkv = (4, 2) if kw.get("group_shared") else (2, 1)         # more than 2048 rows, or a shared list takes 4 per workgroup
     S, P = NB * Bs - 17, P_blocks * Bs                             # a partial last block as well
     g = torch.Generator().manual_seed(NB + k)
     q = torch.randn((B, Hq, S, D), generator=g).to(torch.bfloat16)

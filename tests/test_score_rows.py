@@ -103,6 +103,13 @@ def test_sixteen_row_tiles_only_where_sixteen_rows_of_head_dim_128_read_them(row
     assert rows_of(NB, NBk, heads, D=D, mass=mass, what="sixteen_row_tiles") == want
 
 
+# The GPU test of group means takes 8 and 16 rows per workgroup, pooled in the kernel, at every number of key registers.
+@pytest.mark.parametrize("NB,NBk,heads,group,Bs,D,rows", [(47, 47, 64, 2, 64, 64, 8), (89, 289, 32, 2, 64, 64, 8), (90, 590, 32, 3, 64, 128, 8), (90, 1090, 32, 2, 64, 128, 8),
+                                                          (520, 520, 16, 2, 64, 128, 16), (48, 48, 32, 2, 128, 64, 4), (42, 342, 32, 3, 64, 128, 4)])
+def test_the_shapes_of_the_gpu_test_of_group_means(rows_of, NB, NBk, heads, group, Bs, D, rows):
+    assert rows_of(NB, NBk, heads, Bs=Bs, D=D, group=group) == rows and rows_of(NB, NBk, heads, Bs=Bs, D=D, group=group, what="pooled_in_kernel")
+
+
 # The GPU test of every option on every score kernel takes the kernels that it names.
 @pytest.mark.parametrize("option", SCORE_OPTIONS)
 @pytest.mark.parametrize("kernel", SCORE_KERNELS)
@@ -111,4 +118,5 @@ def test_the_shapes_of_the_gpu_test_take_the_kernels_they_name(rows_of, kernel, 
     B, Hq, Hkv, NB, P = score_case(kernel, option)
     rows, blocks = kernel
     assert blocks // 2 < P + NB <= blocks
-    assert rows_of(NB, P + NB, B * (Hkv if SCORE_OPTIONS[option].get("group_shared") else Hq), D=D) == rows
+    shared = SCORE_OPTIONS[option].get("group_shared")
+    assert rows_of(NB, P + NB, B * (Hkv if shared else Hq), D=D, group=Hq // Hkv if shared else None) == rows
