@@ -205,7 +205,10 @@ int sparse_prefill_topk_from_scores(const spa_params *p, const float *pooled_sco
  * (sparse_prefill_check_lists counts the rows that break the rules).
  * Of p this call uses the shape, strides and scale; the pattern fields fix T and
  * serve as a hint of how uneven the rows are (a dense strip or strided columns
- * make the library deal the query blocks to the chip's partitions one by one).
+ * make the library deal the query blocks to the chip's partitions one by one).  They are taken to
+ * hold for every head and every row: lists made with budgets per head (up to 20 % where whole KV
+ * heads differ) or with a falling budget (up to 8 % in a short call) lose time here that
+ * sparse_prefill_fused_ex, which knows of the budgets, does not lose.
  * ws: spa_workspace_bytes() bytes of scratch, 256-byte aligned; its contents
  * need not survive between calls. */
 int sparse_prefill_attn(const spa_params *p, const void *q, const void *k, const void *v,

@@ -11,7 +11,7 @@
 //   Phase 0 - query pooling (step 1 for Q, in the kernel).  The workgroup streams its R
 //   query blocks from Q and pools them itself, so that the Q stream of the select stage
 //   (four fifths of its bytes) runs while other workgroups score and select; the split
-//   pooled queries go straight to LDS.  (Group-shared lists: the mean of the group's pooled
+//   pooled queries go straight to LDS.  (Lists shared by a group: the mean of its heads' pooled
 //   queries.)
 //   Phase 1 - scores on the matrix cores.  The fp32 pooled vectors are split
 //   into a bf16 head and a bf16 tail (x = hi + lo, |x - hi - lo| <= 2^-18 |x|)
@@ -1246,8 +1246,8 @@ __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs 
 
 // Small calls (small_call): one launch instead of prepare_kv_kernel (or pool_kernel) and the score kernel.  Every workgroup pools the K blocks
 // its rows can see itself, from L2, and the workgroups behind the first n_score transpose two blocks of V each.
-// Bound by launches and latency: 512 tokens of one head, head_dim 64, blocks of 64, 19.1 -> 16.3 us for the whole call (prepare_kv_kernel 2.9 us
-// and its launch away, 1.5 us more here).
+// Bound by launches and latency: 512 tokens of one head, head_dim 64, blocks of 64, 18.8 -> 16.1 us for the whole call.  The kernels take as long
+// as before (2.9 + 4.9 us, now 7.7): what goes is the launch.
 template <int D, bool EXT>
 __global__ __launch_bounds__(512, 4) void score_topk_small_kernel(ScoreArgs a, KeyArgs keys, int n_tiles, int n_score) {
     extern __shared__ __attribute__((aligned(128))) float S[];
