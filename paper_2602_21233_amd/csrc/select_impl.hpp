@@ -29,7 +29,8 @@
 //   digit into 256 LDS counters, a prefix sum over the lanes finds the bin of the wanted
 //   rank; a pass that takes its whole bin ends early).  Ties at the threshold are
 //   resolved by block index with a running prefix count, and static U top-k is written
-//   in ascending order from the keys in registers.  With a cumulative-mass budget a
+//   in ascending order from the keys in registers.  Longer rows whose static blocks are sinks and
+//   window alone first try a tighter bound that leaves a short list (take_best).  With a cumulative-mass budget a
 //   weighted variant of the same search first finds how many blocks the row may take.
 // topk_from_scores_kernel applies the same rule to caller-supplied scores (one
 // wavefront per row, keys in LDS).
@@ -234,6 +235,9 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 // different banks, with 32-row ones the two lane halves (4 words there take no measurably longer: 118.5 against 118.2 us at 65536 tokens)
 constexpr int row_pad(int D, int R) { return sixteen_row_products(D, R) ? 4 : 8; }
 
+// does the row's static pattern consist of sinks and window alone?
+__device__ __forceinline__ bool plain_row(const Pattern& pt, int i) { return pt.stride <= 0 && i < pt.NB - pt.n_dense; }
+
 // sum of v over the 64 lanes (DPP row reductions + row broadcasts), returned wave-uniform
 __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
@@ -354,6 +358,165 @@ __device__ __forceinline__ void find_threshold_hist(const uint32_t (&key)[MAXC],
     need_eq = want;
 }
 
+// the score a rank key came from (keys >= 2; -0 has become +0)
+__device__ __forceinline__ float score_of_key(uint32_t key) {
+    uint32_t u = key - 1u;
+    u = (u & 0x80000000u) ? (u ^ 0x80000000u) : ~u;
+    return __uint_as_float(u);
+}
+
+// v_max_f32 as it is: a NaN operand gives the other one.  (From C the compiler quiets every operand first, another instruction a score.)
+__device__ __forceinline__ float max_num(float x, float y) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+
+// A row of the plain A-shape by its few best candidates: the lists of the general way (rank keys of the whole row, find_threshold_hist, one
+// pass over the row to write it) for a third of the instructions.  x[m] is the score of block 64 m + lane; candidates are the blocks [c0, c1),
+// sinks those before, the local window those from c1 to i; kk candidates are wanted.
+//   1. Every lane keeps its two largest scores.  At least kk of these 128 values reach L, their kk-th largest to within 2^-10 of the span, and
+//      so do as many blocks; on scores without a pattern along the row about kk / 8 more of them do.
+//   2. The blocks that reach L go to a list in LDS, in block order.  Whatever L is, the kk best are among them if there are kk or more, as all
+//      others rank lower (NaN, which ranks lowest, never reaches L).
+//   3. The kk-th largest rank key of the list, by halves: a compare and a count of the ballot per 64 of them.  Ties go to the first in the list.
+// Returns false, with nothing written to memory, where that does not do: more than 128 wanted, sinks beyond the first 64 blocks, fewer than kk finite
+// scores in the lanes' pairs, or a list that would not fit (many equal scores).
+// What bounds it: instructions issued, with four wavefronts to a SIMD.  At 262144 tokens a workgroup of the general way spent 21 of its 63 us
+// here, 7 each on rank keys, search and writing.  Select calls, general way against this one: 262144 tokens of 40/8 heads 704 -> 630 us (with a
+// budget of 16 663 -> 582, of 127 714 -> 658), of 8 heads 225 -> 215, 2048 blocks of 64 402 -> 336, all scores equal 356 -> 315, 8192 queries
+// over 98304 tokens, blocks of 64, 86 -> 79, 131072 tokens 244 -> 236, head_dim 64 154 -> 143, with a dense strip 286 -> 275.
+// For rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows: with 8 a wavefront has one row, and the other workgroups' streams
+// hide it (131072 tokens of 8 heads 106.1 and 107.4, 98304 of 16 heads 86.6 and 88.6).  With 512 blocks it gives nothing (117.1 and 117.0 us at
+// 65536 tokens), with 256 the general way is a few instructions a score already (59.6 and 60.8 at 32768), and with 4096 the 64 scores of a lane
+// do not stay in registers (448 and 517).  Not for lists that heads share, where the query stream of all heads hides the selection (131072
+// tokens 210 and 212).
+template <int MAXC>
+__device__ __forceinline__ bool take_best(const float (&x)[MAXC], int i, int c0, int c1, int kk, int T, float2* list, int32_t* __restrict__ idx_row,
+                                          int32_t* __restrict__ cnt_out, int lane) {
+    constexpr int Q = MAXC / 4, LQ = Q == 4 ? 2 : 3;          // the row goes by quarters, so that a short one is not paid in full
+    static_assert(Q == 1 << LQ, "rows of 1024 or 2048 blocks");
+    constexpr int CAP = 512, NY = CAP / 64;                   // list entries: in the place of the row's scores, which are in x alone from here on
+    const int n = i + 1, n_cand = c1 - c0;
+    int n_list = 0;
+    uint32_t y[NY];                                           // rank keys of the list, 0 past its end
+    int yj[NY];                                               // and their blocks
+    uint32_t thr = 0u;
+    int need_eq = 0;
+    const bool all = kk == n_cand;                            // every block up to i
+    if (!all && kk > 0) {
+        if (kk > 128 || c0 > 64) return false;
+        const int q_last = (c1 - 1) >> (6 + LQ);              // quarter of the last candidate
+        float m1 = -INFINITY, m2 = -INFINITY;
+        // only in the first and the last quarter can a block not be a candidate
+        auto candidate = [&](int m, bool edge) {
+            return !edge || (uint32_t)((m << 6) + lane - c0) < (uint32_t)n_cand ? x[m] : -INFINITY;
+        };
+        static_for_sel<4>([&](auto q_tag) {
+            constexpr int q = decltype(q_tag)::value;
+            if (q > q_last) return;                           // wave-uniform, as are all branches here
+            auto quarter = [&](bool edge) {
+#pragma unroll
+                for (int m = q * Q; m < (q + 1) * Q; ++m) {
+                    const float v = candidate(m, edge);
+                    m2 = __builtin_amdgcn_fmed3f(m1, m2, v);
+                    m1 = max_num(m1, v);
+                }
+            };
+            if (q == 0 || q == q_last) quarter(true); else quarter(false);
+        });
+        const uint32_t u1 = rank_key(m1), u2 = rank_key(m2);
+        const uint32_t H = wave_max_u32(u1), L0 = wave_min_u32(kk <= 64 ? u1 : u2);
+        uint32_t L = L0;                                      // kk or more of the 128 reach it
+        uint32_t over = H + 1u;                               // fewer than kk do
+#pragma nounroll
+        for (int step = 0; step < 10 && over - L > 1u; ++step) {
+            const uint32_t mid = L + ((over - L) >> 1);
+            const int c = __popcll(__ballot(u1 >= mid)) + __popcll(__ballot(u2 >= mid));
+            if (c >= kk) L = mid; else over = mid;
+            if (c == kk) break;
+        }
+        if (L <= rank_key(-INFINITY)) return false;           // what is no candidate must not reach it
+        const float Lf = score_of_key(L);
+        bool fits = true;
+        static_for_sel<4>([&](auto q_tag) {
+            constexpr int q = decltype(q_tag)::value;
+            if (q > q_last || !fits || (L == H && n_list >= kk)) return;      // of equal scores the first kk will do
+            auto quarter = [&](bool edge) {
+#pragma unroll
+                for (int m = q * Q; m < (q + 1) * Q; ++m) {
+                    const float v = candidate(m, edge);
+                    const bool in = v >= Lf;
+                    const uint64_t mask = __ballot(in);
+                    const int at = n_list;
+                    n_list += __popcll(mask);
+                    fits = n_list <= CAP;
+                    if (in && fits) list[at + lanes_below(mask, lane)] = make_float2(v, __int_as_float((m << 6) + lane));
+                }
+            };
+            if (q == 0 || q == q_last) quarter(true); else quarter(false);
+        });
+        if (!fits || n_list < kk) return false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        static_for_sel<NY>([&](auto t_tag) {
+            constexpr int t = decltype(t_tag)::value;
+            y[t] = 0u;
+            if (64 * t >= n_list) return;
+            const float2 e = list[64 * t + lane];
+            y[t] = 64 * t + lane < n_list ? rank_key(e.x) : 0u;
+            yj[t] = __float_as_int(e.y);
+        });
+        if (n_list > kk) {
+            auto count = [&](uint32_t at_least) {
+                int c = 0;
+                static_for_sel<NY>([&](auto t_tag) {
+                    constexpr int t = decltype(t_tag)::value;
+                    if (64 * t < n_list) c += __popcll(__ballot(y[t] >= at_least));
+                });
+                return c;
+            };
+            uint32_t lo = L, hi = H + 1u;                     // kk or more of the list reach lo, fewer hi
+            int c_lo = n_list;
+#pragma nounroll
+            while (hi - lo > 1u && c_lo != kk) {
+                const uint32_t mid = lo + ((hi - lo) >> 1);
+                const int c = count(mid);
+                if (c >= kk) { lo = mid; c_lo = c; } else hi = mid;
+            }
+            thr = lo - 1u;
+            if (c_lo != kk) { need_eq = kk - count(lo + 1u); thr = lo; }
+        }
+    }
+    // sinks, the chosen candidates, the window: ascending as they are
+    int out_pos;
+    if (all) {
+        for (int t = lane; t < n; t += 64) idx_row[t] = t;
+        out_pos = n;
+    } else {
+        for (int t = lane; t < c0; t += 64) idx_row[t] = t;
+        out_pos = c0;
+        if (kk > 0) {
+            int eq_seen = 0;
+            static_for_sel<NY>([&](auto t_tag) {
+                constexpr int t = decltype(t_tag)::value;
+                if (64 * t >= n_list) return;
+                const bool is_eq = need_eq > 0 && y[t] == thr;
+                const uint64_t eq_mask = __ballot(is_eq);
+                const bool take = y[t] > thr || (is_eq && eq_seen + lanes_below(eq_mask, lane) < need_eq);
+                const uint64_t take_mask = __ballot(take);
+                if (take) idx_row[out_pos + lanes_below(take_mask, lane)] = yj[t];
+                eq_seen += __popcll(eq_mask);
+                out_pos += __popcll(take_mask);
+            });
+        }
+        for (int t = lane; t < n - c1; t += 64) idx_row[out_pos + t] = c1 + t;
+        out_pos += n - c1;
+    }
+    for (int t = out_pos + lane; t < T; t += 64) idx_row[t] = -1;
+    if (lane == 0) *cnt_out = out_pos;
+    return true;
+}
+
 // ---- cumulative-mass budget (the rule of the FlexPrefill family, named among the dynamic algorithms
 // in Sec. 4.1.1 / "Other Sparse Attention Strategies" of Sec. 4.1.2; no formula in the paper) ----------
 // A row takes, in ranking order, the fewest candidates for which the selected blocks (static ones
@@ -380,13 +543,6 @@ __device__ __forceinline__ uint32_t mass_weight(float x, float m) {
     p = __fmaf_rn(p, f, 1.0f);
     const float w = ldexpf(p, (int)n);
     return (uint32_t)__fadd_rn(__fmul_rn(w, 524288.0f), 0.5f);
-}
-
-// the score a rank key came from (keys >= 2; -0 has become +0)
-__device__ __forceinline__ float score_of_key(uint32_t key) {
-    uint32_t u = key - 1u;
-    u = (u & 0x80000000u) ? (u ^ 0x80000000u) : ~u;
-    return __uint_as_float(u);
 }
 
 // Number of candidates the mass budget lets the query block at block position i take (before the
@@ -992,6 +1148,24 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
         // keys and static flags of the row's blocks stay in registers until the lists are written;
         // rows are causal: a row early in the sequence fills only its first chunks of 64 blocks
         const int chunks = (n + 63) >> 6;                 // wave-uniform
+        int k_i = row_budget(k_rows, iq, k);
+        const int64_t row = (int64_t)bh * NB + iq;
+        int32_t* idx_row = idx + row * T;
+        constexpr bool BEST = !MASS && !GROUP && (MAXC == 32 || (MAXC == 16 && R == 16));       // which rows: see take_best
+        float x[BEST ? MAXC : 1];
+        if constexpr (BEST) {
+            static_for_sel<4>([&](auto q_tag) {
+                constexpr int q = decltype(q_tag)::value, Q = MAXC / 4;
+                if (q * Q >= chunks) return;
+#pragma unroll
+                for (int m = q * Q; m < (q + 1) * Q; ++m) x[m] = srow[(m << 6) + lane];
+            });
+            if (!EXT || plain_row(pt, i)) {
+                const int c0 = pt.ns < n ? pt.ns : n, c1 = i - pt.nl + 1 > c0 ? i - pt.nl + 1 : c0;
+                const int kk = k_i < c1 - c0 ? k_i : c1 - c0;
+                if (take_best<MAXC>(x, i, c0, c1, kk, T, reinterpret_cast<float2*>(S + r * LD), idx_row, cnt + row, lane)) continue;
+            }
+        }
         uint32_t key[MAXC];
         uint64_t is_static_bits = 0ull;                   // bit m: block 64 m + lane is static
 #pragma unroll
@@ -1000,7 +1174,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
             if (m < chunks) {
                 const int j = (m << 6) + lane;            // < MAXC*64 <= LD: always inside the row
                 const bool st = j <= i && static_block<EXT>(pt, i, j);
-                const uint32_t kv = rank_key(srow[j]);    // columns past the computed tiles hold junk: masked next
+                const uint32_t kv = rank_key(BEST ? x[BEST ? m : 0] : srow[j]);    // columns past the computed tiles hold junk: masked next
                 key[m] = (j <= i && !st) ? kv : 0u;
                 is_static_bits |= st ? (1ull << m) : 0ull;
             }
@@ -1019,7 +1193,6 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
             int overlap = n_sink - first_local; if (overlap < 0) overlap = 0;
             n_cand = n - (n_sink + n_local - overlap);
         }
-        int k_i = row_budget(k_rows, iq, k);
         uint32_t* hist = reinterpret_cast<uint32_t*>(S + R * LD) + 256 * wave;
         if constexpr (MASS) {                             // the mass budget on top of the count budgets
             int k_m;                                      // rows of up to 2048 blocks: weights kept in registers
@@ -1039,8 +1212,6 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
         else find_threshold_hist<MAXC, MAXC>(key, kk, n_cand, hist, lane, thr, need_eq);
 
         // emit static U top-k in ascending block order
-        const int64_t row = (int64_t)bh * NB + iq;
-        int32_t* idx_row = idx + row * T;
         int eq_seen = 0, out_pos = 0;
 #pragma unroll
         for (int m = 0; m < MAXC; ++m) {
@@ -1168,6 +1339,11 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
             for (int m = CC; m < MAXC; ++m) x[m] = -INFINITY;
         }
         const int k_i = row_budget(a.k_rows, iq, k);
+        if (!GROUP && (!EXT || plain_row(pt, i))) {
+            const int c0 = pt.ns < n ? pt.ns : n, c1 = i - pt.nl + 1 > c0 ? i - pt.nl + 1 : c0;
+            const int kk = k_i < c1 - c0 ? k_i : c1 - c0;
+            if (take_best<MAXC>(x, i, c0, c1, kk, T, reinterpret_cast<float2*>(S + r * LD), idx_row, cnt + row, lane)) return;
+        }
         {
             uint32_t key[MAXC];
             uint64_t is_static_bits = 0ull;

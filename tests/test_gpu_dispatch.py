@@ -245,6 +245,25 @@ def test_options_on_every_score_kernel(spa, oracle, kernel, option, D):
                 assert torch.isneginf(sp[b, h, i, m:off + nb]).all()
 
 
+# Rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows, are selected from a list of the blocks that reach a bound, up to 128 of a budget, 64 sinks and 512 entries, and the
+# general way (the other kernels, too) past any of these.  Budgets and sinks on both sides; scores of `distinct` values (0: all different; 2: more equal ones than the
+# list holds; 1: all equal; 40: ties at the threshold inside a list).  The caller-score kernel, which keeps whole rows, is the reference.
+@pytest.mark.parametrize("kernel", [(4, 1024), (8, 1024), (8, 2048), (16, 1024), (16, 2048)], ids=lambda k: f"{k[0]}rows{k[1]}")
+@pytest.mark.parametrize("distinct", [0, 40, 2, 1])
+def test_lists_by_bound(spa, kernel, distinct):
+    NB, Hq, P = SCORE_KERNELS[kernel]
+    Hkv, D, Bs = Hq // 4, 64 if kernel[0] == 8 else 128, 64
+    q = _normal((1, Hq, NB * Bs, D), 71)
+    k = _normal((1, Hkv, (P + NB) * Bs, D), 72)
+    if distinct:
+        which = torch.randint(0, distinct, (P + NB,), generator=torch.Generator().manual_seed(73)).cuda()
+        k = k.view(1, Hkv, P + NB, Bs, D)[:, :, which].reshape(1, Hkv, -1, D).contiguous()
+    for ns, nl, topk in ((1, 4, 1), (0, 1, 64), (1, 4, 65), (64, 2, 127), (65, 2, 64), (3, 70, 128), (1, 4, 129), (2, 3, 0), (5, 9, P + NB - 20)):
+        idx, cnt, sp = spa.select(q, k, Bs, ns, nl, topk, return_scores=True)
+        want_idx, want_cnt = spa.topk_from_scores(sp, ns, nl, topk)
+        assert torch.equal(cnt, want_cnt) and torch.equal(idx, want_idx), (ns, nl, topk)
+
+
 # Chunks of the diagonal block that start behind a wavefront's last query (32 queries each) are left out: values there may be
 # anything, the wavefront's rows keep their bits.
 @pytest.mark.parametrize("D,Bs", [(128, 64), (64, 64), (128, 128), (64, 128)])
