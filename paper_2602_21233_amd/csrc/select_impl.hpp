@@ -1014,72 +1014,80 @@ __host__ __device__ constexpr int key_tile_at() {
     return R * LD + NWV * 256 + 2 * (NWV / 4) * (256 / (D / 8)) * D;
 }
 
-// Means of the key blocks 0 .. n_blk - 1 (n_blk <= 32; kh: the head's first token, Skv tokens) to an operand tile in LDS, in
-// the layout and with the arithmetic of the pooling kernel (pool.hip).  Two groups of 256 threads take the blocks in turn, two in flight
-// each; all loads are unconditional, tokens past the end re-read the last one and count 0.  Ends with a barrier.
+// Means of the key blocks 0 .. n_blk - 1 (kh: the head's first token, Skv tokens) to an operand tile in LDS, in the layout and with the
+// arithmetic of the pooling kernel (pool.hip).  Two groups of 256 threads take the blocks in turn.  What bounds it is latency, so load() asks
+// for all of them at once, before the queries are pooled (up to 128 KB of K in 64 registers a lane), and reduce() finds them there: two blocks
+// in flight behind the queries took 3.1 us of a workgroup's 6.7 at 512 tokens, head_dim 64, blocks of 64.
+// All loads are unconditional within a block, tokens past the end re-read the last one and count 0.
 template <int D, int BS, int NWV>
-__device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t, int n_blk, int Skv, float* part_base, __bf16* tile) {
-    constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, NGRP = NWV / 4;
-    const int t = threadIdx.x, grp = t >> 8, t256 = t & 255, prow = t256 / TPR, chunk = t256 % TPR;
-    typedef float (*Part)[D];
-    Part const part = reinterpret_cast<Part>(part_base) + grp * 2 * RPP;
-    uint4 raw[2][PASSES];
-    auto block_of = [&](int x) { const int j = x * NGRP + grp; return j < n_blk ? j : n_blk - 1; };
-    auto load = [&](auto slot_tag, int x) {
-        constexpr int SLOT = decltype(slot_tag)::value;
-        const int j = block_of(x), last = Skv - 1 - j * BS;
+struct StagedKeys {
+    static constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, NGRP = NWV / 4, SLOTS = 16 / PASSES;
+    static_assert(SLOTS % 2 == 0, "reduced in pairs");
+    static constexpr int kMostBlocks = SLOTS * NGRP;
+    uint4 raw[SLOTS][PASSES];
+
+    __device__ __forceinline__ void load(const uint16_t* kh, int64_t stride_t, int n_blk, int Skv) {
+        const int grp = threadIdx.x >> 8, t256 = threadIdx.x & 255, prow = t256 / TPR, chunk = t256 % TPR;
+        static_for_sel<SLOTS>([&](auto s_tag) {
+            constexpr int s = decltype(s_tag)::value;
+            if (s * NGRP >= n_blk) return;                    // workgroup-uniform
+            const int j = s * NGRP + grp < n_blk ? s * NGRP + grp : n_blk - 1, last = Skv - 1 - j * BS;
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-            const int row = p * RPP + prow < last ? p * RPP + prow : last;
-            raw[SLOT][p] = *reinterpret_cast<const uint4*>(kh + (int64_t)(j * BS + row) * stride_t + chunk * 8);
-        }
-    };
-    auto reduce = [&](auto slot_tag, int x) {
-        constexpr int SLOT = decltype(slot_tag)::value;
-        const int j = block_of(x), n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-            const uint32_t keep = p * RPP + prow < n_valid ? 0xffffffffu : 0u;
-            const uint4 w = make_uint4(raw[SLOT][p].x & keep, raw[SLOT][p].y & keep, raw[SLOT][p].z & keep, raw[SLOT][p].w & keep);
-            acc[0] += bf16_lo(w.x); acc[1] += bf16_hi(w.x);
-            acc[2] += bf16_lo(w.y); acc[3] += bf16_hi(w.y);
-            acc[4] += bf16_lo(w.z); acc[5] += bf16_hi(w.z);
-            acc[6] += bf16_lo(w.w); acc[7] += bf16_hi(w.w);
-        }
-        Part const buf = part + SLOT * RPP;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) buf[prow][chunk * 8 + e] = acc[e];
-        load(slot_tag, x + 2);
-        __syncthreads();
-        if (t256 < D && x * NGRP + grp < n_blk) {
-            float sum = 0.f;
-#pragma unroll
-            for (int r = 0; r < RPP; ++r) sum += buf[r][t256];
-            float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
-            asm("" : "+v"(mean));                         // rounded before it is split, as in the pooling kernel
-            const __bf16 hi = (__bf16)mean;
-            const int at = key_tile_offset(kKeyTiles32, t256, j);
-            tile[at] = hi;
-            tile[at + key_tail(kKeyTiles32)] = (__bf16)(mean - (float)hi);
-        }
-    };
-    load(IC_sel<0>{}, 0);
-    load(IC_sel<1>{}, 1);
-    const int n = (n_blk + NGRP - 1) / NGRP;
-#pragma nounroll
-    for (int x = 0; x < n; x += 2) {                      // the same number of rounds for both groups
-        reduce(IC_sel<0>{}, x);
-        reduce(IC_sel<1>{}, x + 1);
+            for (int p = 0; p < PASSES; ++p) {
+                const int row = p * RPP + prow < last ? p * RPP + prow : last;
+                raw[s][p] = *reinterpret_cast<const uint4*>(kh + (int64_t)(j * BS + row) * stride_t + chunk * 8);
+            }
+        });
     }
-    __syncthreads();
-}
+    // part_base: 2 * NGRP * RPP * D words of LDS.  Ends with a barrier.
+    __device__ __forceinline__ void reduce(int n_blk, int Skv, float* part_base, __bf16* tile) {
+        const int grp = threadIdx.x >> 8, t256 = threadIdx.x & 255, prow = t256 / TPR, chunk = t256 % TPR;
+        typedef float (*Part)[D];
+        Part const part = reinterpret_cast<Part>(part_base) + grp * 2 * RPP;
+        static_for_sel<SLOTS / 2>([&](auto pair_tag) {
+            constexpr int s0 = 2 * decltype(pair_tag)::value;
+            if (s0 * NGRP >= n_blk) return;
+            static_for_sel<2>([&](auto o_tag) {               // partial sums of the pair's token rows
+                constexpr int s = s0 + decltype(o_tag)::value;
+                if (s * NGRP >= n_blk) return;
+                const int j = s * NGRP + grp < n_blk ? s * NGRP + grp : n_blk - 1, n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
+                float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int p = 0; p < PASSES; ++p) {
+                    const uint32_t keep = p * RPP + prow < n_valid ? 0xffffffffu : 0u;
+                    const uint4 w = make_uint4(raw[s][p].x & keep, raw[s][p].y & keep, raw[s][p].z & keep, raw[s][p].w & keep);
+                    acc[0] += bf16_lo(w.x); acc[1] += bf16_hi(w.x);
+                    acc[2] += bf16_lo(w.y); acc[3] += bf16_hi(w.y);
+                    acc[4] += bf16_lo(w.z); acc[5] += bf16_hi(w.z);
+                    acc[6] += bf16_lo(w.w); acc[7] += bf16_hi(w.w);
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) part[(s - s0) * RPP + prow][chunk * 8 + e] = acc[e];
+            });
+            __syncthreads();
+            const int s = s0 + t256 / D, d = t256 % D, j = s * NGRP + grp;   // threads 0 .. D - 1 the first block's columns, D .. 2 D - 1 the second's
+            if (t256 < 2 * D && j < n_blk) {
+                const int n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
+                float sum = 0.f;
+#pragma unroll
+                for (int r = 0; r < RPP; ++r) sum += part[(s - s0) * RPP + r][d];
+                float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
+                asm("" : "+v"(mean));                         // rounded before it is split, as in the pooling kernel
+                const __bf16 hi = (__bf16)mean;
+                const int at = key_tile_offset(kKeyTiles32, d, j);
+                tile[at] = hi;
+                tile[at + key_tail(kKeyTiles32)] = (__bf16)(mean - (float)hi);
+            }
+            __syncthreads();
+        });
+    }
+};
 
 // Scores, top-k and merged lists of the query blocks i0 .. i0 + R - 1 of head bh = b * Hq + h, by a
 // 512-thread workgroup.  S: R * (MAXC * 64 + row_pad) floats of LDS for the scores, then 256 counters per
 // wavefront.  Ends without a barrier; the caller must not reuse S before one.
 // The split pooled queries are staged in LDS by stage_queries.
-template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, bool KIN = false>
+template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, int KIN = 0>
 __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S, const KeyArgs* keys = nullptr) {
     constexpr int LD = MAXC * 64 + row_pad(D, R);
     const float* __restrict__ kp = a.kp;
@@ -1103,20 +1111,22 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
     const int n_jt = ((i_last + off) >> 5) + 1;           // 32-wide key-block tiles with some causal j
 
     // ---- phase 0 / phase 1 ------------------------------------------------------------
-    stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
-    const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
-    if constexpr (KIN) {                                  // one tile, pooled by the workgroup itself
+    if constexpr (KIN > 0) {                              // one tile, pooled by the workgroup itself, KIN tokens a block
         constexpr int part_at = 2 * (NWV / 4) * (256 / (D / 8)) * D <= R * LD ? 0 : R * LD + NWV * 256;
         float* const tile = S + key_tile_at<D, R, LD, NWV>();
         const int Skv_b = keys->Skv - a.S + entry_len(a.seq_lens, b, a.S);
         const uint16_t* const kh = keys->k + b * keys->ks.b + (h / G) * keys->ks.h;
-        int n_blk = (Skv_b + a.Bs - 1) / a.Bs;            // the entry's blocks; causally visible ones
+        int n_blk = (Skv_b + KIN - 1) / KIN;              // the entry's blocks; causally visible ones
         n_blk = n_blk < i_last + off + 1 ? n_blk : i_last + off + 1;
-        if (n_blk <= 0) {                                 // an empty entry: its rows get empty lists
-        } else if (a.Bs == 128) stage_keys<D, 128, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
-        else stage_keys<D, 64, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
+        StagedKeys<D, KIN, NWV> staged;                   // an empty entry has no blocks: its rows get empty lists
+        staged.load(kh, keys->ks.t, n_blk, Skv_b);
+        stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
+        staged.reduce(n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
         kbase = tile;
+    } else {
+        stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
     }
+    const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
     score_tiles<D, R, LD, D / 16, NWV>(a, kbase, qlds, S, 0, wave, n_jt, bh, i0, lvbase);
     if (scores_out != nullptr) {                          // key blocks past the last computed tile
         const int j_first = 32 * n_jt;
@@ -1422,29 +1432,29 @@ __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs 
 
 // Small calls (small_call): one launch instead of prepare_kv_kernel (or pool_kernel) and the score kernel.  Every workgroup pools the K blocks
 // its rows can see itself, from L2, and the workgroups behind the first n_score transpose two blocks of V each.
-// Bound by launches and latency: 512 tokens of one head, head_dim 64, blocks of 64, 18.8 -> 16.1 us for the whole call.  The kernels take as long
-// as before (2.9 + 4.9 us, now 7.7): what goes is the launch.
-template <int D, bool EXT>
-__global__ __launch_bounds__(512, 4) void score_topk_small_kernel(ScoreArgs a, KeyArgs keys, int n_tiles, int n_score) {
+// Bound by launches and latency.  Against two launches 512 tokens of one head, head_dim 64, blocks of 64, took 16.8 us instead of 18.8; with all of
+// K asked for before the queries 16.2 (replayed from a graph 16.3 -> 15.3; 300 tokens of 32/8 heads 15.4 -> 14.6, 384 tokens with head_dim 128,
+// blocks of 128, 21.3 -> 20.4).  One workgroup's wavefronts on a SIMD are two, so it may have 256 registers.
+template <int D, int BS, bool EXT>
+__global__ __launch_bounds__(512, 2) void score_topk_small_kernel(ScoreArgs a, KeyArgs keys, int n_tiles, int n_score) {
     extern __shared__ __attribute__((aligned(128))) float S[];
     constexpr int R = 4, NWV = 8;
     const int wg = blockIdx.x;
     if (wg < n_score) {
-        score_topk_rows<D, R, 4, EXT, false, NWV, false, true>(a, wg / n_tiles, (n_tiles - 1 - wg % n_tiles) * R, S, &keys);
+        score_topk_rows<D, R, 4, EXT, false, NWV, false, BS>(a, wg / n_tiles, (n_tiles - 1 - wg % n_tiles) * R, S, &keys);
         return;
     }
     const int half = threadIdx.x >> 8, x = 2 * (wg - n_score) + half;        // block of V
     const int hy = x / a.NBk, blk = x % a.NBk;
     const int b = hy / keys.Hkv, h = hy % keys.Hkv;
     const int Sb = hy < keys.n_heads ? keys.Skv - a.S + entry_len(a.seq_lens, b, a.S) : 0;
-    int n_valid = Sb - blk * a.Bs;
-    n_valid = n_valid < 0 ? 0 : (n_valid > a.Bs ? a.Bs : n_valid);
-    const uint16_t* src = keys.v + (n_valid > 0 ? b * keys.vs.b + h * keys.vs.h + (int64_t)blk * a.Bs * keys.vs.t : 0);
-    uint16_t* dst = keys.vt + (int64_t)x * D * a.Bs;
-    uint16_t* tile = reinterpret_cast<uint16_t*>(S) + half * (a.Bs * (D + 2));
+    int n_valid = Sb - blk * BS;
+    n_valid = n_valid < 0 ? 0 : (n_valid > BS ? BS : n_valid);
+    const uint16_t* src = keys.v + (n_valid > 0 ? b * keys.vs.b + h * keys.vs.h + (int64_t)blk * BS * keys.vs.t : 0);
+    uint16_t* dst = keys.vt + (int64_t)x * D * BS;
+    uint16_t* tile = reinterpret_cast<uint16_t*>(S) + half * (BS * (D + 2));
     const int tid = threadIdx.x & 255;
-    if (a.Bs == 128) value_block<D, 128, true, false>(tid, src, keys.vs.t, n_valid, tile, nullptr, dst, keys.halves, nullptr);
-    else value_block<D, 64, true, false>(tid, src, keys.vs.t, n_valid, tile, nullptr, dst, keys.halves, nullptr);
+    value_block<D, BS, true, false>(tid, src, keys.vs.t, n_valid, tile, nullptr, dst, keys.halves, nullptr);
 }
 
 // Dynamic LDS above the default cap has to be requested per kernel and device.  That is done on the
@@ -1549,18 +1559,19 @@ hipError_t launch_plain(const ScoreCall& c) {
     return extended(c.d) ? launch_mfma_q<D, R, MAXC, true, false>(c) : launch_mfma_q<D, R, MAXC, false, false>(c);
 }
 
-template <int D, bool EXT>
+template <int D, int BS, bool EXT>
 hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
+    if (c.d.NBk > StagedKeys<D, BS, 8>::kMostBlocks) return hipErrorInvalidValue;
     constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + row_pad(D, 4), 8>() + 32 * D) * sizeof(float);
-    const size_t v_lds = keys.vt != nullptr ? 2 * c.d.Bs * (D + 2) * sizeof(uint16_t) : 0;
+    const size_t v_lds = keys.vt != nullptr ? 2 * BS * (D + 2) * sizeof(uint16_t) : 0;
     const size_t lds = v_lds > score_lds ? v_lds : score_lds;
     // asked for once, for the largest call: a fused call in a capture may follow selections that need less
-    constexpr size_t v_most = 2 * 128 * (D + 2) * sizeof(uint16_t);
-    hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, EXT>, v_most > score_lds ? v_most : score_lds);
+    constexpr size_t v_most = 2 * BS * (D + 2) * sizeof(uint16_t);
+    hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, BS, EXT>, v_most > score_lds ? v_most : score_lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + 3) / 4, n_score = n_tiles * c.d.B * c.d.Hq;
     const int n_v = keys.vt != nullptr ? (c.d.B * c.d.Hkv * c.d.NBk + 1) / 2 : 0;
-    hipLaunchKernelGGL((score_topk_small_kernel<D, EXT>), dim3((unsigned)(n_score + n_v)), dim3(512), lds, c.st, c.a, keys, n_tiles, n_score);
+    hipLaunchKernelGGL((score_topk_small_kernel<D, BS, EXT>), dim3((unsigned)(n_score + n_v)), dim3(512), lds, c.st, c.a, keys, n_tiles, n_score);
     return hipGetLastError();
 }
 
@@ -1585,7 +1596,9 @@ hipError_t SPA_CAT(launch_score_topk_d, SPA_SELECT_D)(SPA_SCORE_TOPK_ARGS) {
 hipError_t SPA_CAT(launch_score_small_d, SPA_SELECT_D)(SPA_SCORE_SMALL_ARGS) {
     const ScoreCall c{d, score_args(d, nullptr, k_rows, head_pattern, nullptr, idx, cnt, scores_or_null, q, qs, 1, nullptr), st};
     const KeyArgs keys{(const uint16_t*)k, ks, (const uint16_t*)v, vs, (uint16_t*)vt_or_null, d.Skv, d.Hkv, vt_in_halves(d) ? 1 : 0, d.B * d.Hkv};
-    return extended(d) ? launch_small_e<SPA_SELECT_D, true>(c, keys) : launch_small_e<SPA_SELECT_D, false>(c, keys);
+    const bool ext = extended(d);
+    if (d.Bs == 128) return ext ? launch_small_e<SPA_SELECT_D, 128, true>(c, keys) : launch_small_e<SPA_SELECT_D, 128, false>(c, keys);
+    return ext ? launch_small_e<SPA_SELECT_D, 64, true>(c, keys) : launch_small_e<SPA_SELECT_D, 64, false>(c, keys);
 }
 
 #else
