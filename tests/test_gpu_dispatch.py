@@ -264,6 +264,21 @@ def test_lists_by_bound(spa, kernel, distinct):
         assert torch.equal(cnt, want_cnt) and torch.equal(idx, want_idx), (ns, nl, topk)
 
 
+# A mass budget is not searched for where the count budget cannot reach it whatever the scores.  Equal scores weigh 2^19 each, the most there is:
+# the rows of one call then lie on both sides of that line and on it.  The caller-score kernel, which always searches, is the reference.
+@pytest.mark.parametrize("NB,Bs,D", [(200, 64, 64), (300, 64, 128), (600, 64, 128), (1100, 64, 64)])
+@pytest.mark.parametrize("equal", [True, False])
+def test_mass_budget_beyond_the_count_budget(spa, NB, Bs, D, equal):
+    q, k = _normal((1, 4, NB * Bs, D), 81), _normal((1, 2, NB * Bs, D), 82)
+    if equal:
+        k.zero_()
+    sched = (torch.arange(NB, dtype=torch.int32) % 90).cuda()
+    for topk, gamma, kw in ((1, 0.5, {}), (45, 0.25, {}), (89, 0.5, dict(top_k_per_block=sched)), (NB, 1.0, {}), (20, 0.5, dict(n_dense_q_blocks=3))):
+        idx, cnt, sp = spa.select(q, k, Bs, 1, 2, topk, return_scores=True, mass_gamma=gamma, **kw)
+        want_idx, want_cnt = spa.topk_from_scores(sp, 1, 2, topk, mass_gamma=gamma, **kw)
+        assert torch.equal(cnt, want_cnt) and torch.equal(idx, want_idx), (topk, gamma)
+
+
 # Chunks of the diagonal block that start behind a wavefront's last query (32 queries each) are left out: values there may be
 # anything, the wavefront's rows keep their bits.
 @pytest.mark.parametrize("D,Bs", [(128, 64), (64, 64), (128, 128), (64, 128)])
