@@ -1564,15 +1564,24 @@ hipError_t launch_plain(const ScoreCall& c) {
     return extended(c.d) ? launch_mfma_q<D, R, MAXC, true, false>(c) : launch_mfma_q<D, R, MAXC, false, false>(c);
 }
 
+// LDS of a small call's workgroups: those that score, those that transpose V
+template <int D>
+constexpr size_t small_score_lds() { return (key_tile_at<D, 4, 4 * 64 + row_pad(D, 4), 8>() + 32 * D) * sizeof(float); }
+template <int D, int BS>
+constexpr size_t small_v_lds() { return 2 * BS * (D + 2) * sizeof(uint16_t); }
+template <int D, int BS, bool EXT>
+hipError_t allow_small_lds() {
+    return allow_lds((const void*)score_topk_small_kernel<D, BS, EXT>, small_v_lds<D, BS>() > small_score_lds<D>() ? small_v_lds<D, BS>() : small_score_lds<D>());
+}
+
 template <int D, int BS, bool EXT>
 hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
     if (c.d.NBk > StagedKeys<D, BS, 8>::kMostBlocks) return hipErrorInvalidValue;
-    constexpr size_t score_lds = (key_tile_at<D, 4, 4 * 64 + row_pad(D, 4), 8>() + 32 * D) * sizeof(float);
-    const size_t v_lds = keys.vt != nullptr ? 2 * BS * (D + 2) * sizeof(uint16_t) : 0;
-    const size_t lds = v_lds > score_lds ? v_lds : score_lds;
-    // asked for once, for the largest call: a fused call in a capture may follow selections that need less
-    constexpr size_t v_most = 2 * BS * (D + 2) * sizeof(uint16_t);
-    hipError_t e = allow_lds((const void*)score_topk_small_kernel<D, BS, EXT>, v_most > score_lds ? v_most : score_lds);
+    const size_t v_lds = keys.vt != nullptr ? small_v_lds<D, BS>() : 0;
+    const size_t lds = v_lds > small_score_lds<D>() ? v_lds : small_score_lds<D>();
+    // asked for once, for the largest call and for both block sizes: a fused call in a capture may follow calls that need less, or another kernel
+    hipError_t e = allow_small_lds<D, 64, EXT>();
+    if (e == hipSuccess) e = allow_small_lds<D, 128, EXT>();
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + 3) / 4, n_score = n_tiles * c.d.B * c.d.Hq;
     const int n_v = keys.vt != nullptr ? (c.d.B * c.d.Hkv * c.d.NBk + 1) / 2 : 0;
