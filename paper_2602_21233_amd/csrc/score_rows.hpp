@@ -74,9 +74,11 @@ constexpr bool sixteen_row_products(int D, int R) { return D == 128 && R == 16; 
 inline KeyLayout key_layout(const Dims& d) { return sixteen_row_products(d.D, score_rows(d)) ? kKeyTiles16 : kKeyTiles32; }
 
 // Does a call go through score_topk_small_kernel, one launch instead of two?  Where the launches are what it takes: the score workgroups then
-// pool all of the K they see, two blocks at a time, one round after the other, which pays up to 64 KB of K a head, and to 96 KB in two rounds
-// (4 blocks).  Two launches against one, calls in a row, fused: 300 tokens of 32/8 heads with head_dim 64 (3 blocks) 19.9 and 17.5 us, 384
-// with head_dim 128 (3 blocks, 96 KB) 22.2 and 21.9, 512 with head_dim 64, blocks of 64 (8 blocks, 64 KB), 19.8 and 18.9, of one head 19.9
+// pool all of the K they see themselves, which pays up to 64 KB of K a head, and to 96 KB in 4 blocks.  The line was drawn when they pooled two
+// blocks at a time, one round after the other; with all of K asked for at once 128 KB in up to 6 blocks would gain 2 to 4 % (512 tokens, head_dim
+// 128, blocks of 128, 23.6 and 22.7, 384 with blocks of 64 19.0 and 18.8, 640 with head_dim 64, blocks of 128, 20.4 and 19.6) and more blocks
+// lose as much (768 with head_dim 64, blocks of 64, from a graph 17.2 and 18.0).  Two launches against one as it was then, calls in a row, fused:
+// 300 tokens of 32/8 heads with head_dim 64 (3 blocks) 19.9 and 17.5 us, 384 with head_dim 128 (3 blocks, 96 KB) 22.2 and 21.9, 512 with head_dim 64, blocks of 64 (8 blocks, 64 KB), 19.8 and 18.9, of one head 19.9
 // and 17.5; but 384 with head_dim 128, blocks of 64 (6 blocks, 96 KB), 19.7 and 20.1, 640 with head_dim 64 (10 and 5 blocks, 80 KB) 20.0 and
 // 21.2, 20.3 and 20.9.  Replayed from a graph, where a launch costs less, the first four are 17.1 and 16.6, 21.8 and 21.4, 17.5 and 18.1,
 // 16.8 and 17.1.  Selections alone 15.7 and 12.9 in a row; from a graph 6.9 and 6.5 with 4 blocks of 64, 7.4 and 7.7 with 8, 8.1 and 8.7 with
