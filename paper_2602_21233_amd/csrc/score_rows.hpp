@@ -84,9 +84,16 @@ inline KeyLayout key_layout(const Dims& d) { return sixteen_row_products(d.D, sc
 // 16.8 and 17.1.  Selections alone 15.7 and 12.9 in a row; from a graph 6.9 and 6.5 with 4 blocks of 64, 7.4 and 7.7 with 8, 8.1 and 8.7 with
 // 2 of 128, head_dim 128. (At most 8 key blocks then: they are one tile.)  Not with a mass budget, shared lists or the output-aware score,
 // whose kernels it would double.
+constexpr int kSmallKeys = 64 << 10, kSmallKeysFewBlocks = 96 << 10, kFewBlocks = 4;
 inline bool small_call(const Dims& d, bool rank_by_values) {
     const int64_t k_bytes = (int64_t)d.Skv * d.D * 2;
-    return d.gamma_q16 < 0 && !d.shared && !rank_by_values && (k_bytes <= 64 << 10 || (k_bytes <= 96 << 10 && d.NBk <= 4)) && score_rows(d) == 4;
+    return d.gamma_q16 < 0 && !d.shared && !rank_by_values && (k_bytes <= kSmallKeys || (k_bytes <= kSmallKeysFewBlocks && d.NBk <= kFewBlocks)) &&
+           score_rows(d) == 4;
+}
+// the most key blocks such a call has: what its workgroups hold registers for
+constexpr int most_small_blocks(int D, int Bs) {
+    const int block = 2 * D * Bs, few = kSmallKeysFewBlocks / block < kFewBlocks ? kSmallKeysFewBlocks / block : kFewBlocks;
+    return kSmallKeys / block > few ? kSmallKeys / block : few;
 }
 
 // Lists shared by several heads: do the workgroups of the score kernel pool the queries of all of them themselves?  Each streams as many

@@ -1019,74 +1019,70 @@ __host__ __device__ constexpr int key_tile_at() {
     return R * LD + NWV * 256 + 2 * (NWV / 4) * (256 / (D / 8)) * D;
 }
 
-// Means of the key blocks 0 .. n_blk - 1 (kh: the head's first token, Skv tokens) to an operand tile in LDS, in the layout and with the
-// arithmetic of the pooling kernel (pool.hip).  Two groups of 256 threads take the blocks in turn.  What bounds it is latency, so load() asks
-// for all of them at once, before the queries are pooled (up to 128 KB of K in 64 registers a lane), and reduce() finds them there: two blocks
-// in flight behind the queries took 3.1 us of a workgroup's 6.7 at 512 tokens, head_dim 64, blocks of 64.
-// All loads are unconditional within a block, tokens past the end re-read the last one and count 0.
+// Means of the key blocks 0 .. n_blk - 1 (n_blk <= most_small_blocks; kh: the head's first token, Skv tokens) to an operand tile in LDS, in the
+// layout and with the arithmetic of the pooling kernel (pool.hip).  Two groups of 256 threads take the blocks in turn.  What bounds it is latency,
+// so all of the blocks are asked for before the first is reduced (up to 64 KB of K in 32 registers a lane, three blocks of 32 KB in 64); two in flight,
+// a memory latency and a barrier a round, took 3.1 us of a workgroup's 6.7 at 512 tokens, head_dim 64, blocks of 64.  Asking for them before the
+// queries are pooled as well gives 0.1 us more there and needs 94 to 163 registers instead of 72 and 111: a workgroup less to a CU, and
+// batches of short prompts up to 40 % slower (10 prompts of 384 tokens, 32/8 heads, head_dim 128, blocks of 128, from a graph: 53.7 us, this way 48.7, two in
+// flight 49.8; their selection 18.7, 14.4, 15.8; 32 chunks of 64 queries over 448 tokens, head_dim 64, blocks of 64, 41.8, 37.4, 39.0).
+// part_base: 2 * NGRP * RPP * D words of LDS.  All loads are unconditional within a block, tokens past the end re-read the last one and count 0.
+// Ends with a barrier.
 template <int D, int BS, int NWV>
-struct StagedKeys {
-    static constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, NGRP = NWV / 4, SLOTS = 16 / PASSES;
+__device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t, int n_blk, int Skv, float* part_base, __bf16* tile) {
+    constexpr int TPR = D / 8, RPP = 256 / TPR, PASSES = BS / RPP, NGRP = NWV / 4, SLOTS = (most_small_blocks(D, BS) + NGRP - 1) / NGRP;
     static_assert(SLOTS % 2 == 0, "reduced in pairs");
-    static constexpr int kMostBlocks = SLOTS * NGRP;
+    const int grp = threadIdx.x >> 8, t256 = threadIdx.x & 255, prow = t256 / TPR, chunk = t256 % TPR;
+    typedef float (*Part)[D];
+    Part const part = reinterpret_cast<Part>(part_base) + grp * 2 * RPP;
     uint4 raw[SLOTS][PASSES];
-
-    __device__ __forceinline__ void load(const uint16_t* kh, int64_t stride_t, int n_blk, int Skv) {
-        const int grp = threadIdx.x >> 8, t256 = threadIdx.x & 255, prow = t256 / TPR, chunk = t256 % TPR;
-        static_for_sel<SLOTS>([&](auto s_tag) {
-            constexpr int s = decltype(s_tag)::value;
-            if (s * NGRP >= n_blk) return;                    // workgroup-uniform
-            const int j = s * NGRP + grp < n_blk ? s * NGRP + grp : n_blk - 1, last = Skv - 1 - j * BS;
+    static_for_sel<SLOTS>([&](auto s_tag) {
+        constexpr int s = decltype(s_tag)::value;
+        if (s * NGRP >= n_blk) return;                        // workgroup-uniform
+        const int j = s * NGRP + grp < n_blk ? s * NGRP + grp : n_blk - 1, last = Skv - 1 - j * BS;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int row = p * RPP + prow < last ? p * RPP + prow : last;
+            raw[s][p] = *reinterpret_cast<const uint4*>(kh + (int64_t)(j * BS + row) * stride_t + chunk * 8);
+        }
+    });
+    static_for_sel<SLOTS / 2>([&](auto pair_tag) {
+        constexpr int s0 = 2 * decltype(pair_tag)::value;
+        if (s0 * NGRP >= n_blk) return;
+        static_for_sel<2>([&](auto o_tag) {                   // partial sums of the pair's token rows
+            constexpr int s = s0 + decltype(o_tag)::value;
+            if (s * NGRP >= n_blk) return;
+            const int j = s * NGRP + grp < n_blk ? s * NGRP + grp : n_blk - 1, n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
+            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int p = 0; p < PASSES; ++p) {
-                const int row = p * RPP + prow < last ? p * RPP + prow : last;
-                raw[s][p] = *reinterpret_cast<const uint4*>(kh + (int64_t)(j * BS + row) * stride_t + chunk * 8);
+                const uint32_t keep = p * RPP + prow < n_valid ? 0xffffffffu : 0u;
+                const uint4 w = make_uint4(raw[s][p].x & keep, raw[s][p].y & keep, raw[s][p].z & keep, raw[s][p].w & keep);
+                acc[0] += bf16_lo(w.x); acc[1] += bf16_hi(w.x);
+                acc[2] += bf16_lo(w.y); acc[3] += bf16_hi(w.y);
+                acc[4] += bf16_lo(w.z); acc[5] += bf16_hi(w.z);
+                acc[6] += bf16_lo(w.w); acc[7] += bf16_hi(w.w);
             }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) part[(s - s0) * RPP + prow][chunk * 8 + e] = acc[e];
         });
-    }
-    // part_base: 2 * NGRP * RPP * D words of LDS.  Ends with a barrier.
-    __device__ __forceinline__ void reduce(int n_blk, int Skv, float* part_base, __bf16* tile) {
-        const int grp = threadIdx.x >> 8, t256 = threadIdx.x & 255, prow = t256 / TPR, chunk = t256 % TPR;
-        typedef float (*Part)[D];
-        Part const part = reinterpret_cast<Part>(part_base) + grp * 2 * RPP;
-        static_for_sel<SLOTS / 2>([&](auto pair_tag) {
-            constexpr int s0 = 2 * decltype(pair_tag)::value;
-            if (s0 * NGRP >= n_blk) return;
-            static_for_sel<2>([&](auto o_tag) {               // partial sums of the pair's token rows
-                constexpr int s = s0 + decltype(o_tag)::value;
-                if (s * NGRP >= n_blk) return;
-                const int j = s * NGRP + grp < n_blk ? s * NGRP + grp : n_blk - 1, n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
-                float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+        const int s = s0 + t256 / D, d = t256 % D, j = s * NGRP + grp;       // threads 0 .. D - 1 the first block's columns, D .. 2 D - 1 the second's
+        if (t256 < 2 * D && j < n_blk) {
+            const int n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
+            float sum = 0.f;
 #pragma unroll
-                for (int p = 0; p < PASSES; ++p) {
-                    const uint32_t keep = p * RPP + prow < n_valid ? 0xffffffffu : 0u;
-                    const uint4 w = make_uint4(raw[s][p].x & keep, raw[s][p].y & keep, raw[s][p].z & keep, raw[s][p].w & keep);
-                    acc[0] += bf16_lo(w.x); acc[1] += bf16_hi(w.x);
-                    acc[2] += bf16_lo(w.y); acc[3] += bf16_hi(w.y);
-                    acc[4] += bf16_lo(w.z); acc[5] += bf16_hi(w.z);
-                    acc[6] += bf16_lo(w.w); acc[7] += bf16_hi(w.w);
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) part[(s - s0) * RPP + prow][chunk * 8 + e] = acc[e];
-            });
-            __syncthreads();
-            const int s = s0 + t256 / D, d = t256 % D, j = s * NGRP + grp;   // threads 0 .. D - 1 the first block's columns, D .. 2 D - 1 the second's
-            if (t256 < 2 * D && j < n_blk) {
-                const int n_valid = Skv - j * BS < BS ? Skv - j * BS : BS;
-                float sum = 0.f;
-#pragma unroll
-                for (int r = 0; r < RPP; ++r) sum += part[(s - s0) * RPP + r][d];
-                float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
-                asm("" : "+v"(mean));                         // rounded before it is split, as in the pooling kernel
-                const __bf16 hi = (__bf16)mean;
-                const int at = key_tile_offset(kKeyTiles32, d, j);
-                tile[at] = hi;
-                tile[at + key_tail(kKeyTiles32)] = (__bf16)(mean - (float)hi);
-            }
-            __syncthreads();
-        });
-    }
-};
+            for (int r = 0; r < RPP; ++r) sum += part[(s - s0) * RPP + r][d];
+            float mean = n_valid == BS ? sum * (1.0f / (float)BS) : sum / (float)n_valid;
+            asm("" : "+v"(mean));                             // rounded before it is split, as in the pooling kernel
+            const __bf16 hi = (__bf16)mean;
+            const int at = key_tile_offset(kKeyTiles32, d, j);
+            tile[at] = hi;
+            tile[at + key_tail(kKeyTiles32)] = (__bf16)(mean - (float)hi);
+        }
+        __syncthreads();
+    });
+}
 
 // Scores, top-k and merged lists of the query blocks i0 .. i0 + R - 1 of head bh = b * Hq + h, by a
 // 512-thread workgroup.  S: R * (MAXC * 64 + row_pad) floats of LDS for the scores, then 256 counters per
@@ -1116,6 +1112,8 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
     const int n_jt = ((i_last + off) >> 5) + 1;           // 32-wide key-block tiles with some causal j
 
     // ---- phase 0 / phase 1 ------------------------------------------------------------
+    stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
+    const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
     if constexpr (KIN > 0) {                              // one tile, pooled by the workgroup itself, KIN tokens a block
         constexpr int part_at = 2 * (NWV / 4) * (256 / (D / 8)) * D <= R * LD ? 0 : R * LD + NWV * 256;
         float* const tile = S + key_tile_at<D, R, LD, NWV>();
@@ -1123,15 +1121,10 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
         const uint16_t* const kh = keys->k + b * keys->ks.b + (h / G) * keys->ks.h;
         int n_blk = (Skv_b + KIN - 1) / KIN;              // the entry's blocks; causally visible ones
         n_blk = n_blk < i_last + off + 1 ? n_blk : i_last + off + 1;
-        StagedKeys<D, KIN, NWV> staged;                   // an empty entry has no blocks: its rows get empty lists
-        staged.load(kh, keys->ks.t, n_blk, Skv_b);
-        stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
-        staged.reduce(n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
+        // an empty entry has no blocks: its rows get empty lists
+        if (n_blk > 0) stage_keys<D, KIN, NWV>(kh, keys->ks.t, n_blk, Skv_b, S + part_at, reinterpret_cast<__bf16*>(tile));
         kbase = tile;
-    } else {
-        stage_queries<D, R, R * LD, NWV, GROUP>(a, bh, i0, S);
     }
-    const __bf16* const qlds = reinterpret_cast<const __bf16*>(S + R * LD);
     score_tiles<D, R, LD, D / 16, NWV>(a, kbase, qlds, S, 0, wave, n_jt, bh, i0, lvbase);
     if (scores_out != nullptr) {                          // key blocks past the last computed tile
         const int j_first = 32 * n_jt;
@@ -1438,10 +1431,11 @@ __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs 
 // Small calls (small_call): one launch instead of prepare_kv_kernel (or pool_kernel) and the score kernel.  Every workgroup pools the K blocks
 // its rows can see itself, from L2, and the workgroups behind the first n_score transpose two blocks of V each.
 // Bound by launches and latency.  Against two launches 512 tokens of one head, head_dim 64, blocks of 64, took 16.8 us instead of 18.8; with all of
-// K asked for before the queries 16.2 (replayed from a graph 16.3 -> 15.3; 300 tokens of 32/8 heads 15.4 -> 14.6, 384 tokens with head_dim 128,
-// blocks of 128, 21.3 -> 20.4).  One workgroup's wavefronts on a SIMD are two, so it may have 256 registers.
+// a workgroup's K in flight at once 16.2 (replayed from a graph 16.3 -> 15.5; 300 tokens of 32/8 heads 15.4 -> 14.7, 384 tokens with head_dim 128,
+// blocks of 128, 21.3 -> 20.4).  Batches of short prompts have up to 2048 workgroups, so as many share a CU as its LDS holds: two, three with
+// head_dim 64, within 128 and 80 registers.
 template <int D, int BS, bool EXT>
-__global__ __launch_bounds__(512, 2) void score_topk_small_kernel(ScoreArgs a, KeyArgs keys, int n_tiles, int n_score) {
+__global__ __launch_bounds__(512, D == 64 ? 6 : 4) void score_topk_small_kernel(ScoreArgs a, KeyArgs keys, int n_tiles, int n_score) {
     extern __shared__ __attribute__((aligned(128))) float S[];
     constexpr int R = 4, NWV = 8;
     const int wg = blockIdx.x;
@@ -1576,7 +1570,7 @@ hipError_t allow_small_lds() {
 
 template <int D, int BS, bool EXT>
 hipError_t launch_small_e(const ScoreCall& c, const KeyArgs& keys) {
-    if (c.d.NBk > StagedKeys<D, BS, 8>::kMostBlocks) return hipErrorInvalidValue;
+    if (c.d.NBk > most_small_blocks(D, BS)) return hipErrorInvalidValue;
     const size_t v_lds = keys.vt != nullptr ? small_v_lds<D, BS>() : 0;
     const size_t lds = v_lds > small_score_lds<D>() ? v_lds : small_score_lds<D>();
     // asked for once, for the largest call and for both block sizes: a fused call in a capture may follow calls that need less, or another kernel

@@ -18,6 +18,7 @@ extern "C" int score_rows(const spa_params* p, int mass) { return spa::score_row
 extern "C" int pooled_in_kernel(const spa_params* p, int mass) { return spa::group_pooled_in_kernel(lists_of(p, mass)); }
 extern "C" int one_launch(const spa_params* p, int mass) { return spa::small_call(lists_of(p, mass), false); }
 extern "C" int one_launch_by_values(const spa_params* p, int mass) { return spa::small_call(lists_of(p, mass), true); }
+extern "C" int most_small_blocks(const spa_params* p, int) { return spa::most_small_blocks(p->head_dim, p->block_size); }
 extern "C" int sixteen_row_tiles(const spa_params* p, int mass) { return spa::key_layout(lists_of(p, mass)) == spa::kKeyTiles16; }
 """
 
@@ -91,6 +92,14 @@ def test_one_launch_for_small_calls(rows_of, NB, NBk, Bs, D, want):
     assert ask() == want
     assert not ask(mass=True) and not ask(group=2) and not ask(what="one_launch_by_values")
     assert not ask(heads=1024 // NB + 1)                   # more than 1024 rows: not 4 per workgroup
+
+
+# ... whose kernel has registers for as many blocks as such a call may have, and no more: what they cost is workgroups that share a CU.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Bs", [64, 128])
+def test_small_calls_have_registers_for_their_blocks(rows_of, D, Bs):
+    taken = [n for n in range(1, 40) if rows_of(1, n, 8, Bs=Bs, D=D, what="one_launch")]
+    assert rows_of(1, 1, 8, Bs=Bs, D=D, what="most_small_blocks") == max(taken) == len(taken)
 
 
 # 16-row products, and the pooled K laid out for them, are for 16 rows of head_dim 128: 4 or 8 rows lose 1 to 2.5 % to them or to their
