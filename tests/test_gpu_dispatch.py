@@ -21,22 +21,26 @@ def _normal(shape, seed):
 
 
 # A fused call may be captured after nothing but selections and attention calls: what a small call's kernel needs for V^T has been asked for by the
-# first selection.  (First of the tests that launch that kernel, so that none of them has asked for it.)
-@pytest.mark.parametrize("D,Bs,kw", [(128, 128, {}), (64, 64, dict(stride_blocks=3))])
-def test_a_small_fused_call_is_captured_after_selections(spa, D, Bs, kw):
+# first selection, also if that had the other block size, which is another kernel.  (First of the tests that launch these kernels, one for each head
+# size and kind of pattern, so that none of them has asked for it.)
+@pytest.mark.parametrize("D,Bs,before,kw", [(128, 128, 128, {}), (64, 64, 64, dict(stride_blocks=3)), (64, 64, 128, {}), (128, 128, 64, dict(stride_blocks=3))])
+def test_a_small_fused_call_is_captured_after_selections(spa, D, Bs, before, kw):
     from paper_2602_21233_amd import binding
     S, ns, nl, k = 3 * Bs - 5, 1, 1, 1
     q, kk, v = _normal((1, 4, S, D), 71), _normal((1, 2, S, D), 72), _normal((1, 2, S, D), 73)
-    idx, cnt = spa.select(q, kk, Bs, ns, nl, k, **kw)
-    want = spa.attn(q, kk, v, idx, cnt, Bs, pattern=(ns, nl, k, kw.get("stride_blocks", 0), 0))
+    spa.select(q, kk, before, ns, nl, k, **kw)
     p = binding.make_params(batch=1, n_q_heads=4, n_kv_heads=2, seq_len=S, head_dim=D, block_size=Bs, n_sink_blocks=ns, n_local_blocks=nl,
                             top_k_blocks=k, q=q, k=kk, v=v, out=q, **kw)
     ws = torch.empty(spa.workspace_bytes(p), dtype=torch.uint8, device="cuda")
     out = torch.empty_like(q)
+    pattern = (ns, nl, k, kw.get("stride_blocks", 0), 0)
+    spa.attn(q, kk, v, *_random_lists(1, 4, 3, 0, 3, 3, 74), Bs, pattern=pattern)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         spa.fused(q, kk, v, Bs, ns, nl, k, workspace=ws, out=out, **kw)
+    idx, cnt = spa.select(q, kk, Bs, ns, nl, k, **kw)
+    want = spa.attn(q, kk, v, idx, cnt, Bs, pattern=pattern)
     for rep in range(3):
         out.zero_()
         ws.random_(0, 255)
@@ -245,23 +249,39 @@ def test_options_on_every_score_kernel(spa, oracle, kernel, option, D):
                 assert torch.isneginf(sp[b, h, i, m:off + nb]).all()
 
 
-# Rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows, are selected from a list of the blocks that reach a bound, up to 128 of a budget, 64 sinks and 512 entries, and the
-# general way (the other kernels, too) past any of these.  Budgets and sinks on both sides; scores of `distinct` values (0: all different; 2: more equal ones than the
-# list holds; 1: all equal; 40: ties at the threshold inside a list).  The caller-score kernel, which keeps whole rows, is the reference.
-@pytest.mark.parametrize("kernel", [(4, 1024), (8, 1024), (8, 2048), (16, 1024), (16, 2048)], ids=lambda k: f"{k[0]}rows{k[1]}")
-@pytest.mark.parametrize("distinct", [0, 40, 2, 1])
-def test_lists_by_bound(spa, kernel, distinct):
+# Rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows, are selected from a list of the blocks that reach a bound, up to 128 of
+# a budget, 64 sinks and 512 entries, and the general way (the other two kernels here, too) past any of these.  Budgets and sinks on both sides.
+# Scores by `keys`: all different; of 40, 2 or 1 distinct values (ties at the threshold inside a list, more equal ones than it holds, all equal);
+# "special": NaN, infinities, huge values and zeros in places; "few": most are NaN or -infinity, so that rows have fewer finite ones than wanted.
+# The caller-score kernel, which keeps whole rows, is the reference.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kernel", [(4, 1024), (4, 2048), (8, 1024), (8, 2048), (16, 1024), (16, 2048)], ids=lambda k: f"{k[0]}rows{k[1]}")
+@pytest.mark.parametrize("keys", [0, 40, 2, 1, "special", "few"])
+def test_lists_by_bound(spa, kernel, keys, D):
     NB, Hq, P = SCORE_KERNELS[kernel]
-    Hkv, D, Bs = Hq // 4, 64 if kernel[0] == 8 else 128, 64
-    q = _normal((1, Hq, NB * Bs, D), 71)
-    k = _normal((1, Hkv, (P + NB) * Bs, D), 72)
-    if distinct:
-        which = torch.randint(0, distinct, (P + NB,), generator=torch.Generator().manual_seed(73)).cuda()
+    Hkv, Bs = Hq // 4, 64
+    g = torch.Generator("cuda").manual_seed(71)
+    q = torch.randn((1, Hq, NB * Bs, D), generator=g, device="cuda").to(torch.bfloat16)
+    k = torch.randn((1, Hkv, (P + NB) * Bs, D), generator=g, device="cuda").to(torch.bfloat16)
+    if keys in (40, 2, 1):
+        which = torch.randint(0, keys, (P + NB,), generator=g, device="cuda")
         k = k.view(1, Hkv, P + NB, Bs, D)[:, :, which].reshape(1, Hkv, -1, D).contiguous()
+    elif keys:
+        # kinds of block: NaN, and with queries and keys of one sign each scores beyond the largest number
+        q = q.abs() * 1e3
+        kind = torch.rand((1, Hkv, P + NB), generator=g, device="cuda").repeat_interleave(Bs, 2)[..., None]
+        nan, neg, pos, huge, zero = (0.47, 0.94, 0.95, 0.96, 0.97) if keys == "few" else (0.05, 0.1, 0.12, 0.16, 0.2)
+        k = k.where(kind >= nan, float("nan")).where((kind < nan) | (kind >= neg), -k.abs() * 1e36).where((kind < neg) | (kind >= pos), k.abs() * 1e36)
+        k = k.where((kind < pos) | (kind >= huge), k * 1e30).where((kind < huge) | (kind >= zero), 0.0)
     for ns, nl, topk in ((1, 4, 1), (0, 1, 64), (1, 4, 65), (64, 2, 127), (65, 2, 64), (3, 70, 128), (1, 4, 129), (2, 3, 0), (5, 9, P + NB - 20)):
         idx, cnt, sp = spa.select(q, k, Bs, ns, nl, topk, return_scores=True)
         want_idx, want_cnt = spa.topk_from_scores(sp, ns, nl, topk)
         assert torch.equal(cnt, want_cnt) and torch.equal(idx, want_idx), (ns, nl, topk)
+    if keys in ("special", "few"):
+        seen = sp[..., :P]                                     # causal for every row
+        assert seen.isnan().any() and seen.isposinf().any() and seen.isneginf().any() and (seen == 0).any()
+        finite = seen.isfinite().sum(-1)
+        assert (finite > 128).all() if keys == "special" else (finite < 127).any() and (finite > 1).all()
 
 
 # A mass budget is not searched for where the count budget cannot reach it whatever the scores.  Equal scores weigh 2^19 each, the most there is:
