@@ -34,26 +34,29 @@ inline int score_rows(const Dims& d) {
     if (d.NBk <= 512) return 8;
     const bool two_chunks = d.NBk > 1024;
     if (!plain) return two_chunks ? 8 : 16;
-    // 513 .. 2048 blocks.  Many rows: 16, as 8 re-read the pooled K twice as often (blocks of 128, 8 against 16: 186 and 181 us at 768 blocks
-    // and 24576 rows, 257 and 248 at 1024 and 32768; 731 and 700 at 262144 tokens and 81920 rows, 385 and 363 at 40960, where 16 rows are
-    // scored in two chunks of 1024 columns to keep two workgroups per CU).
+    // 513 .. 2048 blocks.  All figures from here on: select calls over 8 KV heads, us with 8 and with 16 rows.  The lines were drawn before the
+    // 16-row kernels selected from lists by bound (take_best), which the 8-row ones do only beyond 1024 blocks, and have not been moved since:
+    // some calls on the side of 8 now lose up to 13 % against 16.
+    // Many rows: 16, as 8 re-read the pooled K twice as often (blocks of 128: 185 and 181 at 768 blocks and 24576 rows, 255 and 236 at 1024 and
+    // 32768; 707 and 615 at 262144 tokens and 81920 rows, 327 and 304 at 163840 tokens and 40960, where 16 rows are scored in two chunks of
+    // 1024 columns to keep two workgroups per CU; but 220 and 223 at 768 blocks and 30720 rows).
     if (rows > (two_chunks ? 32768 : 16384)) return 16;
     // Fewer: more workgroups, unless they only make more rounds.  With blocks of 128 the query stream, twice as long for a row, hides the
-    // rounds, and 8 are the better or equal choice up to 1024 blocks (16 against 8: 8192 queries over 98304 tokens, 2048 rows, 71.8 and 63.8
-    // us; 98304 tokens of 8 heads 85.3 and 79.4; 131072 of 16 heads, 16384 rows, 144 and 134).  In two chunks, with their 16-row products, 16
-    // have become the better choice in places (175 and 167 at 196608 tokens of 8 heads, 238 and 231 at 262144, but 304 and 318 with 16 heads,
-    // 32768 rows; 174 and 177 at 163840 of 16 heads; 177 and 187 for 25600 queries over 230400 tokens); the line has not been moved since.
+    // rounds, and 8 are the better choice up to 1024 blocks (8192 queries over 98304 tokens, 2048 rows, 62.7 and 68.2; 98304 tokens of 8 heads
+    // 78.4 and 85.5; 131072 of 16 heads, 16384 rows, 154 and 162; but with head_dim 64 92.4 and 90.0).  In two chunks 16 have become the
+    // better choice from about 20000 rows on (160 and 162 at 196608 tokens of 8 heads, 219 and 223 at 262144, but 195 and 189 at 163840 of 16
+    // heads, 241 and 235 at 196608, 339 and 310 at 262144, 32768 rows) and over a long prefix (25600 queries over 230400 tokens, 171 and 158).
     if (d.Bs == 128) return 8;
-    // With blocks of 64 the rounds of 512 workgroups (two per CU) show.  Up to 1.5 rounds of 8-row workgroups (6144 rows) 8 rows win whatever
-    // the count, by up to 27 %.  From there on:
+    // With blocks of 64 the rounds of 512 workgroups (two per CU) show.  Up to 1.5 rounds of 8-row workgroups (6144 rows) 8 rows win (1600 rows
+    // of 1000 blocks 45.2 and 50.1, 5120 of 640 43.5 and 49.5).  From there on:
     //   - over a prefix at least as long as the chunk all rows are about as long, and what counts is `depth`, how many of them a place works
-    //     through one after the other: 8 rows where that is less (12797 queries over 51200 tokens, 40 heads, 89.7 with 16, 88.7 us with 8;
-    //     but since 16-row products 19197 over 44800 tokens 101 and 110, 38397 over 51200 of 16 heads 91.5 and 94.9), 16 where it is the same
-    //     (12797 over 51200 tokens, 32 heads, 72.5 against 78.5 us with 8; 25597 over 102400 tokens, 40 heads, 190 against 215);
+    //     through one after the other: 16 where that is the same (12797 queries over 51200 tokens, 32 heads, 76.9 and 66.7; 25597 over 102400
+    //     tokens, 40 heads, 180 and 148), 8 rows where that is less, which since lists by bound no longer pays (12797 over 51200 tokens, 40
+    //     heads, 80.9 and 77.2, 19197 over 44800 102 and 88.5, 38397 over 51200 of 16 heads 102 and 96.2);
     //   - rows that differ in length are dealt longest first and even the rounds out.  8 rows win up to one round of 16-row workgroups (52413
-    //     tokens of 8 heads, 59.1 with 16, 57.7 us with 8) and, with head_dim 64 or two chunks, up to 14336 rows (95997 tokens of 8 heads
-    //     113.9 and 112.0; 47485 tokens of 16 heads, head_dim 64, 45.1 and 43.7).  16 elsewhere: 40957 tokens of 16 heads 52.7 against 55.0
-    //     us with 8, 113341 tokens of 16 heads, head_dim 64, 134 against 142, 28288 rows of 1247 blocks 177 against 199.
+    //     tokens of 8 heads 56.4 and 58.6) and, with head_dim 64 or two chunks, up to 14336 rows (95997 tokens of 8 heads 104 and 104; 47485
+    //     tokens of 16 heads, head_dim 64, 46.4 and 50.9).  16 elsewhere: 113341 tokens of 16 heads, head_dim 64, 133 and 120, 28288 rows of 1247
+    //     blocks 183 and 160, 64000 tokens of 16 heads 102 and 96.9 (40957 tokens 62.2 and 63.7).
     const int64_t wg8 = heads * ((d.NB + 7) / 8), wg16 = heads * ((d.NB + 15) / 16);
     if (wg8 <= 768) return 8;
     if (d.off >= d.NB) {
@@ -74,16 +77,16 @@ constexpr bool sixteen_row_products(int D, int R) { return D == 128 && R == 16; 
 inline KeyLayout key_layout(const Dims& d) { return sixteen_row_products(d.D, score_rows(d)) ? kKeyTiles16 : kKeyTiles32; }
 
 // Does a call go through score_topk_small_kernel, one launch instead of two?  Where the launches are what it takes: the score workgroups then
-// pool all of the K they see themselves, which pays up to 64 KB of K a head, and to 96 KB in 4 blocks.  The line was drawn when they pooled two
-// blocks at a time, one round after the other; with all of K asked for at once 128 KB in up to 6 blocks would gain 2 to 4 % (512 tokens, head_dim
-// 128, blocks of 128, 23.6 and 22.7, 384 with blocks of 64 19.0 and 18.8, 640 with head_dim 64, blocks of 128, 20.4 and 19.6) and more blocks
-// lose as much (768 with head_dim 64, blocks of 64, from a graph 17.2 and 18.0).  Two launches against one as it was then, calls in a row, fused:
-// 300 tokens of 32/8 heads with head_dim 64 (3 blocks) 19.9 and 17.5 us, 384 with head_dim 128 (3 blocks, 96 KB) 22.2 and 21.9, 512 with head_dim 64, blocks of 64 (8 blocks, 64 KB), 19.8 and 18.9, of one head 19.9
-// and 17.5; but 384 with head_dim 128, blocks of 64 (6 blocks, 96 KB), 19.7 and 20.1, 640 with head_dim 64 (10 and 5 blocks, 80 KB) 20.0 and
-// 21.2, 20.3 and 20.9.  Replayed from a graph, where a launch costs less, the first four are 17.1 and 16.6, 21.8 and 21.4, 17.5 and 18.1,
-// 16.8 and 17.1.  Selections alone 15.7 and 12.9 in a row; from a graph 6.9 and 6.5 with 4 blocks of 64, 7.4 and 7.7 with 8, 8.1 and 8.7 with
-// 2 of 128, head_dim 128. (At most 8 key blocks then: they are one tile.)  Not with a mass budget, shared lists or the output-aware score,
-// whose kernels it would double.
+// pool all of the K they see themselves, which pays up to 64 KB of K a head, and to 96 KB in 4 blocks.  Two launches against one, 32/8 heads, calls
+// in a row, fused: 300 tokens with head_dim 64, blocks of 128, 18.6 and 15.9 us, 384 with head_dim 128 (3 blocks, 96 KB) 22.7 and 21.2, 512 with
+// head_dim 64, blocks of 64 (8 blocks, 64 KB), 18.7 and 16.7, of one head 18.5 and 15.9; replayed from a graph, where a launch costs less, 16.3 and
+// 15.1, 21.7 and 20.4, 16.0 and 16.1, 15.4 and 14.9.  Selections alone 14.6 and 11.7 in a row; from a graph 7.6 and 6.2 with 4 blocks of 64, 7.6
+// and 7.4 with 8, 8.1 and 7.0 with 2 of 128, head_dim 128.  Batches, from a graph: 10 prompts of 384 tokens, head_dim 128, 50.6 and 48.8, their
+// selection alone 12.4 and 14.4; 8 of 256 in blocks of 64 30.6 and 29.2, alone 8.0 and 8.6.
+// 128 KB in up to 6 blocks would gain 1 to 5 % as well (fused in a row, 512 tokens with head_dim 128, blocks of 128, 23.8 and 22.7, 384 with blocks of 64
+// 19.4 and 19.0, 640 with head_dim 64, blocks of 128, 20.3 and 19.8), more blocks lose 1 to 5 % (512 with head_dim 128, blocks of 64, 19.3 and 19.5, 768
+// with head_dim 64 18.5 and 19.0): the line, drawn when K was pooled two blocks at a time, has not been moved.
+// (At most 8 key blocks: they are one tile.)  Not with a mass budget, shared lists or the output-aware score, whose kernels it would double.
 constexpr int kSmallKeys = 64 << 10, kSmallKeysFewBlocks = 96 << 10, kFewBlocks = 4;
 inline bool small_call(const Dims& d, bool rank_by_values) {
     const int64_t k_bytes = (int64_t)d.Skv * d.D * 2;

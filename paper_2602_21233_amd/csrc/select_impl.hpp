@@ -386,6 +386,9 @@ __device__ __forceinline__ float max_num(float x, float y) {
 // here, 7 each on rank keys, search and writing.  Select calls, general way against this one: 262144 tokens of 40/8 heads 704 -> 630 us (with a
 // budget of 16 663 -> 582, of 127 714 -> 658), of 8 heads 225 -> 215, 2048 blocks of 64 402 -> 336, all scores equal 356 -> 315, 8192 queries
 // over 98304 tokens, blocks of 64, 86 -> 79, 131072 tokens 244 -> 236, head_dim 64 154 -> 143, with a dense strip 286 -> 275.
+// Few rows, 4 to a workgroup: 512 queries over 130048 tokens, blocks of 64, head_dim 64, 47.6 -> 40.6, 2000 over 196608, blocks of 128, 55.3 -> 49.9, with
+// head_dim 128 94.6 -> 88.9.  Where the general way has to follow after all: budgets beyond 128, many sinks, strided calls within 1.2 % of
+// before; rows without finite scores, which it is done with at once, 1 to 6 % longer.
 // For rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows: with 8 a wavefront has one row, and the other workgroups' streams
 // hide it (131072 tokens of 8 heads 106.1 and 107.4, 98304 of 16 heads 86.6 and 88.6).  With 512 blocks it gives nothing (117.1 and 117.0 us at
 // 65536 tokens), with 256 the general way is a few instructions a score already (59.6 and 60.8 at 32768), and with 4096 the 64 scores of a lane
@@ -408,6 +411,7 @@ __device__ __forceinline__ bool take_best(const float (&x)[MAXC], int i, int c0,
         if (kk > 128 || c0 > 64) return false;
         const int q_last = (c1 - 1) >> (6 + LQ);              // quarter of the last candidate
         float m1 = -INFINITY, m2 = -INFINITY;
+        asm("" : "+v"(m2));                                   // a known -infinity would make the second score's med3 min(m1, v): m1 twice if v is a NaN
         // only in the first and the last quarter can a block not be a candidate
         auto candidate = [&](int m, bool edge) {
             return !edge || (uint32_t)((m << 6) + lane - c0) < (uint32_t)n_cand ? x[m] : -INFINITY;
@@ -456,7 +460,7 @@ __device__ __forceinline__ bool take_best(const float (&x)[MAXC], int i, int c0,
             };
             if (q == 0 || q == q_last) quarter(true); else quarter(false);
         });
-        if (!fits || n_list < kk) return false;
+        if (!fits || n_list < kk) return false;               // (fewer only if a lane had counted a score twice)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         static_for_sel<NY>([&](auto t_tag) {
             constexpr int t = decltype(t_tag)::value;
@@ -627,7 +631,7 @@ __device__ int mass_budget_row(ScoreFn score, int i, const Pattern& pt, uint32_t
 // A weight is 2^19 at most, so k_count blocks cannot hold more than k_count times that: where the target is beyond it, which is most rows if
 // their scores are close to each other, the four passes over the row are left out.  Select calls, gamma 0.9, scores of random keys: 65536
 // tokens 134.9 -> 122.3 us, 131072 298 -> 264, 262144 of 40/8 heads 894 -> 816, 2048 blocks of 64 of 16 heads 322 -> 273; rows that keep a few
-// blocks 131.0 and 130.8.
+// blocks 131.0 and 130.8.  (Longer rows and caller-supplied scores go through mass_budget_row, which always searches.)
 template <int MAXC, typename ScoreFn>
 __device__ __forceinline__ int mass_budget_regs(const uint32_t (&key)[MAXC], uint64_t is_static_bits, ScoreFn score, int i,
                                                 int chunks, uint32_t gamma_q16, int k_count, uint32_t* hist, int lane) {
