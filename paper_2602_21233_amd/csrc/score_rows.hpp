@@ -66,6 +66,27 @@ inline int score_rows(const Dims& d) {
     return wg16 <= 512 || (rows <= 14336 && (two_chunks || d.D == 64)) ? 8 : 16;
 }
 
+// Is a call's kernel one that selects rows from a list of the blocks that reach a bound (take_best) where it can?  Not where no row does: static
+// columns, more than 64 sinks, a budget too close to the 128 values that the bound is taken from.  And only where enough rows get one, as
+// the others pay for both ways' instructions in one kernel (61437 tokens of 16 heads, head_dim 64, blocks of 64, 128 wanted and so the general
+// way for all of them, 56.8 us in a kernel without lists, 61.5 in one with them).  Select calls, us without and with lists:
+//   - up to 1024 blocks, 16 rows a workgroup, it takes rows of 352 blocks and more with the budget on average, less of that for many rows of head_dim
+//     128: 40 heads from the first block on, head_dim 64, 64 wanted, 826 blocks of 64 105.5 and 107.5, 951 of 128 164.8 and 161.5; 32
+//     heads, 8 wanted, 768 of 128 100.4 and 98.6; head_dim 128, blocks of 64, 32 heads, 64 wanted, 799 119.7 and 116.6, 670 99.1 and 99.6, 16
+//     heads, 8 wanted, 700 53.1 and 55.2.  Over 900 random calls with such kernels this choice takes 0.1 % more time than the better one of
+//     each, lists always 0.6, lists never 2.4 (at most 5, 8 and 19 %).
+//   - beyond 1024 blocks all up to 124 wanted (116 to 124 wanted of 1025 to 1280 blocks 0.92 to 1.04 of the time without, of 1536 and more
+//     0.79 to 0.97), and 128 of many long rows (more than 1536 blocks, more than 16384 rows 0.93 to 1.01; up to 16384 rows 0.96 to 1.06; 1025 to
+//     1280 blocks 0.98 to 1.11).
+constexpr int kFewWanted = 112;
+constexpr bool has_lists_by_bound(int R, int max_chunks) { return max_chunks == 32 || (max_chunks == 16 && R == 16); }
+inline bool lists_by_bound(const Dims& d) {
+    if (d.gamma_q16 >= 0 || d.shared || d.stride > 0 || d.ns > 64 || d.NBk <= 512 || d.NBk > 2048) return false;
+    const bool many = (int64_t)d.B * d.Hq * d.NB > 16384;
+    if (d.NBk <= 1024) return score_rows(d) == 16 && d.k <= kFewWanted && d.off + d.NB / 2 >= 352 + (d.D == 128 && many ? d.k / 4 : d.k);
+    return d.k <= 124 || (d.k <= 128 && d.NBk > 1536 && many);
+}
+
 // Which matrix products score R rows: 16x16x32 ones for 16 rows of head_dim 128, 32x32x16 ones, whose surplus rows are copies, for the
 // others.  With 16 rows of head_dim 128 the former halve the matrix work and the LDS reads, and their 8 accumulators instead of 16 end the
 // spills of the two-chunk kernel (select calls, 262144 tokens of 40/8 heads 759 -> 695 us, blocks of 64 2048 of 32 heads 431 -> 406, 1247 of

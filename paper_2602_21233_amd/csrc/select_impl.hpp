@@ -380,15 +380,21 @@ __device__ __forceinline__ float max_num(float x, float y) {
 //   2. The blocks that reach L go to a list in LDS, in block order.  Whatever L is, the kk best are among them if there are kk or more, as all
 //      others rank lower (NaN, which ranks lowest, never reaches L).
 //   3. The kk-th largest rank key of the list, by halves: a compare and a count of the ballot per 64 of them.  Ties go to the first in the list.
-// Returns false, with nothing written to memory, where that does not do: more than 128 wanted, sinks beyond the first 64 blocks, fewer than kk finite
-// scores in the lanes' pairs, or a list that would not fit (many equal scores).
+// Returns false, with nothing written to memory, where that does not do: too many wanted (below), sinks beyond the first 64
+// blocks, fewer than kk finite scores in the lanes' pairs, or a list that would not fit (many equal scores).  Which calls come here: lists_by_bound.
 // What bounds it: instructions issued, with four wavefronts to a SIMD.  At 262144 tokens a workgroup of the general way spent 21 of its 63 us
 // here, 7 each on rank keys, search and writing.  Select calls, general way against this one: 262144 tokens of 40/8 heads 704 -> 630 us (with a
-// budget of 16 663 -> 582, of 127 714 -> 658), of 8 heads 225 -> 215, 2048 blocks of 64 402 -> 336, all scores equal 356 -> 315, 8192 queries
+// budget of 16 663 -> 582), of 8 heads 225 -> 215, 2048 blocks of 64 402 -> 336, all scores equal 356 -> 315, 8192 queries
 // over 98304 tokens, blocks of 64, 86 -> 79, 131072 tokens 244 -> 236, head_dim 64 154 -> 143, with a dense strip 286 -> 275.
 // Few rows, 4 to a workgroup: 512 queries over 130048 tokens, blocks of 64, head_dim 64, 47.6 -> 40.6, 2000 over 196608, blocks of 128, 55.3 -> 49.9, with
-// head_dim 128 94.6 -> 88.9.  Where the general way has to follow after all: budgets beyond 128, many sinks, strided calls within 1.2 % of
-// before; rows without finite scores, which it is done with at once, 1 to 6 % longer.
+// head_dim 128 94.6 -> 88.9.  Rows without finite scores, which the general way is done with at once, take 1 to 6 % longer, as it has to follow.
+// Short rows and large budgets: the closer the wanted ones come to the 128 of the lanes' pairs, the lower the bound and the longer the list, up to most
+// of a short row, whereas the general way costs by quarters of the row.  Rows of one length, 64 heads of 64 query blocks, blocks of 64, head_dim 64,
+// general way and this one: in kernels of up to 1024 blocks 64 wanted of 288 22.4 and 23.5 us, of 480 26.4 and 26.6, of 640 30.2 and 29.0, 112 of 288
+// 22.1 and 25.3, of 640 30.8 and 30.6, 128 of 1024 39.6 and 43.1; in those of up to 2048, whose quarters are longer, 64 wanted gain 1.4 at 288 and lose
+// 0.4 at 160, 112 gain 0.6 at 352 and lose 0.8 at 288, 128 lose 2.4 to 5 at any length.  That is weighed for the call (lists_by_bound), not the row,
+// as a kernel that does both pays for it: 65533 tokens of 16 heads, 64 wanted, 58.4 us the general way, 55.4 this way, 59.0 with rows of up to 320
+// blocks the general way and the others this way; over 350 random calls such lines are worth 0.2 %.  Above 112 wanted there is one, at 1024.
 // For rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows: with 8 a wavefront has one row, and the other workgroups' streams
 // hide it (131072 tokens of 8 heads 106.1 and 107.4, 98304 of 16 heads 86.6 and 88.6).  With 512 blocks it gives nothing (117.1 and 117.0 us at
 // 65536 tokens), with 256 the general way is a few instructions a score already (59.6 and 60.8 at 32768), and with 4096 the 64 scores of a lane
@@ -408,7 +414,7 @@ __device__ __forceinline__ bool take_best(const float (&x)[MAXC], int i, int c0,
     int need_eq = 0;
     const bool all = kk == n_cand;                            // every block up to i
     if (!all && kk > 0) {
-        if (kk > 128 || c0 > 64) return false;
+        if (kk > 128 || c0 > 64 || (kk > kFewWanted && n_cand < 1024)) return false;
         const int q_last = (c1 - 1) >> (6 + LQ);              // quarter of the last candidate
         float m1 = -INFINITY, m2 = -INFINITY;
         asm("" : "+v"(m2));                                   // a known -infinity would make the second score's med3 min(m1, v): m1 twice if v is a NaN
@@ -1092,8 +1098,9 @@ __device__ __forceinline__ void stage_keys(const uint16_t* kh, int64_t stride_t,
 // 512-thread workgroup.  S: R * (MAXC * 64 + row_pad) floats of LDS for the scores, then 256 counters per
 // wavefront.  Ends without a barrier; the caller must not reuse S before one.
 // The split pooled queries are staged in LDS by stage_queries.
-template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, int KIN = 0>
+template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, bool BEST, int KIN = 0>
 __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh, const int i0, float* S, const KeyArgs* keys = nullptr) {
+    static_assert(!BEST || (!MASS && !GROUP && has_lists_by_bound(R, MAXC)), "lists by bound are for these kernels");
     constexpr int LD = MAXC * 64 + row_pad(D, R);
     const float* __restrict__ kp = a.kp;
     const int Hq = a.Hq, G = a.G, NB = a.NB, NBk = a.NBk, off = a.off, T = a.T;
@@ -1163,7 +1170,6 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
         int k_i = row_budget(k_rows, iq, k);
         const int64_t row = (int64_t)bh * NB + iq;
         int32_t* idx_row = idx + row * T;
-        constexpr bool BEST = !MASS && !GROUP && (MAXC == 32 || (MAXC == 16 && R == 16));       // which rows: see take_best
         float x[BEST ? MAXC : 1];
         if constexpr (BEST) {
             static_for_sel<4>([&](auto q_tag) {
@@ -1252,7 +1258,7 @@ __device__ __forceinline__ void score_topk_rows(const ScoreArgs& a, const int bh
 // first chunk wait in registers (16 per lane and row) while the second chunk is scored, then each
 // row is selected exactly as in the plain kernel, from 32 scores per lane.  (No cumulative-mass
 // variant: that budget keeps the 8-row kernel.)
-template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
+template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP, bool BEST>
 __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, const int bh, const int i0, float* S) {
     constexpr int CC = 16;                     // 64-block register chunks per column chunk
     constexpr int CW = CC * 64;                // key blocks per column chunk
@@ -1351,7 +1357,7 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
             for (int m = CC; m < MAXC; ++m) x[m] = -INFINITY;
         }
         const int k_i = row_budget(a.k_rows, iq, k);
-        if (!GROUP && (!EXT || plain_row(pt, i))) {
+        if (BEST && (!EXT || plain_row(pt, i))) {
             const int c0 = pt.ns < n ? pt.ns : n, c1 = i - pt.nl + 1 > c0 ? i - pt.nl + 1 : c0;
             const int kk = k_i < c1 - c0 ? k_i : c1 - c0;
             if (take_best<MAXC>(x, i, c0, c1, kk, T, reinterpret_cast<float2*>(S + r * LD), idx_row, cnt + row, lane)) return;
@@ -1408,19 +1414,19 @@ __device__ __forceinline__ void score_topk_rows_chunked(const ScoreArgs& a, cons
     });
 }
 
-template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP>
+template <int D, int R, int MAXCH, bool EXT, int NWV, bool GROUP, bool BEST>
 __global__ __launch_bounds__(NWV * 64, 4) void score_topk_chunked_kernel(ScoreArgs a, int n_tiles) {
     extern __shared__ __attribute__((aligned(128))) float S[];   // [R][1024 + row_pad] scores of one column chunk, then the staged queries
     const int nwg = gridDim.x;
     int wg = blockIdx.x;
     if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);   // each XCD a contiguous slice, as in the plain kernel
     const int tile = n_tiles - 1 - wg % n_tiles;          // long rows first
-    score_topk_rows_chunked<D, R, MAXCH, EXT, NWV, GROUP>(a, wg / n_tiles, tile * R, S);
+    score_topk_rows_chunked<D, R, MAXCH, EXT, NWV, GROUP, BEST>(a, wg / n_tiles, tile * R, S);
 }
 
 // Two workgroups per CU (4 wavefronts per SIMD): at most 128 registers, which is why the query
 // operands are staged in LDS.
-template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP>
+template <int D, int R, int MAXC, bool EXT, bool MASS, int NWV, bool GROUP, bool BEST>
 __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs a, int n_tiles) {
     extern __shared__ __attribute__((aligned(128))) float S[];   // [R][LD] scores of this workgroup's rows, then 256 counters per wave
     // Workgroup ids go round robin over the 8 XCDs; give each XCD a contiguous slice of the
@@ -1429,7 +1435,7 @@ __global__ __launch_bounds__(NWV * 64, 4) void score_topk_mfma_kernel(ScoreArgs 
     int wg = blockIdx.x;
     if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
     const int tile = n_tiles - 1 - wg % n_tiles;          // long rows first
-    score_topk_rows<D, R, MAXC, EXT, MASS, NWV, GROUP>(a, wg / n_tiles, tile * R, S);
+    score_topk_rows<D, R, MAXC, EXT, MASS, NWV, GROUP, BEST>(a, wg / n_tiles, tile * R, S);
 }
 
 // Small calls (small_call): one launch instead of prepare_kv_kernel (or pool_kernel) and the score kernel.  Every workgroup pools the K blocks
@@ -1444,7 +1450,7 @@ __global__ __launch_bounds__(512, D == 64 ? 6 : 4) void score_topk_small_kernel(
     constexpr int R = 4, NWV = 8;
     const int wg = blockIdx.x;
     if (wg < n_score) {
-        score_topk_rows<D, R, 4, EXT, false, NWV, false, BS>(a, wg / n_tiles, (n_tiles - 1 - wg % n_tiles) * R, S, &keys);
+        score_topk_rows<D, R, 4, EXT, false, NWV, false, false, BS>(a, wg / n_tiles, (n_tiles - 1 - wg % n_tiles) * R, S, &keys);
         return;
     }
     const int half = threadIdx.x >> 8, x = 2 * (wg - n_score) + half;        // block of V
@@ -1510,43 +1516,50 @@ struct ScoreCall {
     hipStream_t st;
 };
 
-template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, int NWV = (R * (MAXC * 64 + row_pad(D, R)) * 4 > 80 * 1024 ? 16 : 8)>
+template <int D, int R, int MAXC, bool EXT, bool MASS, bool GROUP, bool BEST = false, int NWV = (R * (MAXC * 64 + row_pad(D, R)) * 4 > 80 * 1024 ? 16 : 8)>
 hipError_t launch_mfma_e(const ScoreCall& c) {
     constexpr size_t part_words = 2 * (NWV / 4) * (256 / (D / 8)) * D;    // partial sums of the in-kernel pooling
     constexpr size_t lds = ((size_t)R * (MAXC * 64 + row_pad(D, R)) + NWV * 256 +
                             (part_words > (size_t)R * (MAXC * 64 + row_pad(D, R)) ? part_words : 0)) * sizeof(float);
-    hipError_t e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP>, lds);
+    hipError_t e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP, BEST>, lds);
+    if constexpr (!MASS && !GROUP && has_lists_by_bound(R, MAXC))         // a capture may follow calls with another budget, which is the other kernel
+        if (e == hipSuccess) e = allow_lds((const void*)score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP, !BEST>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
     dim3 grid((unsigned)(n_tiles * c.d.B * c.d.Hq));
-    hipLaunchKernelGGL((score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
+    hipLaunchKernelGGL((score_topk_mfma_kernel<D, R, MAXC, EXT, MASS, NWV, GROUP, BEST>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
     return hipGetLastError();
 }
 
 template <int D, int R, int MAXC, bool EXT, bool MASS>
 hipError_t launch_mfma_q(const ScoreCall& c) {
     if (c.a.group > 1) return launch_mfma_e<D, R, MAXC, EXT, MASS, true>(c);
+    if constexpr (!MASS && has_lists_by_bound(R, MAXC))
+        if (lists_by_bound(c.d)) return launch_mfma_e<D, R, MAXC, EXT, MASS, false, true>(c);
     return launch_mfma_e<D, R, MAXC, EXT, MASS, false>(c);
 }
 
-template <int D, int MAXCH, bool EXT, bool GROUP>
+template <int D, int MAXCH, bool EXT, bool GROUP, bool BEST = false>
 hipError_t launch_chunked_e(const ScoreCall& c) {
     constexpr int R = 16, NWV = 8;
     constexpr size_t lds = ((size_t)R * (1024 + row_pad(D, R)) + NWV * 256) * sizeof(float);
     static_assert(2 * (NWV / 4) * (256 / (D / 8)) * D <= R * (1024 + row_pad(D, R)), "the pooling partial sums fit the score space");
-    hipError_t e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP>, lds);
+    hipError_t e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP, BEST>, lds);
+    if constexpr (!GROUP)
+        if (e == hipSuccess) e = allow_lds((const void*)score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP, !BEST>, lds);
     if (e != hipSuccess) return e;
     const int n_tiles = (c.d.NB + R - 1) / R;
     dim3 grid((unsigned)(n_tiles * c.d.B * c.d.Hq));
-    hipLaunchKernelGGL((score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
+    hipLaunchKernelGGL((score_topk_chunked_kernel<D, R, MAXCH, EXT, NWV, GROUP, BEST>), grid, dim3(NWV * 64), lds, c.st, c.a, n_tiles);
     return hipGetLastError();
 }
 
 template <int D, int MAXCH>
 hipError_t launch_chunked(const ScoreCall& c) {
-    const bool group = c.a.group > 1;
-    if (extended(c.d)) return group ? launch_chunked_e<D, MAXCH, true, true>(c) : launch_chunked_e<D, MAXCH, true, false>(c);
-    return group ? launch_chunked_e<D, MAXCH, false, true>(c) : launch_chunked_e<D, MAXCH, false, false>(c);
+    const bool group = c.a.group > 1, best = lists_by_bound(c.d), ext = extended(c.d);
+    if (group) return ext ? launch_chunked_e<D, MAXCH, true, true>(c) : launch_chunked_e<D, MAXCH, false, true>(c);
+    if (best) return ext ? launch_chunked_e<D, MAXCH, true, false, true>(c) : launch_chunked_e<D, MAXCH, false, false, true>(c);
+    return ext ? launch_chunked_e<D, MAXCH, true, false>(c) : launch_chunked_e<D, MAXCH, false, false>(c);
 }
 
 template <int D, int R, int MAXC>

@@ -249,7 +249,7 @@ def test_options_on_every_score_kernel(spa, oracle, kernel, option, D):
                 assert torch.isneginf(sp[b, h, i, m:off + nb]).all()
 
 
-# Rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows, are selected from a list of the blocks that reach a bound, up to 128 of
+# Rows of 1025 to 2048 blocks, and from 513 on in workgroups of 16 rows, are selected from a list of the blocks that reach a bound, up to 112 of
 # a budget, 64 sinks and 512 entries, and the general way (the other two kernels here, too) past any of these.  Budgets and sinks on both sides.
 # Scores by `keys`: all different; of 40, 2 or 1 distinct values (ties at the threshold inside a list, more equal ones than it holds, all equal);
 # "special": NaN, infinities, huge values and zeros in places; "few": most are NaN or -infinity, so that rows have fewer finite ones than wanted.
@@ -273,7 +273,8 @@ def test_lists_by_bound(spa, kernel, keys, D):
         nan, neg, pos, huge, zero = (0.47, 0.94, 0.95, 0.96, 0.97) if keys == "few" else (0.05, 0.1, 0.12, 0.16, 0.2)
         k = k.where(kind >= nan, float("nan")).where((kind < nan) | (kind >= neg), -k.abs() * 1e36).where((kind < neg) | (kind >= pos), k.abs() * 1e36)
         k = k.where((kind < pos) | (kind >= huge), k * 1e30).where((kind < huge) | (kind >= zero), 0.0)
-    for ns, nl, topk in ((1, 4, 1), (0, 1, 64), (1, 4, 65), (64, 2, 127), (65, 2, 64), (3, 70, 128), (1, 4, 129), (2, 3, 0), (5, 9, P + NB - 20)):
+    for ns, nl, topk in ((1, 4, 1), (0, 1, 64), (1, 4, 65), (64, 2, 127), (65, 2, 64), (3, 70, 128), (1, 4, 129), (2, 3, 0), (5, 9, P + NB - 20),
+                         (1, 4, 112), (2, 3, 113)):
         idx, cnt, sp = spa.select(q, k, Bs, ns, nl, topk, return_scores=True)
         want_idx, want_cnt = spa.topk_from_scores(sp, ns, nl, topk)
         assert torch.equal(cnt, want_cnt) and torch.equal(idx, want_idx), (ns, nl, topk)
@@ -282,6 +283,24 @@ def test_lists_by_bound(spa, kernel, keys, D):
         assert seen.isnan().any() and seen.isposinf().any() and seen.isneginf().any() and (seen == 0).any()
         finite = seen.isfinite().sum(-1)
         assert (finite > 128).all() if keys == "special" else (finite < 127).any() and (finite > 1).all()
+
+
+# ... and in calls whose first rows have fewer candidates than wanted, or only a few more, or, with budgets above 112, less than the 1024 that these take
+# (128 is for the last shape alone).
+SHORT_ROWS = {"16rows1024": (700, 32, 230), "8rows2048": (1030, 8, 0), "16rows2048": (1030, 32, 0), "16rows2048long": (600, 32, 950)}
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("shape", SHORT_ROWS)
+def test_lists_by_bound_of_short_rows(spa, shape, D):
+    NB, Hq, P = SHORT_ROWS[shape]
+    g = torch.Generator("cuda").manual_seed(75)
+    q = torch.randn((1, Hq, NB * 64, D), generator=g, device="cuda").to(torch.bfloat16)
+    k = torch.randn((1, Hq // 4, (P + NB) * 64, D), generator=g, device="cuda").to(torch.bfloat16)
+    for ns, nl, topk in ((1, 4, 1), (0, 1, 64), (64, 2, 65), (3, 70, 112), (1, 4, 113), (2, 1, 128)):
+        idx, cnt, sp = spa.select(q, k, 64, ns, nl, topk, return_scores=True)
+        want_idx, want_cnt = spa.topk_from_scores(sp, ns, nl, topk)
+        assert torch.equal(cnt, want_cnt) and torch.equal(idx, want_idx), (ns, nl, topk)
 
 
 # A mass budget is not searched for where the count budget cannot reach it whatever the scores.  Equal scores weigh 2^19 each, the most there is:

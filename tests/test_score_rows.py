@@ -5,7 +5,7 @@ import pytest
 
 from host_shim import compile_shim
 from paper_2602_21233_amd import binding
-from test_gpu_dispatch import SCORE_KERNELS, SCORE_OPTIONS, score_case
+from test_gpu_dispatch import SCORE_KERNELS, SCORE_OPTIONS, SHORT_ROWS, score_case
 
 SHIM = r"""
 #include "score_rows.hpp"
@@ -19,6 +19,7 @@ extern "C" int pooled_in_kernel(const spa_params* p, int mass) { return spa::gro
 extern "C" int one_launch(const spa_params* p, int mass) { return spa::small_call(lists_of(p, mass), false); }
 extern "C" int one_launch_by_values(const spa_params* p, int mass) { return spa::small_call(lists_of(p, mass), true); }
 extern "C" int most_small_blocks(const spa_params* p, int) { return spa::most_small_blocks(p->head_dim, p->block_size); }
+extern "C" int lists_by_bound(const spa_params* p, int mass) { return spa::lists_by_bound(lists_of(p, mass)); }
 extern "C" int sixteen_row_tiles(const spa_params* p, int mass) { return spa::key_layout(lists_of(p, mass)) == spa::kKeyTiles16; }
 """
 
@@ -27,11 +28,11 @@ extern "C" int sixteen_row_tiles(const spa_params* p, int mass) { return spa::ke
 def rows_of(tmp_path_factory):
     lib = compile_shim(tmp_path_factory.mktemp("score_rows"), SHIM)
 
-    def ask(NB, NBk, heads, Bs=64, D=128, mass=False, what="score_rows", group=None):
+    def ask(NB, NBk, heads, Bs=64, D=128, mass=False, what="score_rows", group=None, **kw):
         """heads: lists; group: query heads that share one (None: a list for each)"""
-        p = binding.make_params(batch=1, n_q_heads=heads * (group or 1), n_kv_heads=heads if group else 1, seq_len=NB * Bs - 3, head_dim=D,
-                                block_size=Bs, n_sink_blocks=1, n_local_blocks=4, top_k_blocks=64, kv_prefix_len=(NBk - NB) * Bs,
-                                lists_per_kv_head=group is not None)
+        p = binding.make_params(**dict(dict(batch=1, n_q_heads=heads * (group or 1), n_kv_heads=heads if group else 1, seq_len=NB * Bs - 3,
+                                            head_dim=D, block_size=Bs, n_sink_blocks=1, n_local_blocks=4, top_k_blocks=64,
+                                            kv_prefix_len=(NBk - NB) * Bs, lists_per_kv_head=group is not None), **kw))
         return getattr(lib, what)(ctypes.byref(p), int(mass))
     return ask
 
@@ -117,6 +118,34 @@ def test_sixteen_row_tiles_only_where_sixteen_rows_of_head_dim_128_read_them(row
                                                           (520, 520, 16, 2, 64, 128, 16), (48, 48, 32, 2, 128, 64, 4), (42, 342, 32, 3, 64, 128, 4)])
 def test_the_shapes_of_the_gpu_test_of_group_means(rows_of, NB, NBk, heads, group, Bs, D, rows):
     assert rows_of(NB, NBk, heads, Bs=Bs, D=D, group=group) == rows and rows_of(NB, NBk, heads, Bs=Bs, D=D, group=group, what="pooled_in_kernel")
+
+
+# Rows are selected from a list of the blocks that reach a bound where enough of them are long enough for the budget.  Measured, select calls, without and
+# with lists: 700 blocks from the first on, 8 wanted, 53.1 and 55.2 us; 768 100.4 and 98.6; 826 blocks, 64 wanted, 105.5 and 107.5; rows of 384
+# to 768 blocks 64.3 and 61.8, of 260 to 520 80.2 and 82.0; head_dim 128, 799 blocks, 119.7 and 116.6; all 128 wanted of 960 blocks 56.8 and 61.5.
+@pytest.mark.parametrize("NB,NBk,heads,D,topk,want", [
+    (700, 700, 32, 64, 8, False), (768, 768, 32, 128, 8, True), (826, 826, 40, 64, 64, False), (960, 960, 32, 64, 64, True), (384, 768, 64, 64, 64, True),
+    (260, 520, 64, 64, 64, False), (799, 799, 32, 128, 64, True), (652, 652, 32, 128, 64, False), (799, 799, 16, 128, 64, False), (960, 960, 32, 64, 128, False),
+    (1024, 1024, 32, 128, 64, True), (200, 1000, 40, 128, 112, False), (512, 512, 40, 128, 8, False), (200, 1000, 32, 64, 112, True),
+    (200, 1000, 32, 64, 113, False), (100, 1025, 8, 64, 124, True), (100, 1025, 8, 64, 125, False), (32, 2048, 32, 64, 64, True), (2048, 2048, 40, 128, 128, True),
+    (2048, 2048, 40, 64, 128, True), (1700, 1700, 8, 64, 128, False), (2048, 2048, 40, 128, 129, False), (100, 2048, 40, 128, 128, False),
+    (100, 1500, 40, 128, 128, False), (2049, 2049, 40, 128, 8, False)])
+def test_lists_by_bound_where_they_are_faster(rows_of, NB, NBk, heads, D, topk, want):
+    ask = lambda **kw: bool(rows_of(NB, NBk, heads, D=D, what="lists_by_bound", **dict(dict(top_k_blocks=topk), **kw)))
+    assert ask() == want and ask(n_dense_q_blocks=3) == want and ask(n_sink_blocks=64) == want
+    assert not ask(mass=True) and not ask(group=2) and not ask(stride_blocks=16) and not ask(n_sink_blocks=65)
+
+
+# The GPU tests of lists by bound take the kernels that they name.
+@pytest.mark.parametrize("shape", SHORT_ROWS)
+@pytest.mark.parametrize("D", [64, 128])
+def test_the_shapes_of_the_gpu_tests_of_lists_by_bound(rows_of, shape, D):
+    NB, heads, P = SHORT_ROWS[shape]
+    assert rows_of(NB, P + NB, heads, D=D) == (8 if shape.startswith("8") else 16)
+    lists = [k for k in (1, 64, 65, 112, 113, 128) if rows_of(NB, P + NB, heads, D=D, what="lists_by_bound", top_k_blocks=k)]
+    assert lists == [1, 64, 65, 112] + ([113] if P + NB > 1024 else []) + ([128] if shape.endswith("long") else [])
+    for kernel, (NB, heads, P) in SCORE_KERNELS.items():
+        assert bool(rows_of(NB, P + NB, heads, D=D, what="lists_by_bound")) == (kernel[1] == 2048 or kernel == (16, 1024))
 
 
 # The GPU test of every option on every score kernel takes the kernels that it names.
