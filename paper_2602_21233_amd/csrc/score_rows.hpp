@@ -37,26 +37,26 @@ inline int score_rows(const Dims& d) {
     // 513 .. 2048 blocks.  All figures from here on: select calls over 8 KV heads, us with 8 and with 16 rows.  The lines were drawn before the
     // 16-row kernels selected from lists by bound (take_best), which the 8-row ones do only beyond 1024 blocks, and have not been moved since:
     // some calls on the side of 8 now lose up to 13 % against 16.
-    // Many rows: 16, as 8 re-read the pooled K twice as often (blocks of 128: 185 and 181 at 768 blocks and 24576 rows, 255 and 236 at 1024 and
-    // 32768; 707 and 615 at 262144 tokens and 81920 rows, 327 and 304 at 163840 tokens and 40960, where 16 rows are scored in two chunks of
-    // 1024 columns to keep two workgroups per CU; but 220 and 223 at 768 blocks and 30720 rows).
+    // Many rows: 16, as 8 re-read the pooled K twice as often (blocks of 128: 186 and 181 at 768 blocks and 24576 rows, 257 and 237 at 1024 and
+    // 32768; 703 and 619 at 262144 tokens and 81920 rows, 326 and 304 at 163840 tokens and 40960, where 16 rows are scored in two chunks of
+    // 1024 columns to keep two workgroups per CU; but 221 and 224 at 768 blocks and 30720 rows).
     if (rows > (two_chunks ? 32768 : 16384)) return 16;
     // Fewer: more workgroups, unless they only make more rounds.  With blocks of 128 the query stream, twice as long for a row, hides the
     // rounds, and 8 are the better choice up to 1024 blocks (8192 queries over 98304 tokens, 2048 rows, 62.7 and 68.2; 98304 tokens of 8 heads
-    // 78.4 and 85.5; 131072 of 16 heads, 16384 rows, 154 and 162; but with head_dim 64 92.4 and 90.0).  In two chunks 16 have become the
-    // better choice from about 20000 rows on (160 and 162 at 196608 tokens of 8 heads, 219 and 223 at 262144, but 195 and 189 at 163840 of 16
-    // heads, 241 and 235 at 196608, 339 and 310 at 262144, 32768 rows) and over a long prefix (25600 queries over 230400 tokens, 171 and 158).
+    // 78.7 and 84.1; 131072 of 16 heads, 16384 rows, 154 and 162; but with head_dim 64 92.2 and 90.2).  In two chunks 16 have become the
+    // better choice from about 20000 rows on (160 and 162 at 196608 tokens of 8 heads, 219 and 222 at 262144, but 197 and 189 at 163840 of 16
+    // heads, 242 and 234 at 196608, 336 and 310 at 262144, 32768 rows) and over a long prefix (25600 queries over 230400 tokens, 172 and 158).
     if (d.Bs == 128) return 8;
     // With blocks of 64 the rounds of 512 workgroups (two per CU) show.  Up to 1.5 rounds of 8-row workgroups (6144 rows) 8 rows win (1600 rows
-    // of 1000 blocks 45.2 and 50.1, 5120 of 640 43.5 and 49.5).  From there on:
+    // of 1000 blocks 45.5 and 50.3, 5120 of 640 43.4 and 46.9).  From there on:
     //   - over a prefix at least as long as the chunk all rows are about as long, and what counts is `depth`, how many of them a place works
-    //     through one after the other: 16 where that is the same (12797 queries over 51200 tokens, 32 heads, 76.9 and 66.7; 25597 over 102400
-    //     tokens, 40 heads, 180 and 148), 8 rows where that is less, which since lists by bound no longer pays (12797 over 51200 tokens, 40
-    //     heads, 80.9 and 77.2, 19197 over 44800 102 and 88.5, 38397 over 51200 of 16 heads 102 and 96.2);
+    //     through one after the other: 16 where that is the same (12797 queries over 51200 tokens, 32 heads, 77.2 and 66.9; 25597 over 102400
+    //     tokens, 40 heads, 183 and 150), 8 rows where that is less, which since lists by bound no longer pays (12797 over 51200 tokens, 40
+    //     heads, 81.5 and 77.7, 19197 over 44800 103 and 89.6, 38397 over 51200 of 16 heads 102 and 95.7);
     //   - rows that differ in length are dealt longest first and even the rounds out.  8 rows win up to one round of 16-row workgroups (52413
-    //     tokens of 8 heads 56.4 and 58.6) and, with head_dim 64 or two chunks, up to 14336 rows (95997 tokens of 8 heads 104 and 104; 47485
-    //     tokens of 16 heads, head_dim 64, 46.4 and 50.9).  16 elsewhere: 113341 tokens of 16 heads, head_dim 64, 133 and 120, 28288 rows of 1247
-    //     blocks 183 and 160, 64000 tokens of 16 heads 102 and 96.9 (40957 tokens 62.2 and 63.7).
+    //     tokens of 8 heads 57.0 and 57.8) and, with head_dim 64 or two chunks, up to 14336 rows (95997 tokens of 8 heads 105 and 105; 47485
+    //     tokens of 16 heads, head_dim 64, 47.3 and 48.9).  16 elsewhere: 113341 tokens of 16 heads, head_dim 64, 135 and 121, 28288 rows of 1247
+    //     blocks 183 and 160, 64000 tokens of 16 heads 103 and 97.4, 40957 62.2 and 60.4.
     const int64_t wg8 = heads * ((d.NB + 7) / 8), wg16 = heads * ((d.NB + 15) / 16);
     if (wg8 <= 768) return 8;
     if (d.off >= d.NB) {
@@ -73,11 +73,11 @@ inline int score_rows(const Dims& d) {
 //   - up to 1024 blocks, 16 rows a workgroup, it takes rows of 352 blocks and more with the budget on average, less of that for many rows of head_dim
 //     128: 40 heads from the first block on, head_dim 64, 64 wanted, 826 blocks of 64 105.5 and 107.5, 951 of 128 164.8 and 161.5; 32
 //     heads, 8 wanted, 768 of 128 100.4 and 98.6; head_dim 128, blocks of 64, 32 heads, 64 wanted, 799 119.7 and 116.6, 670 99.1 and 99.6, 16
-//     heads, 8 wanted, 700 53.1 and 55.2.  Over 900 random calls with such kernels this choice takes 0.1 % more time than the better one of
-//     each, lists always 0.6, lists never 2.4 (at most 5, 8 and 19 %).
-//   - beyond 1024 blocks all up to 124 wanted (116 to 124 wanted of 1025 to 1280 blocks 0.92 to 1.04 of the time without, of 1536 and more
-//     0.79 to 0.97), and 128 of many long rows (more than 1536 blocks, more than 16384 rows 0.93 to 1.01; up to 16384 rows 0.96 to 1.06; 1025 to
-//     1280 blocks 0.98 to 1.11).
+//     heads, 8 wanted, 700 53.1 and 55.2.  Over 900 random calls with such kernels this choice takes 0.15 % more time than the better one of
+//     each, lists always 0.9, lists never 2.6 (at most 4, 10 and 19 %).
+//   - beyond 1024 blocks all up to 124 wanted (116 to 124 wanted of 1025 to 1280 blocks 0.91 to 1.01 of the time without, of 1536 and more
+//     0.84 to 0.98), and 128 of many long rows (more than 1536 blocks, more than 16384 rows 0.95 to 0.99; up to 16384 rows 0.96 to 1.06; 1025 to
+//     1280 blocks 0.99 to 1.09).
 constexpr int kFewWanted = 112;
 constexpr bool has_lists_by_bound(int R, int max_chunks) { return max_chunks == 32 || (max_chunks == 16 && R == 16); }
 inline bool lists_by_bound(const Dims& d) {
